@@ -884,7 +884,7 @@ struct Sim3 {
     size_t e_off[8] = {}, e_bytes = 0, i_off[5] = {}, i_bytes = 0;
     size_t w_status = 0, w_nused = 0, w_cnt = 0, w_pml = 0, w_ant = 0, w_st_z = 0, w_st_rec = 0, w_st_cnt = 0,
            w_seg_e = 0, w_seg_i = 0, w_box_e[2] = {}, w_box_i[2] = {}, w_counts = 0, w_cursor = 0, w_tot = 0,
-           w_lists = 0, w_mis = 0,
+           w_nmis = 0, w_mis = 0,
            w_bytes = 0;
     int64_t cap = 0;
     int nst_max = 0, stcap = 1, p_cur = 0, since_sort = 0;
@@ -976,7 +976,7 @@ void layout3(const bf_config* c, Sim3* L)
         L->w_box_i[k] = take(sizeof(bf3::Box3) * L->seg_cap);
     }
     L->w_counts = take(sizeof(int) * L->tl.ntiles);
-    L->w_lists = take(sizeof(int) * (2 + (size_t)L->seg_cap));
+    L->w_nmis = take(sizeof(int) * (2 + (size_t)L->seg_cap));   // one is used; the size keeps the layout
     L->w_mis = take(sizeof(int) * 2 * (size_t)L->cap);
     L->w_cursor = take(sizeof(int) * L->tl.ntiles);
     L->w_pml = take(sizeof(double) * 3 * 2 * 3 * (size_t)(L->g.S[0] + L->g.S[1] + L->g.S[2]));
@@ -1259,7 +1259,7 @@ bf_status step3(bf_sim* s, int nsteps)
         const bool mc = s->cfg.gather_kind == 1;
         if (mc) bf3::launch3_nodes<R>(g, f, s->stream);
         bf3::launch3_gpd<R>(g, f, electrons3<R>(s, L.p_cur), seg3<R>(s, 0), box3(s, 0, L.bb_cur),
-                            box3(s, 0, 1 - L.bb_cur), L.nseg, pp, L.pz, w3<int>(s, L.w_status), w3<int>(s, L.w_lists),
+                            box3(s, 0, 1 - L.bb_cur), L.nseg, pp, L.pz, w3<int>(s, L.w_status), w3<int>(s, L.w_nmis),
                             w3<int2>(s, L.w_mis), mc, s->stream);
         s->tock(ev, BF_PHASE_PUSH);
         ev = s->tick();
@@ -1444,8 +1444,14 @@ bf_status read_particles3(bf_sim* s, int species, std::vector<double>* cols, int
         const double w = species == 0 ? rv(6, p) : rv(3, p);
         if (w == 0.0) continue;
         const double* xyz = (const double*)raw[0].data();
-        const double x = xyz[p] * d[0], y = ((const double*)raw[1].data())[p] * d[1];
-        double z = ((const double*)raw[2].data())[p];
+        // on periodic axes the electrons are unwrapped between sorts
+        auto fold = [&](int a, double v) {
+            if (species != 0 || !L.g.per[a]) return v;
+            const double len = (double)L.g.N[a], r = v - std::floor(v / len) * len;
+            return r >= len ? r - len : r;
+        };
+        const double x = fold(0, xyz[p]) * d[0], y = fold(1, ((const double*)raw[1].data())[p]) * d[1];
+        double z = fold(2, ((const double*)raw[2].data())[p]);
         if (species == 1) z = z - (s->beta * s->t / d[2] + (double)s->shift);
         cols[0].push_back((double)((const uint32_t*)raw[ncol - 1].data())[p]);
         cols[1].push_back(x);

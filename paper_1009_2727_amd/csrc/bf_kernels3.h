@@ -44,7 +44,8 @@ struct F3 {
 };
 
 template <typename R>
-struct E3 {     // electrons: positions in cells of the current window (FP64)
+struct E3 {     // electrons: positions in cells of the current window (FP64), unwrapped on periodic
+                // axes between sorts
     double *x, *y, *z;
     R *ux, *uy, *uz, *w;
     uint32_t* id;
@@ -148,11 +149,11 @@ template <typename R> void launch3_zero_j(const G3& g, const F3<R>& f, hipStream
 // gather, push and deposit of the electrons of nseg segments (one workgroup each); bin holds
 // each segment's cell box at the start of the step, bout receives the box after the push (in
 // the next window frame); pz = z planes of the LDS box
-// lists: 2 + nseg ints of scratch, mis: one int2 per particle slot (particles outside their
-// segment's box and segments too large for LDS are pushed in a second pass, on HBM)
+// nmis: one int of scratch, mis: one int2 per particle slot (particles outside their segment's
+// staged box are pushed in a second pass, on HBM)
 template <typename R>
 void launch3_gpd(const G3& g, const F3<R>& f, const E3<R>& e, const Seg3* seg, const Box3* bin, Box3* bout,
-                 int nseg, const Push3& pp, int pz, int* status, int* lists, int2* mis, bool mc, hipStream_t s);
+                 int nseg, const Push3& pp, int pz, int* status, int* nmis, int2* mis, bool mc, hipStream_t s);
 // momentum-conserving gather, first step: E^n and B^n = (B^{n-1/2} + B^{n+1/2})/2 interpolated to
 // the nodes (the mean over the Yee locations around each node along the staggered axes) into f.G
 template <typename R> void launch3_nodes(const G3& g, const F3<R>& f, hipStream_t s);

@@ -907,9 +907,8 @@ __device__ __forceinline__ R rsq(R x)
 // of the order of the adds: a contribution v becomes round(v / q), q = max|k| sum|w| / 2^46
 // over the segment, through one FMA with 1.5 * 2^52 whose bit pattern is 0x4338000000000000 +
 // round(v / q); the low 48 bits of the raw sum, sign-extended, are the exact sum.  FP64 runs
-// add in FP64.  A particle whose cell lies outside its segment's box, and every particle of a
-// segment whose box exceeds the LDS pitches, takes the same steps on the fields and current
-// in HBM.
+// add in FP64.  A particle whose cell lies outside its segment's staged box takes the same steps
+// on the fields and current in HBM.
 
 constexpr int GT = 768;        // threads of an electron segment workgroup
 constexpr int GTI = 256;       // threads of an ion segment workgroup
@@ -1269,8 +1268,9 @@ __device__ __forceinline__ bool electron3(const G3& g, const F3<R>& f, const Box
     for (int a = 0; a < 3; a++) {
         const double L = (double)g.N[a];
         if (g.per[a]) {
-            if (r1[a] < 0.0) r1[a] += L;
-            else if (r1[a] >= L) r1[a] -= L;
+            // unwrapped between sorts (the sort folds it), at most one period outside the box
+            if (r1[a] < -L) r1[a] += L;
+            else if (r1[a] >= 2.0 * L) r1[a] -= L;
         } else if (r1[a] < 0.0 || r1[a] >= L) {
             alive = false;
         }
@@ -1304,12 +1304,48 @@ __device__ __forceinline__ void box_of(const Box3& bb, int pz, BoxL<R>& bx, bool
     lds = bx.ext[0] <= BPX && bx.ext[1] <= BPY && bx.ext[2] <= pz;
 }
 
-// Staged segments.  A segment whose box exceeds the LDS pitches goes to the list big, a particle
-// outside its segment's box to the list mis (segment, particle); k3_gpd_hbm pushes both.
+// The box of a segment whose particles have spread beyond the pitches (cells bb): along each
+// axis that is too long, the longest window that fits, centred on the particles' mean position.
+// A tile of 4 rows leaves one row of slack, so a few particles that left it on either side are
+// enough to get here; nearly all are still inside the window.
+template <typename R>
+__device__ void clamp_box(const E3<R>& e, const Seg3& sg, const Box3& bb, int pz, BoxL<R>& bx, double* red)
+{
+    const int cap[3] = {BPX, BPY, pz};
+    double m[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int p = sg.start + threadIdx.x; p < sg.start + sg.count; p += GT)
+        if (e.w[p] != R(0)) {
+            m[0] += e.x[p];
+            m[1] += e.y[p];
+            m[2] += e.z[p];
+            m[3] += 1.0;
+        }
+#pragma unroll
+    for (int a = 0; a < 4; a++) {
+        m[a] = block_sum3<GT>(m[a], red);
+        __syncthreads();   // red is reused
+    }
+    if (m[3] == 0.0) return;   // every particle is gone: the box is not used
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        if (bx.ext[a] <= cap[a]) continue;
+        // a particle in cell c fits while lo + 2 <= c <= lo + cap - 4
+        const int lo = (int)floor(m[a] / m[3] - 0.5 * (cap[a] - 5) + 0.5) - 2;
+        bx.lo[a] = min(max(lo, bb.lo[a] - 2), bb.hi[a] + 4 - cap[a]);
+        bx.ext[a] = cap[a];
+    }
+}
+
+// Staged segments.  Bound by LDS (the gather's reads and the deposit's 8-byte adds).  A particle
+// outside its segment's box goes to the list mis (segment, particle), which k3_gpd_hbm pushes: a
+// staged particle costs about 0.1 ns of the whole kernel, one on HBM several times that.  A
+// segment that outgrew the pitches stages the window clamp_box chooses and lists only the
+// particles outside it; sending such segments to HBM whole cost 4.9 of 24 ms per step on
+// 128x128x1024 cells with the laser at its peak, and 1.97 of 2.7 ms on 61x45x203.
 template <typename R, bool MC>
 __global__ void __launch_bounds__(GT) k3_gpd(G3 g, F3<R> f, E3<R> e, const Seg3* __restrict__ seg,
                                              const Box3* __restrict__ bin, Box3* __restrict__ bout, Push3 pp, int pz,
-                                             int* status, int* big, int* nbig, int2* mis, int* nmis)
+                                             int* status, int2* mis, int* nmis)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem3[];
     __shared__ int red[6][GT / 64];
@@ -1321,85 +1357,46 @@ __global__ void __launch_bounds__(GT) k3_gpd(G3 g, F3<R> f, E3<R> e, const Seg3*
         BoxL<R> bx;
         bool lds;
         box_of(bb, pz, bx, lds);
+        if (!lds) clamp_box(e, sg, bb, pz, bx, redd);
         bx.j = reinterpret_cast<typename Acc3<R>::T*>(smem3);
         bx.f = reinterpret_cast<R*>(bx.j + 3 * bx.n);
         const int end = sg.start + sg.count;
         double js = 1.0, jq = 1.0;
-        if (lds) {
-            if constexpr (Acc3<R>::fixed) {
-                double sw = 0.0;
-                for (int p = sg.start + threadIdx.x; p < end; p += GT) sw += fabs((double)e.w[p]);
-                sw = block_sum3<GT>(sw, redd);
-                const double bound = fmax(fabs(pp.jk[0]), fmax(fabs(pp.jk[1]), fabs(pp.jk[2]))) * sw;
-                if (bound > 0.0) { js = FX_RANGE / bound; jq = bound / FX_RANGE; }
-            }
-            stage_box<GT, R, true, MC>(g, f, bx, 3);
-            __syncthreads();
-            for (int p = sg.start + threadIdx.x; p < end; p += GT)
-                if (!electron3<true, MC>(g, f, bx, e, p, pp, js, status, nb)) mis[atomicAdd(nmis, 1)] = make_int2(blockIdx.x, p);
-            __syncthreads();
-            flush_box<GT>(g, f, bx, 0, 3, jq);
-        } else if (threadIdx.x == 0) {
-            big[atomicAdd(nbig, 1)] = blockIdx.x;
+        if constexpr (Acc3<R>::fixed) {
+            double sw = 0.0;
+            for (int p = sg.start + threadIdx.x; p < end; p += GT) sw += fabs((double)e.w[p]);
+            sw = block_sum3<GT>(sw, redd);
+            const double bound = fmax(fabs(pp.jk[0]), fmax(fabs(pp.jk[1]), fabs(pp.jk[2]))) * sw;
+            if (bound > 0.0) { js = FX_RANGE / bound; jq = bound / FX_RANGE; }
         }
+        stage_box<GT, R, true, MC>(g, f, bx, 3);
+        __syncthreads();
+        for (int p = sg.start + threadIdx.x; p < end; p += GT)
+            if (!electron3<true, MC>(g, f, bx, e, p, pp, js, status, nb)) mis[atomicAdd(nmis, 1)] = make_int2(blockIdx.x, p);
+        __syncthreads();
+        flush_box<GT>(g, f, bx, 0, 3, jq);
     }
     block_box<GT>(nb, red, &bout[blockIdx.x]);
 }
 
-// box bounds of a wave's particles into a segment's box (one lane per wave)
-__device__ __forceinline__ void wave_grow(int nb[6], Box3* out)
-{
-#pragma unroll
-    for (int q = 0; q < 6; q++)
-        for (int o = 32; o > 0; o >>= 1) {
-            const int v = __shfl_xor(nb[q], o);
-            nb[q] = (q & 1) ? max(nb[q], v) : min(nb[q], v);
-        }
-    if (__lane_id() == 0 && nb[0] <= nb[1]) {
-#pragma unroll
-        for (int a = 0; a < 3; a++) {
-            atomicMin(&out->lo[a], nb[2 * a]);
-            atomicMax(&out->hi[a], nb[2 * a + 1]);
-        }
-    }
-}
-
-// the particles k3_gpd left: whole segments of list big (one workgroup each, in turn) and
-// single particles of list mis, on the fields and current in HBM; their cells widen the
+// the particles k3_gpd left (list mis), on the fields and current in HBM; their cells widen the
 // segments' next boxes
 template <typename R, bool MC>
-__global__ void __launch_bounds__(NT) k3_gpd_hbm(G3 g, F3<R> f, E3<R> e, const Seg3* __restrict__ seg,
-                                                 Box3* __restrict__ bout, Push3 pp, int* status, const int* big,
-                                                 const int* nbig, const int2* mis, const int* nmis)
+__global__ void __launch_bounds__(NT) k3_gpd_hbm(G3 g, F3<R> f, E3<R> e, Box3* __restrict__ bout, Push3 pp,
+                                                 int* status, const int2* mis, const int* nmis)
 {
     const BoxL<R> none{};
-    const int nb_ = *nbig;
-    for (int b = blockIdx.x; b < nb_; b += gridDim.x) {
-        const int q = big[b];
-        const Seg3 sg = seg[q];
-        const int end = sg.start + sg.count;
-        for (int base = sg.start; base < end; base += NT) {
-            int nb[6] = {INT_MAX, INT_MIN, INT_MAX, INT_MIN, INT_MAX, INT_MIN};
-            const int p = base + threadIdx.x;
-            if (p < end) electron3<false, MC>(g, f, none, e, p, pp, 1.0, status, nb);
-            wave_grow(nb, &bout[q]);
-        }
-    }
     const int nm = *nmis;
-    for (int base = blockIdx.x * NT; base < nm; base += gridDim.x * NT) {
+    for (int i = blockIdx.x * NT + threadIdx.x; i < nm; i += gridDim.x * NT) {
         int nb[6] = {INT_MAX, INT_MIN, INT_MAX, INT_MIN, INT_MAX, INT_MIN};
-        const int i = base + threadIdx.x;
-        int q = 0;
-        if (i < nm) {
-            const int2 m = mis[i];
-            q = m.x;
-            electron3<false, MC>(g, f, none, e, m.y, pp, 1.0, status, nb);
-        }
+        const int2 m = mis[i];
+        electron3<false, MC>(g, f, none, e, m.y, pp, 1.0, status, nb);
         // lanes may belong to different segments: one atomic set per lane
-        if (i < nm && nb[0] <= nb[1]) {
+        if (nb[0] <= nb[1]) {
+#pragma unroll
             for (int a = 0; a < 3; a++) {
-                atomicMin(&bout[q].lo[a], nb[2 * a]);
-                atomicMax(&bout[q].hi[a], nb[2 * a + 1]);
+                atomicMin(&bout[m.x].lo[a], nb[2 * a]);
+                atomicMax(&bout[m.x].hi[a], nb[2 * a + 1]);
             }
         }
     }
@@ -1714,6 +1711,14 @@ __global__ void __launch_bounds__(NT) k3_window(G3 g, F3<R> f, int d)
 
 // ---- tile sort ----------------------------------------------------------------------------------
 
+// position on an axis folded into the box when the axis is periodic
+__device__ __forceinline__ double fold3(const G3& g, int a, double v)
+{
+    if (!g.per[a]) return v;
+    const double L = (double)g.N[a], r = v - floor(v / L) * L;
+    return r >= L ? r - L : r;
+}
+
 // tile of a position (cells, clamped into the interior)
 __device__ __forceinline__ int tile_key3(const G3& g, const Tiles3& tl, double x, double y, double z)
 {
@@ -1736,7 +1741,7 @@ __global__ void __launch_bounds__(NT) k3_sort_count_e(G3 g, Tiles3 tl, E3<R> e, 
     for (int base = blockIdx.x * NT; base < n; base += gridDim.x * NT) {
         const int p = base + threadIdx.x;
         const bool act = p < n && e.w[p] != R(0);
-        const int key = act ? tile_key3(g, tl, e.x[p], e.y[p], e.z[p]) : 0;
+        const int key = act ? tile_key3(g, tl, fold3(g, 0, e.x[p]), fold3(g, 1, e.y[p]), fold3(g, 2, e.z[p])) : 0;
         bf::wave_slot(counts, key, act);
     }
 }
@@ -1800,7 +1805,7 @@ __global__ void __launch_bounds__(NT) k3_sort_scatter_e(G3 g, Tiles3 tl, E3<R> s
         double x = 0, y = 0, z = 0;
         int key = 0;
         if (act) {
-            x = src.x[p]; y = src.y[p]; z = src.z[p];
+            x = fold3(g, 0, src.x[p]); y = fold3(g, 1, src.y[p]); z = fold3(g, 2, src.z[p]);
             key = tile_key3(g, tl, x, y, z);
         }
         const int d = bf::wave_slot(cursor, key, act);
@@ -2362,27 +2367,29 @@ void launch3_zero_j(const G3& g, const F3<R>& f, hipStream_t s)
     hipLaunchKernelGGL(k3_zero3, cells_grid(g), cells_block(), 0, s, g, f.J[0], f.J[1], f.J[2]);
 }
 
+// a kernel and not a memset: the step may be captured into a graph
+__global__ void k3_clear_count(int* n) { *n = 0; }
+
 template <typename R, bool MC>
 void gpd_launch(const G3& g, const F3<R>& f, const E3<R>& e, const Seg3* seg, const Box3* bin, Box3* bout,
-                int nseg, const Push3& pp, int pz, int* status, int* lists, int2* mis, hipStream_t s)
+                int nseg, const Push3& pp, int pz, int* status, int* nmis, int2* mis, hipStream_t s)
 {
     const size_t lds = (size_t)BPL * pz * box_cell_bytes<R>();
-    int *nbig = lists, *nmis = lists + 1, *big = lists + 2;
-    (void)hipMemsetAsync(lists, 0, 2 * sizeof(int), s);
+    hipLaunchKernelGGL(k3_clear_count, dim3(1), dim3(1), 0, s, nmis);
     (void)hipFuncSetAttribute((const void*)k3_gpd<R, MC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((k3_gpd<R, MC>), dim3(nseg), dim3(GT), lds, s, g, f, e, seg, bin, bout, pp, pz, status, big,
-                       nbig, mis, nmis);
-    hipLaunchKernelGGL((k3_gpd_hbm<R, MC>), dim3(std::min(HBM_GRID, nseg)), dim3(NT), 0, s, g, f, e, seg, bout, pp,
-                       status, big, nbig, mis, nmis);
+    hipLaunchKernelGGL((k3_gpd<R, MC>), dim3(nseg), dim3(GT), lds, s, g, f, e, seg, bin, bout, pp, pz, status, mis,
+                       nmis);
+    hipLaunchKernelGGL((k3_gpd_hbm<R, MC>), dim3(std::min(HBM_GRID, nseg)), dim3(NT), 0, s, g, f, e, bout, pp, status,
+                       mis, nmis);
 }
 
 template <typename R>
 void launch3_gpd(const G3& g, const F3<R>& f, const E3<R>& e, const Seg3* seg, const Box3* bin, Box3* bout,
-                 int nseg, const Push3& pp, int pz, int* status, int* lists, int2* mis, bool mc, hipStream_t s)
+                 int nseg, const Push3& pp, int pz, int* status, int* nmis, int2* mis, bool mc, hipStream_t s)
 {
     if (nseg <= 0) return;
-    if (mc) gpd_launch<R, true>(g, f, e, seg, bin, bout, nseg, pp, pz, status, lists, mis, s);
-    else gpd_launch<R, false>(g, f, e, seg, bin, bout, nseg, pp, pz, status, lists, mis, s);
+    if (mc) gpd_launch<R, true>(g, f, e, seg, bin, bout, nseg, pp, pz, status, nmis, mis, s);
+    else gpd_launch<R, false>(g, f, e, seg, bin, bout, nseg, pp, pz, status, nmis, mis, s);
 }
 
 // ---- momentum-conserving gather: fields to the nodes ---------------------------------------------

@@ -154,6 +154,34 @@ def test_3d_spreading_segments_match_oracle(real, tol):
 
 
 @gpu
+@pytest.mark.parametrize("real,tol,gather", [("f64", 1e-11, 0), ("f32", 1e-5, 0), ("f32", 1e-5, 1)])
+@pytest.mark.parametrize("box", [(37, 9, 31), (15, 21, 16)])
+def test_3d_clamped_windows_match_oracle(real, tol, gather, box):
+    # absorbing faces and no re-sort: most tiles outgrow the staged box along one axis or more and
+    # stage the window around their mean position, the particles outside it going through HBM
+    nx, ny, nz = box
+    d = (0.1, 0.11, 0.09)
+    cfg = pi.make_config3(nx, ny, nz, *d, pml_cells=6, ck="ck2", theta=0.1, filter_npass=1, real=real, seed=6,
+                          gather_kind=gather)
+    from paper_1009_2727_amd import Sim
+    sim = Sim(cfg, capacity=9000, sort_every=1000)
+    ref = Oracle3(cfg)
+    for k, name in enumerate(["Ex", "Ey", "Ez", "Bx", "By", "Bz"]):
+        f = pi.random_field(ref.shape, seed=310 + k, amp=0.2)
+        ref.set_field(name, f)
+        sim.set_field(name, f)
+    p = pi.random_electrons3(8000, nx, ny, nz, d, seed=13, umax=4.0, margin=0.5)
+    ref.set_electrons(p)
+    sim.load_electrons(p)
+    ref.step(7)
+    sim.step(7)
+    assert sim.sync_status() == 0
+    for n in FIELDS:
+        a, b = sim.field(n), ref.field(n)
+        assert np.abs(a - b).max() <= tol * max(np.abs(b).max(), 1.0), n
+
+
+@gpu
 def test_3d_full_size_faraday_and_sampled_electrons_match_oracle():
     # The 3D workload at its full size (128x128x1024, 8 ppc, 134 M electrons) in the benchmark's
     # launch configuration (default tiles, sort every 80 steps).  After three steps the fields

@@ -651,6 +651,13 @@ void learned_filter(bf_sim* s, const FieldSet<float>& f)
     s->run([=](hipStream_t st) { lf::forward_fused(a.in, a.out, a.d, 3, pk, st); });
 }
 
+// the one-launch filter continues a line oddly about its ends: it needs 2 reach + 3 cells on a
+// non-periodic axis
+bool filter_fits(const Geo& g, int reach)
+{
+    return (g.perx || g.Sx >= 2 * reach + 3) && (g.perz || g.Sz >= 2 * reach + 3);
+}
+
 // batched recording is FP32 only (a batch is created from FP32 runs)
 template <typename R>
 BatchRec* batch_rec(bf_sim* s)
@@ -787,41 +794,53 @@ bf_status step_impl(bf_sim* s, int nsteps)
             s->run([=](hipStream_t st) { launch_antenna<R>(g, f, xm, ap, st); });
         }
         s->tock(t_ph, BF_PHASE_ANTENNA);
-        // filter
+        // filter, then Ampere + PML (E^{n+1} into the E^{n-1} set); unit-stride passes and Ampere
+        // are one launch, timed as the filter phase
         s->slot = SLOT_FILTER;
         t_ph = s->tick();
+        bool advanced = false;
         if (c.filter_kind == BF_FILTER_LEARNED) {
             if constexpr (sizeof(R) == 4) learned_filter(s, f);
         } else if (c.filter_npass > 0) {
-            // the line filter, one run at a time also in a batch (per run it beats the batched
-            // tile filter)
             bf3::FiltSeq fs;
             bf3::filter_seq(c.filter_npass, c.filter_compensate, c.filter_strides, &fs);
-            const bf3::G3 g3 = g3_of(g, c);
-            const FieldSet<R> ff = f;
-            R* tmp0 = s->arr<R>(A_JT);
-            R* tmp1 = s->arr<R>(A_JT + 1);
-            R* tmp2 = s->arr<R>(A_JT + 2);
-            s->run([=](hipStream_t st) {
-                R* in[3] = {ff.J[0], ff.J[1], ff.J[2]};
-                R* out[3] = {ff.Jf[0], ff.Jf[1], ff.Jf[2]};
-                R* tmp[3] = {tmp0, tmp1, tmp2};
-                const int hx[3] = {1, 0, 0}, hz[3] = {0, 0, 1};
-                bf3::launch_filter_xz<R>(g3, in, tmp, out, hx, hz, 3, fs, st);
-            });
-        }
-        s->tock(t_ph, BF_PHASE_FILTER);
-        // Ampere + PML (E^{n+1} into the E^{n-1} set)
-        s->slot = SLOT_AMPERE;
-        t_ph = s->tick();
-        if constexpr (sizeof(R) == 4) {
-            if (rb) {
-                const int gx = (g.Sx + 63) / 64, gz = (g.Sz + 3) / 4;
-                rb->ampere.push_back(AmpereDesc<float>{g, f, pm, (float)sc.dt, (float)sc.idx, (float)sc.idz, gx});
-                rb->n_ampere.push_back(gx * gz);
+            bf3::FiltStencil fst;
+            if (bf3::unit_stencil(fs, fst) && filter_fits(g, fs.reach)) {
+                Stencil2 st2;
+                st2.reach = fs.reach;
+                for (int m = 0; m < 7; m++) st2.c[m] = fst.c[m];
+                // one launch per run also in a batch: each fills the chip by itself
+                s->run([=](hipStream_t st) { launch_filter_ampere<R>(g, f, pm, st2, sc, st); });
+                advanced = true;
+            } else {
+                // strided passes: the line filter, one run at a time also in a batch
+                const bf3::G3 g3 = g3_of(g, c);
+                const FieldSet<R> ff = f;
+                R* tmp0 = s->arr<R>(A_JT);
+                R* tmp1 = s->arr<R>(A_JT + 1);
+                R* tmp2 = s->arr<R>(A_JT + 2);
+                s->run([=](hipStream_t st) {
+                    R* in[3] = {ff.J[0], ff.J[1], ff.J[2]};
+                    R* out[3] = {ff.Jf[0], ff.Jf[1], ff.Jf[2]};
+                    R* tmp[3] = {tmp0, tmp1, tmp2};
+                    const int hx[3] = {1, 0, 0}, hz[3] = {0, 0, 1};
+                    bf3::launch_filter_xz<R>(g3, in, tmp, out, hx, hz, 3, fs, st);
+                });
             }
         }
-        if (!rb) launch_ampere<R>(g, f, pm, sc, s->stream);
+        s->tock(t_ph, BF_PHASE_FILTER);
+        s->slot = SLOT_AMPERE;
+        t_ph = s->tick();
+        if (!advanced) {
+            if constexpr (sizeof(R) == 4) {
+                if (rb) {
+                    const int gx = (g.Sx + 63) / 64, gz = (g.Sz + 3) / 4;
+                    rb->ampere.push_back(AmpereDesc<float>{g, f, pm, (float)sc.dt, (float)sc.idx, (float)sc.idz, gx});
+                    rb->n_ampere.push_back(gx * gz);
+                }
+            }
+            if (!rb) launch_ampere<R>(g, f, pm, sc, s->stream);
+        }
         s->tock(t_ph, BF_PHASE_AMPERE);
         s->e_cur ^= 1;
         s->b_cur ^= 1;

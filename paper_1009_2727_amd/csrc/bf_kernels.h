@@ -169,6 +169,17 @@ void launch_faraday(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm, con
 template <typename R>
 void launch_ampere(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm, const SolverCoef& c,
                    hipStream_t s);
+// one axis of a sequence of unit-stride filter passes as a symmetric stencil: c[m] weights the
+// values m cells to either side
+struct Stencil2 {
+    int reach;
+    double c[7];
+};
+// the filter along x and z (raw J into Jf) and Ampere with the result; 1 <= reach <= 6, and at
+// least 2 reach + 3 stored cells on a non-periodic axis
+template <typename R>
+void launch_filter_ampere(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm, const Stencil2& st,
+                          const SolverCoef& c, hipStream_t s);
 template <typename R>
 struct PtrList {
     R* p[32];

@@ -125,6 +125,14 @@ struct FiltSeq {
 };
 // builds the sequence; false when it exceeds FSEQ_MAX passes or FREACH_MAX cells of reach
 bool filter_seq(int npass, int comp, int stride_mask, FiltSeq* fs);
+// a sequence of unit-stride passes along one axis as one symmetric stencil (the product of its
+// 3-point stencils): c[m] weights the values m cells to either side; false for strided passes, no
+// passes, and reaches beyond FT_RMAX
+constexpr int FT_RMAX = 6;
+struct FiltStencil {
+    double c[FT_RMAX + 1];
+};
+bool unit_stencil(const FiltSeq& fs, FiltStencil& st);
 // the whole filter on J (FP64 accumulators) into the run's type, one launch per axis for the
 // three components (Jf <- J along x, Jg <- Jf along y, Jf <- Jg along z); out[] receives each
 // component's result.  Without passes J is copied into Jf.

@@ -444,12 +444,8 @@ __global__ void __launch_bounds__(NT) k3_fline(G3 g, Lines3<TI, TO> L, FiltSeq f
 // copy column and the y copy row are staged beside the tile, the z copy plane is written as it
 // is filtered.  Consecutive work items (neighbouring y tiles at the same z run) go to the same
 // XCD so that the reach they share is read once from its L2.
-constexpr int FT_TX = 32, FT_TY = 32, FT_QY = 4, FT_NT = 256, FT_RMAX = 6;
+constexpr int FT_TX = 32, FT_TY = 32, FT_QY = 4, FT_NT = 256;
 static_assert(FT_TX * FT_TY == FT_NT * FT_QY, "one thread per x column and FT_QY rows");
-
-struct FiltStencil {
-    double c[FT_RMAX + 1];
-};
 
 template <typename T> struct Vec16;
 template <> struct Vec16<float> {
@@ -2210,9 +2206,7 @@ void fline(const G3& g, const Lines3<TI, TO>& L, int ncomp, const FiltSeq& fs, h
                        ncolb);
 }
 
-// the stencil of a sequence of unit-stride passes (the product of its 3-point stencils); false
-// for strided passes and for reaches beyond FT_RMAX
-static bool unit_stencil(const FiltSeq& fs, FiltStencil& st)
+bool unit_stencil(const FiltSeq& fs, FiltStencil& st)
 {
     const int R = fs.reach;
     if (fs.n < 1 || R < 1 || R > FT_RMAX) return false;

@@ -682,7 +682,7 @@ bf_status step_impl(bf_sim* s, int nsteps)
         hipEvent_t t_ph = s->tick();
         if constexpr (sizeof(R) == 4) {
             if (rb) {
-                const int gx = (g.Sx + 63) / 64, gz = (g.Sz + 3) / 4;
+                const int gx = (g.Sx + FARADAY_TX - 1) / FARADAY_TX, gz = (g.Sz + FARADAY_TZ - 1) / FARADAY_TZ;
                 rb->faraday.push_back(FaradayDesc<float>{g, f, pm, (float)sc.dt, (float)sc.a2, (float)sc.b2,
                                                          (float)sc.theta, (float)sc.idx, (float)sc.idz,
                                                          sc.theta > 0.0 ? 1 : 0, gx});

@@ -127,13 +127,14 @@ struct StationParams {
 };
 
 // ---- batched runs: per-run arguments of the persistent launch of each phase ------------
+constexpr int FARADAY_TX = 32, FARADAY_TZ = 8;   // cells of a Faraday workgroup
 template <typename R>
 struct FaradayDesc {
     Geo g;
     FieldSet<R> f;
     PmlTab<R> pm;
     R dt, a2, b2, th, idx, idz;
-    int fried, gx;     // Friedman on; blocks per row of the 64 x 4 block grid
+    int fried, gx;     // Friedman on; blocks per row of the grid of Faraday tiles
 };
 template <typename R>
 struct AmpereDesc {

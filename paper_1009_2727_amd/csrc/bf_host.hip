@@ -1222,7 +1222,7 @@ hipError_t inject3(bf_sim* s, int64_t nrows)
     ip.uz0 = -s->gamma * s->beta;
     ip.shift = (double)s->shift;
     int* nu = w3<int>(s, L.w_nused);
-    bf3::launch3_inject<R>(L.g, L.tl, electrons3<R>(s, L.p_cur), ions3<R>(s, L.p_cur), nu, nu + 1, seg3<R>(s, 0),
+    bf3::launch3_inject<R>(L.g, L.tl, electrons3<R>(s, L.p_cur), ions3<R>(s, L.p_cur), nu, nu + 1, nu + 2, seg3<R>(s, 0),
                            box3(s, 0, L.bb_cur), seg3<R>(s, 1), box3(s, 1, L.bb_cur), L.nseg, ip,
                            w3<int>(s, L.w_status), s->stream);
     L.nseg += (int)nrows * chunks;
@@ -1252,14 +1252,13 @@ bf_status step3(bf_sim* s, int nsteps)
         bf3::F3<R> f = fields3<R>(s);
         const bf3::G3 g = L.g;
         hipEvent_t ev = s->tick();
-        bf3::launch3_faraday<R>(g, f, pml, ck, s->theta, s->dt, s->stream);
+        bf3::launch3_faraday<R>(g, f, pml, ck, s->theta, s->dt, w3<int>(s, L.w_nmis), s->stream);
         if (s->theta > 0.0) {   // the new Friedman average is in the other buffer
             L.eb_cur ^= 1;
             f = fields3<R>(s);
         }
         bf3::launch3_stations<R>(g, f, w3<double>(s, L.w_st_z), s->nst, s->gamma, s->beta, s->t, (double)s->shift,
                                  w3<double>(s, L.w_st_rec), w3<int>(s, L.w_st_cnt), L.stcap, s->stream);
-        bf3::launch3_zero_j<R>(g, f, s->stream);        // the current of this step starts at zero
         s->tock(ev, BF_PHASE_FARADAY);
         // the window shift at the end of this step (particles are rebased in the push)
         const double t1 = (double)(s->step + 1) * s->dt;

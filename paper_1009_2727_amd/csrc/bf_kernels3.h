@@ -106,10 +106,11 @@ struct Antenna3 {
 constexpr int ST3_CAPACITY = 1, ST3_NONFINITE = 2;
 
 // Faraday + PML, with Friedman's E-tilde (theta > 0) made from E, E^{n-1} and Ebar on the fly;
-// the new Ebar is written to f.T (the caller swaps the two Ebar buffers after the step)
+// the new Ebar is written to f.T (the caller swaps the two Ebar buffers after the step).  Clears
+// the current accumulators and *nmis for the step's deposit
 template <typename R>
 void launch3_faraday(const G3& g, const F3<R>& f, const Pml3& pml, const double ck[3], double theta, double dt,
-                     hipStream_t s);
+                     int* nmis, hipStream_t s);
 template <typename R>
 void launch3_ampere(const G3& g, const F3<R>& f, const R* const J[3], const Pml3& pml, double dt, hipStream_t s);
 // The passes of the current filter along one axis (Sec. 4.1, Eqs. 3ptfilter and
@@ -153,11 +154,10 @@ double* launch3_filter_nodal(const G3& g, double* a, double* b, double* c, const
 template <typename R>
 void launch3_rho(const G3& g, const E3<R>& e, int ne, const I3<R>& ion, int ni, double zsh, const double* ant,
                  int na, int pol, double za, double aw, double vol_inv, double* rho, hipStream_t s);
-template <typename R> void launch3_zero_j(const G3& g, const F3<R>& f, hipStream_t s);
 // gather, push and deposit of the electrons of nseg segments (one workgroup each); bin holds
 // each segment's cell box at the start of the step, bout receives the box after the push (in
 // the next window frame); pz = z planes of the LDS box
-// nmis: one int of scratch, mis: one int2 per particle slot (particles outside their segment's
+// nmis: one int, zero before the call, mis: one int2 per particle slot (particles outside their segment's
 // staged box are pushed in a second pass, on HBM)
 template <typename R>
 void launch3_gpd(const G3& g, const F3<R>& f, const E3<R>& e, const Seg3* seg, const Box3* bin, Box3* bout,
@@ -177,8 +177,8 @@ void launch3_antenna(const G3& g, const F3<R>& f, double* xm, const double* xh, 
 // c of plane r becomes segment seg_base + r * chunks + c (table and box of each species)
 template <typename R>
 void launch3_inject(const G3& g, const Tiles3& tl, const E3<R>& e, const I3<R>& ion, int* nused_e, int* nused_i,
-                    Seg3* seg_e, Box3* box_e, Seg3* seg_i, Box3* box_i, int seg_base, const Inject3& ip,
-                    int* status, hipStream_t s);
+                    int* ticket, Seg3* seg_e, Box3* box_e, Seg3* seg_i, Box3* box_i, int seg_base,
+                    const Inject3& ip, int* status, hipStream_t s);
 // window moved by d planes (zoff already advanced): clear the planes that wrapped round, drop
 // split parts in planes that just left the z PML, keep tangential E zero on the end walls
 template <typename R>
@@ -186,8 +186,8 @@ void launch3_window(const G3& g, const F3<R>& f, const Pml3& pml, int d, hipStre
 // counting sort of the live particles (w != 0) of slots [0, *nused) of src by tile, through dst
 // (scatter by tile into dst, then each tile back into src in plasma-lattice order, ppc
 // particles per lattice cell):
-// segment t = tile t with its cell box, *nused = live count; counts/cursor hold ntiles ints,
-// tot one int of scratch.  Ions are binned at z0 - zsh.
+// segment t = tile t with its cell box, *nused = live count; counts/cursor hold ntiles ints
+// (counts zero before the call and after it), tot one int of scratch.  Ions are binned at z0 - zsh.
 template <typename R>
 void launch3_sort_e(const G3& g, const Tiles3& tl, const E3<R>& src, const E3<R>& dst, int* nused, int* counts,
                     int* cursor, int* tot, Seg3* seg, Box3* box, int64_t cap, int ppc, hipStream_t s);

@@ -77,13 +77,20 @@ static_assert(CBX * CBY == NT, "per-cell launches use NT threads");
 
 // ---- field solver ---------------------------------------------------------------------------
 
-// split update of one component from its curl terms t1 (axis A1, the stored part) and t2
-template <int A1, int A2, typename R>
-__device__ __forceinline__ R split_update(R old, R* sp, long o, R t1, R t2, const Pml3& pml, const int q[3],
-                                          const int h[3], R dt)
+// a component of stagger h at stored index q of axis a lies in the absorbing layer (sigma > 0)
+__device__ __forceinline__ bool in_layer(const G3& g, int a, int q, int h)
 {
-    const double s1 = pml.sig[A1][h[A1]][q[A1]], s2 = pml.sig[A2][h[A2]][q[A2]];
-    if (s1 == 0.0 && s2 == 0.0) return old + dt * (t1 + t2);
+    const int p2 = 2 * (q - g.P[a]) + h;   // twice the interior position
+    return !g.per[a] && (p2 < 0 || p2 > 2 * g.N[a]);
+}
+
+// split update of one component from its curl terms t1 (axis A1, the stored part) and t2; the
+// coefficient tables are read inside the layer only
+template <int A1, int A2, typename R>
+__device__ __forceinline__ R split_update(const G3& g, R old, R* sp, long o, R t1, R t2, const Pml3& pml,
+                                          const int q[3], const int h[3], R dt)
+{
+    if (!in_layer(g, A1, q[A1], h[A1]) && !in_layer(g, A2, q[A2], h[A2])) return old + dt * (t1 + t2);
     const R x1 = (R)pml.xi[A1][h[A1]][q[A1]], c1 = (R)pml.c[A1][h[A1]][q[A1]];
     const R x2 = (R)pml.xi[A2][h[A2]][q[A2]], c2 = (R)pml.c[A2][h[A2]][q[A2]];
     R p1 = sp[o];
@@ -95,14 +102,27 @@ __device__ __forceinline__ R split_update(R old, R* sp, long o, R t1, R t2, cons
 }
 
 // Faraday with Friedman's E-tilde made on the fly.  A workgroup owns a 32 x 8 tile of (x, y)
-// and FMZ planes along z; it marches up z keeping three planes (k - 1, k, k + 1) of E-tilde with
+// and a run of planes along z; it marches up z keeping three planes (k - 1, k, k + 1) of E-tilde with
 // a one-cell (x, y) halo in LDS, so each E value is read from HBM once per tile instead of once
 // per stencil point.  Delta* (Sec. 4.2) reaches one cell along every axis.  With Friedman
 // damping (Sec. 4.3), E-tilde = (1 + theta/4) E^n - E^{n-1}/2 + (1/2 - theta/4) Ebar^n with the
 // recursion Ebar^n = (1 - theta/2) E^{n-1} + (theta/2) Ebar^{n-1}; the new Ebar goes to the
 // second Ebar buffer (f.T), written by the tile that owns the cell, so no workgroup reads a
 // value another one has already replaced.  Cells beyond a non-periodic edge read 0.
-constexpr int FMX = CBX, FMY = CBY, FMZ = 16;
+constexpr int FMX = CBX, FMY = CBY;
+// Planes of a workgroup's run: 16, halved while the launch has less than two workgroups per CU.  A
+// run's planes are one serial chain of about 4 us each, so short runs win on small boxes although
+// each adds two border planes: 33 x 31 x 69 cells in FP64 80 -> FARADAY_TINY us for Faraday.
+// Longer runs than 16 measured slower on large boxes (0.95 ms at 32 against 0.90 ms).
+constexpr int FMZ = 16, FMZ_MIN = 2;
+
+inline int run_planes(const G3& g)
+{
+    const long tiles = (long)((g.S[0] + FMX - 1) / FMX) * ((g.S[1] + FMY - 1) / FMY);
+    int n = FMZ;
+    while (n > FMZ_MIN && tiles * ((g.S[2] + n - 1) / n) < 512) n /= 2;
+    return n;
+}
 constexpr int FPX = FMX + 2, FPP = (FMX + 2) * (FMY + 2);
 
 // Delta*_AX of one E-tilde component from the three LDS planes pl[0..2] = k - 1, k, k + 1 at
@@ -148,7 +168,7 @@ __device__ __forceinline__ void faraday_cell(const G3& g, const F3<R>& f, const 
     const R* p1[3] = {sT[sl[0]][A1], sT[sl[1]][A1], sT[sl[2]][A1]};
     const R t1 = -dstar_lds<A1>(p2, cx, cy, h[A1], a, b, cg, (R)(1.0 / g.d[A1]));
     const R t2 = dstar_lds<A2>(p1, cx, cy, h[A2], a, b, cg, (R)(1.0 / g.d[A2]));
-    f.B[C][o] = split_update<A1, A2>(old, f.SB[C], o, t1, t2, pml, q, h, dt);
+    f.B[C][o] = split_update<A1, A2>(g, old, f.SB[C], o, t1, t2, pml, q, h, dt);
 }
 
 // the E-tilde inputs of the padded-plane cells a thread loads (two at most: FPP <= 2 NT)
@@ -160,13 +180,15 @@ struct PlaneRegs {
 };
 
 template <typename R, bool FRIED>
-__global__ void __launch_bounds__(NT) k3_faraday(G3 g, F3<R> f, Pml3 pml, R a, R b, R cg, R dt, R th)
+__global__ void __launch_bounds__(NT) k3_faraday(G3 g, F3<R> f, Pml3 pml, R a, R b, R cg, R dt, R th, int run,
+                                                  int* nmis)
 {
     static_assert(FPP <= 2 * NT, "a thread loads at most two cells of a padded plane");
     __shared__ R sT[3][3][FPP];   // [ring slot][component][padded plane cell]
     const int tid = (int)(threadIdx.y * FMX + threadIdx.x);
     const int x0 = (int)blockIdx.x * FMX, y0 = (int)blockIdx.y * FMY;
-    const int k0 = (int)blockIdx.z * FMZ, k1 = min(k0 + FMZ, g.S[2]);
+    const int k0 = (int)blockIdx.z * run, k1 = min(k0 + run, g.S[2]);
+    if (nmis && blockIdx.x + blockIdx.y + blockIdx.z == 0 && tid == 0) *nmis = 0;
     // issue the loads of plane kk (stored z index, k0 - 1 .. k1); they complete while the
     // previous plane is computed
     auto fetch = [&](int kk, PlaneRegs<R>& r) {
@@ -231,6 +253,10 @@ __global__ void __launch_bounds__(NT) k3_faraday(G3 g, F3<R> f, Pml3 pml, R a, R
             faraday_cell<0>(g, f, pml, sT, sl, q, o, cx, cy, a, b, cg, dt);
             faraday_cell<1>(g, f, pml, sT, sl, q, o, cx, cy, a, b, cg, dt);
             faraday_cell<2>(g, f, pml, sT, sl, q, o, cx, cy, a, b, cg, dt);
+            // the current of this step starts at zero; the last step's stays readable until here
+            f.J[0][o] = 0.0;
+            f.J[1][o] = 0.0;
+            f.J[2][o] = 0.0;
         }
         __syncthreads();
     }
@@ -239,7 +265,7 @@ __global__ void __launch_bounds__(NT) k3_faraday(G3 g, F3<R> f, Pml3 pml, R a, R
 // dE_C/dt = Delta_A1 B_A2 - Delta_A2 B_A1 - J_C; E_C sits on a half node along C, nodes along
 // A1, A2, so each difference takes B at the cell and one cell below; conducting walls keep the
 // tangential components at 0 (nodes 0 and S-1 of a non-periodic axis stay untouched).  A
-// workgroup owns a 32 x 8 (x, y) tile and FMZ planes and marches up z with planes k - 1 and k of
+// workgroup owns a 32 x 8 (x, y) tile and a run of planes and marches up z with planes k - 1 and k of
 // B (and the cells one below in x and y) in LDS, loading plane k + 1 while computing plane k.
 constexpr int APX = FMX + 1, APP = (FMX + 1) * (FMY + 1);
 
@@ -266,18 +292,19 @@ __device__ __forceinline__ void ampere_cell(const G3& g, const F3<R>& f, const R
     };
     const R t1 = diff(A2, A1) - J[C][o];
     const R t2 = -diff(A1, A2);
-    f.E[C][o] = split_update<A1, A2>(old, f.SE[C], o, t1, t2, pml, q, h, dt);
+    f.E[C][o] = split_update<A1, A2>(g, old, f.SE[C], o, t1, t2, pml, q, h, dt);
 }
 
 template <typename R>
-__global__ void __launch_bounds__(NT) k3_ampere(G3 g, F3<R> f, const R* J0, const R* J1, const R* J2, Pml3 pml, R dt)
+__global__ void __launch_bounds__(NT) k3_ampere(G3 g, F3<R> f, const R* J0, const R* J1, const R* J2, Pml3 pml, R dt,
+                                                 int run)
 {
     static_assert(APP <= 2 * NT, "a thread loads at most two cells of a padded plane");
     __shared__ R sB[2][3][APP];
     const R* J[3] = {J0, J1, J2};
     const int tid = (int)(threadIdx.y * FMX + threadIdx.x);
     const int x0 = (int)blockIdx.x * FMX, y0 = (int)blockIdx.y * FMY;
-    const int k0 = (int)blockIdx.z * FMZ, k1 = min(k0 + FMZ, g.S[2]);
+    const int k0 = (int)blockIdx.z * run, k1 = min(k0 + run, g.S[2]);
     R rv[2][3];
     auto fetch = [&](int kk) {
         const int kz = nb(kk, 0, g.S[2], g.per[2]);
@@ -752,16 +779,6 @@ __global__ void __launch_bounds__(FT_NT) k3_filt3(G3 g, Lines3<double, TO> L, Fi
     }
 }
 
-__global__ void __launch_bounds__(NT) k3_zero3(G3 g, double* a, double* b, double* c)
-{
-    int q[3];
-    if (!cell_of(g, q)) return;
-    const long o = o3(g, q[0], q[1], q[2]);
-    a[o] = 0.0;
-    b[o] = 0.0;
-    c[o] = 0.0;
-}
-
 // ---- particles --------------------------------------------------------------------------------
 
 // cubic B-spline weights of nodes j0-1 .. j0+2 for a particle at fraction f of cell j0
@@ -838,8 +855,13 @@ __device__ void gather3(const G3& g, const F3<R>& f, const double r[3], R E[3], 
 // Esirkepov's 3D deposit of one particle moving r0 -> r1 (cells, |move| < 1 cell per axis):
 //   W_C = DS_C (S0_A1 S0_A2 + DS_A1 S0_A2 / 2 + S0_A1 DS_A2 / 2 + DS_A1 DS_A2 / 3),
 //   J_C(node + 1/2) - J_C(node - 1/2) = k_C W_C   (k_C = -q w / (d_A1 d_A2 dt))
-__device__ void esirkepov3(const G3& g, double* const* J, const double r0[3], const double r1[3], const double k[3])
+// here node m1 of the window along A1, (C, A1, A2) cyclic
+template <int C>
+__device__ __forceinline__ void esirkepov3_row(const G3& g, double* const* J, const double r0[3], const double r1[3],
+                                               double k, int m1)
 {
+    constexpr int A1 = (C + 1) % 3, A2 = (C + 2) % 3;
+    if (k == 0.0) return;
     double S0[3][5], DS[3][5];
     int base[3];
 #pragma unroll
@@ -853,35 +875,47 @@ __device__ void esirkepov3(const G3& g, double* const* J, const double r0[3], co
 #pragma unroll
         for (int m = 0; m < 5; m++) DS[a][m] = s1[m] - S0[a][m];
     }
+    const int s1 = sidx(g, A1, base[A1] + m1);
+    if (s1 < 0) return;
+    double sa = 0.0, da = 0.0;
 #pragma unroll
-    for (int c = 0; c < 3; c++) {
-        if (k[c] == 0.0) continue;
-        const int a1 = (c + 1) % 3, a2 = (c + 2) % 3;
-        int sc[4];
-#pragma unroll
-        for (int m = 0; m < 4; m++) sc[m] = sidx(g, c, base[c] + m);
-        for (int m1 = 0; m1 < 5; m1++) {
-            const int s1 = sidx(g, a1, base[a1] + m1);
-            if (s1 < 0) continue;
-            for (int m2 = 0; m2 < 5; m2++) {
-                const int s2 = sidx(g, a2, base[a2] + m2);
-                if (s2 < 0) continue;
-                const double T = S0[a1][m1] * S0[a2][m2] + 0.5 * DS[a1][m1] * S0[a2][m2] +
-                                 0.5 * S0[a1][m1] * DS[a2][m2] + DS[a1][m1] * DS[a2][m2] * (1.0 / 3.0);
-                if (T == 0.0) continue;
-                double acc = 0.0;
-#pragma unroll
-                for (int mc = 0; mc < 4; mc++) {
-                    acc += k[c] * DS[c][mc] * T;
-                    if (acc == 0.0 || sc[mc] < 0) continue;
-                    int q[3];
-                    q[c] = sc[mc];
-                    q[a1] = s1;
-                    q[a2] = s2;
-                    atomicAdd(&J[c][o3(g, q[0], q[1], q[2])], acc);
-                }
-            }
+    for (int m = 0; m < 5; m++)
+        if (m == m1) {
+            sa = S0[A1][m];
+            da = DS[A1][m];
         }
+    int sc[4];
+    double kp[4], pd = 0.0;
+#pragma unroll
+    for (int m = 0; m < 4; m++) {
+        sc[m] = sidx(g, C, base[C] + m);
+        pd += k * DS[C][m];
+        kp[m] = pd;
+    }
+#pragma unroll
+    for (int m2 = 0; m2 < 5; m2++) {
+        const int s2 = sidx(g, A2, base[A2] + m2);
+        const double T = sa * (S0[A2][m2] + 0.5 * DS[A2][m2]) + da * (0.5 * S0[A2][m2] + DS[A2][m2] * (1.0 / 3.0));
+        if (s2 < 0 || T == 0.0) continue;
+#pragma unroll
+        for (int mc = 0; mc < 4; mc++) {
+            const double v = kp[mc] * T;
+            if (v == 0.0 || sc[mc] < 0) continue;
+            int q[3];
+            q[C] = sc[mc];
+            q[A1] = s1;
+            q[A2] = s2;
+            atomicAdd(&J[C][o3(g, q[0], q[1], q[2])], v);
+        }
+    }
+}
+
+__device__ void esirkepov3(const G3& g, double* const* J, const double r0[3], const double r1[3], const double k[3])
+{
+    for (int m1 = 0; m1 < 5; m1++) {
+        esirkepov3_row<0>(g, J, r0, r1, k[0], m1);
+        esirkepov3_row<1>(g, J, r0, r1, k[1], m1);
+        esirkepov3_row<2>(g, J, r0, r1, k[2], m1);
     }
 }
 
@@ -1478,29 +1512,46 @@ __global__ void __launch_bounds__(GTI, 4) k3_gpi(G3 g, F3<R> f, I3<R> ion, const
 
 // laser antenna: per transverse cell a + particle fixed at the cell centre and a - particle
 // moving along the polarisation (x or y) with the sheet current K = -2 E_perp (FP64
-// throughout); xm holds the moving particle's coordinate along the polarisation
+// throughout); xm holds the moving particle's coordinate along the polarisation.  AT threads share
+// a pair, one for each current component and node along one of its transverse axes: one thread
+// per pair is a chain of up to 600 dependent adds, 40 us whatever the size of the plane
+// (ANTENNA_AFTER).
+constexpr int AT = 15, AP = 16;          // threads of a pair, pairs of a workgroup
 template <typename R>
-__global__ void __launch_bounds__(64) k3_antenna(G3 g, F3<R> f, double* xm, const double* xh, const double* yh,
-                                                 Antenna3 a, Push3 pp)
+__global__ void __launch_bounds__(AT * AP) k3_antenna(G3 g, F3<R> f, double* xm, const double* xh, const double* yh,
+                                                      Antenna3 a, Push3 pp)
 {
-    const int q = blockIdx.x * 64 + threadIdx.x;
-    if (q >= a.n) return;
-    const double xu = xh[q] * g.d[0], yu = yh[q] * g.d[1];
-    const double tau = a.tm / a.gamma - a.t0;
-    const double r2 = (xu - a.xc) * (xu - a.xc) + (yu - a.yc) * (yu - a.yc);
-    const double E = a.e0g * exp(-r2 / (a.w0 * a.w0)) * exp(-tau * tau / (2.0 * a.sig_t * a.sig_t)) * sin(a.omega * tau);
-    const double K = -2.0 * E;
-    const double v = K * g.d[0] * g.d[1] / (-1.0 * a.aw);    // um per unit time, along pol
-    const double x0 = xm[q], x1 = x0 + v * pp.dt / g.d[a.pol];
-    double m0[3] = {xh[q], yh[q], a.za}, m1[3] = {xh[q], yh[q], a.zb};
-    m0[a.pol] = x0;
-    m1[a.pol] = x1;
-    const double km[3] = {pp.jk[0] * a.aw, pp.jk[1] * a.aw, pp.jk[2] * a.aw};   // q = -1
-    esirkepov3(g, f.J, m0, m1, km);
-    const double h0[3] = {xh[q], yh[q], a.za}, h1[3] = {xh[q], yh[q], a.zb};
-    const double kp[3] = {-km[0], -km[1], -km[2]};                           // q = +1
-    esirkepov3(g, f.J, h0, h1, kp);
-    xm[q] = x1;
+    const int part = (int)threadIdx.x / AP, q = blockIdx.x * AP + (int)threadIdx.x % AP;
+    double x1 = 0.0;
+    if (q < a.n) {
+        const double xu = xh[q] * g.d[0], yu = yh[q] * g.d[1];
+        const double tau = a.tm / a.gamma - a.t0;
+        const double r2 = (xu - a.xc) * (xu - a.xc) + (yu - a.yc) * (yu - a.yc);
+        const double E = a.e0g * exp(-r2 / (a.w0 * a.w0)) * exp(-tau * tau / (2.0 * a.sig_t * a.sig_t)) * sin(a.omega * tau);
+        const double K = -2.0 * E;
+        const double v = K * g.d[0] * g.d[1] / (-1.0 * a.aw);    // um per unit time, along pol
+        const double x0 = xm[q];
+        x1 = x0 + v * pp.dt / g.d[a.pol];
+        double m0[3] = {xh[q], yh[q], a.za}, m1[3] = {xh[q], yh[q], a.zb};
+        m0[a.pol] = x0;
+        m1[a.pol] = x1;
+        const double km[3] = {pp.jk[0] * a.aw, pp.jk[1] * a.aw, pp.jk[2] * a.aw};   // q = -1
+        const double h0[3] = {xh[q], yh[q], a.za}, h1[3] = {xh[q], yh[q], a.zb};
+        const double kp[3] = {-km[0], -km[1], -km[2]};                           // q = +1
+        const int row = part % 5;
+        if (part < 5) {
+            esirkepov3_row<0>(g, f.J, m0, m1, km[0], row);
+            esirkepov3_row<0>(g, f.J, h0, h1, kp[0], row);
+        } else if (part < 10) {
+            esirkepov3_row<1>(g, f.J, m0, m1, km[1], row);
+            esirkepov3_row<1>(g, f.J, h0, h1, kp[1], row);
+        } else {
+            esirkepov3_row<2>(g, f.J, m0, m1, km[2], row);
+            esirkepov3_row<2>(g, f.J, h0, h1, kp[2], row);
+        }
+    }
+    __syncthreads();                     // every thread of the pair has read xm
+    if (part == 0 && q < a.n) xm[q] = x1;
 }
 
 // ---- charge density (Gauss diagnostic) ---------------------------------------------------------
@@ -1572,17 +1623,12 @@ __device__ __forceinline__ double u01(uint64_t seed, uint64_t k)
 // chunk becomes a segment whose box spans its cells and the plane's z cells.  The particle id
 // (and so its random offsets) depends only on the plane, the cell and k.
 template <typename R>
-__global__ void __launch_bounds__(NT) k3_inject(G3 g, Tiles3 tl, E3<R> e, I3<R> ion, const int* nused_e,
-                                                const int* nused_i, Seg3* seg_e, Box3* box_e, Seg3* seg_i,
-                                                Box3* box_i, int seg_base, Inject3 ip, int* status)
+__device__ __forceinline__ void inject_one(const G3& g, const Tiles3& tl, const E3<R>& e, const I3<R>& ion, int be,
+                                           int bi, Seg3* seg_e, Box3* box_e, Seg3* seg_i, Box3* box_i, int seg_base,
+                                           const Inject3& ip, int* status, bool room, int64_t gq)
 {
     const int N0 = g.N[0], N1 = g.N[1], tx = tl.t[0], ty = tl.t[1];
     const int64_t per_plane = (int64_t)N0 * N1 * ip.ppc;
-    const int64_t total = per_plane * ip.nrows;
-    const int64_t gq = (int64_t)blockIdx.x * NT + threadIdx.x;
-    if (gq >= total) return;
-    const int be = *nused_e, bi = ip.ion_mode ? *nused_i : 0;
-    const bool room = (int64_t)be + total <= ip.cap && (int64_t)bi + total <= ip.cap;
     if (!room) {
         if (gq == 0) atomicOr(status, ST3_CAPACITY);
     }
@@ -1648,22 +1694,42 @@ __global__ void __launch_bounds__(NT) k3_inject(G3 g, Tiles3 tl, E3<R> e, I3<R> 
     }
 }
 
-// the injected particles enter the counters once the injection kernel has read them
-__global__ void k3_bump(int* nused_e, int* nused_i, int64_t total, int64_t cap, int ion_mode)
+template <typename R>
+__global__ void __launch_bounds__(NT) k3_inject(G3 g, Tiles3 tl, E3<R> e, I3<R> ion, int* nused_e, int* nused_i,
+                                                int* ticket, Seg3* seg_e, Box3* box_e, Seg3* seg_i, Box3* box_i,
+                                                int seg_base, Inject3 ip, int* status)
 {
-    const int be = *nused_e, bi = ion_mode ? *nused_i : 0;
-    if ((int64_t)be + total > cap || (int64_t)bi + total > cap) return;
-    *nused_e = be + (int)total;
-    if (ion_mode) *nused_i = bi + (int)total;
+    const int64_t total = (int64_t)g.N[0] * g.N[1] * ip.ppc * ip.nrows;
+    const int64_t gq = (int64_t)blockIdx.x * NT + threadIdx.x;
+    const int be = *nused_e, bi = ip.ion_mode ? *nused_i : 0;
+    const bool room = (int64_t)be + total <= ip.cap && (int64_t)bi + total <= ip.cap;
+    if (gq < total) inject_one(g, tl, e, ion, be, bi, seg_e, box_e, seg_i, box_i, seg_base, ip, status, room, gq);
+    __syncthreads();
+    // the injected particles enter the counters once every workgroup has read them: the last one
+    // to get here writes them and leaves the ticket at 0
+    if (threadIdx.x == 0 && atomicAdd(ticket, 1) == (int)gridDim.x - 1) {
+        *ticket = 0;
+        if (room) {
+            *nused_e = be + (int)total;
+            if (ip.ion_mode) *nused_i = bi + (int)total;
+        }
+    }
 }
 
-
-// window moved by d planes (zoff already advanced)
+// window moved by d planes (zoff already advanced): the launch's planes are the |d| new ones, the
+// two walls, and the |d| + 2 at the inner edge of the layer that content came out of
 template <typename R>
 __global__ void __launch_bounds__(NT) k3_window(G3 g, F3<R> f, int d)
 {
     int q[3];
     if (!cell_of(g, q)) return;
+    {
+        const int m = abs(d), z = (int)blockIdx.z;
+        if (z < m) q[2] = d > 0 ? g.S[2] - 1 - z : z;
+        else if (z < m + 2) q[2] = z == m ? 0 : g.S[2] - 1;
+        else q[2] = (d > 0 ? g.P[2] + g.N[2] - m - 1 : g.P[2] - 1) + (z - m - 2);
+        if (q[2] < 0 || q[2] >= g.S[2]) return;
+    }
     const int Sz = g.S[2], k = q[2];
     const long o = o3(g, q[0], q[1], k);
     if ((d > 0 && k >= Sz - d) || (d < 0 && k < -d)) {
@@ -1726,6 +1792,13 @@ __device__ __forceinline__ int tile_key3(const G3& g, const Tiles3& tl, double x
         key = key * tl.nt[a] + c / tl.t[a];
     }
     return key;
+}
+
+// a kernel and not a memset: the step may be captured into a graph
+__global__ void __launch_bounds__(NT) k3_clear(int* p, int n)
+{
+    const int i = blockIdx.x * NT + threadIdx.x;
+    if (i < n) p[i] = 0;
 }
 
 constexpr int SORT_GRID = 4096;   // workgroups of the grid-stride sort passes
@@ -1833,8 +1906,6 @@ __global__ void __launch_bounds__(NT) k3_sort_scatter_i(G3 g, Tiles3 tl, I3<R> s
         }
     }
 }
-
-__global__ void k3_set_count(int* nused, const int* tot) { *nused = *tot; }
 
 // Order within each tile after the scatter, by the particle's place in the plasma lattice: its
 // id encodes the lattice plane l, the cell (i, j) and the index k < ppc within the cell, and
@@ -2020,9 +2091,10 @@ __device__ void order_tile3(TileOrder& ts, int C, int N, Cell cell_of_q, Copy co
 
 template <typename R>
 __global__ void __launch_bounds__(ORD_THREADS) k3_sort_order_e(G3 g, Tiles3 tl, E3<R> src, E3<R> dst,
-                                                               const Seg3* seg, int ppc)
+                                                               const Seg3* seg, int ppc, int* nused, const int* tot)
 {
     __shared__ TileOrder ts;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *nused = *tot;   // the passes before this one read the old count
     const Seg3 sg = seg[blockIdx.x];
     if (sg.count <= 0) return;
     const int o = sg.start;
@@ -2040,9 +2112,10 @@ __global__ void __launch_bounds__(ORD_THREADS) k3_sort_order_e(G3 g, Tiles3 tl, 
 
 template <typename R>
 __global__ void __launch_bounds__(ORD_THREADS) k3_sort_order_i(G3 g, Tiles3 tl, I3<R> src, I3<R> dst,
-                                                               const Seg3* seg, int ppc)
+                                                               const Seg3* seg, int ppc, int* nused, const int* tot)
 {
     __shared__ TileOrder ts;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *nused = *tot;   // the passes before this one read the old count
     const Seg3 sg = seg[blockIdx.x];
     if (sg.count <= 0) return;
     const int o = sg.start;
@@ -2132,24 +2205,26 @@ __global__ void k3_stations(G3 g, F3<R> f, const double* zlab, int nst, double g
 
 template <typename R>
 void launch3_faraday(const G3& g, const F3<R>& f, const Pml3& pml, const double ck[3], double theta, double dt,
-                     hipStream_t s)
+                     int* nmis, hipStream_t s)
 {
+    const int run = run_planes(g);
     const dim3 grid((unsigned)((g.S[0] + FMX - 1) / FMX), (unsigned)((g.S[1] + FMY - 1) / FMY),
-                    (unsigned)((g.S[2] + FMZ - 1) / FMZ));
+                    (unsigned)((g.S[2] + run - 1) / run));
     if (theta > 0.0)
         hipLaunchKernelGGL((k3_faraday<R, true>), grid, cells_block(), 0, s, g, f, pml, (R)ck[0], (R)ck[1], (R)ck[2],
-                           (R)dt, (R)theta);
+                           (R)dt, (R)theta, run, nmis);
     else
         hipLaunchKernelGGL((k3_faraday<R, false>), grid, cells_block(), 0, s, g, f, pml, (R)ck[0], (R)ck[1],
-                           (R)ck[2], (R)dt, (R)theta);
+                           (R)ck[2], (R)dt, (R)theta, run, nmis);
 }
 
 template <typename R>
 void launch3_ampere(const G3& g, const F3<R>& f, const R* const J[3], const Pml3& pml, double dt, hipStream_t s)
 {
+    const int run = run_planes(g);
     const dim3 grid((unsigned)((g.S[0] + FMX - 1) / FMX), (unsigned)((g.S[1] + FMY - 1) / FMY),
-                    (unsigned)((g.S[2] + FMZ - 1) / FMZ));
-    hipLaunchKernelGGL((k3_ampere<R>), grid, cells_block(), 0, s, g, f, J[0], J[1], J[2], pml, (R)dt);
+                    (unsigned)((g.S[2] + run - 1) / run));
+    hipLaunchKernelGGL((k3_ampere<R>), grid, cells_block(), 0, s, g, f, J[0], J[1], J[2], pml, (R)dt, run);
 }
 
 bool filter_seq(int npass, int comp, int stride_mask, FiltSeq* fs)
@@ -2355,21 +2430,11 @@ void launch3_rho(const G3& g, const E3<R>& e, int ne, const I3<R>& ion, int ni, 
                            ant, na, pol, za, aw, vol_inv, rho);
 }
 
-template <typename R>
-void launch3_zero_j(const G3& g, const F3<R>& f, hipStream_t s)
-{
-    hipLaunchKernelGGL(k3_zero3, cells_grid(g), cells_block(), 0, s, g, f.J[0], f.J[1], f.J[2]);
-}
-
-// a kernel and not a memset: the step may be captured into a graph
-__global__ void k3_clear_count(int* n) { *n = 0; }
-
 template <typename R, bool MC>
 void gpd_launch(const G3& g, const F3<R>& f, const E3<R>& e, const Seg3* seg, const Box3* bin, Box3* bout,
                 int nseg, const Push3& pp, int pz, int* status, int* nmis, int2* mis, hipStream_t s)
 {
     const size_t lds = (size_t)BPL * pz * box_cell_bytes<R>();
-    hipLaunchKernelGGL(k3_clear_count, dim3(1), dim3(1), 0, s, nmis);
     (void)hipFuncSetAttribute((const void*)k3_gpd<R, MC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL((k3_gpd<R, MC>), dim3(nseg), dim3(GT), lds, s, g, f, e, seg, bin, bout, pp, pz, status, mis,
                        nmis);
@@ -2435,19 +2500,18 @@ void launch3_antenna(const G3& g, const F3<R>& f, double* xm, const double* xh, 
                      const Antenna3& a, const Push3& pp, hipStream_t s)
 {
     if (a.n <= 0) return;
-    hipLaunchKernelGGL((k3_antenna<R>), dim3((a.n + 63) / 64), dim3(64), 0, s, g, f, xm, xh, yh, a, pp);
+    hipLaunchKernelGGL((k3_antenna<R>), dim3((a.n + AP - 1) / AP), dim3(AT * AP), 0, s, g, f, xm, xh, yh, a, pp);
 }
 
 template <typename R>
 void launch3_inject(const G3& g, const Tiles3& tl, const E3<R>& e, const I3<R>& ion, int* nused_e, int* nused_i,
-                    Seg3* seg_e, Box3* box_e, Seg3* seg_i, Box3* box_i, int seg_base, const Inject3& ip,
-                    int* status, hipStream_t s)
+                    int* ticket, Seg3* seg_e, Box3* box_e, Seg3* seg_i, Box3* box_i, int seg_base,
+                    const Inject3& ip, int* status, hipStream_t s)
 {
     const int64_t total = (int64_t)g.N[0] * g.N[1] * ip.ppc * ip.nrows;
     if (total <= 0) return;
     hipLaunchKernelGGL((k3_inject<R>), dim3((unsigned)((total + NT - 1) / NT)), dim3(NT), 0, s, g, tl, e, ion,
-                       nused_e, nused_i, seg_e, box_e, seg_i, box_i, seg_base, ip, status);
-    hipLaunchKernelGGL(k3_bump, dim3(1), dim3(1), 0, s, nused_e, nused_i, total, ip.cap, ip.ion_mode);
+                       nused_e, nused_i, ticket, seg_e, box_e, seg_i, box_i, seg_base, ip, status);
 }
 
 template <typename R>
@@ -2455,7 +2519,9 @@ void launch3_window(const G3& g, const F3<R>& f, const Pml3& pml, int d, hipStre
 {
     (void)pml;
     if (d == 0) return;
-    hipLaunchKernelGGL((k3_window<R>), cells_grid(g), cells_block(), 0, s, g, f, d);
+    dim3 grid = cells_grid(g);
+    grid.z = (unsigned)(2 * std::abs(d) + 5);
+    hipLaunchKernelGGL((k3_window<R>), grid, cells_block(), 0, s, g, f, d);
 }
 
 template <typename R>
@@ -2463,12 +2529,12 @@ void launch3_sort_e(const G3& g, const Tiles3& tl, const E3<R>& src, const E3<R>
                     int* cursor, int* tot, Seg3* seg, Box3* box, int64_t cap, int ppc, hipStream_t s)
 {
     const dim3 grid((unsigned)std::min<int64_t>(SORT_GRID, (cap + NT - 1) / NT));
-    (void)hipMemsetAsync(counts, 0, sizeof(int) * tl.ntiles, s);
+    hipLaunchKernelGGL(k3_clear, dim3((unsigned)((tl.ntiles + NT - 1) / NT)), dim3(NT), 0, s, counts, tl.ntiles);
     hipLaunchKernelGGL((k3_sort_count_e<R>), grid, dim3(NT), 0, s, g, tl, src, nused, counts);
     hipLaunchKernelGGL(k3_sort_scan, dim3(1), dim3(1024), 0, s, g, tl, counts, cursor, seg, box, tot);
     hipLaunchKernelGGL((k3_sort_scatter_e<R>), grid, dim3(NT), 0, s, g, tl, src, dst, nused, cursor);
-    hipLaunchKernelGGL((k3_sort_order_e<R>), dim3(tl.ntiles), dim3(ORD_THREADS), 0, s, g, tl, dst, src, seg, ppc);
-    hipLaunchKernelGGL(k3_set_count, dim3(1), dim3(1), 0, s, nused, tot);
+    hipLaunchKernelGGL((k3_sort_order_e<R>), dim3(tl.ntiles), dim3(ORD_THREADS), 0, s, g, tl, dst, src, seg, ppc,
+                       nused, tot);
 }
 
 template <typename R>
@@ -2476,12 +2542,12 @@ void launch3_sort_i(const G3& g, const Tiles3& tl, const I3<R>& src, const I3<R>
                     int* counts, int* cursor, int* tot, Seg3* seg, Box3* box, int64_t cap, int ppc, hipStream_t s)
 {
     const dim3 grid((unsigned)std::min<int64_t>(SORT_GRID, (cap + NT - 1) / NT));
-    (void)hipMemsetAsync(counts, 0, sizeof(int) * tl.ntiles, s);
+    hipLaunchKernelGGL(k3_clear, dim3((unsigned)((tl.ntiles + NT - 1) / NT)), dim3(NT), 0, s, counts, tl.ntiles);
     hipLaunchKernelGGL((k3_sort_count_i<R>), grid, dim3(NT), 0, s, g, tl, src, zsh, nused, counts);
     hipLaunchKernelGGL(k3_sort_scan, dim3(1), dim3(1024), 0, s, g, tl, counts, cursor, seg, box, tot);
     hipLaunchKernelGGL((k3_sort_scatter_i<R>), grid, dim3(NT), 0, s, g, tl, src, dst, zsh, nused, cursor);
-    hipLaunchKernelGGL((k3_sort_order_i<R>), dim3(tl.ntiles), dim3(ORD_THREADS), 0, s, g, tl, dst, src, seg, ppc);
-    hipLaunchKernelGGL(k3_set_count, dim3(1), dim3(1), 0, s, nused, tot);
+    hipLaunchKernelGGL((k3_sort_order_i<R>), dim3(tl.ntiles), dim3(ORD_THREADS), 0, s, g, tl, dst, src, seg, ppc,
+                       nused, tot);
 }
 
 template <typename R>
@@ -2503,11 +2569,10 @@ void launch3_stations(const G3& g, const F3<R>& f, const double* zlab, int nst, 
 
 #define BF3_INST(R)                                                                                           \
     template void launch3_faraday<R>(const G3&, const F3<R>&, const Pml3&, const double*, double, double,   \
-                                     hipStream_t);                                                          \
+                                     int*, hipStream_t);                                                          \
     template void launch3_ampere<R>(const G3&, const F3<R>&, const R* const*, const Pml3&, double,          \
                                     hipStream_t);                                                           \
     template void launch3_filter<R>(const G3&, const F3<R>&, const FiltSeq&, const R**, hipStream_t);        \
-    template void launch3_zero_j<R>(const G3&, const F3<R>&, hipStream_t);                                  \
     template void launch3_rho<R>(const G3&, const E3<R>&, int, const I3<R>&, int, double, const double*, int,   \
                                  int, double, double, double, double*, hipStream_t);                       \
     template void launch3_count_live<R>(const R*, int, int*, hipStream_t);                                  \
@@ -2518,7 +2583,7 @@ void launch3_stations(const G3& g, const F3<R>& f, const double* zlab, int nst, 
                                  double, double, double, const Push3&, int, hipStream_t);                   \
     template void launch3_antenna<R>(const G3&, const F3<R>&, double*, const double*, const double*,        \
                                      const Antenna3&, const Push3&, hipStream_t);                           \
-    template void launch3_inject<R>(const G3&, const Tiles3&, const E3<R>&, const I3<R>&, int*, int*, Seg3*,   \
+    template void launch3_inject<R>(const G3&, const Tiles3&, const E3<R>&, const I3<R>&, int*, int*, int*, Seg3*, \
                                     Box3*, Seg3*, Box3*, int, const Inject3&, int*, hipStream_t);          \
     template void launch3_window<R>(const G3&, const F3<R>&, const Pml3&, int, hipStream_t);                \
     template void launch3_sort_e<R>(const G3&, const Tiles3&, const E3<R>&, const E3<R>&, int*, int*, int*,   \

@@ -112,7 +112,7 @@ __device__ __forceinline__ R split_update(const G3& g, R old, R* sp, long o, R t
 constexpr int FMX = CBX, FMY = CBY;
 // Planes of a workgroup's run: 16, halved while the launch has less than two workgroups per CU.  A
 // run's planes are one serial chain of about 4 us each, so short runs win on small boxes although
-// each adds two border planes: 33 x 31 x 69 cells in FP64 80 -> FARADAY_TINY us for Faraday.
+// each adds two border planes: 33 x 31 x 69 cells in FP64 80 -> 18 us for Faraday.
 // Longer runs than 16 measured slower on large boxes (0.95 ms at 32 against 0.90 ms).
 constexpr int FMZ = 16, FMZ_MIN = 2;
 
@@ -806,103 +806,109 @@ __device__ __forceinline__ void window5(double f, bool hi, double s[5])
     s[4] = hi ? w3 : 0.0;
 }
 
-// gather of E^n and B^n = (B^{n-1/2} + B^{n+1/2}) / 2 at r (cells), cubic weights at each
-// component's stagger
+// gather of E^n and B^n = (B^{n-1/2} + B^{n+1/2}) / 2 at r (cells, the same in every lane) by the
+// 64 lanes of a wave, one stencil node each; cubic weights at each component's stagger
 template <bool MC, typename R>
-__device__ void gather3(const G3& g, const F3<R>& f, const double r[3], R E[3], R B[3])
+__device__ __forceinline__ void gather3_wave(const G3& g, const F3<R>& f, const double r[3], R E[3], R B[3])
 {
-    R w[3][2][4];
-    int id[3][2][4];
+    const int lane = threadIdx.x & 63, m[3] = {lane & 3, (lane >> 2) & 3, lane >> 4};
+    R w[3][2];
+    int id[3][2];
 #pragma unroll
     for (int a = 0; a < 3; a++)
 #pragma unroll
         for (int h = 0; h < 2; h++) {
             const double xs = r[a] - 0.5 * h;
             const int j0 = (int)floor(xs);
-            bspline4((R)(xs - j0), w[a][h]);
-#pragma unroll
-            for (int m = 0; m < 4; m++) id[a][h][m] = sidx(g, a, j0 - 1 + m);
+            R v[4];
+            bspline4((R)(xs - j0), v);
+            w[a][h] = m[a] == 0 ? v[0] : m[a] == 1 ? v[1] : m[a] == 2 ? v[2] : v[3];
+            id[a][h] = sidx(g, a, j0 - 1 + m[a]);
         }
+    R val[6];
 #pragma unroll
     for (int c = 0; c < 6; c++) {
         int hx = c < 3 ? (c == 0) : (c != 3), hy = c < 3 ? (c == 1) : (c != 4), hz = c < 3 ? (c == 2) : (c != 5);
         if (MC) hx = hy = hz = 0;
-        R acc = R(0), acc2 = R(0);
-        const R* F = MC ? f.G[c] : (c < 3 ? f.E[c] : f.B[c - 3]);
-        const R* Fo = c < 3 ? f.E[c] : f.Bo[c - 3];
-        for (int k = 0; k < 4; k++) {
-            const int sk = id[2][hz][k];
-            if (sk < 0) continue;
-            for (int j = 0; j < 4; j++) {
-                const int sj = id[1][hy][j];
-                if (sj < 0) continue;
-                const R wjk = w[1][hy][j] * w[2][hz][k];
+        const int si = id[0][hx], sj = id[1][hy], sk = id[2][hz];
+        const bool in = si >= 0 && sj >= 0 && sk >= 0;
+        const long o = in ? o3(g, si, sj, sk) : 0;
+        R v;
+        if (MC) v = f.G[c][o];
+        else if (c < 3) v = f.E[c][o];
+        else v = R(0.5) * (f.B[c - 3][o] + f.Bo[c - 3][o]);
+        val[c] = in ? w[0][hx] * (w[1][hy] * w[2][hz]) * v : R(0);
+    }
 #pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const int si = id[0][hx][i];
-                    if (si < 0) continue;
-                    const long o = o3(g, si, sj, sk);
-                    acc += w[0][hx][i] * wjk * F[o];
-                    if (!MC && c >= 3) acc2 += w[0][hx][i] * wjk * Fo[o];
-                }
-            }
-        }
-        if (c < 3) E[c] = acc;
-        else B[c - 3] = MC ? acc : R(0.5) * (acc + acc2);
+    for (int c = 0; c < 6; c++) {
+        for (int o = 32; o > 0; o >>= 1) val[c] += __shfl_xor(val[c], o);
+        if (c < 3) E[c] = val[c];
+        else B[c - 3] = val[c];
     }
 }
 
-// Esirkepov's 3D deposit of one particle moving r0 -> r1 (cells, |move| < 1 cell per axis):
-//   W_C = DS_C (S0_A1 S0_A2 + DS_A1 S0_A2 / 2 + S0_A1 DS_A2 / 2 + DS_A1 DS_A2 / 3),
-//   J_C(node + 1/2) - J_C(node - 1/2) = k_C W_C   (k_C = -q w / (d_A1 d_A2 dt))
-// here node m1 of the window along A1, (C, A1, A2) cyclic
-template <int C>
-__device__ __forceinline__ void esirkepov3_row(const G3& g, double* const* J, const double r0[3], const double r1[3],
-                                               double k, int m1)
-{
-    constexpr int A1 = (C + 1) % 3, A2 = (C + 2) % 3;
-    if (k == 0.0) return;
+// shape factors of a particle moving r0 -> r1 (cells, |move| < 1 cell per axis) on the 5-node
+// windows that start at base
+struct Move3 {
     double S0[3][5], DS[3][5];
     int base[3];
+    __device__ __forceinline__ Move3(const double r0[3], const double r1[3])
+    {
 #pragma unroll
-    for (int a = 0; a < 3; a++) {
-        const int i0 = (int)floor(r0[a]), i1 = (int)floor(r1[a]);
-        const int b = min(i0, i1) - 1;
-        base[a] = b;
-        double s1[5];
-        window5(r0[a] - i0, i0 > b + 1, S0[a]);
-        window5(r1[a] - i1, i1 > b + 1, s1);
+        for (int a = 0; a < 3; a++) {
+            const int i0 = (int)floor(r0[a]), i1 = (int)floor(r1[a]);
+            const int b = min(i0, i1) - 1;
+            base[a] = b;
+            double s1[5];
+            window5(r0[a] - i0, i0 > b + 1, S0[a]);
+            window5(r1[a] - i1, i1 > b + 1, s1);
 #pragma unroll
-        for (int m = 0; m < 5; m++) DS[a][m] = s1[m] - S0[a][m];
+            for (int m = 0; m < 5; m++) DS[a][m] = s1[m] - S0[a][m];
+        }
     }
-    const int s1 = sidx(g, A1, base[A1] + m1);
-    if (s1 < 0) return;
+};
+
+// Esirkepov's 3D deposit of a move:
+//   W_C = DS_C (S0_A1 S0_A2 + DS_A1 S0_A2 / 2 + S0_A1 DS_A2 / 2 + DS_A1 DS_A2 / 3),
+//   J_C(node + 1/2) - J_C(node - 1/2) = k_C W_C   (k_C = -q w / (d_A1 d_A2 dt))
+// here node m1 of the window along A1, (C, A1, A2) cyclic, and nodes m0 .. m0 + NC - 1 along C
+template <int C, int NC>
+__device__ __forceinline__ void esirkepov3_row(const G3& g, double* const* J, const Move3& mv, double k, int m1,
+                                               int m0)
+{
+    constexpr int A1 = (C + 1) % 3, A2 = (C + 2) % 3;
+    const int s1 = sidx(g, A1, mv.base[A1] + m1);
+    if (k == 0.0 || s1 < 0) return;
     double sa = 0.0, da = 0.0;
 #pragma unroll
     for (int m = 0; m < 5; m++)
         if (m == m1) {
-            sa = S0[A1][m];
-            da = DS[A1][m];
+            sa = mv.S0[A1][m];
+            da = mv.DS[A1][m];
         }
-    int sc[4];
-    double kp[4], pd = 0.0;
+    int sc[NC];
+    double kp[NC], pd = 0.0;
 #pragma unroll
     for (int m = 0; m < 4; m++) {
-        sc[m] = sidx(g, C, base[C] + m);
-        pd += k * DS[C][m];
-        kp[m] = pd;
+        pd += k * mv.DS[C][m];
+#pragma unroll
+        for (int n = 0; n < NC; n++)
+            if (m == m0 + n) kp[n] = pd;
     }
 #pragma unroll
+    for (int n = 0; n < NC; n++) sc[n] = sidx(g, C, mv.base[C] + m0 + n);
+#pragma unroll
     for (int m2 = 0; m2 < 5; m2++) {
-        const int s2 = sidx(g, A2, base[A2] + m2);
-        const double T = sa * (S0[A2][m2] + 0.5 * DS[A2][m2]) + da * (0.5 * S0[A2][m2] + DS[A2][m2] * (1.0 / 3.0));
+        const int s2 = sidx(g, A2, mv.base[A2] + m2);
+        const double T = sa * (mv.S0[A2][m2] + 0.5 * mv.DS[A2][m2]) +
+                         da * (0.5 * mv.S0[A2][m2] + mv.DS[A2][m2] * (1.0 / 3.0));
         if (s2 < 0 || T == 0.0) continue;
 #pragma unroll
-        for (int mc = 0; mc < 4; mc++) {
-            const double v = kp[mc] * T;
-            if (v == 0.0 || sc[mc] < 0) continue;
+        for (int n = 0; n < NC; n++) {
+            const double v = kp[n] * T;
+            if (v == 0.0 || sc[n] < 0) continue;
             int q[3];
-            q[C] = sc[mc];
+            q[C] = sc[n];
             q[A1] = s1;
             q[A2] = s2;
             atomicAdd(&J[C][o3(g, q[0], q[1], q[2])], v);
@@ -910,13 +916,23 @@ __device__ __forceinline__ void esirkepov3_row(const G3& g, double* const* J, co
     }
 }
 
-__device__ void esirkepov3(const G3& g, double* const* J, const double r0[3], const double r1[3], const double k[3])
+// the J_z part alone, by one thread (a rigid ion)
+__device__ void esirkepov3_z(const G3& g, double* const* J, const double r0[3], const double r1[3], double kz)
 {
-    for (int m1 = 0; m1 < 5; m1++) {
-        esirkepov3_row<0>(g, J, r0, r1, k[0], m1);
-        esirkepov3_row<1>(g, J, r0, r1, k[1], m1);
-        esirkepov3_row<2>(g, J, r0, r1, k[2], m1);
-    }
+    const Move3 mv(r0, r1);
+    for (int m1 = 0; m1 < 5; m1++) esirkepov3_row<2, 4>(g, J, mv, kz, m1, 0);
+}
+
+// the whole deposit by the 64 lanes of a wave (r0, r1, k the same in every lane): four lanes, one
+// per node along C, share each of the 15 rows
+__device__ __forceinline__ void esirkepov3_wave(const G3& g, double* const* J, const double r0[3], const double r1[3],
+                                                const double k[3])
+{
+    const Move3 mv(r0, r1);
+    const int lane = threadIdx.x & 63, row = (lane >> 2) % 5, m = lane & 3, c = lane / 20;
+    if (c == 0) esirkepov3_row<0, 1>(g, J, mv, k[0], row, m);
+    else if (c == 1) esirkepov3_row<1, 1>(g, J, mv, k[1], row, m);
+    else if (c == 2) esirkepov3_row<2, 1>(g, J, mv, k[2], row, m);
 }
 
 template <typename R>
@@ -1229,8 +1245,9 @@ __device__ __forceinline__ void grow(int nb[6], int a, int c)
 }
 
 // one electron: gather, Boris push (q/m = -1), deposit, absorption, window rebase; on the
-// staged box (LDS) or on the fields and current in HBM.  The staged form returns false,
-// leaving the particle untouched, when its cell lies outside the box.
+// staged box (LDS, one thread a particle) or on the fields and current in HBM (the 64 lanes of a
+// wave share the particle p).  The staged form returns false, leaving the particle untouched,
+// when its cell lies outside the box.
 template <bool LDS, bool MC, typename R>
 __device__ __forceinline__ bool electron3(const G3& g, const F3<R>& f, const BoxL<R>& bx, const E3<R>& e, int p,
                                           const Push3& pp, double js, int* status, int nb[6])
@@ -1241,7 +1258,7 @@ __device__ __forceinline__ bool electron3(const G3& g, const F3<R>& f, const Box
     if (LDS && !in_box(bx, r0)) return false;
     R E[3], B[3];
     if constexpr (LDS) gather_box<MC>(bx, r0, E, B);
-    else gather3<MC>(g, f, r0, E, B);
+    else gather3_wave<MC>(g, f, r0, E, B);
     const R h = (R)(-0.5 * pp.dt);
     R ux = e.ux[p], uy = e.uy[p], uz = e.uz[p];
     if (pp.vay) {
@@ -1287,7 +1304,7 @@ __device__ __forceinline__ bool electron3(const G3& g, const F3<R>& f, const Box
             const double ks[3] = {k[0] * js, k[1] * js, k[2] * js};
             deposit_box(bx, r0, r1, ks);
         } else {
-            esirkepov3(g, f.J, r0, r1, k);
+            esirkepov3_wave(g, f.J, r0, r1, k);
         }
     } else {
         atomicOr(status, ST3_NONFINITE);
@@ -1409,25 +1426,24 @@ __global__ void __launch_bounds__(GT) k3_gpd(G3 g, F3<R> f, E3<R> e, const Seg3*
     block_box<GT>(nb, red, &bout[blockIdx.x]);
 }
 
-// the particles k3_gpd left (list mis), on the fields and current in HBM; their cells widen the
-// segments' next boxes
+// The particles k3_gpd left (list mis), on the fields and current in HBM, one wave each; their
+// cells widen the segments' next boxes.  Bound by latency: one lane per stencil node makes it a
+// few dependent loads where one thread per particle walked 64 nodes of nine arrays and 300 adds
+// (47 -> 8 us a step on 12x10x48 cells in FP64 with a few such particles, 190 -> 11 us on
+// 61x45x203).
 template <typename R, bool MC>
 __global__ void __launch_bounds__(NT) k3_gpd_hbm(G3 g, F3<R> f, E3<R> e, Box3* __restrict__ bout, Push3 pp,
                                                  int* status, const int2* mis, const int* nmis)
 {
     const BoxL<R> none{};
-    const int nm = *nmis;
-    for (int i = blockIdx.x * NT + threadIdx.x; i < nm; i += gridDim.x * NT) {
+    const int nm = *nmis, nw = gridDim.x * (NT / 64), lane = threadIdx.x & 63;
+    for (int i = __builtin_amdgcn_readfirstlane(blockIdx.x * (NT / 64) + threadIdx.x / 64); i < nm; i += nw) {
         int nb[6] = {INT_MAX, INT_MIN, INT_MAX, INT_MIN, INT_MAX, INT_MIN};
         const int2 m = mis[i];
         electron3<false, MC>(g, f, none, e, m.y, pp, 1.0, status, nb);
-        // lanes may belong to different segments: one atomic set per lane
-        if (nb[0] <= nb[1]) {
-#pragma unroll
-            for (int a = 0; a < 3; a++) {
-                atomicMin(&bout[m.x].lo[a], nb[2 * a]);
-                atomicMax(&bout[m.x].hi[a], nb[2 * a + 1]);
-            }
+        if (nb[0] <= nb[1] && lane < 3) {
+            atomicMin(&bout[m.x].lo[lane], lane == 0 ? nb[0] : lane == 1 ? nb[2] : nb[4]);
+            atomicMax(&bout[m.x].hi[lane], lane == 0 ? nb[1] : lane == 1 ? nb[3] : nb[5]);
         }
     }
 }
@@ -1491,8 +1507,7 @@ __global__ void __launch_bounds__(GTI, 4) k3_gpi(G3 g, F3<R> f, I3<R> ion, const
             if (lds && in_box(bx, r0)) {
                 deposit_box_z(bx, x, y, r0[2], r1[2], kz * js);
             } else {
-                const double k[3] = {0.0, 0.0, kz};
-                esirkepov3(g, f.J, r0, r1, k);
+                esirkepov3_z(g, f.J, r0, r1, kz);
             }
             if (!g.per[2] && (r1[2] < 0.0 || r1[2] >= (double)g.N[2])) {
                 ion.w[p] = R(0);
@@ -1514,8 +1529,8 @@ __global__ void __launch_bounds__(GTI, 4) k3_gpi(G3 g, F3<R> f, I3<R> ion, const
 // moving along the polarisation (x or y) with the sheet current K = -2 E_perp (FP64
 // throughout); xm holds the moving particle's coordinate along the polarisation.  AT threads share
 // a pair, one for each current component and node along one of its transverse axes: one thread
-// per pair is a chain of up to 600 dependent adds, 40 us whatever the size of the plane
-// (ANTENNA_AFTER).
+// per pair is a chain of up to 600 adds, 40 us on 12 x 10 and 61 x 45 cells against 13 and 19 us
+// (128 x 128 cells: 50 us against 69 us, each thread repeating the pair's shape factors).
 constexpr int AT = 15, AP = 16;          // threads of a pair, pairs of a workgroup
 template <typename R>
 __global__ void __launch_bounds__(AT * AP) k3_antenna(G3 g, F3<R> f, double* xm, const double* xh, const double* yh,
@@ -1538,16 +1553,17 @@ __global__ void __launch_bounds__(AT * AP) k3_antenna(G3 g, F3<R> f, double* xm,
         const double km[3] = {pp.jk[0] * a.aw, pp.jk[1] * a.aw, pp.jk[2] * a.aw};   // q = -1
         const double h0[3] = {xh[q], yh[q], a.za}, h1[3] = {xh[q], yh[q], a.zb};
         const double kp[3] = {-km[0], -km[1], -km[2]};                           // q = +1
+        const Move3 mm(m0, m1), mh(h0, h1);
         const int row = part % 5;
         if (part < 5) {
-            esirkepov3_row<0>(g, f.J, m0, m1, km[0], row);
-            esirkepov3_row<0>(g, f.J, h0, h1, kp[0], row);
+            esirkepov3_row<0, 4>(g, f.J, mm, km[0], row, 0);
+            esirkepov3_row<0, 4>(g, f.J, mh, kp[0], row, 0);
         } else if (part < 10) {
-            esirkepov3_row<1>(g, f.J, m0, m1, km[1], row);
-            esirkepov3_row<1>(g, f.J, h0, h1, kp[1], row);
+            esirkepov3_row<1, 4>(g, f.J, mm, km[1], row, 0);
+            esirkepov3_row<1, 4>(g, f.J, mh, kp[1], row, 0);
         } else {
-            esirkepov3_row<2>(g, f.J, m0, m1, km[2], row);
-            esirkepov3_row<2>(g, f.J, h0, h1, kp[2], row);
+            esirkepov3_row<2, 4>(g, f.J, mm, km[2], row, 0);
+            esirkepov3_row<2, 4>(g, f.J, mh, kp[2], row, 0);
         }
     }
     __syncthreads();                     // every thread of the pair has read xm

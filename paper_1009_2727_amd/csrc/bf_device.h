@@ -40,8 +40,10 @@ __device__ __forceinline__ long gofs(const Geo& g, int i, int k)
 // wrap/clip a stored index: periodic axes wrap, others return -1 outside [0, S)
 __device__ __forceinline__ int swrap(int i, int S, int per)
 {
-    if (per) { i %= S; return i < 0 ? i + S : i; }
-    return (i < 0 || i >= S) ? -1 : i;
+    if ((unsigned)i < (unsigned)S) return i;
+    if (!per) return -1;
+    i %= S;
+    return i < 0 ? i + S : i;
 }
 
 // last valid stored index of a component with stagger h on an axis (non-periodic axes keep

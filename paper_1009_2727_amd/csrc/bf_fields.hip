@@ -30,10 +30,11 @@ constexpr int FDX = FARADAY_TX, FDZ = FARADAY_TZ, FDP = FDX + 2, FDN = FDP * (FD
 
 template <typename R, bool FRIED>
 __device__ __forceinline__ void faraday_block(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm,
-                                              R dt, R a2, R b2, R th, R idx, R idz, int bx, int by)
+                                              R dt, R a2, R b2, R th, R idx, R idz, int* nfar, int bx, int by)
 {
     __shared__ R sT[3][FDN];
     const int x0 = bx * FDX, z0 = by * FDZ;
+    if (bx + by == 0 && threadIdx.x == 0) *nfar = 0;
     for (int q = threadIdx.x; q < FDN; q += 256) {
         const int a = q % FDP, b = q / FDP;
         int i = x0 - 1 + a, k = z0 - 1 + b;
@@ -121,9 +122,9 @@ __device__ __forceinline__ void faraday_block(const Geo& g, const FieldSet<R>& f
 
 template <typename R, bool FRIED>
 __global__ void __launch_bounds__(256) k_faraday(Geo g, FieldSet<R> f, PmlTab<R> pm, R dt, R a2,
-                                                 R b2, R th, R idx, R idz)
+                                                 R b2, R th, R idx, R idz, int* nfar)
 {
-    faraday_block<R, FRIED>(g, f, pm, dt, a2, b2, th, idx, idz, blockIdx.x, blockIdx.y);
+    faraday_block<R, FRIED>(g, f, pm, dt, a2, b2, th, idx, idz, nfar, blockIdx.x, blockIdx.y);
 }
 
 // E^{n+1} of stored cell (i, k) from the current j[3] there
@@ -353,11 +354,11 @@ __global__ void __launch_bounds__(256) k_faraday_batch(const FaradayDesc<R>* __r
         const FaradayDesc<R>& D = d[r];
         const int local = it - q.off[r];
         if (D.fried)
-            faraday_block<R, true>(D.g, D.f, D.pm, D.dt, D.a2, D.b2, D.th, D.idx, D.idz, local % D.gx,
-                                   local / D.gx);
+            faraday_block<R, true>(D.g, D.f, D.pm, D.dt, D.a2, D.b2, D.th, D.idx, D.idz, D.nfar,
+                                   local % D.gx, local / D.gx);
         else
-            faraday_block<R, false>(D.g, D.f, D.pm, D.dt, D.a2, D.b2, D.th, D.idx, D.idz, local % D.gx,
-                                    local / D.gx);
+            faraday_block<R, false>(D.g, D.f, D.pm, D.dt, D.a2, D.b2, D.th, D.idx, D.idz, D.nfar,
+                                    local % D.gx, local / D.gx);
     }
 }
 
@@ -517,15 +518,15 @@ void launch_ampere_batch(const AmpereDesc<R>* d, const QueueRef& q, int nblocks,
 
 template <typename R>
 void launch_faraday(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm, const SolverCoef& c,
-                    hipStream_t s)
+                    int* nfar, hipStream_t s)
 {
     dim3 grid((g.Sx + FDX - 1) / FDX, (g.Sz + FDZ - 1) / FDZ);
     if (c.theta > 0.0)
         hipLaunchKernelGGL((k_faraday<R, true>), grid, dim3(256), 0, s, g, f, pm, (R)c.dt, (R)c.a2,
-                           (R)c.b2, (R)c.theta, (R)c.idx, (R)c.idz);
+                           (R)c.b2, (R)c.theta, (R)c.idx, (R)c.idz, nfar);
     else
         hipLaunchKernelGGL((k_faraday<R, false>), grid, dim3(256), 0, s, g, f, pm, (R)c.dt, (R)c.a2,
-                           (R)c.b2, (R)c.theta, (R)c.idx, (R)c.idz);
+                           (R)c.b2, (R)c.theta, (R)c.idx, (R)c.idz, nfar);
 }
 
 template <typename R>
@@ -619,7 +620,7 @@ void launch_fill_int(int* p, int n, int v, hipStream_t s)
 
 #define BF_INST(R)                                                                                 \
     template void launch_faraday<R>(const Geo&, const FieldSet<R>&, const PmlTab<R>&,              \
-                                    const SolverCoef&, hipStream_t);                               \
+                                    const SolverCoef&, int*, hipStream_t);                         \
     template void launch_nodes<R>(const Geo&, const FieldSet<R>&, hipStream_t);                       \
     template void launch_ampere<R>(const Geo&, const FieldSet<R>&, const PmlTab<R>&,               \
                                    const SolverCoef&, hipStream_t);                                \

@@ -677,6 +677,9 @@ bf_status step_impl(bf_sim* s, int nsteps)
         const FieldSet<R> f = field_set<R>(s);
         const Geo g = s->g;
         BatchRec* rb = batch_rec<R>(s);
+        // electrons outside their staged window: listed in the sort's scratch copy, which holds
+        // nothing between sorts, and counted in the third word of the counters
+        const FarList far{reinterpret_cast<int2*>(s->buf[1 + (1 - s->p_cur)]), nused_e(s) + 2};
         // Faraday + Friedman + PML
         s->slot = SLOT_FARADAY;
         hipEvent_t t_ph = s->tick();
@@ -685,11 +688,11 @@ bf_status step_impl(bf_sim* s, int nsteps)
                 const int gx = (g.Sx + FARADAY_TX - 1) / FARADAY_TX, gz = (g.Sz + FARADAY_TZ - 1) / FARADAY_TZ;
                 rb->faraday.push_back(FaradayDesc<float>{g, f, pm, (float)sc.dt, (float)sc.a2, (float)sc.b2,
                                                          (float)sc.theta, (float)sc.idx, (float)sc.idz,
-                                                         sc.theta > 0.0 ? 1 : 0, gx});
+                                                         far.n, sc.theta > 0.0 ? 1 : 0, gx});
                 rb->n_faraday.push_back(gx * gz);
             }
         }
-        if (!rb) launch_faraday<R>(g, f, pm, sc, s->stream);
+        if (!rb) launch_faraday<R>(g, f, pm, sc, far.n, s->stream);
         // stations (E^n, B^n)
         if (s->nst > 0) {
             StationParams sp;
@@ -728,28 +731,54 @@ bf_status step_impl(bf_sim* s, int nsteps)
             int4* bo = bb_e(s, 1 - s->bb_cur);
             if constexpr (sizeof(R) == 4) {
                 if (rb && s->nseg_e > 0) {
-                    rb->gpd.push_back(GpdDesc<float>{g, f, e, sg, bi, bo, pp, status_word(s)});
+                    rb->gpd.push_back(GpdDesc<float>{g, f, e, sg, bi, bo, pp, far, status_word(s)});
                     rb->n_gpd.push_back(s->nseg_e);
                 }
             }
-            if (!rb) launch_gpd<R>(g, f, e, sg, bi, bo, s->nseg_e, pp, status_word(s), c.gather_kind == 1, s->stream);
+            if (!rb)
+                launch_gpd<R>(g, f, e, sg, bi, bo, s->nseg_e, pp, far, status_word(s), c.gather_kind == 1, s->stream);
         }
         s->tock(t_ph, BF_PHASE_PUSH);
-        // rigid ions: deposit-only J_z
+        // rigid ions (deposit-only J_z), the antenna, and the electrons the staged push left: one
+        // launch, timed as the ions
         s->slot = SLOT_IONS;
         t_ph = s->tick();
-        if (s->have_plasma && s->plasma.ion_mode == 1) {
-            const IonArrays<R> ion = ions<R>(s, s->p_cur);
-            const Segment* sg = seg_i(s, s->sg_cur);
-            const int4* bi = bb_i(s, s->bb_cur);
-            int4* bo = bb_i(s, 1 - s->bb_cur);
-            const double za = ion_shift(s, s->t), zb = ion_shift(s, t1);
-            const R fjz = (R)(-1.0 / (c.dx_um * s->dt));
-            // batched runs launch their ions one run at a time too: the hardware's dispatch of
-            // one workgroup per segment balances the uneven segments better than a persistent
-            // launch over all runs
-            const int nsi = s->nseg_i;
-            s->run([=](hipStream_t st) { launch_ions<R>(g, f, ion, sg, bi, bo, nsi, za, zb, d, fjz, st); });
+        {
+            SourceParams<R> sp{};
+            if (s->have_plasma && s->plasma.ion_mode == 1) {
+                sp.ion = ions<R>(s, s->p_cur);
+                sp.iseg = seg_i(s, s->sg_cur);
+                sp.ibbin = bb_i(s, s->bb_cur);
+                sp.ibbout = bb_i(s, 1 - s->bb_cur);
+                sp.zsh_a = ion_shift(s, s->t);
+                sp.zsh_b = ion_shift(s, t1);
+                sp.fjz = (R)(-1.0 / (c.dx_um * s->dt));
+                sp.nion = s->nseg_i;
+            }
+            if (s->have_laser) {
+                AntennaParams& ap = sp.ap;
+                ap.n = c.nx;
+                ap.za = (s->za_lab / s->gamma - s->beta * s->t) / c.dz_um - (double)s->shift;
+                ap.zb = (s->za_lab / s->gamma - s->beta * t1) / c.dz_um - (double)s->shift;
+                ap.tmid = s->t + 0.5 * s->dt;
+                ap.gamma = s->gamma; ap.e0 = s->e0; ap.omega = s->omega; ap.w0 = s->w0;
+                ap.sig_t = s->sig_t; ap.t0 = s->t0; ap.dx_um = c.dx_um; ap.xc_um = 0.5 * c.nx * c.dx_um;
+                ap.weight = s->aw; ap.dt = s->dt; ap.dx = c.dx_um; ap.dz = c.dz_um;
+                ap.active = (ap.za >= 0.0 && ap.za < (double)c.nz) ? 1 : 0;
+                ap.pol = s->pol;
+                sp.xm = s->w<double>(L.w_ant);
+            }
+            sp.far = far;
+            sp.e = electrons<R>(s, s->p_cur);
+            sp.ebbout = bb_e(s, 1 - s->bb_cur);
+            sp.pp = pp;
+            sp.status = status_word(s);
+            const int nse = s->nseg_e;
+            const bool mc = c.gather_kind == 1;
+            // batched runs launch their sources one run at a time too: the hardware's dispatch of
+            // one workgroup per segment balances the uneven ion segments better than a
+            // persistent launch over all runs
+            s->run([=](hipStream_t st) { launch_sources<R>(g, f, sp, nse, mc, st); });
         }
         s->tock(t_ph, BF_PHASE_IONS);
         // beam through the injection plane (single runs only: a batch rejects beam runs)
@@ -776,24 +805,6 @@ bf_status step_impl(bf_sim* s, int nsteps)
             if (bp.rec >= 0) s->beam_rec++;
             s->tock(t_ph, BF_PHASE_BEAM);
         }
-        // antenna
-        s->slot = SLOT_ANTENNA;
-        t_ph = s->tick();
-        if (s->have_laser) {
-            AntennaParams ap;
-            ap.n = c.nx;
-            ap.za = (s->za_lab / s->gamma - s->beta * s->t) / c.dz_um - (double)s->shift;
-            ap.zb = (s->za_lab / s->gamma - s->beta * t1) / c.dz_um - (double)s->shift;
-            ap.tmid = s->t + 0.5 * s->dt;
-            ap.gamma = s->gamma; ap.e0 = s->e0; ap.omega = s->omega; ap.w0 = s->w0;
-            ap.sig_t = s->sig_t; ap.t0 = s->t0; ap.dx_um = c.dx_um; ap.xc_um = 0.5 * c.nx * c.dx_um;
-            ap.weight = s->aw; ap.dt = s->dt; ap.dx = c.dx_um; ap.dz = c.dz_um;
-            ap.active = (ap.za >= 0.0 && ap.za < (double)c.nz) ? 1 : 0;
-            ap.pol = s->pol;
-            double* xm = s->w<double>(L.w_ant);
-            s->run([=](hipStream_t st) { launch_antenna<R>(g, f, xm, ap, st); });
-        }
-        s->tock(t_ph, BF_PHASE_ANTENNA);
         // filter, then Ampere + PML (E^{n+1} into the E^{n-1} set); unit-stride passes and Ampere
         // are one launch, timed as the filter phase
         s->slot = SLOT_FILTER;

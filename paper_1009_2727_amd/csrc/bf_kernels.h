@@ -76,6 +76,12 @@ struct PushParams {
     int vay;           // 1: Vay's pusher, 0: Boris
 };
 
+// electrons left to the pass on HBM: n entries of (segment, particle)
+struct FarList {
+    int2* list;
+    int* n;
+};
+
 struct InjectParams {
     int64_t row0;      // first lattice row to create
     int nrows, nchunks, tile_x, ppc, ion_mode;
@@ -97,6 +103,29 @@ struct AntennaParams {
     double dt, dx, dz; // um
     int active;
     int pol;           // 0: the - sheet moves along x (J_x); 1: along y, out of the plane (J_y)
+};
+
+// one launch of the current's sources beside the staged electrons (launch_sources)
+template <typename R>
+struct SourceParams {
+    // rigid ions of nion segments: z = z0 - zsh_a at t_n, z0 - zsh_b at t_{n+1}
+    IonArrays<R> ion;
+    const Segment* iseg;
+    const int4* ibbin;
+    int4* ibbout;
+    int nion;
+    double zsh_a, zsh_b;
+    R fjz;
+    // antenna
+    double* xm;
+    AntennaParams ap;
+    int na;            // its workgroups
+    // electrons left by the staged push
+    FarList far;
+    ElectronArrays<R> e;
+    int4* ebbout;
+    PushParams<R> pp;
+    int* status;
 };
 
 // particle beam launched through a lab-fixed plane (Sec. 3.1.1): FP64 state in the work buffer
@@ -134,6 +163,7 @@ struct FaradayDesc {
     FieldSet<R> f;
     PmlTab<R> pm;
     R dt, a2, b2, th, idx, idz;
+    int* nfar;         // cleared for the step's push
     int fried, gx;     // Friedman on; blocks per row of the grid of Faraday tiles
 };
 template <typename R>
@@ -153,6 +183,7 @@ struct GpdDesc {
     const int4* bbin;
     int4* bbout;
     PushParams<R> pp;
+    FarList far;
     int* status;
 };
 
@@ -164,9 +195,10 @@ template <typename R>
 void launch_gpd_batch(const GpdDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s);
 
 // ---- launchers (stream-ordered) -------------------------------------------------------
+// Faraday; clears the raw current and *nfar for the step's deposit
 template <typename R>
 void launch_faraday(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm, const SolverCoef& c,
-                    hipStream_t s);
+                    int* nfar, hipStream_t s);
 template <typename R>
 void launch_ampere(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm, const SolverCoef& c,
                    hipStream_t s);
@@ -200,18 +232,17 @@ void launch_stations(const Geo& g, const FieldSet<R>& f, const StationParams& sp
 // the nodes (the mean over the Yee locations around each node along the staggered axes) into f.G
 template <typename R>
 void launch_nodes(const Geo& g, const FieldSet<R>& f, hipStream_t s);
-// gather, push and deposit; mc: the gather reads f.G with nodal weights for every component
+// gather, push and deposit; mc: the gather reads f.G with nodal weights for every component.
+// Electrons outside their segment's staged window are appended to far (far.n zero before the
+// call); launch_sources, after it, pushes them
 template <typename R>
 void launch_gpd(const Geo& g, const FieldSet<R>& f, const ElectronArrays<R>& e,
                 const Segment* seg, const int4* bbox_in, int4* bbox_out, int nseg,
-                const PushParams<R>& pp, int* status, bool mc, hipStream_t s);
+                const PushParams<R>& pp, const FarList& far, int* status, bool mc, hipStream_t s);
+// the rigid ions of sp.nion segments, the antenna when sp.ap.active, and the electrons of sp.far
+// (a run of nseg_e electron segments); sp.na is set here
 template <typename R>
-void launch_ions(const Geo& g, const FieldSet<R>& f, const IonArrays<R>& ion, const Segment* seg,
-                 const int4* bbox_in, int4* bbox_out, int nseg, double zsh_a, double zsh_b,
-                 int shift, R fjz, hipStream_t s);
-template <typename R>
-void launch_antenna(const Geo& g, const FieldSet<R>& f, double* xminus, const AntennaParams& ap,
-                    hipStream_t s);
+void launch_sources(const Geo& g, const FieldSet<R>& f, SourceParams<R> sp, int nseg_e, bool mc, hipStream_t s);
 template <typename R>
 void launch_inject(const Geo& g, const ElectronArrays<R>& e, const IonArrays<R>& ion,
                    Segment* seg_e, int4* bbox_e, Segment* seg_i, int4* bbox_i,

@@ -7,13 +7,14 @@
 //    components).  Each thread then pushes particles (Boris), deposits the Esirkepov current
 //    (charge-conserving, Sec. 4.2.2) into the LDS tile with LDS atomics, writes the particle
 //    back (positions FP64, rebased by the window shift), and the tile is flushed to HBM with
-//    global atomics.  A segment whose box does not fit the LDS budget (or a particle outside
-//    its box) takes the same code with global memory accessors.
-//  * k_ions: rigid ions (at rest in the lab) deposit their J_z from z0 - beta c t.
-//  * k_antenna: the laser antenna's +/- sheet particles (Sec. 3.1.2), in FP64 per pair.
+//    global atomics.  Particles outside the staged window go to a list.
+//  * k_sources, after it: the rigid ions (at rest in the lab) deposit their J_z from
+//    z0 - beta c t; the laser antenna's +/- sheet particles (Sec. 3.1.2), in FP64 per pair; and
+//    the electrons of k_gpd's list, on the fields and current in HBM.
 //  * k_inject: creates plasma lattice rows at the front plane (Sec. 3.1.1).
 //  * k_sort_*: counting sort by tile (histogram, scan, scatter) that also drops absorbed
 //    particles and folds periodic coordinates back into the box.
+#include <algorithm>
 #include <climits>
 #include "bf_kernels.h"
 
@@ -21,7 +22,8 @@ namespace bf {
 
 constexpr int NTHR = 256;
 
-// sum of v over the workgroup, returned to every thread (red: NTHR/64 doubles of LDS)
+// sum of v over the workgroup of NTH threads, returned to every thread (red: NTH/64 doubles of LDS)
+template <int NTH = NTHR>
 __device__ __forceinline__ double block_sum(double v, double* red)
 {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -29,7 +31,7 @@ __device__ __forceinline__ double block_sum(double v, double* red)
     __syncthreads();
     double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < NTHR / 64; w++) t += red[w];
+    for (int w = 0; w < NTH / 64; w++) t += red[w];
     return t;
 }
 
@@ -39,8 +41,9 @@ __device__ __forceinline__ double block_sum(double v, double* red)
 // conflicting when their word indices agree mod 16; a pitch of 0 (mod 16) keeps a lane whose
 // stencil starts one row lower (a z face crossed in the step) on the slot of its column.
 constexpr int TPX = 32;                 // row pitch of the staged tile (cells)
-// rows of the staged tile: 6 field planes + 3 FP64 current planes stay under 64 KB
-template <typename R> constexpr int trows() { return sizeof(R) == 4 ? 31 : 21; }
+// rows of the staged tile (6 field planes + 3 current planes of 8 bytes): FP32 tiles take 39 KB, so
+// that four workgroups fit a CU's LDS; the default tile needs 14 rows, and 12 are left for drift
+template <typename R> constexpr int trows() { return sizeof(R) == 4 ? 26 : 21; }
 template <typename R> constexpr int tcells() { return TPX * trows<R>(); }
 
 // Current accumulator of the staged tile.  FP32 runs accumulate in 64-bit integer fixed
@@ -180,7 +183,9 @@ __device__ __forceinline__ void window5(double f, bool hi, double s[5])
 //   W_y = S0_x S0_z + DS_x S0_z/2 + S0_x DS_z/2 + DS_x DS_z/3,
 // J_x(i+1/2) - J_x(i-1/2) = cx W_x(i) (likewise z), J_y = cy W_y.  Evaluated in factored
 // form: J_x(m,b) = cx (S0_z+S1_z)(b)/2 * sum_{k<=m} DS_x(k),  J_z likewise, and
-// W_y = S0_x (S0_z/3 + S1_z/6) + S1_x (S0_z/6 + S1_z/3).
+// W_y = S0_x (S0_z/3 + S1_z/6) + S1_x (S0_z/6 + S1_z/3).  When no particle of the wave crosses a
+// cell face along x (most waves: the transverse motion is slow), the window's fifth column has no
+// weight and the prefix sum is complete at the fourth: those 14 of 65 adds are skipped.
 template <typename A>
 __device__ __forceinline__ void esirkepov(const A& acc, int ix, double fx, int iz, double fz, int ix1,
                                           double fx1, int iz1, double fz1, double cx, double cz,
@@ -193,6 +198,7 @@ __device__ __forceinline__ void esirkepov(const A& acc, int ix, double fx, int i
     window5(fz, iz > bz + 1, S0z);
     window5(fz1, iz1 > bz + 1, S1z);
     const auto h = acc.handle(bx, bz);
+    const bool anyx = __ballot(ix1 != ix) != 0ull;
     if (cx != 0.0) {
         double czf[5];
 #pragma unroll
@@ -200,6 +206,7 @@ __device__ __forceinline__ void esirkepov(const A& acc, int ix, double fx, int i
         double pd = 0.0;
 #pragma unroll
         for (int m = 0; m < 4; m++) {
+            if (m == 3 && !anyx) continue;
             pd += S1x[m] - S0x[m];
 #pragma unroll
             for (int b = 0; b < 5; b++) acc.dep(h, 0, m, b, acc.prod(pd, czf[b]));
@@ -214,7 +221,10 @@ __device__ __forceinline__ void esirkepov(const A& acc, int ix, double fx, int i
         for (int b = 0; b < 4; b++) {
             pd += S1z[b] - S0z[b];
 #pragma unroll
-            for (int m = 0; m < 5; m++) acc.dep(h, 2, m, b, acc.prod(pd, cxf[m]));
+            for (int m = 0; m < 5; m++) {
+                if (m == 4 && !anyx) continue;
+                acc.dep(h, 2, m, b, acc.prod(pd, cxf[m]));
+            }
         }
     }
     if (cy != 0.0) {
@@ -228,7 +238,10 @@ __device__ __forceinline__ void esirkepov(const A& acc, int ix, double fx, int i
 #pragma unroll
         for (int b = 0; b < 5; b++)
 #pragma unroll
-            for (int m = 0; m < 5; m++) acc.dep(h, 1, m, b, acc.prod2(S0x[m], P[b], S1x[m], Q[b]));
+            for (int m = 0; m < 5; m++) {
+                if (m == 4 && !anyx) continue;
+                acc.dep(h, 1, m, b, acc.prod2(S0x[m], P[b], S1x[m], Q[b]));
+            }
     }
 }
 
@@ -339,44 +352,34 @@ __device__ __forceinline__ void store_electron(const ElectronArrays<R>& e, int p
     if (st.w == R(0)) e.w[p] = R(0);
 }
 
-// one electron with accessor A: gather, push, deposit, absorb (w = 0), rebase; st is advanced
-// in place (the caller writes it back) and the box is updated.  The caller guarantees the
-// gather window [ix-2, ix+2] and the deposit window [ix-2, ix+3] (one-cell move) are
-// addressable through A.  js scales the current into A's units.
-template <bool MC, typename R, typename A>
-__device__ __forceinline__ void advance_electron(const A& acc, const Geo& g, const PushParams<R>& pp,
-                                                 EState<R>& st, double js, int* status, int& x0,
-                                                 int& x1, int& z0, int& z1)
+// momenta after the push in E, B, and the velocity
+template <typename R>
+__device__ __forceinline__ void push_electron(const PushParams<R>& pp, const R E[3], const R B[3], R u[3], R v[3])
 {
-    const double x = st.x, z = st.z;
-    const R w = st.w;
-    R ux = st.ux, uy = st.uy, uz = st.uz;
-    const int ix = (int)floor(x), iz = (int)floor(z);
-    R E[3], B[3];
-    gather<MC>(acc, x, z, E, B);
-    if (pp.vay) vay(pp.qdt2, E, B, ux, uy, uz);
-    else boris(pp.qdt2, E, B, ux, uy, uz);
-    const R ig = rsqrt_(R(1) + ux * ux + uy * uy + uz * uz);
-    const R vx = ux * ig, vy = uy * ig, vz = uz * ig;
-    const double xn = x + (double)(pp.dtdx * vx), zn = z + (double)(pp.dtdz * vz);
-    const int ix1 = (int)floor(xn), iz1 = (int)floor(zn);
-    if (abs(ix1 - ix) <= 1 && abs(iz1 - iz) <= 1) {
-        const double jw = js * (double)w;
-        esirkepov(acc, ix, x - ix, iz, z - iz, ix1, xn - ix1, iz1, zn - iz1, jw * (double)pp.fjx,
-                  jw * (double)pp.fjz, jw * (double)(pp.fjy * vy));
-    } else {
-        atomicOr(status, ST_NONFINITE);   // faster than light: only a non-finite state gets here
-    }
-    if (!isfinite(ux + uy + uz)) atomicOr(status, ST_NONFINITE);
+    if (pp.vay) vay(pp.qdt2, E, B, u[0], u[1], u[2]);
+    else boris(pp.qdt2, E, B, u[0], u[1], u[2]);
+    const R ig = rsqrt_(R(1) + u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+#pragma unroll
+    for (int a = 0; a < 3; a++) v[a] = u[a] * ig;
+}
+
+// the pushed state after its move to (xn, zn): absorbed (w = 0) outside the interior, else rebased
+// into the next window frame and its cell added to the box
+template <typename R>
+__device__ __forceinline__ void finish_electron(const Geo& g, const PushParams<R>& pp, double xn, double zn,
+                                                const R u[3], EState<R>& st, int* status, int& x0, int& x1, int& z0,
+                                                int& z1)
+{
+    if (!isfinite(u[0] + u[1] + u[2])) atomicOr(status, ST_NONFINITE);
     bool alive = true;
     if (!g.perx && (xn < 0.0 || xn >= (double)g.Nx)) alive = false;
     if (!g.perz && (zn < 0.0 || zn >= (double)g.Nz)) alive = false;
-    const double zr = zn - (double)pp.shift;   // rebase into the next window frame
+    const double zr = zn - (double)pp.shift;
     st.x = xn;
     st.z = zr;
-    st.ux = ux;
-    st.uy = uy;
-    st.uz = uz;
+    st.ux = u[0];
+    st.uy = u[1];
+    st.uz = u[2];
     if (!alive) {
         st.w = R(0);
     } else {
@@ -386,26 +389,92 @@ __device__ __forceinline__ void advance_electron(const A& acc, const Geo& g, con
     }
 }
 
-constexpr int MISFIT_CAP = 256;
+// one electron on the staged tile: gather, push, deposit, absorb, rebase; st is advanced in place
+// (the caller writes it back) and the box is updated.  The caller guarantees the gather window
+// [ix-2, ix+2] and the deposit window [ix-2, ix+3] (one-cell move) lie in the tile.  js scales
+// the current into the tile's units.
+template <bool MC, typename R, typename A>
+__device__ __forceinline__ void advance_electron(const A& acc, const Geo& g, const PushParams<R>& pp,
+                                                 EState<R>& st, double js, int* status, int& x0,
+                                                 int& x1, int& z0, int& z1)
+{
+    const double x = st.x, z = st.z;
+    const int ix = (int)floor(x), iz = (int)floor(z);
+    R E[3], B[3], u[3] = {st.ux, st.uy, st.uz}, v[3];
+    gather<MC>(acc, x, z, E, B);
+    push_electron(pp, E, B, u, v);
+    const double xn = x + (double)(pp.dtdx * v[0]), zn = z + (double)(pp.dtdz * v[2]);
+    const int ix1 = (int)floor(xn), iz1 = (int)floor(zn);
+    if (abs(ix1 - ix) <= 1 && abs(iz1 - iz) <= 1) {
+        const double jw = js * (double)st.w;
+        esirkepov(acc, ix, x - ix, iz, z - iz, ix1, xn - ix1, iz1, zn - iz1, jw * (double)pp.fjx,
+                  jw * (double)pp.fjz, jw * (double)(pp.fjy * v[1]));
+    } else {
+        atomicOr(status, ST_NONFINITE);   // faster than light: only a non-finite state gets here
+    }
+    finish_electron(g, pp, xn, zn, u, st, status, x0, x1, z0, z1);
+}
 
-// gather, push and deposit of particle segment s by one workgroup
-template <typename R, bool MC = false>
+// The window of a segment whose box has outgrown the staged tile (particles spread since the last
+// sort, as in a heated plasma): along each axis that is too long, the longest window that
+// fits, centred on the particles' mean position; a particle in cell c fits while
+// lo + 2 <= c <= lo + n - 4.
+template <typename R, int NTH>
+__device__ __forceinline__ void clamp_window(const ElectronArrays<R>& e, const Segment& sg, const int4& bb,
+                                             LdsAcc<R>& lds, double* redd)
+{
+    double m[3] = {0.0, 0.0, 0.0};
+    for (int p = sg.start + threadIdx.x; p < sg.start + sg.count; p += NTH)
+        if (e.w[p] != R(0)) {
+            m[0] += e.x[p];
+            m[1] += e.z[p];
+            m[2] += 1.0;
+        }
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+        m[a] = block_sum<NTH>(m[a], redd);
+        __syncthreads();   // redd is reused
+    }
+    if (m[2] == 0.0) m[2] = 1.0;   // every particle is gone: any window does
+    if (lds.lx > TPX) {
+        const int lo = (int)floor(m[0] / m[2] - 0.5 * (TPX - 5) + 0.5) - 2;
+        lds.xb = min(max(lo, bb.x - 2), bb.y + 4 - TPX);
+        lds.lx = TPX;
+    }
+    if (lds.lz > trows<R>()) {
+        const int lo = (int)floor(m[1] / m[2] - 0.5 * (trows<R>() - 5) + 0.5) - 2;
+        lds.zb = min(max(lo, bb.z - 2), bb.w + 4 - trows<R>());
+        lds.lz = trows<R>();
+    }
+}
+
+// Gather, push and deposit of particle segment s by one workgroup of NTH threads.  Bound by VALU
+// issue on large grids (about 650 instructions per 64 electrons) and by the chain of its phases'
+// latencies on small ones.  Particles outside the staged window are appended to the list far
+// (segment, particle) and pushed by k_sources: carrying the global accessors here made it 203 KB
+// of code and 168 registers, and cold instruction fetches dominated small launches.
+// Per step: 43 -> 14 us on 75 x 1691 cells at 1 particle a cell, 70 -> 23 us on 64 x 512 at 4 in
+// FP64, 0.425 -> 0.38 ms on 256 x 4096 at 16 (16.8 M electrons, four workgroups per CU).
+template <typename R, bool MC, int NTH>
 __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, const ElectronArrays<R>& e,
                                             const Segment* __restrict__ seg, const int4* __restrict__ bbin,
-                                            int4* __restrict__ bbout, const PushParams<R>& pp, int* status,
-                                            int s)
+                                            int4* __restrict__ bbout, const PushParams<R>& pp, const FarList& far,
+                                            int* status, int s)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];   // 16-byte aligned: FP64 DS ops
-    __shared__ int4 red[NTHR / 64];
-    __shared__ double redd[NTHR / 64];
-    __shared__ int misfit[MISFIT_CAP];
-    __shared__ int nmisfit;
+    __shared__ int4 red[NTH / 64];
+    __shared__ double redd[NTH / 64];
     const Segment sg = seg[s];
     const int4 bb = bbin[s];
     if (sg.count <= 0 || bb.x > bb.y || bb.z > bb.w) {
         if (threadIdx.x == 0) bbout[s] = make_int4(INT_MAX, INT_MIN, INT_MAX, INT_MIN);
         return;
     }
+    const int end = sg.start + sg.count;
+    // the first particle's state travels while the tile is staged
+    int p = sg.start + threadIdx.x;
+    EState<R> nxt{}, done{};
+    if (p < end) nxt = load_electron(e, p);
     LdsAcc<R> lds;
     lds.xb = bb.x - 2;
     lds.zb = bb.z - 2;
@@ -415,159 +484,103 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
     constexpr int TCELLS = tcells<R>();
     using JT = typename LdsAcc<R>::JT;
     lds.j = reinterpret_cast<JT*>(lds.f + 6 * TCELLS);   // 6 TCELLS elements: 8-byte aligned
-    // A box larger than the staged tile (particles spread since the last sort, as in a heated
-    // plasma) still stages the largest window, centred on the box, while each thread can
-    // remember which of its particles fall outside (at most 64 per thread); those are pushed with
-    // the global accessors after the tile is flushed.  Larger segments take the global accessors
-    // throughout.
-    const bool fits = lds.lx <= TPX && lds.lz <= trows<R>();
-    const bool use_lds = fits || sg.count <= 64 * NTHR;
-    if (!fits && use_lds) {
-        // a particle in cell ix fits while xb + 2 <= ix <= xb + lx - 4
-        if (lds.lx > TPX) {
-            lds.xb = ((bb.x + bb.y) >> 1) - 2 - (TPX - 6) / 2;
-            lds.lx = TPX;
-        }
-        if (lds.lz > trows<R>()) {
-            lds.zb = ((bb.z + bb.w) >> 1) - 2 - (trows<R>() - 6) / 2;
-            lds.lz = trows<R>();
-        }
-    }
+    if (lds.lx > TPX || lds.lz > trows<R>()) clamp_window<R, NTH>(e, sg, bb, lds, redd);
     int x0 = INT_MAX, x1 = INT_MIN, z0 = INT_MAX, z1 = INT_MIN;
-    const int end = sg.start + sg.count;
-    const int L = lds.lx * lds.lz;
-    if (use_lds) {
-        double js = 1.0, jq = 1.0;   // current into tile units and back
-        if constexpr (LdsAcc<R>::FIX) {
-            double sw = 0.0;
-            for (int p = sg.start + threadIdx.x; p < end; p += NTHR) sw += fabs((double)e.w[p]);
-            sw = block_sum(sw, redd);
-            const double fj = fmax(fabs((double)pp.fjx), fmax(fabs((double)pp.fjz), fabs((double)pp.fjy)));
-            const double bound = fj * sw;   // |v_y| < 1 and every weight factor is <= 1
-            if (bound > 0.0) { js = FIX_RANGE / bound; jq = bound / FIX_RANGE; }
-        }
-        if (threadIdx.x == 0) nmisfit = 0;
-        for (int q = threadIdx.x; q < L; q += NTHR) {
-            const int a = q % lds.lx, b = q / lds.lx;
-            const int i = swrap(lds.xb + a + g.Px, g.Sx, g.perx);
-            const int k = swrap(lds.zb + b + g.Pz, g.Sz, g.perz);
-            R v[6] = {0, 0, 0, 0, 0, 0};
-            if (i >= 0 && k >= 0) {
-                const long o = gofs(g, i, k);
-                if constexpr (MC) {
-#pragma unroll
-                    for (int c = 0; c < 6; c++) v[c] = f.G[c][o];
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 3; c++) {
-                        v[c] = f.E[c][o];
-                        v[3 + c] = R(0.5) * (f.B[c][o] + f.Bn[c][o]);
-                    }
-                }
-            }
-            const int t = b * TPX + a;
-#pragma unroll
-            for (int c = 0; c < 6; c++) lds.f[c * TCELLS + t] = v[c];
-#pragma unroll
-            for (int c = 0; c < 3; c++) lds.j[c * TCELLS + t] = JT(0);
-        }
-        __syncthreads();
-        // the next particle's state is read while the current one is pushed (the loop is
-        // otherwise bound by the HBM latency of its loads); its result is written back at the
-        // top of the next iteration, ahead of the following prefetch, so that waiting for the
-        // prefetch never waits for fresh stores
-        int p = sg.start + threadIdx.x;
-        EState<R> nxt{}, done{};
-        int pdone = -1;
-        uint64_t late = 0;   // bit k: this thread's k-th particle lies outside the staged window
-        if (p < end) nxt = load_electron(e, p);
-        for (int k = 0; p < end; p += NTHR, k++) {
-            EState<R> cur = nxt;
-            // the prefetched registers are taken here, before this iteration's stores and
-            // loads are issued, so the wait for them covers only memory operations issued one
-            // iteration ago (an empty asm that reads them; it emits no instruction)
-            asm volatile("" ::"v"(cur.x), "v"(cur.z), "v"(cur.ux), "v"(cur.uy), "v"(cur.uz), "v"(cur.w)
-                         : "memory");
-            if (pdone >= 0) store_electron(e, pdone, done);
-            pdone = -1;
-            if (p + NTHR < end) nxt = load_electron(e, p + NTHR);
-            if (cur.w == R(0)) continue;
-            const int ix = (int)floor(cur.x), iz = (int)floor(cur.z);
-            if (!lds.inside(ix - 2, ix + 3, iz - 2, iz + 3)) {
-                if (k < 64) {
-                    late |= 1ull << k;
-                } else {
-                    const int slot = atomicAdd(&nmisfit, 1);
-                    if (slot < MISFIT_CAP) misfit[slot] = p;
-                    else atomicOr(status, ST_SEGMENTS);
-                }
-                continue;
-            }
-            advance_electron<MC>(lds, g, pp, cur, js, status, x0, x1, z0, z1);
-            done = cur;
-            pdone = p;
-        }
-        if (pdone >= 0) store_electron(e, pdone, done);
-        __syncthreads();
-        for (int q = threadIdx.x; q < L; q += NTHR) {
-            const int a = q % lds.lx, b = q / lds.lx;
-            const int i = swrap(lds.xb + a + g.Px, g.Sx, g.perx);
-            const int k = swrap(lds.zb + b + g.Pz, g.Sz, g.perz);
-            if (i < 0 || k < 0) continue;
+    const int L = lds.lz * TPX;
+    for (int q = threadIdx.x; q < L; q += NTH) {
+        const int a = q % TPX, b = q / TPX;
+        const int i = a < lds.lx ? swrap(lds.xb + a + g.Px, g.Sx, g.perx) : -1;
+        const int k = swrap(lds.zb + b + g.Pz, g.Sz, g.perz);
+        R v[6] = {0, 0, 0, 0, 0, 0};
+        if (i >= 0 && k >= 0) {
             const long o = gofs(g, i, k);
-            const int t = b * TPX + a;
+            if constexpr (MC) {
 #pragma unroll
-            for (int c = 0; c < 3; c++) {
-                R v;
-                if constexpr (LdsAcc<R>::FIX) v = (R)(fix_value(lds.j[c * TCELLS + t]) * jq);
-                else v = (R)lds.j[c * TCELLS + t];
-                if (v != R(0)) atomicAdd(&f.J[c][o], v);
+                for (int c = 0; c < 6; c++) v[c] = f.G[c][o];
+            } else {
+#pragma unroll
+                for (int c = 0; c < 3; c++) {
+                    v[c] = f.E[c][o];
+                    v[3 + c] = R(0.5) * (f.B[c][o] + f.Bn[c][o]);
+                }
             }
         }
-        // particles outside the staged window: global accessors
-        const int nm = min(nmisfit, MISFIT_CAP);
-        if (nm > 0 || late) {
-            const GlobAcc<R> glb = make_glob<MC>(g, f);
-            while (late) {
-                const int b = __builtin_ctzll(late);
-                late &= late - 1;
-                const int q = sg.start + threadIdx.x + b * NTHR;
-                EState<R> st = load_electron(e, q);
-                advance_electron<MC>(glb, g, pp, st, 1.0, status, x0, x1, z0, z1);
-                store_electron(e, q, st);
-            }
-            for (int q = threadIdx.x; q < nm; q += NTHR) {
-                const int p = misfit[q];
-                EState<R> st = load_electron(e, p);
-                advance_electron<MC>(glb, g, pp, st, 1.0, status, x0, x1, z0, z1);
-                store_electron(e, p, st);
-            }
-        }
+#pragma unroll
+        for (int c = 0; c < 6; c++) lds.f[c * TCELLS + q] = v[c];
+#pragma unroll
+        for (int c = 0; c < 3; c++) lds.j[c * TCELLS + q] = JT(0);
+    }
+    double js = 1.0, jq = 1.0;   // current into tile units and back
+    if constexpr (LdsAcc<R>::FIX) {
+        double sw = fabs((double)nxt.w);
+        for (int q = p + NTH; q < end; q += NTH) sw += fabs((double)e.w[q]);
+        sw = block_sum<NTH>(sw, redd);
+        const double fj = fmax(fabs((double)pp.fjx), fmax(fabs((double)pp.fjz), fabs((double)pp.fjy)));
+        const double bound = fj * sw;   // |v_y| < 1 and every weight factor is <= 1
+        if (bound > 0.0) { js = FIX_RANGE / bound; jq = bound / FIX_RANGE; }
     } else {
-        const GlobAcc<R> glb = make_glob<MC>(g, f);
-        for (int p = sg.start + threadIdx.x; p < end; p += NTHR) {
-            EState<R> st = load_electron(e, p);
-            if (st.w == R(0)) continue;
-            advance_electron<MC>(glb, g, pp, st, 1.0, status, x0, x1, z0, z1);
-            store_electron(e, p, st);
+        __syncthreads();
+    }
+    // the next particle's state is read while the current one is pushed (the loop is otherwise
+    // bound by the HBM latency of its loads); its result is written back at the top of the next
+    // iteration, ahead of the following prefetch, so that waiting for the prefetch never waits
+    // for fresh stores
+    int pdone = -1;
+    for (; p < end; p += NTH) {
+        EState<R> cur = nxt;
+        // the prefetched registers are taken here, before this iteration's stores and
+        // loads are issued, so the wait for them covers only memory operations issued one
+        // iteration ago (an empty asm that reads them; it emits no instruction)
+        asm volatile("" ::"v"(cur.x), "v"(cur.z), "v"(cur.ux), "v"(cur.uy), "v"(cur.uz), "v"(cur.w)
+                     : "memory");
+        if (pdone >= 0) store_electron(e, pdone, done);
+        pdone = -1;
+        if (p + NTH < end) nxt = load_electron(e, p + NTH);
+        if (cur.w == R(0)) continue;
+        const int ix = (int)floor(cur.x), iz = (int)floor(cur.z);
+        if (!lds.inside(ix - 2, ix + 3, iz - 2, iz + 3)) {
+            far.list[atomicAdd(far.n, 1)] = make_int2(s, p);
+            continue;
+        }
+        advance_electron<MC>(lds, g, pp, cur, js, status, x0, x1, z0, z1);
+        done = cur;
+        pdone = p;
+    }
+    if (pdone >= 0) store_electron(e, pdone, done);
+    __syncthreads();
+    for (int q = threadIdx.x; q < L; q += NTH) {
+        const int a = q % TPX, b = q / TPX;
+        const int i = a < lds.lx ? swrap(lds.xb + a + g.Px, g.Sx, g.perx) : -1;
+        const int k = swrap(lds.zb + b + g.Pz, g.Sz, g.perz);
+        if (i < 0 || k < 0) continue;
+        const long o = gofs(g, i, k);
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            R v;
+            if constexpr (LdsAcc<R>::FIX) v = (R)(fix_value(lds.j[c * TCELLS + q]) * jq);
+            else v = (R)lds.j[c * TCELLS + q];
+            if (v != R(0)) atomicAdd(&f.J[c][o], v);
         }
     }
     block_bbox(x0, x1, z0, z1, red);
     if (threadIdx.x == 0) bbout[s] = make_int4(x0, x1, z0, z1);
 }
 
+// FP64 workgroups are twice as large: their tiles hold the same particles, but a register budget
+// of 256 leaves two waves per SIMD, so a small grid has too few of them in flight at 256 threads.
+template <typename R> constexpr int gpd_threads() { return sizeof(R) == 4 ? 256 : 512; }
+
 template <typename R, bool MC>
-__global__ void __launch_bounds__(NTHR, sizeof(R) == 4 ? 3 : 1) k_gpd(Geo g, FieldSet<R> f, ElectronArrays<R> e,
-                                              const Segment* __restrict__ seg,
-                                              const int4* __restrict__ bbin, int4* __restrict__ bbout,
-                                              PushParams<R> pp, int* status)
+__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
+    k_gpd(Geo g, FieldSet<R> f, ElectronArrays<R> e, const Segment* __restrict__ seg, const int4* __restrict__ bbin,
+          int4* __restrict__ bbout, PushParams<R> pp, FarList far, int* status)
 {
-    gpd_segment<R, MC>(g, f, e, seg, bbin, bbout, pp, status, blockIdx.x);
+    gpd_segment<R, MC, gpd_threads<R>()>(g, f, e, seg, bbin, bbout, pp, far, status, blockIdx.x);
 }
 
 template <typename R>
-__global__ void __launch_bounds__(NTHR, sizeof(R) == 4 ? 3 : 1) k_gpd_batch(const GpdDesc<R>* __restrict__ d,
-                                                                            QueueRef q)
+__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1) k_gpd_batch(const GpdDesc<R>* __restrict__ d,
+                                                                                        QueueRef q)
 {
     __shared__ int slot;
     int r = 0;
@@ -576,7 +589,114 @@ __global__ void __launch_bounds__(NTHR, sizeof(R) == 4 ? 3 : 1) k_gpd_batch(cons
         if (it < 0) return;
         r = run_of(q, it, r);
         const GpdDesc<R>& D = d[r];
-        gpd_segment<R>(D.g, D.f, D.e, D.seg, D.bbin, D.bbout, D.pp, D.status, it - q.off[r]);
+        gpd_segment<R, false, gpd_threads<R>()>(D.g, D.f, D.e, D.seg, D.bbin, D.bbout, D.pp, D.far, D.status,
+                                                it - q.off[r]);
+    }
+}
+
+// ---- electrons outside their staged window, on HBM ----------------------------------------
+// sum over the 16 lanes of a particle
+template <typename R>
+__device__ __forceinline__ R sum16(R v)
+{
+    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+// the cubic B-spline at distance r from a node
+template <typename R>
+__device__ __forceinline__ R spline3(R r)
+{
+    const R d = fabs(r), t = R(2) - d;
+    const R near = R(2.0 / 3.0) - d * d * (R(1) - R(0.5) * d), far = t * t * t * R(1.0 / 6.0);
+    return d < R(1) ? near : d < R(2) ? far : R(0);
+}
+
+// Particle p of segment s by 16 lanes, one stencil node each for the gather and two of the 25
+// nodes for the deposit: a few dependent loads, where one thread would walk 16 nodes of nine
+// arrays and 65 adds.  Lanes 0-4 hold the deposit's shape factors of the window's x nodes, lanes
+// 5-9 those of its z nodes; the others fetch them by shuffles, which keeps the registers of the
+// ion path it shares a kernel with.
+template <bool MC, typename R>
+__device__ __forceinline__ void far_electron(const Geo& g, const FieldSet<R>& f, const ElectronArrays<R>& e,
+                                             const PushParams<R>& pp, int4* bbout, int* status, int s, int p)
+{
+    const int n = threadIdx.x & 15, a = n & 3, b = n >> 2;
+    EState<R> st = load_electron(e, p);
+    const double x = st.x, z = st.z;
+    const int ix = (int)floor(x), iz = (int)floor(z);
+    auto at = [&](int jx, int jz) -> long {
+        const int i = swrap(jx + g.Px, g.Sx, g.perx), k = swrap(jz + g.Pz, g.Sz, g.perz);
+        return i < 0 || k < 0 ? -1 : gofs(g, i, k);
+    };
+    // this lane's node and weight for each stagger along x and z
+    R wx[2], wz[2];
+    int jx[2], jz[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const double xs = x - 0.5 * h, zs = z - 0.5 * h;
+        jx[h] = (int)floor(xs) - 1 + a;
+        jz[h] = (int)floor(zs) - 1 + b;
+        wx[h] = spline3((R)(xs - jx[h]));
+        wz[h] = spline3((R)(zs - jz[h]));
+    }
+    R E[3], B[3];
+#pragma unroll
+    for (int c = 0; c < 6; c++) {
+        // staggers: E_x (half, node), E_y (node, node), E_z (node, half), B_x (node, half),
+        // B_y (half, half), B_z (half, node); the node values have none
+        const int hx = !MC && (c == 0 || c == 4 || c == 5), hz = !MC && (c == 2 || c == 3 || c == 4);
+        const long o = at(jx[hx], jz[hz]);
+        R v = R(0);
+        if (o >= 0) v = MC ? f.G[c][o] : c < 3 ? f.E[c][o] : R(0.5) * (f.B[c - 3][o] + f.Bn[c - 3][o]);
+        v = sum16(wx[hx] * wz[hz] * v);
+        if (c < 3) E[c] = v;
+        else B[c - 3] = v;
+    }
+    R u[3] = {st.ux, st.uy, st.uz}, v[3];
+    push_electron(pp, E, B, u, v);
+    const double xn = x + (double)(pp.dtdx * v[0]), zn = z + (double)(pp.dtdz * v[2]);
+    const int ix1 = (int)floor(xn), iz1 = (int)floor(zn);
+    if (abs(ix1 - ix) <= 1 && abs(iz1 - iz) <= 1) {
+        const double w = (double)st.w;
+        const int bx = min(ix, ix1) - 1, bz = min(iz, iz1) - 1;
+        const bool isx = n < 5;
+        const int node = isx ? bx + n : bz + n - 5;
+        const double s0 = spline3((isx ? x : z) - node), s1 = spline3((isx ? xn : zn) - node);
+        double pd = s1 - s0;             // becomes the prefix sum over the axis' nodes
+        for (int o = 1; o < 5; o <<= 1) {
+            const double up = __shfl_up(pd, o, 16);
+            if ((isx ? n : n - 5) >= o) pd += up;
+        }
+#pragma unroll 1
+        for (int q = n; q < 32; q += 16) {
+            const int m = q % 5, k = min(q / 5, 4);
+            const double s0x = __shfl(s0, m, 16), s1x = __shfl(s1, m, 16), s0z = __shfl(s0, 5 + k, 16),
+                         s1z = __shfl(s1, 5 + k, 16);
+            const double px = __shfl(pd, m, 16), pz = __shfl(pd, 5 + k, 16);
+            const long o = q < 25 ? at(bx + m, bz + k) : -1;
+            if (o < 0) continue;
+            const double vx = m < 4 ? w * (double)pp.fjx * px * 0.5 * (s0z + s1z) : 0.0;
+            const double vz = k < 4 ? w * (double)pp.fjz * pz * 0.5 * (s0x + s1x) : 0.0;
+            const double vy = w * (double)(pp.fjy * v[1]) *
+                              (s0x * (s0z / 3.0 + s1z / 6.0) + s1x * (s0z / 6.0 + s1z / 3.0));
+            if (vx != 0.0) atomicAdd(&f.J[0][o], (R)vx);
+            if (vz != 0.0) atomicAdd(&f.J[2][o], (R)vz);
+            if (vy != 0.0) atomicAdd(&f.J[1][o], (R)vy);
+        }
+    } else {
+        atomicOr(status, ST_NONFINITE);   // faster than light: only a non-finite state gets here
+    }
+    int x0 = INT_MAX, x1 = INT_MIN, z0 = INT_MAX, z1 = INT_MIN;
+    finish_electron(g, pp, xn, zn, u, st, status, x0, x1, z0, z1);
+    if (n == 0) {
+        store_electron(e, p, st);
+        if (x0 <= x1) {
+            atomicMin(&bbout[s].x, x0);
+            atomicMax(&bbout[s].y, x1);
+            atomicMin(&bbout[s].z, z0);
+            atomicMax(&bbout[s].w, z1);
+        }
     }
 }
 
@@ -695,16 +815,6 @@ __device__ __forceinline__ void ion_segment(const Geo& g, const FieldSet<R>& f, 
     if (threadIdx.x == 0) bbout[s] = make_int4(x0, x1, z0, z1);
 }
 
-template <typename R>
-__global__ void __launch_bounds__(NTHR) k_ions(Geo g, FieldSet<R> f, IonArrays<R> ion,
-                                               const Segment* __restrict__ seg,
-                                               const int4* __restrict__ bbin, int4* __restrict__ bbout,
-                                               double zsh_a, double zsh_b, int shift, R fjz)
-{
-    ion_segment<R>(g, f, ion, seg, bbin, bbout, zsh_a, zsh_b, shift, fjz, blockIdx.x);
-}
-
-
 // ---- antenna (FP64) ------------------------------------------------------------------------
 
 // Esirkepov current of one particle moving (x0, z0) -> (x1, z1) (cells, |move| < 1 cell) with
@@ -749,11 +859,10 @@ __device__ __forceinline__ void esirkepov_cell(double x0, double z0, double x1, 
 // (J_x), along y it keeps its home x and its velocity enters J_y.  Both deposit by Esirkepov in
 // FP64.
 template <typename R>
-__global__ void __launch_bounds__(64) k_antenna(Geo g, FieldSet<R> f, double* xm, AntennaParams ap)
+__device__ __forceinline__ void antenna_pair(const Geo& g, const FieldSet<R>& f, double* xm, const AntennaParams& ap,
+                                             int i)
 {
-    const int i = blockIdx.x;
-    const int lane = threadIdx.x;
-    if (i >= ap.n) return;
+    const int lane = threadIdx.x & 63;
     const double xh = i + 0.5;                   // home position (cells)
     const double xum = xh * ap.dx_um;
     // field to emit: (E0/gamma) f sin(omega t'/gamma - phase) with the lab time elapsed at the
@@ -783,6 +892,31 @@ __global__ void __launch_bounds__(64) k_antenna(Geo g, FieldSet<R> f, double* xm
         }
     }
     if (lane == 0) xm[i] = xb;
+}
+
+// The sources of a step's current beside the staged electrons, in one launch: workgroups
+// [0, nion) take an ion segment each, the next na four antenna pairs (a wave each), the rest the
+// electrons of the list far (16 lanes each, a quarter of a wave).  They only add to J.  As
+// launches of their own the antenna and the list cost 5-6 us each whatever their work.  Bounded
+// to five waves per SIMD in FP32, what the ions reach alone: at three they took 150 us instead
+// of 119 us on 256 x 4096 cells (16.8 M ions).
+template <typename R, bool MC>
+__global__ void __launch_bounds__(NTHR, sizeof(R) == 4 ? 5 : 4) k_sources(Geo g, FieldSet<R> f, SourceParams<R> sp)
+{
+    const int b = blockIdx.x;
+    if (b < sp.nion) {
+        ion_segment<R>(g, f, sp.ion, sp.iseg, sp.ibbin, sp.ibbout, sp.zsh_a, sp.zsh_b, sp.pp.shift, sp.fjz, b);
+    } else if (b < sp.nion + sp.na) {
+        const int i = (b - sp.nion) * (NTHR / 64) + (int)threadIdx.x / 64;
+        if (i < sp.ap.n) antenna_pair<R>(g, f, sp.xm, sp.ap, i);
+    } else {
+        const int n = *sp.far.n, step = (gridDim.x - sp.nion - sp.na) * (NTHR / 16);
+        // the 16 lanes of a particle stay together: i is the same for all of them
+        for (int i = (b - sp.nion - sp.na) * (NTHR / 16) + (int)threadIdx.x / 16; i < n; i += step) {
+            const int2 m = sp.far.list[i];
+            far_electron<MC>(g, f, sp.e, sp.pp, sp.ebbout, sp.status, m.x, m.y);
+        }
+    }
 }
 
 // ---- particle beam through a lab-fixed plane (Sec. 3.1.1) ---------------------------------
@@ -1318,28 +1452,31 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_disperse_i(Geo g, IonArra
 // ---- launchers ---------------------------------------------------------------------------------
 template <typename R>
 void launch_gpd(const Geo& g, const FieldSet<R>& f, const ElectronArrays<R>& e, const Segment* seg,
-                const int4* bbox_in, int4* bbox_out, int nseg, const PushParams<R>& pp, int* status,
-                bool mc, hipStream_t s)
+                const int4* bbox_in, int4* bbox_out, int nseg, const PushParams<R>& pp, const FarList& far,
+                int* status, bool mc, hipStream_t s)
 {
     if (nseg <= 0) return;
     const size_t lds = (size_t)tcells<R>() * (6 * sizeof(R) + 3 * sizeof(typename LdsAcc<R>::JT));
+    const dim3 block(gpd_threads<R>());
     if (mc)
-        hipLaunchKernelGGL((k_gpd<R, true>), dim3(nseg), dim3(NTHR), lds, s, g, f, e, seg, bbox_in, bbox_out,
-                           pp, status);
+        hipLaunchKernelGGL((k_gpd<R, true>), dim3(nseg), block, lds, s, g, f, e, seg, bbox_in, bbox_out, pp, far,
+                           status);
     else
-        hipLaunchKernelGGL((k_gpd<R, false>), dim3(nseg), dim3(NTHR), lds, s, g, f, e, seg, bbox_in, bbox_out,
-                           pp, status);
+        hipLaunchKernelGGL((k_gpd<R, false>), dim3(nseg), block, lds, s, g, f, e, seg, bbox_in, bbox_out, pp, far,
+                           status);
 }
 
 template <typename R>
-void launch_ions(const Geo& g, const FieldSet<R>& f, const IonArrays<R>& ion, const Segment* seg,
-                 const int4* bbox_in, int4* bbox_out, int nseg, double zsh_a, double zsh_b, int shift,
-                 R fjz, hipStream_t s)
+void launch_sources(const Geo& g, const FieldSet<R>& f, SourceParams<R> sp, int nseg_e, bool mc, hipStream_t s)
 {
-    if (nseg <= 0) return;
+    sp.na = sp.ap.active ? (sp.ap.n + NTHR / 64 - 1) / (NTHR / 64) : 0;
+    // the list is nearly always empty or short; its workgroups stride over it
+    const int nfar = nseg_e <= 0 ? 0 : std::min(std::max(nseg_e / 4, 8), 512);
+    const int n = sp.nion + sp.na + nfar;
+    if (n <= 0) return;
     const size_t lds = (size_t)tcells<R>() * sizeof(typename LdsAcc<R>::JT);
-    hipLaunchKernelGGL((k_ions<R>), dim3(nseg), dim3(NTHR), lds, s, g, f, ion, seg, bbox_in, bbox_out,
-                       zsh_a, zsh_b, shift, fjz);
+    if (mc) hipLaunchKernelGGL((k_sources<R, true>), dim3(n), dim3(NTHR), lds, s, g, f, sp);
+    else hipLaunchKernelGGL((k_sources<R, false>), dim3(n), dim3(NTHR), lds, s, g, f, sp);
 }
 
 template <typename R>
@@ -1347,16 +1484,7 @@ void launch_gpd_batch(const GpdDesc<R>* d, const QueueRef& q, int nblocks, hipSt
 {
     const size_t lds = (size_t)tcells<R>() * (6 * sizeof(R) + 3 * sizeof(typename LdsAcc<R>::JT));
     if (q.total > 0)
-        hipLaunchKernelGGL((k_gpd_batch<R>), dim3(nblocks), dim3(NTHR), lds, s, d, q);
-}
-
-
-template <typename R>
-void launch_antenna(const Geo& g, const FieldSet<R>& f, double* xminus, const AntennaParams& ap,
-                    hipStream_t s)
-{
-    if (!ap.active || ap.n <= 0) return;
-    hipLaunchKernelGGL((k_antenna<R>), dim3(ap.n), dim3(64), 0, s, g, f, xminus, ap);
+        hipLaunchKernelGGL((k_gpd_batch<R>), dim3(nblocks), dim3(gpd_threads<R>()), lds, s, d, q);
 }
 
 template <typename R>
@@ -1424,14 +1552,11 @@ void launch_sort_ions(const Geo& g, int tile_x, int tile_z, int ntx, int ntiles,
 
 #define BF_INST(R)                                                                                    \
     template void launch_gpd<R>(const Geo&, const FieldSet<R>&, const ElectronArrays<R>&,             \
-                                const Segment*, const int4*, int4*, int, const PushParams<R>&, int*,  \
-                                bool, hipStream_t);                                                   \
-    template void launch_ions<R>(const Geo&, const FieldSet<R>&, const IonArrays<R>&,                 \
-                                 const Segment*, const int4*, int4*, int, double, double, int, R,     \
-                                 hipStream_t);                                                        \
-    template void launch_gpd_batch<R>(const GpdDesc<R>*, const QueueRef&, int, hipStream_t);          \
-    template void launch_antenna<R>(const Geo&, const FieldSet<R>&, double*, const AntennaParams&,    \
+                                const Segment*, const int4*, int4*, int, const PushParams<R>&,        \
+                                const FarList&, int*, bool, hipStream_t);                             \
+    template void launch_sources<R>(const Geo&, const FieldSet<R>&, SourceParams<R>, int, bool,       \
                                     hipStream_t);                                                     \
+    template void launch_gpd_batch<R>(const GpdDesc<R>*, const QueueRef&, int, hipStream_t);          \
     template void launch_beam<R>(const Geo&, const FieldSet<R>&, const BeamArrays&, const BeamParams&, \
                                  const PushParams<double>&, int*, bool, hipStream_t);                 \
     template void launch_inject<R>(const Geo&, const ElectronArrays<R>&, const IonArrays<R>&,         \

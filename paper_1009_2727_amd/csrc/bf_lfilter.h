@@ -35,22 +35,24 @@ struct Packed {
 };
 
 int chunks(int cin);
-void launch_pack(const float* w, int cin, int cout, bool adjoint, void* wpk, hipStream_t s);
 template <int CIN, int COUT>
 void launch_conv(const View& in, const View& out, const Domain& d, const void* wpk, hipStream_t s);
 void launch_loss(const float* out, const float* target, float* g, const Domain& d, int margin,
                  double inv_count, double* loss, hipStream_t s);
-void launch_adam(float* w, float* m, float* v, const float* g, int n, float lr, float b1, float b2,
-                 float eps, float c1, float c2, hipStream_t s);
-void launch_zero(float* p, int n, hipStream_t s);
+// Adam's part of a training step: parameters and moments (w null: none), c1 = 1/(1 - b1^t) etc.
+struct AdamStep {
+    float *w, *m, *v;
+    float lr, b1, b2, eps, c1, c2;
+};
 void pack_forward(const float* params, const Packed& pk, hipStream_t s);
-void pack_adjoint(const float* params, const Packed& pk, hipStream_t s);
+// the forward and adjoint fragments in one launch, which also clears *clear
+void pack_training(const float* params, const Packed& pk, double* clear, hipStream_t s);
 void forward(const View& in, const View& h1, const View& h2, const View& out, const Domain& d,
              const Packed& pk, hipStream_t s);
 void forward_fused(const View* in, const View* out, const Domain* d, int nplanes, const Packed& pk, hipStream_t s);
 void backward(const View& in, const View& h1, const View& h2, const View& out, const View& gout,
               const View& gh1, const View& gh2, const Domain& d, const Packed& pk, float* dw,
-              hipStream_t s);
+              const double* loss, double* loss_out, float* grad_out, const AdamStep& st, hipStream_t s);
 
 }  // namespace lf
 }  // namespace bf

@@ -18,10 +18,12 @@
 //
 // Training: backward-data is the same convolution with the adjoint weights
 // W'(t, a, b) = W(24 - t, b, a); the weight gradient dW(t, ci, co) = sum_p in(p + o_t, ci)
-// g(p, co) is an MFMA GEMM over pixels (hi/lo products hi*hi + hi*lo + lo*hi); Adam (Kingma &
-// Ba 2015) updates the FP32 master weights.
+// g(p, co) is an MFMA GEMM over pixels (hi/lo products hi*hi + hi*lo + lo*hi), each workgroup's
+// share summed in registers and written once; the last kernel adds the shares in a fixed order
+// and Adam (Kingma & Ba 2015) updates the FP32 master weights.
 #include "bf_lfilter.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace bf {
 namespace lf {
@@ -30,8 +32,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short us8 __attribute__((ext_vector_type(8)));
 
-constexpr int LTX = 64, LTY = 4;   // output tile: 4 rows of 64 pixels, one row per wave
-constexpr int LHX = LTX + 4, LHY = LTY + 4;   // staged input tile with the 2-pixel halo
+// output tile of a convolution: 256 pixels, 64 x 4 or 32 x 8 (a wave takes 64 of them: one row, or
+// two); the 32-wide tile wastes less on images such as 32 x 32 patches
+template <int TX> struct ConvTile {
+    static constexpr int Y = 256 / TX, HX = TX + 4, HY = Y + 4;   // rows; extents with the 2-pixel halo
+};
 
 __device__ __forceinline__ unsigned short bf16_rne(float x)
 {
@@ -61,44 +66,104 @@ __device__ __forceinline__ int dwrap(int i, int n, int per)
     return (i < 0 || i >= n) ? -1 : i;
 }
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// two BF16 values (round to nearest even, in hardware) in one word
+__device__ __forceinline__ unsigned pk_bf16(float a, float b)
+{
+    const bf16x2 p = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(unsigned, p);
+}
+
+// hi and lo BF16 parts of four values
+__device__ __forceinline__ void split4(const float4& v, uint2& hi, uint2& lo)
+{
+    hi.x = pk_bf16(v.x, v.y);
+    hi.y = pk_bf16(v.z, v.w);
+    lo.x = pk_bf16(v.x - __uint_as_float(hi.x << 16), v.y - __uint_as_float(hi.x & 0xffff0000u));
+    lo.y = pk_bf16(v.z - __uint_as_float(hi.y << 16), v.w - __uint_as_float(hi.y & 0xffff0000u));
+}
+
+// A 16-channel tile of ROWS x COLS pixels from (y0, x0), four channels of a pixel per item: every
+// item's load is issued before the first is used (one load at a time made staging the longest
+// part of the training kernels), then put(pixel, first channel, hi, lo) stores it.  Beyond the
+// domain: 0, or wrapped when WRAP asks for the boundary rule.
+template <int ROWS, int COLS, bool WRAP, typename Put>
+__device__ __forceinline__ void stage16(const View& v, const Domain& d, int img, int x0, int y0, Put put)
+{
+    constexpr int N = ROWS * COLS * 4, NI = (N + 255) / 256;
+    float4 r[NI];
+#pragma unroll
+    for (int m = 0; m < NI; m++) {
+        const int q = (int)threadIdx.x + 256 * m, c = 4 * (q & 3), p = q >> 2;
+        int x = x0 + p % COLS, y = y0 + p / COLS;
+        if constexpr (WRAP) {
+            x = dwrap(x, d.nx, d.perx);
+            y = dwrap(y, d.ny, d.pery);
+        }
+        const bool in = q < N && x >= 0 && y >= 0 && x < d.nx && y < d.ny;
+        r[m] = in ? *reinterpret_cast<const float4*>(v.p + vaddr(v, img, y, x) + c) : float4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int m = 0; m < NI; m++) {
+        const int q = (int)threadIdx.x + 256 * m;
+        if (q < N) {
+            uint2 hi, lo;
+            split4(r[m], hi, lo);
+            put(q >> 2, 4 * (q & 3), hi, lo);
+        }
+    }
+}
+
 // stage the input tile (halo 2) as [pixel][hi c0..c(C-1)][lo c0..c(C-1)]
-template <int CIN>
+template <int CIN, int TX>
 __device__ __forceinline__ void stage_input(const View& in, const Domain& d, int img, int x0, int y0,
                                             unsigned short* tile)
 {
-    for (int q = threadIdx.x; q < LHY * LHX * CIN; q += blockDim.x) {
-        const int ci = q % CIN, pix = q / CIN;
-        const int x = dwrap(x0 - 2 + pix % LHX, d.nx, d.perx);
-        const int y = dwrap(y0 - 2 + pix / LHX, d.ny, d.pery);
-        const float v = (x >= 0 && y >= 0) ? in.p[vaddr(in, img, y, x) + ci] : 0.f;
-        const unsigned short hi = bf16_rne(v);
-        tile[pix * 2 * CIN + ci] = hi;
-        tile[pix * 2 * CIN + CIN + ci] = bf16_rne(v - bf16_val(hi));
+    constexpr int HX = ConvTile<TX>::HX, HY = ConvTile<TX>::HY;
+    if constexpr (CIN == 16) {
+        stage16<HY, HX, true>(in, d, img, x0 - 2, y0 - 2, [&](int pix, int c, uint2 hi, uint2 lo) {
+            *reinterpret_cast<uint2*>(tile + pix * 32 + c) = hi;
+            *reinterpret_cast<uint2*>(tile + pix * 32 + 16 + c) = lo;
+        });
+    } else {
+        for (int pix = threadIdx.x; pix < HY * HX; pix += 256) {
+            const int x = dwrap(x0 - 2 + pix % HX, d.nx, d.perx);
+            const int y = dwrap(y0 - 2 + pix / HX, d.ny, d.pery);
+            const float v = (x >= 0 && y >= 0) ? in.p[vaddr(in, img, y, x)] : 0.f;
+            const unsigned short hi = bf16_rne(v);
+            tile[pix * 2] = hi;
+            tile[pix * 2 + 1] = bf16_rne(v - bf16_val(hi));
+        }
     }
 }
 
 // one convolution layer: out(p, co) = sum_{t, ci} W(t, ci, co) in(p + o_t, ci) on the
 // domain, zero padding (or wrap) outside.  wpk holds the packed B fragments (nq x 64 lanes).
-template <int CIN, int COUT>
+template <int CIN, int COUT, int TX>
 __global__ void __launch_bounds__(256) k_lf_conv(View in, View out, Domain d, const us8* __restrict__ wpk)
 {
-    constexpr int NQ = (TAPS * CIN * 2 + 31) / 32;
-    __shared__ __attribute__((aligned(16))) unsigned short tile[LHY * LHX * 2 * CIN];
-    const int img = blockIdx.z, x0 = blockIdx.x * LTX, y0 = blockIdx.y * LTY;
-    stage_input<CIN>(in, d, img, x0, y0, tile);
+    constexpr int NQ = (TAPS * CIN * 2 + 31) / 32, HX = ConvTile<TX>::HX, HY = ConvTile<TX>::HY;
+    __shared__ __attribute__((aligned(16))) unsigned short tile[HY * HX * 2 * CIN];
+    const int img = blockIdx.z, x0 = blockIdx.x * TX, y0 = blockIdx.y * ConvTile<TX>::Y;
+    stage_input<CIN, TX>(in, d, img, x0, y0, tile);
     __syncthreads();
-    const int ty = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
-    f32x4 acc[LTX / 16];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    f32x4 acc[4];
 #pragma unroll
-    for (int m = 0; m < LTX / 16; m++) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int m = 0; m < 4; m++) acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the wave's m-th group of 16 pixels: row and first column in the tile
+    auto row_of = [&](int m) { return (wave * 64 + m * 16) / TX; };
+    auto col_of = [&](int m) { return (m * 16) % TX; };
+#pragma unroll 5
     for (int q = 0; q < NQ; q++) {
         const us8 b = wpk[q * 64 + lane];
 #pragma unroll
-        for (int m = 0; m < LTX / 16; m++) {
-            const int px = m * 16 + i;
+        for (int m = 0; m < 4; m++) {
+            const int px = col_of(m) + i, ty = row_of(m);
             us8 a;
             if constexpr (CIN == 16) {
-                const int pix = (ty + q / 5) * LHX + px + q % 5;   // tap q: offset (q/5-2, q%5-2)
+                const int pix = (ty + q / 5) * HX + px + q % 5;   // tap q: offset (q/5-2, q%5-2)
                 a = *reinterpret_cast<const us8*>(&tile[pix * 32 + g * 8]);
             } else {
 #pragma unroll
@@ -106,7 +171,7 @@ __global__ void __launch_bounds__(256) k_lf_conv(View in, View out, Domain d, co
                     const int t = 16 * q + 4 * g + j / 2;
                     unsigned short h = 0, l = 0;
                     if (t < TAPS) {
-                        const int pix = (ty + t / 5) * LHX + px + t % 5;
+                        const int pix = (ty + t / 5) * HX + px + t % 5;
                         h = tile[pix * 2];
                         l = tile[pix * 2 + 1];
                     }
@@ -117,22 +182,23 @@ __global__ void __launch_bounds__(256) k_lf_conv(View in, View out, Domain d, co
             acc[m] = mfma(a, b, acc[m]);
         }
     }
-    const int y = y0 + ty;
-    if (y < d.ny && i < COUT) {
+    if (i < COUT) {
 #pragma unroll
-        for (int m = 0; m < LTX / 16; m++)
+        for (int m = 0; m < 4; m++) {
+            const int y = y0 + row_of(m);
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const int x = x0 + m * 16 + 4 * g + r;
-                if (x < d.nx) out.p[vaddr(out, img, y, x) + i] = acc[m][r];
+                const int x = x0 + col_of(m) + 4 * g + r;
+                if (x < d.nx && y < d.ny) out.p[vaddr(out, img, y, x) + i] = acc[m][r];
             }
+        }
     }
 }
 
-// packed B fragments of a layer (or of its adjoint), one block per K chunk, 64 threads
-__global__ void k_lf_pack(const float* __restrict__ w, int cin, int cout, int adjoint, us8* wpk)
+// packed B fragment q of a layer (or of its adjoint) by 64 threads
+__device__ __forceinline__ void pack_chunk(const float* __restrict__ w, int cin, int cout, int adjoint, us8* wpk, int q)
 {
-    const int q = blockIdx.x, lane = threadIdx.x, n = lane & 15, g = lane >> 4;
+    const int lane = threadIdx.x, n = lane & 15, g = lane >> 4;
     const int ci_n = adjoint ? cout : cin, co_n = adjoint ? cin : cout;
     us8 v;
 #pragma unroll
@@ -147,55 +213,214 @@ __global__ void k_lf_pack(const float* __restrict__ w, int cin, int cout, int ad
     wpk[q * 64 + lane] = v;
 }
 
-// weight gradient of one layer: dw(t, ci, co) += sum over the tile's pixels of
-// in(p + o_t, ci) g(p, co); rows (t, ci) in M tiles of 16, pixels in K chunks of 32
-template <int CIN, int COUT>
-__global__ void __launch_bounds__(256) k_lf_wgrad(View in, View gout, Domain d, float* dw)
+// the packings a call needs, one block per fragment over all of them, and a double to clear
+struct PackJob {
+    const float* w;
+    int cin, cout, adjoint, nq;
+    us8* out;
+};
+struct PackJobs {
+    PackJob j[5];
+    int n;
+    double* clear;
+};
+__global__ void k_lf_pack(PackJobs J)
 {
-    constexpr int MR = TAPS * CIN, NMT = (MR + 15) / 16;
-    __shared__ __attribute__((aligned(16))) unsigned short tin[LHY * LHX * 2 * CIN];
-    __shared__ __attribute__((aligned(16))) unsigned short tg[LTY * LTX * 32];   // [p][hi 16][lo 16]
-    const int img = blockIdx.z, x0 = blockIdx.x * LTX, y0 = blockIdx.y * LTY;
-    stage_input<CIN>(in, d, img, x0, y0, tin);
-    for (int q = threadIdx.x; q < LTY * LTX * 16; q += blockDim.x) {
-        const int c = q % 16, p = q / 16;
-        const int x = x0 + p % LTX, y = y0 + p / LTX;
-        float v = 0.f;
-        if (c < COUT && x < d.nx && y < d.ny) v = gout.p[vaddr(gout, img, y, x) + c];
-        const unsigned short hi = bf16_rne(v);
-        tg[p * 32 + c] = hi;
-        tg[p * 32 + 16 + c] = bf16_rne(v - bf16_val(hi));
+    int q = blockIdx.x;
+    if (q == 0 && threadIdx.x == 0 && J.clear) *J.clear = 0.0;
+    for (int k = 0; k < J.n; k++) {
+        if (q < J.j[k].nq) {
+            pack_chunk(J.j[k].w, J.j[k].cin, J.j[k].cout, J.j[k].adjoint, J.j[k].out, q);
+            return;
+        }
+        q -= J.j[k].nq;
+    }
+}
+
+// ---- weight gradients ----------------------------------------------------------------------
+// A workgroup goes over tiles of 32 x 8 pixels (blockIdx.x + k gridDim.x) and keeps its sums in
+// registers, so that each writes its share once (share blockIdx.x of part): with a tile per
+// workgroup and an atomic per weight and tile, 1024 workgroups added to the same few hundred
+// addresses, 112, 57 and 30 us for the three layers of 128 patches of 32 x 32, against 8, 17 and
+// 8 us; the whole training step 316 -> 89 us.
+// K is 32 pixels of a row; channels are planes in LDS (hi and lo), so that a lane's eight pixels
+// are one 16-byte read.
+constexpr int WTX = 32, WTY = 8;
+struct WTiles {
+    int nx, ny, total;                  // tiles along x and y of an image, tiles in all
+};
+// plane strides in 16-bit words: 4 (mod 8) dwords, so the 16 lanes of a fragment's rows (one plane
+// each) read 16-byte words that fall in different banks
+constexpr int WG_P = WTY * WTX + 8;            // a channel of the gradient tile
+constexpr int WI_W = 40;                       // row of the 16-channel input tile (36 used)
+constexpr int WI_P = (WTY + 4) * WI_W + 8;     // a channel of it
+
+// 16 channels of a tile into planes hi and lo of COLS-wide rows W words apart, channels P words apart
+template <int ROWS, int COLS, int W, int P, bool WRAP>
+__device__ __forceinline__ void stage_planes(const View& v, const Domain& d, int img, int x0, int y0,
+                                             unsigned short* hi, unsigned short* lo)
+{
+    stage16<ROWS, COLS, WRAP>(v, d, img, x0, y0, [&](int pix, int c, uint2 h, uint2 l) {
+        const int o = c * P + pix / COLS * W + pix % COLS;
+        hi[o] = (unsigned short)h.x;
+        hi[o + P] = (unsigned short)(h.x >> 16);
+        hi[o + 2 * P] = (unsigned short)h.y;
+        hi[o + 3 * P] = (unsigned short)(h.y >> 16);
+        lo[o] = (unsigned short)l.x;
+        lo[o + P] = (unsigned short)(l.x >> 16);
+        lo[o + 2 * P] = (unsigned short)l.y;
+        lo[o + 3 * P] = (unsigned short)(l.y >> 16);
+    });
+}
+
+// eight consecutive 16-bit words of a row from the six dwords that start at word 0, shifted by s words
+template <int S>
+__device__ __forceinline__ us8 window8(const unsigned* w)
+{
+    unsigned r[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+        r[j] = S % 2 == 0 ? w[S / 2 + j] : __builtin_amdgcn_alignbit(w[S / 2 + j + 1], w[S / 2 + j], 16);
+    return __builtin_bit_cast(us8, uint4{r[0], r[1], r[2], r[3]});
+}
+
+// 16 -> 16 channels: rows of the product are (tap, ci), so a wave's 25 accumulators are the 25
+// taps; the taps of one row dy share the lane's window of twelve pixels
+__global__ void __launch_bounds__(256) k_lf_wgrad_wide(View in, View gout, Domain d, WTiles wt, float* part)
+{
+    __shared__ __attribute__((aligned(16))) unsigned short sm[2 * 16 * WI_P + 2 * 16 * WG_P];
+    unsigned short *ih = sm, *il = ih + 16 * WI_P, *gh = il + 16 * WI_P, *gl = gh + 16 * WG_P;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+    f32x4 acc[TAPS];
+#pragma unroll
+    for (int t = 0; t < TAPS; t++) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int tile = blockIdx.x; tile < wt.total; tile += gridDim.x) {
+        const int img = tile / (wt.nx * wt.ny), r = tile % (wt.nx * wt.ny), x0 = r % wt.nx * WTX, y0 = r / wt.nx * WTY;
+        __syncthreads();                // the previous tile is done with the LDS
+        stage_planes<WTY + 4, WTX + 4, WI_W, WI_P, true>(in, d, img, x0 - 2, y0 - 2, ih, il);
+        stage_planes<WTY, WTX, WTX, WG_P, false>(gout, d, img, x0, y0, gh, gl);   // pixels beyond the image: 0
+        __syncthreads();
+#pragma unroll 1
+        for (int yy = 0; yy < 2; yy++) {
+            const int y = 2 * wave + yy;
+            const us8 bh = *reinterpret_cast<const us8*>(gh + i * WG_P + y * WTX + 8 * g);
+            const us8 bl = *reinterpret_cast<const us8*>(gl + i * WG_P + y * WTX + 8 * g);
+#pragma unroll
+            for (int dy = 0; dy < 5; dy++) {
+                unsigned wh[6], wl[6];
+                const int o = i * WI_P + (y + dy) * WI_W + 8 * g;
+                *reinterpret_cast<uint4*>(wh) = *reinterpret_cast<const uint4*>(ih + o);
+                *reinterpret_cast<uint2*>(wh + 4) = *reinterpret_cast<const uint2*>(ih + o + 8);
+                *reinterpret_cast<uint4*>(wl) = *reinterpret_cast<const uint4*>(il + o);
+                *reinterpret_cast<uint2*>(wl + 4) = *reinterpret_cast<const uint2*>(il + o + 8);
+                auto tap = [&](auto dx) {
+                    constexpr int DX = decltype(dx)::value;
+                    const us8 ah = window8<DX>(wh), al = window8<DX>(wl);
+                    f32x4& c = acc[5 * dy + DX];
+                    c = mfma(ah, bh, c);
+                    c = mfma(ah, bl, c);
+                    c = mfma(al, bh, c);
+                };
+                tap(std::integral_constant<int, 0>{});
+                tap(std::integral_constant<int, 1>{});
+                tap(std::integral_constant<int, 2>{});
+                tap(std::integral_constant<int, 3>{});
+                tap(std::integral_constant<int, 4>{});
+            }
+        }
+    }
+    // the four waves' sums, then the share: element (t, ci = 4 g + r, co = i)
+    float* red = reinterpret_cast<float*>(sm);
+    static_assert(sizeof(sm) >= TAPS * 256 * 4, "the share fits the tiles' LDS");
+    for (int w = 0; w < 4; w++) {
+        __syncthreads();
+        if (wave == w) {
+#pragma unroll
+            for (int t = 0; t < TAPS; t++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    float* p = red + t * 256 + (4 * g + r) * 16 + i;
+                    *p = w == 0 ? acc[t][r] : *p + acc[t][r];
+                }
+        }
     }
     __syncthreads();
+    float* out = part + (long)blockIdx.x * TAPS * 256;
+    for (int q = threadIdx.x; q < TAPS * 256; q += 256) out[q] = red[q];
+}
+
+// 1 -> 16 channels: rows of the product are the taps (two groups of 16, 25 used).  A tap's shift
+// along x would leave its eight pixels unaligned: the one-channel tile is kept twice, the second
+// copy one word on, so that every window starts on a dword.  With flip, the transposed problem of
+// a 16 -> 1 layer: dW(t, ci) = sum_q h(q, ci) g(q - o_t), in = g, gout = h and the taps reversed.
+constexpr int WN_W = 40;
+__global__ void __launch_bounds__(256) k_lf_wgrad_narrow(View in, View gout, Domain d, WTiles wt, int flip, float* part)
+{
+    __shared__ __attribute__((aligned(16))) unsigned short sn[2][2][(WTY + 4) * WN_W];   // [hi, lo][copy]
+    __shared__ __attribute__((aligned(16))) unsigned short sg[2 * 16 * WG_P];
+    __shared__ float red[TAPS * 16];
+    unsigned short *gh = sg, *gl = sg + 16 * WG_P;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
-    for (int mt = wave; mt < NMT; mt += 4) {
-        const int r = mt * 16 + i;
-        const bool rowok = r < MR;
-        const int t = rowok ? r / CIN : 0, ci = rowok ? r % CIN : 0;
-        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int kc = 0; kc < LTY * LTX / 32; kc++) {
-            us8 ahi, alo, bhi, blo;
+    // this lane's row of each group: its tap's offset in the tile and which copy holds it
+    int off[2], copy[2];
 #pragma unroll
-            for (int j = 0; j < 8; j++) {
-                const int p = kc * 32 + 8 * g + j;
-                const int pix = (p / LTX + t / 5) * LHX + p % LTX + t % 5;
-                ahi[j] = rowok ? tin[pix * 2 * CIN + ci] : (unsigned short)0;
-                alo[j] = rowok ? tin[pix * 2 * CIN + CIN + ci] : (unsigned short)0;
-                bhi[j] = tg[p * 32 + i];
-                blo[j] = tg[p * 32 + 16 + i];
+    for (int m = 0; m < 2; m++) {
+        const int t = min(16 * m + i, TAPS - 1), dx = t % 5;
+        copy[m] = dx & 1;
+        off[m] = (t / 5) * WN_W + (dx & ~1) + 8 * g;
+    }
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    for (int tile = blockIdx.x; tile < wt.total; tile += gridDim.x) {
+        const int img = tile / (wt.nx * wt.ny), r = tile % (wt.nx * wt.ny), x0 = r % wt.nx * WTX, y0 = r / wt.nx * WTY;
+        __syncthreads();
+        for (int q = threadIdx.x; q < (WTY + 4) * (WTX + 4); q += 256) {
+            const int cx = q % (WTX + 4), cy = q / (WTX + 4);
+            const int x = dwrap(x0 - 2 + cx, d.nx, d.perx), y = dwrap(y0 - 2 + cy, d.ny, d.pery);
+            const float f = (x >= 0 && y >= 0) ? in.p[vaddr(in, img, y, x)] : 0.f;
+            const unsigned short h = bf16_rne(f), l = bf16_rne(f - bf16_val(h));
+            sn[0][0][cy * WN_W + cx] = h;
+            sn[1][0][cy * WN_W + cx] = l;
+            if (cx > 0) {
+                sn[0][1][cy * WN_W + cx - 1] = h;
+                sn[1][1][cy * WN_W + cx - 1] = l;
             }
-            acc = mfma(ahi, bhi, acc);
-            acc = mfma(ahi, blo, acc);
-            acc = mfma(alo, bhi, acc);
         }
-        if (i < COUT) {
+        stage_planes<WTY, WTX, WTX, WG_P, false>(gout, d, img, x0, y0, gh, gl);   // pixels beyond the image: 0
+        __syncthreads();
 #pragma unroll
-            for (int rr = 0; rr < 4; rr++) {
-                const int row = mt * 16 + 4 * g + rr;
-                if (row < MR) atomicAdd(&dw[row * COUT + i], acc[rr]);
+        for (int yy = 0; yy < 2; yy++) {
+            const int y = 2 * wave + yy;
+            const us8 bh = *reinterpret_cast<const us8*>(gh + i * WG_P + y * WTX + 8 * g);
+            const us8 bl = *reinterpret_cast<const us8*>(gl + i * WG_P + y * WTX + 8 * g);
+#pragma unroll
+            for (int m = 0; m < 2; m++) {
+                const unsigned* ph = reinterpret_cast<const unsigned*>(sn[0][copy[m]] + y * WN_W + off[m]);
+                const unsigned* pl = reinterpret_cast<const unsigned*>(sn[1][copy[m]] + y * WN_W + off[m]);
+                const us8 ah = __builtin_bit_cast(us8, uint4{ph[0], ph[1], ph[2], ph[3]});
+                const us8 al = __builtin_bit_cast(us8, uint4{pl[0], pl[1], pl[2], pl[3]});
+                acc[m] = mfma(ah, bh, acc[m]);
+                acc[m] = mfma(ah, bl, acc[m]);
+                acc[m] = mfma(al, bh, acc[m]);
             }
         }
     }
+    for (int w = 0; w < 4; w++) {
+        __syncthreads();
+        if (wave == w) {
+#pragma unroll
+            for (int m = 0; m < 2; m++)
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const int t = 16 * m + 4 * g + r;
+                    if (t >= TAPS) continue;
+                    float* p = red + (flip ? TAPS - 1 - t : t) * 16 + i;
+                    *p = w == 0 ? acc[m][r] : *p + acc[m][r];
+                }
+        }
+    }
+    __syncthreads();
+    float* out = part + (long)blockIdx.x * TAPS * 16;
+    for (int q = threadIdx.x; q < TAPS * 16; q += 256) out[q] = red[q];
 }
 
 // mean squared error over the pixels at least `margin` from the image edges:
@@ -220,24 +445,43 @@ __global__ void __launch_bounds__(256) k_lf_loss(const float* __restrict__ out,
     if (threadIdx.x == 0) atomicAdd(loss, (red[0] + red[1] + red[2] + red[3]) * inv_count);
 }
 
-// Adam on the FP32 master weights; c1 = 1/(1 - beta1^t), c2 = 1/(1 - beta2^t)
-__global__ void k_lf_adam(float* w, float* m, float* v, const float* g, int n, float lr, float b1,
-                          float b2, float eps, float c1, float c2)
+// The end of a training step: the gradient as the sum of the workgroups' shares (32 parameters and
+// 8 slices of the shares per workgroup), the caller's copies of gradient and loss, and Adam on the
+// FP32 master weights when step is set; c1 = 1/(1 - beta1^t), c2 = 1/(1 - beta2^t)
+struct Shares {
+    const float* p[3];                  // of the layers' weights
+    int n[3];
+};
+struct AdamArgs {
+    float *w, *m, *v;
+    float lr, b1, b2, eps, c1, c2;
+    int step;
+};
+__global__ void __launch_bounds__(256) k_lf_finish(Shares S, AdamArgs A, const double* loss, double* loss_out,
+                                                   float* grad_out)
 {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    const float gq = g[q];
-    const float mq = b1 * m[q] + (1.f - b1) * gq;
-    const float vq = b2 * v[q] + (1.f - b2) * gq * gq;
-    m[q] = mq;
-    v[q] = vq;
-    w[q] -= lr * (mq * c1) / (sqrtf(vq * c2) + eps);
-}
-
-__global__ void k_lf_zero(float* p, int n)
-{
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < n) p[q] = 0.f;
+    __shared__ float red[8][32];
+    const int q = blockIdx.x * 32 + (threadIdx.x & 31), slice = threadIdx.x >> 5;
+    static_assert(NPARAM % 32 == 0, "whole workgroups");
+    const int l = q < OFF_W2 ? 0 : q < OFF_W3 ? 1 : 2, first = l == 0 ? OFF_W1 : l == 1 ? OFF_W2 : OFF_W3;
+    const int size = l == 1 ? TAPS * C * C : TAPS * C;
+    float sum = 0.f;
+#pragma unroll 8
+    for (int k = slice; k < S.n[l]; k += 8) sum += S.p[l][(long)k * size + q - first];
+    red[slice][threadIdx.x & 31] = sum;
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0 && loss_out) *loss_out = *loss;
+    if (slice) return;
+    float g = red[0][threadIdx.x];
+#pragma unroll
+    for (int k = 1; k < 8; k++) g += red[k][threadIdx.x];
+    if (grad_out) grad_out[q] = g;
+    if (!A.step) return;
+    const float m = A.b1 * A.m[q] + (1.f - A.b1) * g;
+    const float v = A.b2 * A.v[q] + (1.f - A.b2) * g * g;
+    A.m[q] = m;
+    A.v[q] = v;
+    A.w[q] -= A.lr * (m * A.c1) / (sqrtf(v * A.c2) + A.eps);
 }
 
 // ---- streamed forward pass (inference) ---------------------------------------------------
@@ -273,16 +517,6 @@ struct Planes {
     Domain d[3];
     int n, oh;                      // planes, output rows per workgroup
 };
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// hi and lo BF16 parts (round to nearest even, in hardware) of four consecutive channels of one
-// pixel, stored as two 8-byte words: hi at channel offset 4g, lo at 16 + 4g
-__device__ __forceinline__ unsigned pk_bf16(float a, float b)
-{
-    const bf16x2 p = {(__bf16)a, (__bf16)b};
-    return __builtin_bit_cast(unsigned, p);
-}
 
 // A row of h1 or h2 in LDS is four planes of W pixels x 8 BF16 words: the 32 words of a pixel
 // (hi parts of channels 0-7, 8-15, then lo parts of 0-7, 8-15) split into 16-byte chunks by k, so
@@ -467,26 +701,33 @@ __global__ void __launch_bounds__(256) k_lf_stream(Planes P, const us8* __restri
 
 int chunks(int cin) { return (TAPS * cin * 2 + 31) / 32; }
 
-void launch_pack(const float* w, int cin, int cout, bool adjoint, void* wpk, hipStream_t s)
+static void launch_packs(const PackJobs& J, hipStream_t s)
 {
-    const int nq = chunks(adjoint ? cout : cin);
-    hipLaunchKernelGGL(k_lf_pack, dim3(nq), dim3(64), 0, s, w, cin, cout, adjoint ? 1 : 0,
-                       reinterpret_cast<us8*>(wpk));
+    int n = 0;
+    for (int k = 0; k < J.n; k++) n += J.j[k].nq;
+    hipLaunchKernelGGL(k_lf_pack, dim3(n), dim3(64), 0, s, J);
+}
+
+static PackJob pack_job(const float* w, int cin, int cout, bool adjoint, void* wpk)
+{
+    return PackJob{w, cin, cout, adjoint ? 1 : 0, chunks(adjoint ? cout : cin), reinterpret_cast<us8*>(wpk)};
+}
+
+template <int CIN, int COUT, int TX>
+static void conv_tiles(const View& in, const View& out, const Domain& d, const void* wpk, hipStream_t s)
+{
+    const dim3 grid((d.nx + TX - 1) / TX, (d.ny + ConvTile<TX>::Y - 1) / ConvTile<TX>::Y, d.nimg);
+    hipLaunchKernelGGL((k_lf_conv<CIN, COUT, TX>), grid, dim3(256), 0, s, in, out, d,
+                       reinterpret_cast<const us8*>(wpk));
 }
 
 template <int CIN, int COUT>
 void launch_conv(const View& in, const View& out, const Domain& d, const void* wpk, hipStream_t s)
 {
-    const dim3 grid((d.nx + LTX - 1) / LTX, (d.ny + LTY - 1) / LTY, d.nimg);
-    hipLaunchKernelGGL((k_lf_conv<CIN, COUT>), grid, dim3(256), 0, s, in, out, d,
-                       reinterpret_cast<const us8*>(wpk));
-}
-
-template <int CIN, int COUT>
-void launch_wgrad(const View& in, const View& gout, const Domain& d, float* dw, hipStream_t s)
-{
-    const dim3 grid((d.nx + LTX - 1) / LTX, (d.ny + LTY - 1) / LTY, d.nimg);
-    hipLaunchKernelGGL((k_lf_wgrad<CIN, COUT>), grid, dim3(256), 0, s, in, gout, d, dw);
+    // the tile shape that covers the image with fewer tiles (all of 256 pixels)
+    auto tiles = [&](int tx) { return (long)((d.nx + tx - 1) / tx) * ((d.ny + 256 / tx - 1) / (256 / tx)); };
+    if (tiles(32) < tiles(64)) conv_tiles<CIN, COUT, 32>(in, out, d, wpk, s);
+    else conv_tiles<CIN, COUT, 64>(in, out, d, wpk, s);
 }
 
 template void launch_conv<1, 16>(const View&, const View&, const Domain&, const void*, hipStream_t);
@@ -497,18 +738,6 @@ void launch_loss(const float* out, const float* target, float* g, const Domain& 
                  double inv_count, double* loss, hipStream_t s)
 {
     hipLaunchKernelGGL(k_lf_loss, dim3(256), dim3(256), 0, s, out, target, g, d, margin, inv_count, loss);
-}
-
-void launch_adam(float* w, float* m, float* v, const float* g, int n, float lr, float b1, float b2,
-                 float eps, float c1, float c2, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_lf_adam, dim3((n + 255) / 256), dim3(256), 0, s, w, m, v, g, n, lr, b1, b2,
-                       eps, c1, c2);
-}
-
-void launch_zero(float* p, int n, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_lf_zero, dim3((n + 255) / 256), dim3(256), 0, s, p, n);
 }
 
 // the three-layer forward pass: in (1 channel) -> h1 (16) -> h2 (16) -> out (1 channel), kept
@@ -568,27 +797,58 @@ void forward_fused(const View* in, const View* out, const Domain* d, int nplanes
 
 void pack_forward(const float* params, const Packed& pk, hipStream_t s)
 {
-    launch_pack(params + OFF_W1, 1, C, false, pk.fwd[0], s);
-    launch_pack(params + OFF_W2, C, C, false, pk.fwd[1], s);
-    launch_pack(params + OFF_W3, C, 1, false, pk.fwd[2], s);
+    PackJobs J{};
+    J.n = 3;
+    J.j[0] = pack_job(params + OFF_W1, 1, C, false, pk.fwd[0]);
+    J.j[1] = pack_job(params + OFF_W2, C, C, false, pk.fwd[1]);
+    J.j[2] = pack_job(params + OFF_W3, C, 1, false, pk.fwd[2]);
+    launch_packs(J, s);
 }
 
-void pack_adjoint(const float* params, const Packed& pk, hipStream_t s)
+void pack_training(const float* params, const Packed& pk, double* clear, hipStream_t s)
 {
-    launch_pack(params + OFF_W2, C, C, true, pk.adj[1], s);
-    launch_pack(params + OFF_W3, C, 1, true, pk.adj[2], s);
+    PackJobs J{};
+    J.n = 5;
+    J.j[0] = pack_job(params + OFF_W1, 1, C, false, pk.fwd[0]);
+    J.j[1] = pack_job(params + OFF_W2, C, C, false, pk.fwd[1]);
+    J.j[2] = pack_job(params + OFF_W3, C, 1, false, pk.fwd[2]);
+    J.j[3] = pack_job(params + OFF_W2, C, C, true, pk.adj[1]);
+    J.j[4] = pack_job(params + OFF_W3, C, 1, true, pk.adj[2]);
+    J.clear = clear;
+    launch_packs(J, s);
 }
 
-// one training pass: forward, loss, backward (data and weights); adds the gradient to dw
+// one training pass's backward part (data and weights) and the parameter update.  The layers'
+// gradient shares go where nothing is read any more: W3's over out, W2's over h2, W1's over h1;
+// a layer whose room is less than one share (a few hundred pixels in all) has one workgroup,
+// which writes to dw.
 void backward(const View& in, const View& h1, const View& h2, const View& out, const View& gout,
               const View& gh1, const View& gh2, const Domain& d, const Packed& pk, float* dw,
-              hipStream_t s)
+              const double* loss, double* loss_out, float* grad_out, const AdamStep& st, hipStream_t s)
 {
-    launch_wgrad<16, 1>(h2, gout, d, dw + OFF_W3, s);
+    WTiles wt;
+    wt.nx = (d.nx + WTX - 1) / WTX;
+    wt.ny = (d.ny + WTY - 1) / WTY;
+    wt.total = wt.nx * wt.ny * d.nimg;
+    const long px = (long)d.nimg * d.ny * d.nx;
+    Shares S;
+    auto shares = [&](int l, float* room, long room_floats, int size, int first) {
+        // a workgroup per CU: more only makes more shares to write and add
+        const long n = std::min<long>(std::min<long>(256, wt.total), room_floats / size);
+        S.n[l] = (int)std::max<long>(n, 1);
+        S.p[l] = n >= 1 ? room : dw + first;
+        return const_cast<float*>(S.p[l]);
+    };
+    float* p3 = shares(2, out.p, px, TAPS * C, OFF_W3);
+    hipLaunchKernelGGL(k_lf_wgrad_narrow, dim3(S.n[2]), dim3(256), 0, s, gout, h2, d, wt, 1, p3);
     launch_conv<1, 16>(gout, gh2, d, pk.adj[2], s);
-    launch_wgrad<16, 16>(h1, gh2, d, dw + OFF_W2, s);
+    float* p2 = shares(1, h2.p, px * C, TAPS * C * C, OFF_W2);
+    hipLaunchKernelGGL(k_lf_wgrad_wide, dim3(S.n[1]), dim3(256), 0, s, h1, gh2, d, wt, p2);
     launch_conv<16, 16>(gh2, gh1, d, pk.adj[1], s);
-    launch_wgrad<1, 16>(in, gh1, d, dw + OFF_W1, s);
+    float* p1 = shares(0, h1.p, px * C, TAPS * C, OFF_W1);
+    hipLaunchKernelGGL(k_lf_wgrad_narrow, dim3(S.n[0]), dim3(256), 0, s, in, gh1, d, wt, 0, p1);
+    const AdamArgs A{st.w, st.m, st.v, st.lr, st.b1, st.b2, st.eps, st.c1, st.c2, st.w ? 1 : 0};
+    hipLaunchKernelGGL(k_lf_finish, dim3(NPARAM / 32), dim3(256), 0, s, S, A, loss, loss_out, grad_out);
 }
 
 }  // namespace lf
@@ -764,23 +1024,23 @@ bf_status bf_lf_train_step(void* work, int64_t work_bytes, float* params, float*
     const View vout = image_view(reinterpret_cast<float*>(b + w.out), ny, nx, 1);
     const View gout = image_view(reinterpret_cast<float*>(b + w.gout), ny, nx, 1);
     (void)hipGetLastError();
-    pack_forward(params, pk, s);
-    pack_adjoint(params, pk, s);
+    pack_training(params, pk, loss, s);
     forward(vin, h1, h2, vout, d, pk, s);
-    launch_zero(reinterpret_cast<float*>(loss), 4, s);
     const double count = (double)nimg * (ny - 2 * margin) * (nx - 2 * margin);
     launch_loss(vout.p, target, gout.p, d, margin, 1.0 / count, loss, s);
-    launch_zero(dw, NPARAM, s);
-    backward(vin, h1, h2, vout, gout, gh1, gh2, d, pk, dw, s);
-    if (grad_out && hipMemcpyAsync(grad_out, dw, (size_t)NPARAM * 4, hipMemcpyDeviceToDevice, s) != hipSuccess)
-        return BF_EDEVICE;
-    if (loss_out && hipMemcpyAsync(loss_out, loss, sizeof(double), hipMemcpyDeviceToDevice, s) != hipSuccess)
-        return BF_EDEVICE;
+    AdamStep st{};
     if (lr != 0.f) {
-        const float c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)step)));
-        const float c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)step)));
-        launch_adam(params, adam_m, adam_v, dw, NPARAM, lr, beta1, beta2, eps, c1, c2, s);
+        st.w = params;
+        st.m = adam_m;
+        st.v = adam_v;
+        st.lr = lr;
+        st.b1 = beta1;
+        st.b2 = beta2;
+        st.eps = eps;
+        st.c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)step)));
+        st.c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)step)));
     }
+    backward(vin, h1, h2, vout, gout, gh1, gh2, d, pk, dw, loss, loss_out, grad_out, st, s);
     return hipGetLastError() == hipSuccess ? BF_OK : BF_EDEVICE;
 }
 

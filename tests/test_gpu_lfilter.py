@@ -78,6 +78,27 @@ def test_gradient_and_loss_match_oracle(periodic):
 
 
 @gpu
+@pytest.mark.parametrize("periodic", [(False, False), (True, False), (False, True)])
+@pytest.mark.parametrize("shape", [(1, 7, 9), (2, 9, 70), (1, 40, 33), (3, 8, 64), (280, 13, 11)])
+def test_gradient_at_tile_edges_matches_oracle(shape, periodic):
+    # fewer pixels than one share of the widest layer's gradient, ragged 32 x 8 and 64 x 4 tiles, more
+    # tiles than workgroups; tolerances as in test_gradient_and_loss_match_oracle
+    torch = _torch()
+    from paper_1009_2727_amd import LearnedFilter
+    p = _rand_params(24, 0.2)
+    rng = np.random.default_rng(25)
+    x = rng.normal(size=shape).astype(np.float32)
+    y = rng.normal(size=shape).astype(np.float32)
+    loss, grad = LearnedFilter(p).train_step(torch.tensor(x, device="cuda"), torch.tensor(y, device="cuda"), margin=2,
+                                             lr=0.0, periodic=periodic, want_grad=True)
+    ref_loss, ref_grad = L.loss_and_grad(p, x, y, 2, periodic)
+    assert float(loss.cpu()) == pytest.approx(ref_loss, rel=5e-4)
+    g = grad.cpu().numpy().astype(np.float64)
+    for a, b in ((L.OFF_W1, L.OFF_W2), (L.OFF_W2, L.OFF_W3), (L.OFF_W3, L.NPARAM)):
+        assert np.abs(g[a:b] - ref_grad[a:b]).max() <= 2e-3 * np.abs(ref_grad[a:b]).max()
+
+
+@gpu
 def test_adam_update_matches_oracle():
     torch = _torch()
     from paper_1009_2727_amd import LearnedFilter

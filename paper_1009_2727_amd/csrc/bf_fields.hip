@@ -10,7 +10,6 @@
 //  * k_filter_ampere: the current filter (Sec. 4.1) for unit-stride passes and Ampere in one
 //    launch; other stride masks take the line filter of bf_sim3.hip on the grid seen with one y
 //    plane, then k_ampere.
-//  * k_window_rows: moving-window advance = ring offset change + clearing the new rows.
 //  * k_stations: lab-frame stations (Sec. 3.2).
 //  * k_rho: charge density for the Gauss diagnostic.
 //
@@ -30,11 +29,10 @@ constexpr int FDX = FARADAY_TX, FDZ = FARADAY_TZ, FDP = FDX + 2, FDN = FDP * (FD
 
 template <typename R, bool FRIED>
 __device__ __forceinline__ void faraday_block(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm,
-                                              R dt, R a2, R b2, R th, R idx, R idz, int* nfar, int bx, int by)
+                                              R dt, R a2, R b2, R th, R idx, R idz, int bx, int by)
 {
     __shared__ R sT[3][FDN];
     const int x0 = bx * FDX, z0 = by * FDZ;
-    if (bx + by == 0 && threadIdx.x == 0) *nfar = 0;
     for (int q = threadIdx.x; q < FDN; q += 256) {
         const int a = q % FDP, b = q / FDP;
         int i = x0 - 1 + a, k = z0 - 1 + b;
@@ -122,9 +120,9 @@ __device__ __forceinline__ void faraday_block(const Geo& g, const FieldSet<R>& f
 
 template <typename R, bool FRIED>
 __global__ void __launch_bounds__(256) k_faraday(Geo g, FieldSet<R> f, PmlTab<R> pm, R dt, R a2,
-                                                 R b2, R th, R idx, R idz, int* nfar)
+                                                 R b2, R th, R idx, R idz)
 {
-    faraday_block<R, FRIED>(g, f, pm, dt, a2, b2, th, idx, idz, nfar, blockIdx.x, blockIdx.y);
+    faraday_block<R, FRIED>(g, f, pm, dt, a2, b2, th, idx, idz, blockIdx.x, blockIdx.y);
 }
 
 // E^{n+1} of stored cell (i, k) from the current j[3] there
@@ -354,11 +352,11 @@ __global__ void __launch_bounds__(256) k_faraday_batch(const FaradayDesc<R>* __r
         const FaradayDesc<R>& D = d[r];
         const int local = it - q.off[r];
         if (D.fried)
-            faraday_block<R, true>(D.g, D.f, D.pm, D.dt, D.a2, D.b2, D.th, D.idx, D.idz, D.nfar,
-                                   local % D.gx, local / D.gx);
+            faraday_block<R, true>(D.g, D.f, D.pm, D.dt, D.a2, D.b2, D.th, D.idx, D.idz, local % D.gx,
+                                   local / D.gx);
         else
-            faraday_block<R, false>(D.g, D.f, D.pm, D.dt, D.a2, D.b2, D.th, D.idx, D.idz, D.nfar,
-                                    local % D.gx, local / D.gx);
+            faraday_block<R, false>(D.g, D.f, D.pm, D.dt, D.a2, D.b2, D.th, D.idx, D.idz, local % D.gx,
+                                    local / D.gx);
     }
 }
 
@@ -376,33 +374,6 @@ __global__ void __launch_bounds__(256) k_ampere_batch(const AmpereDesc<R>* __res
     }
 }
 
-
-// ---- moving window -------------------------------------------------------------------------
-// After the ring offset has moved by d rows: clear the d new rows of every array, drop the
-// split x-part of rows that just left the z-PML for the interior (where no x-PML acts), and
-// keep tangential E zero on the two end walls.
-template <typename R>
-__global__ void k_window_rows(Geo g, PtrList<R> arrays, int d, EntryRows er, FieldSet<R> f,
-                              PmlTab<R> pm)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.Sx) return;
-    const int kn0 = d > 0 ? g.Sz - d : 0, kn1 = d > 0 ? g.Sz : -d;
-    for (int a = 0; a < arrays.n; a++)
-        for (int k = kn0; k < kn1; k++) arrays.p[a][gofs(g, i, k)] = R(0);
-    for (int q = 0; q < er.nh; q++)
-        if (!pm.on[0][1][i]) f.Byx[gofs(g, i, er.h[q])] = R(0);
-    for (int q = 0; q < er.nn; q++)
-        if (!pm.on[0][0][i]) f.Eyx[gofs(g, i, er.n[q])] = R(0);
-    const int walls[2] = {0, g.Sz - 1};
-    for (int w = 0; w < 2; w++) {
-        long o = gofs(g, i, walls[w]);
-        f.E[0][o] = R(0); f.E[1][o] = R(0);
-        f.Eo[0][o] = R(0); f.Eo[1][o] = R(0);
-        f.Eb[0][o] = R(0); f.Eb[1][o] = R(0);
-        f.Ebn[0][o] = R(0); f.Ebn[1][o] = R(0);
-    }
-}
 
 // ---- stations ----------------------------------------------------------------------------
 template <typename R>
@@ -518,15 +489,15 @@ void launch_ampere_batch(const AmpereDesc<R>* d, const QueueRef& q, int nblocks,
 
 template <typename R>
 void launch_faraday(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm, const SolverCoef& c,
-                    int* nfar, hipStream_t s)
+                    hipStream_t s)
 {
     dim3 grid((g.Sx + FDX - 1) / FDX, (g.Sz + FDZ - 1) / FDZ);
     if (c.theta > 0.0)
         hipLaunchKernelGGL((k_faraday<R, true>), grid, dim3(256), 0, s, g, f, pm, (R)c.dt, (R)c.a2,
-                           (R)c.b2, (R)c.theta, (R)c.idx, (R)c.idz, nfar);
+                           (R)c.b2, (R)c.theta, (R)c.idx, (R)c.idz);
     else
         hipLaunchKernelGGL((k_faraday<R, false>), grid, dim3(256), 0, s, g, f, pm, (R)c.dt, (R)c.a2,
-                           (R)c.b2, (R)c.theta, (R)c.idx, (R)c.idz, nfar);
+                           (R)c.b2, (R)c.theta, (R)c.idx, (R)c.idz);
 }
 
 template <typename R>
@@ -567,14 +538,6 @@ void launch_filter_ampere(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& p
     case 5: filter_ampere<5, R>(g, f, pm, st, c, s); break;
     case 6: filter_ampere<6, R>(g, f, pm, st, c, s); break;
     }
-}
-
-template <typename R>
-void launch_window_rows(const Geo& g, const PtrList<R>& arrays, int d, const EntryRows& er,
-                        const FieldSet<R>& f, const PmlTab<R>& pm, hipStream_t s)
-{
-    hipLaunchKernelGGL((k_window_rows<R>), dim3((g.Sx + 255) / 256), dim3(256), 0, s, g, arrays, d, er,
-                       f, pm);
 }
 
 template <typename R>
@@ -620,7 +583,7 @@ void launch_fill_int(int* p, int n, int v, hipStream_t s)
 
 #define BF_INST(R)                                                                                 \
     template void launch_faraday<R>(const Geo&, const FieldSet<R>&, const PmlTab<R>&,              \
-                                    const SolverCoef&, int*, hipStream_t);                         \
+                                    const SolverCoef&, hipStream_t);                               \
     template void launch_nodes<R>(const Geo&, const FieldSet<R>&, hipStream_t);                       \
     template void launch_ampere<R>(const Geo&, const FieldSet<R>&, const PmlTab<R>&,               \
                                    const SolverCoef&, hipStream_t);                                \
@@ -628,8 +591,6 @@ void launch_fill_int(int* p, int n, int v, hipStream_t s)
                                           const Stencil2&, const SolverCoef&, hipStream_t);        \
     template void launch_faraday_batch<R>(const FaradayDesc<R>*, const QueueRef&, int, hipStream_t); \
     template void launch_ampere_batch<R>(const AmpereDesc<R>*, const QueueRef&, int, hipStream_t);   \
-    template void launch_window_rows<R>(const Geo&, const PtrList<R>&, int, const EntryRows&,      \
-                                        const FieldSet<R>&, const PmlTab<R>&, hipStream_t);        \
     template void launch_stations<R>(const Geo&, const FieldSet<R>&, const StationParams&,         \
                                      double*, int*, hipStream_t);                                  \
     template void launch_rho<R>(const Geo&, const ElectronArrays<R>&, int, const IonArrays<R>&,    \

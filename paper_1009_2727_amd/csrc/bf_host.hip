@@ -557,23 +557,31 @@ int64_t rows_entering(const bf_sim* s)
     return r - s->next_row;
 }
 
+// creates nrows lattice rows at the front; win: the window's advance of the same step, which rides
+// in the same launch
 template <typename R>
-void inject(bf_sim* s, int64_t nrows)
+void inject(bf_sim* s, int64_t nrows, const WindowParams<R>* win = nullptr)
 {
-    if (nrows <= 0) return;
     const Layout& L = s->L;
-    if (s->nseg_e + nrows * L.nchunks > L.seg_cap) sort_now<R>(s);
-    if (s->nseg_e + nrows * L.nchunks > L.seg_cap) {
-        // more rows than one table holds (initial load of a tall box): split
-        const int64_t per = std::max<int64_t>(1, (L.seg_cap - s->nseg_e) / L.nchunks);
-        while (nrows > 0) {
-            const int64_t n = std::min(nrows, per);
-            inject<R>(s, n);
-            nrows -= n;
-            if (nrows > 0) sort_now<R>(s);
+    if (nrows > 0 && s->nseg_e + nrows * L.nchunks > L.seg_cap) {
+        // the segment table is full
+        if (win) inject<R>(s, 0, win);
+        sort_now<R>(s);
+        if (s->nseg_e + nrows * L.nchunks > L.seg_cap) {
+            // more rows than one table holds (initial load of a tall box): split
+            const int64_t per = std::max<int64_t>(1, (L.seg_cap - s->nseg_e) / L.nchunks);
+            while (nrows > 0) {
+                const int64_t n = std::min(nrows, per);
+                inject<R>(s, n);
+                nrows -= n;
+                if (nrows > 0) sort_now<R>(s);
+            }
+            return;
         }
-        return;
+        win = nullptr;
     }
+    if (nrows <= 0 && !win) return;
+    nrows = std::max<int64_t>(nrows, 0);
     InjectParams ip;
     ip.row0 = s->next_row;
     ip.nrows = (int)nrows;
@@ -603,8 +611,13 @@ void inject(bf_sim* s, int64_t nrows)
         Segment *se = seg_e(s, k), *si = seg_i(s, k);
         int4 *be = bb_e(s, s->bb_cur), *bi = bb_i(s, s->bb_cur);
         int *ne = nused_e(s), *ni = nused_i(s), *stw = status_word(s);
-        s->run([=](hipStream_t st) { launch_inject<R>(g, e, ion, se, be, si, bi, ne, ni, ip, stw, st); });
+        const bool has_win = win != nullptr;
+        const WindowParams<R> w = win ? *win : WindowParams<R>{};
+        s->run([=](hipStream_t st) {
+            launch_advance<R>(g, has_win ? &w : nullptr, e, ion, se, be, si, bi, ne, ni, ip, stw, st);
+        });
     }
+    if (nrows == 0) return;
     s->nseg_e += (int)nrows * L.nchunks;
     if (s->plasma.ion_mode == 1) s->nseg_i = s->nseg_e;
     s->next_row += nrows;
@@ -677,9 +690,6 @@ bf_status step_impl(bf_sim* s, int nsteps)
         const FieldSet<R> f = field_set<R>(s);
         const Geo g = s->g;
         BatchRec* rb = batch_rec<R>(s);
-        // electrons outside their staged window: listed in the sort's scratch copy, which holds
-        // nothing between sorts, and counted in the third word of the counters
-        const FarList far{reinterpret_cast<int2*>(s->buf[1 + (1 - s->p_cur)]), nused_e(s) + 2};
         // Faraday + Friedman + PML
         s->slot = SLOT_FARADAY;
         hipEvent_t t_ph = s->tick();
@@ -688,11 +698,11 @@ bf_status step_impl(bf_sim* s, int nsteps)
                 const int gx = (g.Sx + FARADAY_TX - 1) / FARADAY_TX, gz = (g.Sz + FARADAY_TZ - 1) / FARADAY_TZ;
                 rb->faraday.push_back(FaradayDesc<float>{g, f, pm, (float)sc.dt, (float)sc.a2, (float)sc.b2,
                                                          (float)sc.theta, (float)sc.idx, (float)sc.idz,
-                                                         far.n, sc.theta > 0.0 ? 1 : 0, gx});
+                                                         sc.theta > 0.0 ? 1 : 0, gx});
                 rb->n_faraday.push_back(gx * gz);
             }
         }
-        if (!rb) launch_faraday<R>(g, f, pm, sc, far.n, s->stream);
+        if (!rb) launch_faraday<R>(g, f, pm, sc, s->stream);
         // stations (E^n, B^n)
         if (s->nst > 0) {
             StationParams sp;
@@ -724,63 +734,66 @@ bf_status step_impl(bf_sim* s, int nsteps)
         s->slot = SLOT_PUSH;
         t_ph = s->tick();
         if (c.gather_kind == 1) launch_nodes<R>(g, f, s->stream);      // single runs only (not batched)
-        {
-            const ElectronArrays<R> e = electrons<R>(s, s->p_cur);
-            const Segment* sg = seg_e(s, s->sg_cur);
-            const int4* bi = bb_e(s, s->bb_cur);
-            int4* bo = bb_e(s, 1 - s->bb_cur);
-            if constexpr (sizeof(R) == 4) {
-                if (rb && s->nseg_e > 0) {
-                    rb->gpd.push_back(GpdDesc<float>{g, f, e, sg, bi, bo, pp, far, status_word(s)});
-                    rb->n_gpd.push_back(s->nseg_e);
+        ElectronParams<R> ep;
+        ep.e = electrons<R>(s, s->p_cur);
+        ep.seg = seg_e(s, s->sg_cur);
+        ep.bbin = bb_e(s, s->bb_cur);
+        ep.bbout = bb_e(s, 1 - s->bb_cur);
+        ep.nseg = s->nseg_e;
+        ep.pp = pp;
+        ep.far = reinterpret_cast<int*>(s->buf[1 + (1 - s->p_cur)]);   // the sort's scratch copy: free between sorts
+        ep.status = status_word(s);
+        // rigid ions (deposit-only J_z) and the antenna, in the electrons' launch
+        SourceParams<R> sp{};
+        sp.shift = d;
+        if (s->have_plasma && s->plasma.ion_mode == 1) {
+            sp.ion = ions<R>(s, s->p_cur);
+            sp.iseg = seg_i(s, s->sg_cur);
+            sp.ibbin = bb_i(s, s->bb_cur);
+            sp.ibbout = bb_i(s, 1 - s->bb_cur);
+            sp.zsh_a = ion_shift(s, s->t);
+            sp.zsh_b = ion_shift(s, t1);
+            sp.fjz = (R)(-1.0 / (c.dx_um * s->dt));
+            sp.nion = s->nseg_i;
+        }
+        if (s->have_laser) {
+            AntennaParams& ap = sp.ap;
+            ap.n = c.nx;
+            ap.za = (s->za_lab / s->gamma - s->beta * s->t) / c.dz_um - (double)s->shift;
+            ap.zb = (s->za_lab / s->gamma - s->beta * t1) / c.dz_um - (double)s->shift;
+            ap.tmid = s->t + 0.5 * s->dt;
+            ap.gamma = s->gamma; ap.e0 = s->e0; ap.omega = s->omega; ap.w0 = s->w0;
+            ap.sig_t = s->sig_t; ap.t0 = s->t0; ap.dx_um = c.dx_um; ap.xc_um = 0.5 * c.nx * c.dx_um;
+            ap.weight = s->aw; ap.dt = s->dt; ap.dx = c.dx_um; ap.dz = c.dz_um;
+            ap.active = (ap.za >= 0.0 && ap.za < (double)c.nz) ? 1 : 0;
+            ap.pol = s->pol;
+            sp.xm = s->w<double>(L.w_ant);
+        }
+        if constexpr (sizeof(R) == 4) {
+            if (rb) {
+                if (ep.nseg > 0) {
+                    rb->gpd.push_back(GpdDesc<float>{g, f, ep});
+                    rb->n_gpd.push_back(ep.nseg);
                 }
+                // batched runs launch their sources one run at a time too: the hardware's dispatch
+                // of one workgroup per segment balances the uneven ion segments better than a
+                // persistent launch over all runs
+                s->slot = SLOT_IONS;
+                s->run([=](hipStream_t st) { launch_sources<R>(g, f, sp, st); });
             }
-            if (!rb)
-                launch_gpd<R>(g, f, e, sg, bi, bo, s->nseg_e, pp, far, status_word(s), c.gather_kind == 1, s->stream);
         }
-        s->tock(t_ph, BF_PHASE_PUSH);
-        // rigid ions (deposit-only J_z), the antenna, and the electrons the staged push left: one
-        // launch, timed as the ions
-        s->slot = SLOT_IONS;
-        t_ph = s->tick();
-        {
-            SourceParams<R> sp{};
-            if (s->have_plasma && s->plasma.ion_mode == 1) {
-                sp.ion = ions<R>(s, s->p_cur);
-                sp.iseg = seg_i(s, s->sg_cur);
-                sp.ibbin = bb_i(s, s->bb_cur);
-                sp.ibbout = bb_i(s, 1 - s->bb_cur);
-                sp.zsh_a = ion_shift(s, s->t);
-                sp.zsh_b = ion_shift(s, t1);
-                sp.fjz = (R)(-1.0 / (c.dx_um * s->dt));
-                sp.nion = s->nseg_i;
+        if (!rb) {
+            // with phase timers the ions and the antenna are launched, and timed, by themselves
+            if (c.phase_timers) {
+                launch_particles<R>(g, f, ep, SourceParams<R>{}, c.gather_kind == 1, s->stream);
+                s->tock(t_ph, BF_PHASE_PUSH);
+                t_ph = s->tick();
+                launch_sources<R>(g, f, sp, s->stream);
+                s->tock(t_ph, BF_PHASE_IONS);
+            } else {
+                launch_particles<R>(g, f, ep, sp, c.gather_kind == 1, s->stream);
             }
-            if (s->have_laser) {
-                AntennaParams& ap = sp.ap;
-                ap.n = c.nx;
-                ap.za = (s->za_lab / s->gamma - s->beta * s->t) / c.dz_um - (double)s->shift;
-                ap.zb = (s->za_lab / s->gamma - s->beta * t1) / c.dz_um - (double)s->shift;
-                ap.tmid = s->t + 0.5 * s->dt;
-                ap.gamma = s->gamma; ap.e0 = s->e0; ap.omega = s->omega; ap.w0 = s->w0;
-                ap.sig_t = s->sig_t; ap.t0 = s->t0; ap.dx_um = c.dx_um; ap.xc_um = 0.5 * c.nx * c.dx_um;
-                ap.weight = s->aw; ap.dt = s->dt; ap.dx = c.dx_um; ap.dz = c.dz_um;
-                ap.active = (ap.za >= 0.0 && ap.za < (double)c.nz) ? 1 : 0;
-                ap.pol = s->pol;
-                sp.xm = s->w<double>(L.w_ant);
-            }
-            sp.far = far;
-            sp.e = electrons<R>(s, s->p_cur);
-            sp.ebbout = bb_e(s, 1 - s->bb_cur);
-            sp.pp = pp;
-            sp.status = status_word(s);
-            const int nse = s->nseg_e;
-            const bool mc = c.gather_kind == 1;
-            // batched runs launch their sources one run at a time too: the hardware's dispatch of
-            // one workgroup per segment balances the uneven ion segments better than a
-            // persistent launch over all runs
-            s->run([=](hipStream_t st) { launch_sources<R>(g, f, sp, nse, mc, st); });
         }
-        s->tock(t_ph, BF_PHASE_IONS);
         // beam through the injection plane (single runs only: a batch rejects beam runs)
         if (s->have_beam) {
             t_ph = s->tick();
@@ -862,11 +875,12 @@ bf_status step_impl(bf_sim* s, int nsteps)
         // moving window: advance the ring offset and clear the new rows
         s->slot = SLOT_WINDOW;
         t_ph = s->tick();
+        WindowParams<R> win{};
         if (d != 0) {
             s->g.zoff = (int)(((int64_t)s->g.zoff + d) % L.Sz);
             if (s->g.zoff < 0) s->g.zoff += L.Sz;
             s->shift = s1;
-            EntryRows er{};
+            EntryRows& er = win.er;
             // rows that just left the z-PML for the interior drop their split x-part
             for (int h = 0; h < 2; h++) {
                 for (int k = 0; k < L.Sz; k++) {
@@ -877,13 +891,13 @@ bf_status step_impl(bf_sim* s, int nsteps)
                     if (h == 0 && er.nn < 4) er.n[er.nn++] = k;
                 }
             }
-            const FieldSet<R> f2 = field_set<R>(s);
-            const Geo g2 = s->g;
-            const PtrList<R> arrs = all_arrays<R>(s);
-            s->run([=](hipStream_t st) { launch_window_rows<R>(g2, arrs, d, er, f2, pm, st); });
+            win.f = field_set<R>(s);
+            win.arrays = all_arrays<R>(s);
+            win.d = d;
+            win.pm = pm;
         }
         // plasma injection at the front plane
-        if (s->have_plasma) inject<R>(s, rows_entering(s));
+        inject<R>(s, s->have_plasma ? rows_entering(s) : 0, d != 0 ? &win : nullptr);
         s->tock(t_ph, BF_PHASE_WINDOW);
         s->slot = SLOT_SORT;
         t_ph = s->tick();

@@ -76,12 +76,6 @@ struct PushParams {
     int vay;           // 1: Vay's pusher, 0: Boris
 };
 
-// electrons left to the pass on HBM: n entries of (segment, particle)
-struct FarList {
-    int2* list;
-    int* n;
-};
-
 struct InjectParams {
     int64_t row0;      // first lattice row to create
     int nrows, nchunks, tile_x, ppc, ion_mode;
@@ -105,27 +99,35 @@ struct AntennaParams {
     int pol;           // 0: the - sheet moves along x (J_x); 1: along y, out of the plane (J_y)
 };
 
-// one launch of the current's sources beside the staged electrons (launch_sources)
+// the electrons of nseg segments.  far: one int per particle slot of scratch, where a segment lists
+// its electrons outside the staged window (in its own slots' range)
+template <typename R>
+struct ElectronParams {
+    ElectronArrays<R> e;
+    const Segment* seg;
+    const int4* bbin;
+    int4* bbout;
+    int nseg;
+    PushParams<R> pp;
+    int* far;
+    int* status;
+};
+
+// the other sources of a step's current: rigid ions of nion segments (z = z0 - zsh_a at t_n,
+// z0 - zsh_b at t_{n+1}) and the antenna when ap.active
 template <typename R>
 struct SourceParams {
-    // rigid ions of nion segments: z = z0 - zsh_a at t_n, z0 - zsh_b at t_{n+1}
     IonArrays<R> ion;
     const Segment* iseg;
     const int4* ibbin;
     int4* ibbout;
     int nion;
     double zsh_a, zsh_b;
+    int shift;         // window shift (cells) applied after this step
     R fjz;
-    // antenna
     double* xm;
     AntennaParams ap;
-    int na;            // its workgroups
-    // electrons left by the staged push
-    FarList far;
-    ElectronArrays<R> e;
-    int4* ebbout;
-    PushParams<R> pp;
-    int* status;
+    int na;            // its workgroups (set by the launcher)
 };
 
 // particle beam launched through a lab-fixed plane (Sec. 3.1.1): FP64 state in the work buffer
@@ -163,7 +165,6 @@ struct FaradayDesc {
     FieldSet<R> f;
     PmlTab<R> pm;
     R dt, a2, b2, th, idx, idz;
-    int* nfar;         // cleared for the step's push
     int fried, gx;     // Friedman on; blocks per row of the grid of Faraday tiles
 };
 template <typename R>
@@ -178,13 +179,7 @@ template <typename R>
 struct GpdDesc {
     Geo g;
     FieldSet<R> f;
-    ElectronArrays<R> e;
-    const Segment* seg;
-    const int4* bbin;
-    int4* bbout;
-    PushParams<R> pp;
-    FarList far;
-    int* status;
+    ElectronParams<R> e;
 };
 
 template <typename R>
@@ -195,10 +190,10 @@ template <typename R>
 void launch_gpd_batch(const GpdDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s);
 
 // ---- launchers (stream-ordered) -------------------------------------------------------
-// Faraday; clears the raw current and *nfar for the step's deposit
+// Faraday; clears the raw current for the step's deposit
 template <typename R>
 void launch_faraday(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm, const SolverCoef& c,
-                    int* nfar, hipStream_t s);
+                    hipStream_t s);
 template <typename R>
 void launch_ampere(const Geo& g, const FieldSet<R>& f, const PmlTab<R>& pm, const SolverCoef& c,
                    hipStream_t s);
@@ -222,9 +217,15 @@ struct EntryRows {
     int h[4], nh;   // half-z rows whose split B_y x-part is dropped
     int n[4], nn;   // node-z rows whose split E_y x-part is dropped
 };
+// the window's advance by d rows: what its rows need
 template <typename R>
-void launch_window_rows(const Geo& g, const PtrList<R>& arrays, int d, const EntryRows& er,
-                        const FieldSet<R>& f, const PmlTab<R>& pm, hipStream_t s);
+struct WindowParams {
+    PtrList<R> arrays;
+    int d;
+    EntryRows er;
+    FieldSet<R> f;
+    PmlTab<R> pm;
+};
 template <typename R>
 void launch_stations(const Geo& g, const FieldSet<R>& f, const StationParams& sp,
                      double* rec, int* counts, hipStream_t s);
@@ -232,22 +233,19 @@ void launch_stations(const Geo& g, const FieldSet<R>& f, const StationParams& sp
 // the nodes (the mean over the Yee locations around each node along the staggered axes) into f.G
 template <typename R>
 void launch_nodes(const Geo& g, const FieldSet<R>& f, hipStream_t s);
-// gather, push and deposit; mc: the gather reads f.G with nodal weights for every component.
-// Electrons outside their segment's staged window are appended to far (far.n zero before the
-// call); launch_sources, after it, pushes them
+// gather, push and deposit of the electrons, and the other sources sp (none in an empty one); mc: the
+// gather reads f.G with nodal weights for every component
 template <typename R>
-void launch_gpd(const Geo& g, const FieldSet<R>& f, const ElectronArrays<R>& e,
-                const Segment* seg, const int4* bbox_in, int4* bbox_out, int nseg,
-                const PushParams<R>& pp, const FarList& far, int* status, bool mc, hipStream_t s);
-// the rigid ions of sp.nion segments, the antenna when sp.ap.active, and the electrons of sp.far
-// (a run of nseg_e electron segments); sp.na is set here
+void launch_particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
+                      bool mc, hipStream_t s);
+// the sources alone (batched runs, whose electrons have their own launch)
 template <typename R>
-void launch_sources(const Geo& g, const FieldSet<R>& f, SourceParams<R> sp, int nseg_e, bool mc, hipStream_t s);
+void launch_sources(const Geo& g, const FieldSet<R>& f, SourceParams<R> sp, hipStream_t s);
+// the window's advance (null: none) and the plasma rows of ip (ip.nrows 0: none), in one launch
 template <typename R>
-void launch_inject(const Geo& g, const ElectronArrays<R>& e, const IonArrays<R>& ion,
-                   Segment* seg_e, int4* bbox_e, Segment* seg_i, int4* bbox_i,
-                   int* nused_e, int* nused_i, const InjectParams& ip, int* status,
-                   hipStream_t s);
+void launch_advance(const Geo& g, const WindowParams<R>* wp, const ElectronArrays<R>& e, const IonArrays<R>& ion,
+                    Segment* seg_e, int4* bbox_e, Segment* seg_i, int4* bbox_i, int* nused_e, int* nused_i,
+                    const InjectParams& ip, int* status, hipStream_t s);
 template <typename R>
 void launch_sort_electrons(const Geo& g, int tile_x, int tile_z, int ntx, int ntiles,
                            const ElectronArrays<R>& src, const ElectronArrays<R>& dst,

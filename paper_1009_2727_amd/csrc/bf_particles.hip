@@ -7,11 +7,13 @@
 //    components).  Each thread then pushes particles (Boris), deposits the Esirkepov current
 //    (charge-conserving, Sec. 4.2.2) into the LDS tile with LDS atomics, writes the particle
 //    back (positions FP64, rebased by the window shift), and the tile is flushed to HBM with
-//    global atomics.  Particles outside the staged window go to a list.
-//  * k_sources, after it: the rigid ions (at rest in the lab) deposit their J_z from
-//    z0 - beta c t; the laser antenna's +/- sheet particles (Sec. 3.1.2), in FP64 per pair; and
-//    the electrons of k_gpd's list, on the fields and current in HBM.
-//  * k_inject: creates plasma lattice rows at the front plane (Sec. 3.1.1).
+//    global atomics.  Particles outside the staged window are pushed on HBM afterwards, 16
+//    lanes each.
+//  * k_sources: the rigid ions (at rest in the lab) deposit their J_z from z0 - beta c t, and the
+//    laser antenna's +/- sheet particles (Sec. 3.1.2), in FP64 per pair.  k_particles is both
+//    kernels in one launch; they run apart in batched steps and with phase timers.
+//  * k_advance: the moving window's new rows, and the plasma lattice rows that entered at the
+//    front plane (Sec. 3.1.1).
 //  * k_sort_*: counting sort by tile (histogram, scan, scatter) that also drops absorbed
 //    particles and folds periodic coordinates back into the box.
 #include <algorithm>
@@ -448,26 +450,125 @@ __device__ __forceinline__ void clamp_window(const ElectronArrays<R>& e, const S
     }
 }
 
+// ---- electrons outside their staged window, on HBM ----------------------------------------
+// sum over the 16 lanes of a particle
+template <typename R>
+__device__ __forceinline__ R sum16(R v)
+{
+    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+// the cubic B-spline at distance r from a node
+template <typename R>
+__device__ __forceinline__ R spline3(R r)
+{
+    const R d = fabs(r), t = R(2) - d;
+    const R near = R(2.0 / 3.0) - d * d * (R(1) - R(0.5) * d), far = t * t * t * R(1.0 / 6.0);
+    return d < R(1) ? near : d < R(2) ? far : R(0);
+}
+
+// Particle p by 16 lanes, one stencil node each for the gather and two of the 25
+// nodes for the deposit: a few dependent loads, where one thread would walk 16 nodes of nine
+// arrays and 65 adds.  Lanes 0-4 hold the deposit's shape factors of the window's x nodes, lanes
+// 5-9 those of its z nodes; the others fetch them by shuffles, which keeps it within the registers
+// of the staged push it follows.
+template <bool MC, typename R>
+__device__ __forceinline__ void far_electron(const Geo& g, const FieldSet<R>& f, const ElectronArrays<R>& e,
+                                             const PushParams<R>& pp, int* status, int p, int& x0, int& x1,
+                                             int& z0, int& z1)
+{
+    const int n = threadIdx.x & 15, a = n & 3, b = n >> 2;
+    EState<R> st = load_electron(e, p);
+    const double x = st.x, z = st.z;
+    const int ix = (int)floor(x), iz = (int)floor(z);
+    auto at = [&](int jx, int jz) -> long {
+        const int i = swrap(jx + g.Px, g.Sx, g.perx), k = swrap(jz + g.Pz, g.Sz, g.perz);
+        return i < 0 || k < 0 ? -1 : gofs(g, i, k);
+    };
+    // this lane's node and weight for each stagger along x and z
+    R wx[2], wz[2];
+    int jx[2], jz[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const double xs = x - 0.5 * h, zs = z - 0.5 * h;
+        jx[h] = (int)floor(xs) - 1 + a;
+        jz[h] = (int)floor(zs) - 1 + b;
+        wx[h] = spline3((R)(xs - jx[h]));
+        wz[h] = spline3((R)(zs - jz[h]));
+    }
+    R E[3], B[3];
+#pragma unroll
+    for (int c = 0; c < 6; c++) {
+        // staggers: E_x (half, node), E_y (node, node), E_z (node, half), B_x (node, half),
+        // B_y (half, half), B_z (half, node); the node values have none
+        const int hx = !MC && (c == 0 || c == 4 || c == 5), hz = !MC && (c == 2 || c == 3 || c == 4);
+        const long o = at(jx[hx], jz[hz]);
+        R v = R(0);
+        if (o >= 0) v = MC ? f.G[c][o] : c < 3 ? f.E[c][o] : R(0.5) * (f.B[c - 3][o] + f.Bn[c - 3][o]);
+        v = sum16(wx[hx] * wz[hz] * v);
+        if (c < 3) E[c] = v;
+        else B[c - 3] = v;
+    }
+    R u[3] = {st.ux, st.uy, st.uz}, v[3];
+    push_electron(pp, E, B, u, v);
+    const double xn = x + (double)(pp.dtdx * v[0]), zn = z + (double)(pp.dtdz * v[2]);
+    const int ix1 = (int)floor(xn), iz1 = (int)floor(zn);
+    if (abs(ix1 - ix) <= 1 && abs(iz1 - iz) <= 1) {
+        const double w = (double)st.w;
+        const int bx = min(ix, ix1) - 1, bz = min(iz, iz1) - 1;
+        const bool isx = n < 5;
+        const int node = isx ? bx + n : bz + n - 5;
+        const double s0 = spline3((isx ? x : z) - node), s1 = spline3((isx ? xn : zn) - node);
+        double pd = s1 - s0;             // becomes the prefix sum over the axis' nodes
+        for (int o = 1; o < 5; o <<= 1) {
+            const double up = __shfl_up(pd, o, 16);
+            if ((isx ? n : n - 5) >= o) pd += up;
+        }
+#pragma unroll 1
+        for (int q = n; q < 32; q += 16) {
+            const int m = q % 5, k = min(q / 5, 4);
+            const double s0x = __shfl(s0, m, 16), s1x = __shfl(s1, m, 16), s0z = __shfl(s0, 5 + k, 16),
+                         s1z = __shfl(s1, 5 + k, 16);
+            const double px = __shfl(pd, m, 16), pz = __shfl(pd, 5 + k, 16);
+            const long o = q < 25 ? at(bx + m, bz + k) : -1;
+            if (o < 0) continue;
+            const double vx = m < 4 ? w * (double)pp.fjx * px * 0.5 * (s0z + s1z) : 0.0;
+            const double vz = k < 4 ? w * (double)pp.fjz * pz * 0.5 * (s0x + s1x) : 0.0;
+            const double vy = w * (double)(pp.fjy * v[1]) *
+                              (s0x * (s0z / 3.0 + s1z / 6.0) + s1x * (s0z / 6.0 + s1z / 3.0));
+            if (vx != 0.0) atomicAdd(&f.J[0][o], (R)vx);
+            if (vz != 0.0) atomicAdd(&f.J[2][o], (R)vz);
+            if (vy != 0.0) atomicAdd(&f.J[1][o], (R)vy);
+        }
+    } else {
+        atomicOr(status, ST_NONFINITE);   // faster than light: only a non-finite state gets here
+    }
+    finish_electron(g, pp, xn, zn, u, st, status, x0, x1, z0, z1);
+    if (n == 0) store_electron(e, p, st);
+}
+
 // Gather, push and deposit of particle segment s by one workgroup of NTH threads.  Bound by VALU
 // issue on large grids (about 650 instructions per 64 electrons) and by the chain of its phases'
-// latencies on small ones.  Particles outside the staged window are appended to the list far
-// (segment, particle) and pushed by k_sources: carrying the global accessors here made it 203 KB
+// latencies on small ones.  Particles outside the staged window are listed (far) and pushed on HBM
+// after the tile: with the global accessors unrolled here for one thread a particle it was 203 KB
 // of code and 168 registers, and cold instruction fetches dominated small launches.
-// Per step: 43 -> 14 us on 75 x 1691 cells at 1 particle a cell, 70 -> 23 us on 64 x 512 at 4 in
+// Per step: 43 -> 15 us on 75 x 1691 cells at 1 particle a cell, 70 -> 23 us on 64 x 512 at 4 in
 // FP64, 0.425 -> 0.38 ms on 256 x 4096 at 16 (16.8 M electrons, four workgroups per CU).
 template <typename R, bool MC, int NTH>
-__device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, const ElectronArrays<R>& e,
-                                            const Segment* __restrict__ seg, const int4* __restrict__ bbin,
-                                            int4* __restrict__ bbout, const PushParams<R>& pp, const FarList& far,
-                                            int* status, int s)
+__device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, int s)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];   // 16-byte aligned: FP64 DS ops
     __shared__ int4 red[NTH / 64];
     __shared__ double redd[NTH / 64];
-    const Segment sg = seg[s];
-    const int4 bb = bbin[s];
+    __shared__ int nfar;
+    const Segment sg = ep.seg[s];
+    const int4 bb = ep.bbin[s];
+    const ElectronArrays<R>& e = ep.e;
+    const PushParams<R>& pp = ep.pp;
+    if (threadIdx.x == 0) nfar = 0;      // a barrier comes before its first use
     if (sg.count <= 0 || bb.x > bb.y || bb.z > bb.w) {
-        if (threadIdx.x == 0) bbout[s] = make_int4(INT_MAX, INT_MIN, INT_MAX, INT_MIN);
+        if (threadIdx.x == 0) ep.bbout[s] = make_int4(INT_MAX, INT_MIN, INT_MAX, INT_MIN);
         return;
     }
     const int end = sg.start + sg.count;
@@ -539,10 +640,10 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
         if (cur.w == R(0)) continue;
         const int ix = (int)floor(cur.x), iz = (int)floor(cur.z);
         if (!lds.inside(ix - 2, ix + 3, iz - 2, iz + 3)) {
-            far.list[atomicAdd(far.n, 1)] = make_int2(s, p);
+            ep.far[sg.start + atomicAdd(&nfar, 1)] = p;
             continue;
         }
-        advance_electron<MC>(lds, g, pp, cur, js, status, x0, x1, z0, z1);
+        advance_electron<MC>(lds, g, pp, cur, js, ep.status, x0, x1, z0, z1);
         done = cur;
         pdone = p;
     }
@@ -562,8 +663,12 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
             if (v != R(0)) atomicAdd(&f.J[c][o], v);
         }
     }
+    // the listed particles (the barrier before the flush ordered the list's writes)
+    if (__builtin_expect(nfar > 0, 0))
+        for (int q = threadIdx.x / 16; q < nfar; q += NTH / 16)
+            far_electron<MC>(g, f, e, pp, ep.status, ep.far[sg.start + q], x0, x1, z0, z1);
     block_bbox(x0, x1, z0, z1, red);
-    if (threadIdx.x == 0) bbout[s] = make_int4(x0, x1, z0, z1);
+    if (threadIdx.x == 0) ep.bbout[s] = make_int4(x0, x1, z0, z1);
 }
 
 // FP64 workgroups are twice as large: their tiles hold the same particles, but a register budget
@@ -572,10 +677,9 @@ template <typename R> constexpr int gpd_threads() { return sizeof(R) == 4 ? 256 
 
 template <typename R, bool MC>
 __global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
-    k_gpd(Geo g, FieldSet<R> f, ElectronArrays<R> e, const Segment* __restrict__ seg, const int4* __restrict__ bbin,
-          int4* __restrict__ bbout, PushParams<R> pp, FarList far, int* status)
+    k_gpd(Geo g, FieldSet<R> f, ElectronParams<R> ep)
 {
-    gpd_segment<R, MC, gpd_threads<R>()>(g, f, e, seg, bbin, bbout, pp, far, status, blockIdx.x);
+    gpd_segment<R, MC, gpd_threads<R>()>(g, f, ep, blockIdx.x);
 }
 
 template <typename R>
@@ -589,114 +693,7 @@ __global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1) k_gp
         if (it < 0) return;
         r = run_of(q, it, r);
         const GpdDesc<R>& D = d[r];
-        gpd_segment<R, false, gpd_threads<R>()>(D.g, D.f, D.e, D.seg, D.bbin, D.bbout, D.pp, D.far, D.status,
-                                                it - q.off[r]);
-    }
-}
-
-// ---- electrons outside their staged window, on HBM ----------------------------------------
-// sum over the 16 lanes of a particle
-template <typename R>
-__device__ __forceinline__ R sum16(R v)
-{
-    for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
-// the cubic B-spline at distance r from a node
-template <typename R>
-__device__ __forceinline__ R spline3(R r)
-{
-    const R d = fabs(r), t = R(2) - d;
-    const R near = R(2.0 / 3.0) - d * d * (R(1) - R(0.5) * d), far = t * t * t * R(1.0 / 6.0);
-    return d < R(1) ? near : d < R(2) ? far : R(0);
-}
-
-// Particle p of segment s by 16 lanes, one stencil node each for the gather and two of the 25
-// nodes for the deposit: a few dependent loads, where one thread would walk 16 nodes of nine
-// arrays and 65 adds.  Lanes 0-4 hold the deposit's shape factors of the window's x nodes, lanes
-// 5-9 those of its z nodes; the others fetch them by shuffles, which keeps the registers of the
-// ion path it shares a kernel with.
-template <bool MC, typename R>
-__device__ __forceinline__ void far_electron(const Geo& g, const FieldSet<R>& f, const ElectronArrays<R>& e,
-                                             const PushParams<R>& pp, int4* bbout, int* status, int s, int p)
-{
-    const int n = threadIdx.x & 15, a = n & 3, b = n >> 2;
-    EState<R> st = load_electron(e, p);
-    const double x = st.x, z = st.z;
-    const int ix = (int)floor(x), iz = (int)floor(z);
-    auto at = [&](int jx, int jz) -> long {
-        const int i = swrap(jx + g.Px, g.Sx, g.perx), k = swrap(jz + g.Pz, g.Sz, g.perz);
-        return i < 0 || k < 0 ? -1 : gofs(g, i, k);
-    };
-    // this lane's node and weight for each stagger along x and z
-    R wx[2], wz[2];
-    int jx[2], jz[2];
-#pragma unroll
-    for (int h = 0; h < 2; h++) {
-        const double xs = x - 0.5 * h, zs = z - 0.5 * h;
-        jx[h] = (int)floor(xs) - 1 + a;
-        jz[h] = (int)floor(zs) - 1 + b;
-        wx[h] = spline3((R)(xs - jx[h]));
-        wz[h] = spline3((R)(zs - jz[h]));
-    }
-    R E[3], B[3];
-#pragma unroll
-    for (int c = 0; c < 6; c++) {
-        // staggers: E_x (half, node), E_y (node, node), E_z (node, half), B_x (node, half),
-        // B_y (half, half), B_z (half, node); the node values have none
-        const int hx = !MC && (c == 0 || c == 4 || c == 5), hz = !MC && (c == 2 || c == 3 || c == 4);
-        const long o = at(jx[hx], jz[hz]);
-        R v = R(0);
-        if (o >= 0) v = MC ? f.G[c][o] : c < 3 ? f.E[c][o] : R(0.5) * (f.B[c - 3][o] + f.Bn[c - 3][o]);
-        v = sum16(wx[hx] * wz[hz] * v);
-        if (c < 3) E[c] = v;
-        else B[c - 3] = v;
-    }
-    R u[3] = {st.ux, st.uy, st.uz}, v[3];
-    push_electron(pp, E, B, u, v);
-    const double xn = x + (double)(pp.dtdx * v[0]), zn = z + (double)(pp.dtdz * v[2]);
-    const int ix1 = (int)floor(xn), iz1 = (int)floor(zn);
-    if (abs(ix1 - ix) <= 1 && abs(iz1 - iz) <= 1) {
-        const double w = (double)st.w;
-        const int bx = min(ix, ix1) - 1, bz = min(iz, iz1) - 1;
-        const bool isx = n < 5;
-        const int node = isx ? bx + n : bz + n - 5;
-        const double s0 = spline3((isx ? x : z) - node), s1 = spline3((isx ? xn : zn) - node);
-        double pd = s1 - s0;             // becomes the prefix sum over the axis' nodes
-        for (int o = 1; o < 5; o <<= 1) {
-            const double up = __shfl_up(pd, o, 16);
-            if ((isx ? n : n - 5) >= o) pd += up;
-        }
-#pragma unroll 1
-        for (int q = n; q < 32; q += 16) {
-            const int m = q % 5, k = min(q / 5, 4);
-            const double s0x = __shfl(s0, m, 16), s1x = __shfl(s1, m, 16), s0z = __shfl(s0, 5 + k, 16),
-                         s1z = __shfl(s1, 5 + k, 16);
-            const double px = __shfl(pd, m, 16), pz = __shfl(pd, 5 + k, 16);
-            const long o = q < 25 ? at(bx + m, bz + k) : -1;
-            if (o < 0) continue;
-            const double vx = m < 4 ? w * (double)pp.fjx * px * 0.5 * (s0z + s1z) : 0.0;
-            const double vz = k < 4 ? w * (double)pp.fjz * pz * 0.5 * (s0x + s1x) : 0.0;
-            const double vy = w * (double)(pp.fjy * v[1]) *
-                              (s0x * (s0z / 3.0 + s1z / 6.0) + s1x * (s0z / 6.0 + s1z / 3.0));
-            if (vx != 0.0) atomicAdd(&f.J[0][o], (R)vx);
-            if (vz != 0.0) atomicAdd(&f.J[2][o], (R)vz);
-            if (vy != 0.0) atomicAdd(&f.J[1][o], (R)vy);
-        }
-    } else {
-        atomicOr(status, ST_NONFINITE);   // faster than light: only a non-finite state gets here
-    }
-    int x0 = INT_MAX, x1 = INT_MIN, z0 = INT_MAX, z1 = INT_MIN;
-    finish_electron(g, pp, xn, zn, u, st, status, x0, x1, z0, z1);
-    if (n == 0) {
-        store_electron(e, p, st);
-        if (x0 <= x1) {
-            atomicMin(&bbout[s].x, x0);
-            atomicMax(&bbout[s].y, x1);
-            atomicMin(&bbout[s].z, z0);
-            atomicMax(&bbout[s].w, z1);
-        }
+        gpd_segment<R, false, gpd_threads<R>()>(D.g, D.f, D.e, it - q.off[r]);
     }
 }
 
@@ -726,15 +723,15 @@ __device__ __forceinline__ void ion_current(const A& acc, int ix, double fx, int
     }
 }
 
-template <typename R>
+template <typename R, int NTH>
 __device__ __forceinline__ void ion_segment(const Geo& g, const FieldSet<R>& f, const IonArrays<R>& ion,
                                             const Segment* __restrict__ seg, const int4* __restrict__ bbin,
                                             int4* __restrict__ bbout, double zsh_a, double zsh_b, int shift,
                                             R fjz, int s)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];   // 16-byte aligned: FP64 DS ops
-    __shared__ int4 red[NTHR / 64];
-    __shared__ double redd[NTHR / 64];
+    __shared__ int4 red[NTH / 64];
+    __shared__ double redd[NTH / 64];
     const Segment sg = seg[s];
     const int4 bb = bbin[s];
     if (sg.count <= 0 || bb.x > bb.y || bb.z > bb.w) {
@@ -761,12 +758,12 @@ __device__ __forceinline__ void ion_segment(const Geo& g, const FieldSet<R>& f, 
     if (use_lds) {
         if constexpr (LdsAcc<R>::FIX) {
             double sw = 0.0;
-            for (int p = sg.start + threadIdx.x; p < end; p += NTHR) sw += fabs((double)ion.w[p]);
-            sw = block_sum(sw, redd);
+            for (int p = sg.start + threadIdx.x; p < end; p += NTH) sw += fabs((double)ion.w[p]);
+            sw = block_sum<NTH>(sw, redd);
             const double bound = fabs((double)fjz) * sw;
             if (bound > 0.0) { js = FIX_RANGE / bound; jq = bound / FIX_RANGE; }
         }
-        for (int q = threadIdx.x; q < L; q += NTHR) jz[(q / lds.lx) * TPX + q % lds.lx] = JT(0);
+        for (int q = threadIdx.x; q < L; q += NTH) jz[(q / lds.lx) * TPX + q % lds.lx] = JT(0);
         __syncthreads();
     }
     int x0 = INT_MAX, x1 = INT_MIN, z0 = INT_MAX, z1 = INT_MIN;
@@ -775,10 +772,10 @@ __device__ __forceinline__ void ion_segment(const Geo& g, const FieldSet<R>& f, 
     double nx_ = 0.0, nz_ = 0.0;
     R nw = R(0);
     if (p < end) { nx_ = ion.x[p]; nz_ = ion.z0[p]; nw = ion.w[p]; }
-    for (; p < end; p += NTHR) {
+    for (; p < end; p += NTH) {
         const R w = nw;
         const double x = nx_, zc0 = nz_;
-        if (p + NTHR < end) { nx_ = ion.x[p + NTHR]; nz_ = ion.z0[p + NTHR]; nw = ion.w[p + NTHR]; }
+        if (p + NTH < end) { nx_ = ion.x[p + NTH]; nz_ = ion.z0[p + NTH]; nw = ion.w[p + NTH]; }
         if (w == R(0)) continue;
         const double za = zc0 - zsh_a, zb = zc0 - zsh_b;
         const int ix = (int)floor(x), iz = (int)floor(za), iz1 = (int)floor(zb);
@@ -799,7 +796,7 @@ __device__ __forceinline__ void ion_segment(const Geo& g, const FieldSet<R>& f, 
     }
     if (use_lds) {
         __syncthreads();
-        for (int q = threadIdx.x; q < L; q += NTHR) {
+        for (int q = threadIdx.x; q < L; q += NTH) {
             const int a = q % lds.lx, b = q / lds.lx;
             R v;
             if constexpr (LdsAcc<R>::FIX) v = (R)(fix_value(jz[b * TPX + a]) * jq);
@@ -894,29 +891,33 @@ __device__ __forceinline__ void antenna_pair(const Geo& g, const FieldSet<R>& f,
     if (lane == 0) xm[i] = xb;
 }
 
-// The sources of a step's current beside the staged electrons, in one launch: workgroups
-// [0, nion) take an ion segment each, the next na four antenna pairs (a wave each), the rest the
-// electrons of the list far (16 lanes each, a quarter of a wave).  They only add to J.  As
-// launches of their own the antenna and the list cost 5-6 us each whatever their work.  Bounded
-// to five waves per SIMD in FP32, what the ions reach alone: at three they took 150 us instead
-// of 119 us on 256 x 4096 cells (16.8 M ions).
+// The other sources of a step's current by workgroup b of NTH threads: [0, nion) take an ion
+// segment each, the next na a few antenna pairs (a wave each).
+template <typename R, int NTH>
+__device__ __forceinline__ void source_block(const Geo& g, const FieldSet<R>& f, const SourceParams<R>& sp, int b)
+{
+    if (b < sp.nion) {
+        ion_segment<R, NTH>(g, f, sp.ion, sp.iseg, sp.ibbin, sp.ibbout, sp.zsh_a, sp.zsh_b, sp.shift, sp.fjz, b);
+    } else {
+        const int i = (b - sp.nion) * (NTH / 64) + (int)threadIdx.x / 64;
+        if (i < sp.ap.n) antenna_pair<R>(g, f, sp.xm, sp.ap, i);
+    }
+}
+
+template <typename R>
+__global__ void __launch_bounds__(NTHR) k_sources(Geo g, FieldSet<R> f, SourceParams<R> sp)
+{
+    source_block<R, NTHR>(g, f, sp, blockIdx.x);
+}
+
+// electrons and sources in one launch (they only add to J)
 template <typename R, bool MC>
-__global__ void __launch_bounds__(NTHR, sizeof(R) == 4 ? 5 : 4) k_sources(Geo g, FieldSet<R> f, SourceParams<R> sp)
+__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
+    k_particles(Geo g, FieldSet<R> f, ElectronParams<R> ep, SourceParams<R> sp)
 {
     const int b = blockIdx.x;
-    if (b < sp.nion) {
-        ion_segment<R>(g, f, sp.ion, sp.iseg, sp.ibbin, sp.ibbout, sp.zsh_a, sp.zsh_b, sp.pp.shift, sp.fjz, b);
-    } else if (b < sp.nion + sp.na) {
-        const int i = (b - sp.nion) * (NTHR / 64) + (int)threadIdx.x / 64;
-        if (i < sp.ap.n) antenna_pair<R>(g, f, sp.xm, sp.ap, i);
-    } else {
-        const int n = *sp.far.n, step = (gridDim.x - sp.nion - sp.na) * (NTHR / 16);
-        // the 16 lanes of a particle stay together: i is the same for all of them
-        for (int i = (b - sp.nion - sp.na) * (NTHR / 16) + (int)threadIdx.x / 16; i < n; i += step) {
-            const int2 m = sp.far.list[i];
-            far_electron<MC>(g, f, sp.e, sp.pp, sp.ebbout, sp.status, m.x, m.y);
-        }
-    }
+    if (b < ep.nseg) gpd_segment<R, MC, gpd_threads<R>()>(g, f, ep, b);
+    else source_block<R, gpd_threads<R>()>(g, f, sp, b - ep.nseg);
 }
 
 // ---- particle beam through a lab-fixed plane (Sec. 3.1.1) ---------------------------------
@@ -1020,15 +1021,37 @@ __device__ __forceinline__ double u01(uint64_t seed, uint64_t k)
     return (double)(splitmix64(seed, k) >> 11) * (1.0 / 9007199254740992.0);
 }
 
+// After the ring offset has moved by d rows: clear the |d| new rows of every array, drop the
+// split x-part of rows that just left the z-PML for the interior (where no x-PML acts), and
+// keep tangential E zero on the two end walls; column i.
 template <typename R>
-__global__ void __launch_bounds__(NTHR) k_inject(Geo g, ElectronArrays<R> e, IonArrays<R> ion,
-                                                 Segment* seg_e, int4* bbox_e, Segment* seg_i,
-                                                 int4* bbox_i, int* nused_e, int* nused_i,
-                                                 InjectParams ip, int* status)
+__device__ __forceinline__ void window_column(const Geo& g, const WindowParams<R>& w, int i)
+{
+    const int d = w.d, kn0 = d > 0 ? g.Sz - d : 0, kn1 = d > 0 ? g.Sz : -d;
+    for (int a = 0; a < w.arrays.n; a++)
+        for (int k = kn0; k < kn1; k++) w.arrays.p[a][gofs(g, i, k)] = R(0);
+    for (int q = 0; q < w.er.nh; q++)
+        if (!w.pm.on[0][1][i]) w.f.Byx[gofs(g, i, w.er.h[q])] = R(0);
+    for (int q = 0; q < w.er.nn; q++)
+        if (!w.pm.on[0][0][i]) w.f.Eyx[gofs(g, i, w.er.n[q])] = R(0);
+    const int walls[2] = {0, g.Sz - 1};
+    for (int q = 0; q < 2; q++) {
+        const long o = gofs(g, i, walls[q]);
+        w.f.E[0][o] = R(0); w.f.E[1][o] = R(0);
+        w.f.Eo[0][o] = R(0); w.f.Eo[1][o] = R(0);
+        w.f.Eb[0][o] = R(0); w.f.Eb[1][o] = R(0);
+        w.f.Ebn[0][o] = R(0); w.f.Ebn[1][o] = R(0);
+    }
+}
+
+// lattice row ip.row0 + r, chunk of tile_x columns, by one workgroup
+template <typename R>
+__device__ __forceinline__ void inject_chunk(const Geo& g, const ElectronArrays<R>& e, const IonArrays<R>& ion,
+                                             Segment* seg_e, int4* bbox_e, Segment* seg_i, int4* bbox_i, int* nused_e,
+                                             int* nused_i, const InjectParams& ip, int* status, int chunk, int r)
 {
     __shared__ int sh_start[2];
     __shared__ int4 red[NTHR / 64];
-    const int chunk = blockIdx.x, r = blockIdx.y;
     const int64_t row = ip.row0 + r;
     const int cx0 = chunk * ip.tile_x;
     const int ncell = min(ip.tile_x, g.Nx - cx0);
@@ -1103,6 +1126,24 @@ __global__ void __launch_bounds__(NTHR) k_inject(Geo g, ElectronArrays<R> e, Ion
             seg_i[slot] = Segment{si, count};
             bbox_i[slot] = make_int4(x0, x1, z0, z1);
         }
+    }
+}
+
+// the window's columns by the first nwin workgroups, then a chunk of plasma each: fields and
+// particles do not meet, and a launch of its own costs each 4-6 us whatever its work
+template <typename R>
+__global__ void __launch_bounds__(NTHR) k_advance(Geo g, WindowParams<R> w, int nwin, ElectronArrays<R> e,
+                                                  IonArrays<R> ion, Segment* seg_e, int4* bbox_e, Segment* seg_i,
+                                                  int4* bbox_i, int* nused_e, int* nused_i, InjectParams ip,
+                                                  int* status)
+{
+    const int b = blockIdx.x;
+    if (b < nwin) {
+        const int i = b * NTHR + (int)threadIdx.x;
+        if (i < g.Sx) window_column<R>(g, w, i);
+    } else {
+        inject_chunk<R>(g, e, ion, seg_e, bbox_e, seg_i, bbox_i, nused_e, nused_i, ip, status, (b - nwin) % ip.nchunks,
+                        (b - nwin) / ip.nchunks);
     }
 }
 
@@ -1450,41 +1491,57 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_disperse_i(Geo g, IonArra
 }
 
 // ---- launchers ---------------------------------------------------------------------------------
-template <typename R>
-void launch_gpd(const Geo& g, const FieldSet<R>& f, const ElectronArrays<R>& e, const Segment* seg,
-                const int4* bbox_in, int4* bbox_out, int nseg, const PushParams<R>& pp, const FarList& far,
-                int* status, bool mc, hipStream_t s)
+template <typename R> constexpr size_t gpd_lds()
 {
-    if (nseg <= 0) return;
-    const size_t lds = (size_t)tcells<R>() * (6 * sizeof(R) + 3 * sizeof(typename LdsAcc<R>::JT));
-    const dim3 block(gpd_threads<R>());
-    if (mc)
-        hipLaunchKernelGGL((k_gpd<R, true>), dim3(nseg), block, lds, s, g, f, e, seg, bbox_in, bbox_out, pp, far,
-                           status);
-    else
-        hipLaunchKernelGGL((k_gpd<R, false>), dim3(nseg), block, lds, s, g, f, e, seg, bbox_in, bbox_out, pp, far,
-                           status);
+    return (size_t)tcells<R>() * (6 * sizeof(R) + 3 * sizeof(typename LdsAcc<R>::JT));
 }
 
 template <typename R>
-void launch_sources(const Geo& g, const FieldSet<R>& f, SourceParams<R> sp, int nseg_e, bool mc, hipStream_t s)
+static int antenna_blocks(const SourceParams<R>& sp, int threads)
 {
-    sp.na = sp.ap.active ? (sp.ap.n + NTHR / 64 - 1) / (NTHR / 64) : 0;
-    // the list is nearly always empty or short; its workgroups stride over it
-    const int nfar = nseg_e <= 0 ? 0 : std::min(std::max(nseg_e / 4, 8), 512);
-    const int n = sp.nion + sp.na + nfar;
-    if (n <= 0) return;
-    const size_t lds = (size_t)tcells<R>() * sizeof(typename LdsAcc<R>::JT);
-    if (mc) hipLaunchKernelGGL((k_sources<R, true>), dim3(n), dim3(NTHR), lds, s, g, f, sp);
-    else hipLaunchKernelGGL((k_sources<R, false>), dim3(n), dim3(NTHR), lds, s, g, f, sp);
+    return sp.ap.active ? (sp.ap.n + threads / 64 - 1) / (threads / 64) : 0;
+}
+
+template <typename R>
+void launch_sources(const Geo& g, const FieldSet<R>& f, SourceParams<R> sp, hipStream_t s)
+{
+    sp.na = antenna_blocks(sp, NTHR);
+    const int n = sp.nion + sp.na;
+    if (n > 0)
+        hipLaunchKernelGGL((k_sources<R>), dim3(n), dim3(NTHR),
+                           (size_t)tcells<R>() * sizeof(typename LdsAcc<R>::JT), s, g, f, sp);
+}
+
+template <typename R, bool MC>
+static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, SourceParams<R> sp, hipStream_t s)
+{
+    constexpr int threads = gpd_threads<R>();
+    sp.na = antenna_blocks(sp, threads);
+    const int n = ep.nseg + sp.nion + sp.na;
+    // One launch: the ions and the antenna fill the electrons' tail, and a launch is spared.  20
+    // steps against two launches: 75 x 1691 cells at 1 particle a cell 0.96 -> 0.83 ms, 64 x 512 in
+    // FP64 1.17 -> 0.83 ms, 187 x 1531 at 5 3.31 -> 3.08 ms, 256 x 4096 at 16 13.2 -> 13.0 ms.
+    if (ep.nseg > 0 && n > ep.nseg) {
+        hipLaunchKernelGGL((k_particles<R, MC>), dim3(n), dim3(threads), gpd_lds<R>(), s, g, f, ep, sp);
+        return;
+    }
+    if (ep.nseg > 0) hipLaunchKernelGGL((k_gpd<R, MC>), dim3(ep.nseg), dim3(threads), gpd_lds<R>(), s, g, f, ep);
+    launch_sources<R>(g, f, sp, s);
+}
+
+template <typename R>
+void launch_particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
+                      bool mc, hipStream_t s)
+{
+    if (mc) particles<R, true>(g, f, ep, sp, s);
+    else particles<R, false>(g, f, ep, sp, s);
 }
 
 template <typename R>
 void launch_gpd_batch(const GpdDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s)
 {
-    const size_t lds = (size_t)tcells<R>() * (6 * sizeof(R) + 3 * sizeof(typename LdsAcc<R>::JT));
     if (q.total > 0)
-        hipLaunchKernelGGL((k_gpd_batch<R>), dim3(nblocks), dim3(gpd_threads<R>()), lds, s, d, q);
+        hipLaunchKernelGGL((k_gpd_batch<R>), dim3(nblocks), dim3(gpd_threads<R>()), gpd_lds<R>(), s, d, q);
 }
 
 template <typename R>
@@ -1498,13 +1555,14 @@ void launch_beam(const Geo& g, const FieldSet<R>& f, const BeamArrays& b, const 
 }
 
 template <typename R>
-void launch_inject(const Geo& g, const ElectronArrays<R>& e, const IonArrays<R>& ion, Segment* seg_e,
-                   int4* bbox_e, Segment* seg_i, int4* bbox_i, int* nused_e, int* nused_i,
-                   const InjectParams& ip, int* status, hipStream_t s)
+void launch_advance(const Geo& g, const WindowParams<R>* wp, const ElectronArrays<R>& e, const IonArrays<R>& ion,
+                    Segment* seg_e, int4* bbox_e, Segment* seg_i, int4* bbox_i, int* nused_e, int* nused_i,
+                    const InjectParams& ip, int* status, hipStream_t s)
 {
-    if (ip.nrows <= 0) return;
-    hipLaunchKernelGGL((k_inject<R>), dim3(ip.nchunks, ip.nrows), dim3(NTHR), 0, s, g, e, ion, seg_e,
-                       bbox_e, seg_i, bbox_i, nused_e, nused_i, ip, status);
+    const int nwin = wp ? (g.Sx + NTHR - 1) / NTHR : 0, n = nwin + ip.nrows * ip.nchunks;
+    if (n <= 0) return;
+    hipLaunchKernelGGL((k_advance<R>), dim3(n), dim3(NTHR), 0, s, g, wp ? *wp : WindowParams<R>{}, nwin, e, ion,
+                       seg_e, bbox_e, seg_i, bbox_i, nused_e, nused_i, ip, status);
 }
 
 // two-pass sort: a -> b by tile (consecutive slots per tile), then b -> a ordered within each
@@ -1551,17 +1609,15 @@ void launch_sort_ions(const Geo& g, int tile_x, int tile_z, int ntx, int ntiles,
 }
 
 #define BF_INST(R)                                                                                    \
-    template void launch_gpd<R>(const Geo&, const FieldSet<R>&, const ElectronArrays<R>&,             \
-                                const Segment*, const int4*, int4*, int, const PushParams<R>&,        \
-                                const FarList&, int*, bool, hipStream_t);                             \
-    template void launch_sources<R>(const Geo&, const FieldSet<R>&, SourceParams<R>, int, bool,       \
-                                    hipStream_t);                                                     \
+    template void launch_particles<R>(const Geo&, const FieldSet<R>&, const ElectronParams<R>&,       \
+                                      const SourceParams<R>&, bool, hipStream_t);                     \
+    template void launch_sources<R>(const Geo&, const FieldSet<R>&, SourceParams<R>, hipStream_t);    \
     template void launch_gpd_batch<R>(const GpdDesc<R>*, const QueueRef&, int, hipStream_t);          \
     template void launch_beam<R>(const Geo&, const FieldSet<R>&, const BeamArrays&, const BeamParams&, \
                                  const PushParams<double>&, int*, bool, hipStream_t);                 \
-    template void launch_inject<R>(const Geo&, const ElectronArrays<R>&, const IonArrays<R>&,         \
-                                   Segment*, int4*, Segment*, int4*, int*, int*,                      \
-                                   const InjectParams&, int*, hipStream_t);                           \
+    template void launch_advance<R>(const Geo&, const WindowParams<R>*, const ElectronArrays<R>&,     \
+                                    const IonArrays<R>&, Segment*, int4*, Segment*, int4*, int*,      \
+                                    int*, const InjectParams&, int*, hipStream_t);                    \
     template void launch_sort_electrons<R>(const Geo&, int, int, int, int, const ElectronArrays<R>&,  \
                                            const ElectronArrays<R>&, const Segment*, int, Segment*,   \
                                            int4*, int*, int*, int*, hipStream_t);                     \

@@ -1161,8 +1161,8 @@ bf_status create3(const bf_config* cfg, const bf_buffer_binding* b, int n, void*
         int dev = 0, lds_max = 65536;
         if (hipGetDevice(&dev) == hipSuccess)
             (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-        const int cell = cfg->real_bytes == 4 ? bf3::box_cell_bytes<float>() : bf3::box_cell_bytes<double>();
-        const int fit = lds_max / (bf3::BOX_PL * cell);
+        const int plane = cfg->real_bytes == 4 ? bf3::box_plane_bytes<float>() : bf3::box_plane_bytes<double>();
+        const int fit = lds_max / plane;
         s->d3->pz = std::min(s->d3->tl.t[2] + 7, fit);
     }
     hipError_t e = hipSuccess;

@@ -959,7 +959,7 @@ __device__ __forceinline__ R rsq(R x)
 constexpr int GT = 768;        // threads of an electron segment workgroup
 constexpr int GTI = 256;       // threads of an ion segment workgroup
 constexpr int HBM_GRID = 1024; // workgroups of the pass over the particles left to HBM
-constexpr int BPX = BOX_PX, BPY = BOX_PY, BPL = BOX_PL;
+constexpr int BPX = BOX_PX, BPY = BOX_PY, BPL = BOX_PL, FPL = BOX_FPL;
 
 template <typename R> struct Acc3 { using T = double; static constexpr bool fixed = false; };
 template <> struct Acc3<float> { using T = unsigned long long; static constexpr bool fixed = true; };
@@ -979,7 +979,7 @@ struct BoxL {
     using JT = typename Acc3<R>::T;
     JT* j;         // current planes of n cells (3 for electrons, J_z only for ions)
     R* f;          // 6 field planes of n cells: E x, y, z and B x, y, z (time-centred)
-    int n;         // cells per plane: BPL * planes
+    int n, nf;     // cells per current (BPL * planes) and field component (FPL * planes)
     int lo[3];     // interior cell index of box cell (0, 0, 0)
     int ext[3];    // box extent (cells)
 };
@@ -1024,20 +1024,20 @@ __device__ __forceinline__ void gather_box(const BoxL<R>& bx, const double r[3],
             const double xs = r[a] - 0.5 * h;
             const int j0 = (int)floor(xs);
             bspline4((R)(xs - j0), w[a][h]);
-            ob[a][h] = (j0 - 1 - bx.lo[a]) * bstride(a);
+            ob[a][h] = (j0 - 1 - bx.lo[a]) * (a == 2 ? FPL : bstride(a));
         }
 #pragma unroll
     for (int c = 0; c < 6; c++) {
         const int hx = MC ? 0 : (c < 3 ? (c == 0) : (c != 3)), hy = MC ? 0 : (c < 3 ? (c == 1) : (c != 4)),
                   hz = MC ? 0 : (c < 3 ? (c == 2) : (c != 5));
-        const R* F = bx.f + c * bx.n + ob[0][hx] + ob[1][hy] + ob[2][hz];
+        const R* F = bx.f + c * bx.nf + ob[0][hx] + ob[1][hy] + ob[2][hz];
         R acc = R(0);
 #pragma unroll
         for (int k = 0; k < 4; k++) {
             R tk = R(0);
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const R* row = F + j * BPX + k * BPL;
+                const R* row = F + j * BPX + k * FPL;
                 const R rr = w[0][hx][0] * row[0] + w[0][hx][1] * row[1] + w[0][hx][2] * row[2] + w[0][hx][3] * row[3];
                 tk += w[1][hy][j] * rr;
             }
@@ -1172,7 +1172,7 @@ __device__ void stage_box(const G3& g, const F3<R>& f, const BoxL<R>& bx, int nj
                 }
             }
 #pragma unroll
-            for (int cc = 0; cc < 6; cc++) bx.f[cc * bx.n + t] = v[cc];
+            for (int cc = 0; cc < 6; cc++) bx.f[cc * bx.nf + a + BPX * b + FPL * c] = v[cc];
         }
         for (int cc = 0; cc < nj; cc++) bx.j[cc * bx.n + t] = typename Acc3<R>::T(0);
     }
@@ -1348,6 +1348,7 @@ __device__ __forceinline__ void box_of(const Box3& bb, int pz, BoxL<R>& bx, bool
         bx.ext[a] = bb.hi[a] - bb.lo[a] + 6;
     }
     bx.n = BPL * pz;
+    bx.nf = FPL * pz;
     lds = bx.ext[0] <= BPX && bx.ext[1] <= BPY && bx.ext[2] <= pz;
 }
 
@@ -1635,8 +1636,8 @@ __device__ __forceinline__ double u01(uint64_t seed, uint64_t k)
 
 // lattice planes row0 .. row0+nrows-1 of the lab-fixed plasma into slots base.. (base = the
 // particles in use), one thread per particle.  A plane is laid out in transverse tile chunks
-// (rows of chunks along y, chunks along x, then ppc, then the chunk's cells x-fastest); each
-// chunk becomes a segment whose box spans its cells and the plane's z cells.  The particle id
+// (rows of chunks along y, chunks along x, then ppc, then the chunk's cells, LAT_X columns at a
+// time); each chunk becomes a segment whose box spans its cells and the plane's z cells.  The particle id
 // (and so its random offsets) depends only on the plane, the cell and k.
 template <typename R>
 __device__ __forceinline__ void inject_one(const G3& g, const Tiles3& tl, const E3<R>& e, const I3<R>& ion, int be,
@@ -1659,7 +1660,8 @@ __device__ __forceinline__ void inject_one(const G3& g, const Tiles3& tl, const 
     const int hx = min(tx, N0 - cxi * tx);
     const int ncc = hx * hy;
     const int k = (int)(rem2 / ncc), lc = (int)(rem2 - (int64_t)k * ncc);
-    const int i = cxi * tx + lc % hx, j = cyi * ty + lc / hx;
+    const int blk = lc / (LAT_X * hy), wb = min(LAT_X, hx - blk * LAT_X), lb = lc - blk * LAT_X * hy;
+    const int i = cxi * tx + blk * LAT_X + lb % wb, j = cyi * ty + lb / wb;
     const int64_t l = ip.row0 + r;
     const double c = ip.beta * ip.t / ip.dz + ip.shift;
     if (rem2 == 0) {
@@ -1925,10 +1927,10 @@ __global__ void __launch_bounds__(NT) k3_sort_scatter_i(G3 g, Tiles3 tl, I3<R> s
 
 // Order within each tile after the scatter, by the particle's place in the plasma lattice: its
 // id encodes the lattice plane l, the cell (i, j) and the index k < ppc within the cell, and
-// the tile is laid out by (l, k, j, i), i fastest, over the tile's i, j range.  A wave of 64
-// lanes then holds the k-th particles of one lattice plane over an 8 x 8 block of cells: the
+// the tile is laid out by (l, k, i / LAT_X, j, i mod LAT_X) over the tile's i, j range.  A wave of
+// 64 lanes then holds the k-th particles of one lattice plane over a 16 x 4 block of cells: the
 // lanes sit in distinct (x, y) cells and differ in z by at most one plane (the plasma drifts
-// rigidly), which the LDS box layout keeps in distinct bank pairs.  Ids outside the pattern
+// rigidly), which the LDS box layout keeps in distinct banks.  Ids outside the pattern
 // (particles loaded from outside) only fall in clamped places: any order is valid.  Equal
 // keys are spread level by level (the k-th particle with a key in level k).
 constexpr int ORD_THREADS = 512;
@@ -1957,7 +1959,8 @@ struct LatticeKey {
         const int l = (int)(rest / (uint32_t)(n0 * n1));
         const int li = min(max(i - o0, 0), w0 - 1), lj = min(max(j - o1, 0), w1 - 1);
         const int ll = min(max(l - lmin, 0), lr - 1);
-        return ((ll * ppc + k) * w1 + lj) * w0 + li;
+        const int b = li / LAT_X, wb = min(LAT_X, w0 - b * LAT_X);
+        return (ll * ppc + k) * w1 * w0 + b * LAT_X * w1 + lj * wb + (li - b * LAT_X);
     }
 };
 
@@ -2450,7 +2453,7 @@ template <typename R, bool MC>
 void gpd_launch(const G3& g, const F3<R>& f, const E3<R>& e, const Seg3* seg, const Box3* bin, Box3* bout,
                 int nseg, const Push3& pp, int pz, int* status, int* nmis, int2* mis, hipStream_t s)
 {
-    const size_t lds = (size_t)BPL * pz * box_cell_bytes<R>();
+    const size_t lds = (size_t)box_plane_bytes<R>() * pz;
     (void)hipFuncSetAttribute((const void*)k3_gpd<R, MC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     hipLaunchKernelGGL((k3_gpd<R, MC>), dim3(nseg), dim3(GT), lds, s, g, f, e, seg, bin, bout, pp, pz, status, mis,
                        nmis);

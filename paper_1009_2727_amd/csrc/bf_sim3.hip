@@ -779,6 +779,125 @@ __global__ void __launch_bounds__(FT_NT) k3_filt3(G3 g, Lines3<double, TO> L, Fi
     }
 }
 
+// The same filter on small grids, a cube of FB cells of one component per workgroup.  The ring kernel
+// walks its planes one after the other (two barriers and a round trip to HBM each) and a small grid
+// has too few columns to fill the chip; here the cube with its reach is staged at once and filtered
+// along x, y and z in LDS, three barriers in all, at the price of (1 + 2 RC / FB)^3 loads a cell.
+// Row, column or plane N of the staged cube holds the raw values just past the component's range
+// on its own axis (the copied cells), when they fall in the cube.  Bound by latency up to one
+// round of resident workgroups, then by the LDS passes.  Box against ring kernel with 4 passes and
+// compensation, PML of 8: 12 / 48 us on 12x10x48 cells, 43 / 49 us on 48x48x48 and 61 / 49 us on
+// 64x64x48 in FP64; 36 / 45 us on 64x64x48 and 58 / 45 us on 64x64x96 in FP32.  With 2 passes:
+// 23 / 25 us on 48x48x48 and 33 / 25 us on 64x64x48, FP32 22 / 24 and 33 / 26 us.
+constexpr int FB = 8, FB_NT = 256;
+// cubes (three components) up to which this is the faster kernel
+template <typename R> constexpr long fb_max() { return sizeof(R) == 4 ? 3500 : 2300; }
+
+template <int RC, typename T>
+__global__ void __launch_bounds__(FB_NT) k3_filt_box(G3 g, Lines3<double, T> L, FiltStencil st, int ntx, int nty, int ntz)
+{
+    constexpr int N = FB + 2 * RC, N1 = N + 1, PA = N1 | 1;      // staged cells, odd row pitch
+    constexpr int NA = N1 * N1 * PA;
+    __shared__ T sA[NA];
+    __shared__ T sB[N1 * N1 * FB];
+    __shared__ long tof[3][N1];         // offset of a staged position along each axis
+    __shared__ int tsg[3][N1];          // its sign under the odd continuation
+    int w = blockIdx.x;
+    const int tx = w % ntx; w /= ntx;
+    const int ty = w % nty; w /= nty;
+    const int tz = w % ntz;
+    const int comp = w / ntz;
+    const double* __restrict__ in = L.in[comp];
+    T* __restrict__ out = L.out[comp];
+    const int o[3] = {tx * FB, ty * FB, tz * FB};
+    const int h = (g.per[comp] ? g.S[comp] - 1 : g.S[comp] - 2);   // last filtered position along comp
+    const bool copy = h + 1 < g.S[comp] && h + 1 >= o[comp] && h + 1 < o[comp] + FB;
+    T c[RC + 1];
+#pragma unroll
+    for (int m = 0; m <= RC; m++) c[m] = (T)st.c[m];
+    if (threadIdx.x < 3 * N1) {
+        const int a = threadIdx.x / N1, i = threadIdx.x - a * N1;
+        int sg = 0, j = 0;
+        if (i < N) j = odd_pos(o[a] - RC + i, g.S[a], a == comp ? h : g.S[a] - 1, g.per[a], sg);
+        else if (a == comp && copy) { j = h + 1; sg = 1; }
+        if (a == 2) {
+            j += g.zoff;
+            if (j >= g.S[2]) j -= g.S[2];
+        }
+        tof[a][i] = a == 0 ? j : a == 1 ? (long)j * g.pitch : (long)j * g.plane;
+        tsg[a][i] = sg;
+    }
+    __syncthreads();
+    constexpr int U = 9;                // loads in flight a thread
+    for (int q0 = threadIdx.x; q0 < N1 * N1 * N1; q0 += U * FB_NT) {
+        double v[U];
+        int sg[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int q = min(q0 + u * FB_NT, N1 * N1 * N1 - 1);
+            const int i = q % N1, j = q / N1 % N1, k = q / (N1 * N1);
+            sg[u] = tsg[0][i] * tsg[1][j] * tsg[2][k];
+            v[u] = in[sg[u] ? tof[0][i] + tof[1][j] + tof[2][k] : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int q = min(q0 + u * FB_NT, N1 * N1 * N1 - 1);
+            sA[q / N1 * PA + q % N1] = sg[u] ? (T)sg[u] * (T)v[u] : T(0);
+        }
+    }
+    __syncthreads();
+    // Q outputs from position b along an axis of stride sd in src; the copied position (local index
+    // lc, value raw) when it is among them
+    auto taps = [&](auto qc, const T* src, int sd, int lc, T raw, T* r) {
+        constexpr int Q = decltype(qc)::value;
+        T a[Q + 2 * RC];
+#pragma unroll
+        for (int i = 0; i < Q + 2 * RC; i++) a[i] = src[i * sd];
+#pragma unroll
+        for (int q = 0; q < Q; q++) {
+            T t = c[0] * a[q + RC];
+#pragma unroll
+            for (int m = 1; m <= RC; m++) t += c[m] * (a[q + RC - m] + a[q + RC + m]);
+            r[q] = q == lc ? raw : t;
+        }
+    };
+    const int lc = copy ? h + 1 - o[comp] : -1 - FB;
+    const int ny = comp == 1 ? N1 : N, nz = comp == 2 ? N1 : N;      // rows and planes still needed
+    // x: rows (j, k), 4 outputs an item
+    for (int it = threadIdx.x; it < 2 * ny * nz; it += FB_NT) {
+        const int rw = it >> 1, b = (it & 1) * 4, j = rw % ny, k = rw / ny;
+        const T* src = sA + (k * N1 + j) * PA;
+        T r[4];
+        taps(std::integral_constant<int, 4>{}, src + b, 1, comp == 0 ? lc - b : -1, src[N], r);
+#pragma unroll
+        for (int q = 0; q < 4; q++) sB[(k * N1 + j) * FB + b + q] = r[q];
+    }
+    __syncthreads();
+    // y: columns (i, k), 4 outputs an item, into sA
+    for (int it = threadIdx.x; it < 2 * FB * nz; it += FB_NT) {
+        const int i = it % FB, b = it / FB % 2 * 4, k = it / (2 * FB);
+        const T* src = sB + k * N1 * FB + i;
+        T r[4];
+        taps(std::integral_constant<int, 4>{}, src + b * FB, FB, comp == 1 ? lc - b : -1, src[N * FB], r);
+#pragma unroll
+        for (int q = 0; q < 4; q++) sA[(k * FB + b + q) * FB + i] = r[q];
+    }
+    __syncthreads();
+    // z: columns (i, j), 2 outputs an item
+    {
+        const int i = threadIdx.x % FB, j = threadIdx.x / FB % FB, b = threadIdx.x / (FB * FB) * 2;
+        const T* src = sA + j * FB + i;
+        T r[2];
+        taps(std::integral_constant<int, 2>{}, src + b * FB * FB, FB * FB, comp == 2 ? lc - b : -1, src[N * FB * FB], r);
+        if (o[0] + i < g.S[0] && o[1] + j < g.S[1]) {
+#pragma unroll
+            for (int q = 0; q < 2; q++)
+                if (o[2] + b + q < g.S[2]) out[o3(g, o[0] + i, o[1] + j, o[2] + b + q)] = r[q];
+        }
+    }
+}
+static_assert(FB_NT == FB * FB * FB / 2, "one thread per two outputs");
+
 // ---- particles --------------------------------------------------------------------------------
 
 // cubic B-spline weights of nodes j0-1 .. j0+2 for a particle at fraction f of cell j0
@@ -2325,6 +2444,17 @@ bool filt3(const G3& g, const F3<R>& f, const FiltStencil& st, hipStream_t s)
 {
     for (int a = 0; a < 3; a++)
         if (!g.per[a] && g.S[a] < 2 * RC + 3) return false;
+    Lines3<double, R> L{};
+    for (int c = 0; c < 3; c++) {
+        L.in[c] = f.J[c];
+        L.out[c] = f.Jf[c];
+    }
+    const int nb[3] = {(g.S[0] + FB - 1) / FB, (g.S[1] + FB - 1) / FB, (g.S[2] + FB - 1) / FB};
+    if (3l * nb[0] * nb[1] * nb[2] <= fb_max<R>()) {
+        hipLaunchKernelGGL((k3_filt_box<RC, R>), dim3(3u * nb[0] * nb[1] * nb[2]), dim3(FB_NT), 0, s, g, L, st, nb[0], nb[1],
+                           nb[2]);
+        return true;
+    }
     static int slots = 0;          // workgroups resident on the device at once
     if (!slots) {
         int dev = 0, cus = 0, occ = 0;
@@ -2356,11 +2486,6 @@ bool filt3(const G3& g, const F3<R>& f, const FiltStencil& st, hipStream_t s)
     const int nzs = (S2 + seg - 1) / seg;
     const long nwork = base * nzs;
     const long blocks = (nwork + 7) / 8 * 8;
-    Lines3<double, R> L{};
-    for (int c = 0; c < 3; c++) {
-        L.in[c] = f.J[c];
-        L.out[c] = f.Jf[c];
-    }
     hipLaunchKernelGGL((k3_filt3<RC, R, R>), dim3((unsigned)blocks), dim3(FT_NT), 0, s, g, L, st, seg, nzs,
                        (int)nwork, nxt, nyt);
     return true;

@@ -114,28 +114,14 @@ __device__ __forceinline__ void block_bbox(int& x0, int& x1, int& z0, int& z1, i
     x0 = r.x; x1 = r.y; z0 = r.z; z1 = r.w;
 }
 
-// A device work queue over the items of several runs: run r owns items [off[r], off[r+1]);
-// workgroups take items in increasing order, from an atomic counter (zero before the launch) or
-// in a static grid-stride share.
+// The work items of several runs in one launch: run r owns items [off[r], off[r+1]).
 struct QueueRef {
     const int* off;
     int nrun, total;
-    int* counter;
 };
 
-// the workgroup's next item, or -1 once the queue is drained (every thread gets the same value)
-__device__ __forceinline__ int next_item(const QueueRef& q, int* slot)
-{
-    __syncthreads();   // the previous item is done with the LDS and with *slot
-    if (threadIdx.x == 0) *slot = atomicAdd(q.counter, 1);
-    __syncthreads();
-    const int it = __builtin_amdgcn_readfirstlane(*slot);
-    return it < q.total ? it : -1;
-}
-
 // the workgroup's k-th item of a static grid-stride share of the queue (blockIdx.x + k gridDim.x),
-// or -1 past the end; for phases whose items cost about the same, it spares the counter's atomic
-// round trip per item
+// or -1 past the end; for phases whose items cost about the same
 __device__ __forceinline__ int stride_item(const QueueRef& q, int k)
 {
     __syncthreads();   // the previous item is done with the LDS
@@ -148,6 +134,18 @@ __device__ __forceinline__ int run_of(const QueueRef& q, int it, int r)
 {
     while (r + 1 < q.nrun && q.off[r + 1] <= it) r++;
     return __builtin_amdgcn_readfirstlane(r);
+}
+
+// run owning item `it`, by bisection
+__device__ __forceinline__ int run_of(const QueueRef& q, int it)
+{
+    int lo = 0, hi = q.nrun;
+    while (hi - lo > 1) {
+        const int m = (lo + hi) / 2;
+        if (q.off[m] <= it) lo = m;
+        else hi = m;
+    }
+    return __builtin_amdgcn_readfirstlane(lo);
 }
 
 }  // namespace bf

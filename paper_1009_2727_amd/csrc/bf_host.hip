@@ -771,15 +771,11 @@ bf_status step_impl(bf_sim* s, int nsteps)
         }
         if constexpr (sizeof(R) == 4) {
             if (rb) {
-                if (ep.nseg > 0) {
-                    rb->gpd.push_back(GpdDesc<float>{g, f, ep});
-                    rb->n_gpd.push_back(ep.nseg);
+                const int n = particle_blocks(ep, sp);
+                if (n > 0) {
+                    rb->particles.push_back(ParticleDesc<float>{g, f, ep, sp});
+                    rb->n_particles.push_back(n);
                 }
-                // batched runs launch their sources one run at a time too: the hardware's dispatch
-                // of one workgroup per segment balances the uneven ion segments better than a
-                // persistent launch over all runs
-                s->slot = SLOT_IONS;
-                s->run([=](hipStream_t st) { launch_sources<R>(g, f, sp, st); });
             }
         }
         if (!rb) {
@@ -2042,14 +2038,13 @@ constexpr int BATCH_LANES = 4;  // streams the runs' own launches are spread ove
 
 size_t al256(size_t v) { return (v + 255) / 256 * 256; }
 
-// bytes of one descriptor table for n runs: counters, then per batched phase its
-// descriptors and its item offsets
+// bytes of one descriptor table for n runs: per batched phase its descriptors and its item offsets
 size_t batch_table_bytes(int n)
 {
     const size_t m = (size_t)n;
-    return 256 + al256(m * sizeof(FaradayDesc<float>)) + al256((m + 1) * 4) +
+    return al256(m * sizeof(FaradayDesc<float>)) + al256((m + 1) * 4) +
            al256(m * sizeof(AmpereDesc<float>)) + al256((m + 1) * 4) +
-           al256(m * sizeof(GpdDesc<float>)) + al256((m + 1) * 4);
+           al256(m * sizeof(ParticleDesc<float>)) + al256((m + 1) * 4);
 }
 
 }  // namespace
@@ -2086,11 +2081,11 @@ struct bf_batch {
 
 namespace {
 
-// copies one phase's descriptors and item offsets into the staging table; returns the queue
+// copies one phase's descriptors and item offsets into the staging table; returns the items
 // as seen from the device
 template <typename D>
 QueueRef stage_phase(unsigned char* H, unsigned char* Dv, size_t& o, const std::vector<D>& descs,
-                     const std::vector<int>& items, int* counter_dev, const D** dev_descs)
+                     const std::vector<int>& items, const D** dev_descs)
 {
     const size_t n = descs.size();
     std::memcpy(H + o, descs.data(), n * sizeof(D));
@@ -2100,7 +2095,7 @@ QueueRef stage_phase(unsigned char* H, unsigned char* Dv, size_t& o, const std::
     int total = 0;
     for (size_t r = 0; r < n; r++) { off[r] = total; total += items[r]; }
     off[n] = total;
-    QueueRef q{reinterpret_cast<const int*>(Dv + o), (int)n, total, counter_dev};
+    QueueRef q{reinterpret_cast<const int*>(Dv + o), (int)n, total};
     o = al256(o + (n + 1) * 4);
     return q;
 }
@@ -2122,15 +2117,13 @@ bf_status batch_one_step(bf_batch* b)
     if (b->used[r] && hipEventSynchronize(b->ev[r]) != hipSuccess) return BF_EDEVICE;
     unsigned char* H = b->host[r];
     unsigned char* Dv = b->dev + (size_t)r * b->table;
-    std::memset(H, 0, 256);
-    int* cnt = reinterpret_cast<int*>(Dv);
-    size_t o = 256;
+    size_t o = 0;
     const FaradayDesc<float>* dfar;
     const AmpereDesc<float>* damp;
-    const GpdDesc<float>* dgpd;
-    const QueueRef qf = stage_phase(H, Dv, o, rec.faraday, rec.n_faraday, cnt + 0, &dfar);
-    const QueueRef qa = stage_phase(H, Dv, o, rec.ampere, rec.n_ampere, cnt + 1, &damp);
-    const QueueRef qg = stage_phase(H, Dv, o, rec.gpd, rec.n_gpd, cnt + 2, &dgpd);
+    const ParticleDesc<float>* dpart;
+    const QueueRef qf = stage_phase(H, Dv, o, rec.faraday, rec.n_faraday, &dfar);
+    const QueueRef qa = stage_phase(H, Dv, o, rec.ampere, rec.n_ampere, &damp);
+    const QueueRef qp = stage_phase(H, Dv, o, rec.particles, rec.n_particles, &dpart);
     hipStream_t st = b->stream;
     if (hipMemcpyAsync(Dv, H, o, hipMemcpyHostToDevice, st) != hipSuccess) return BF_EDEVICE;
     auto grid = [&](const QueueRef& q, int per_cu) { return std::max(1, std::min(q.total, per_cu * b->cus)); };
@@ -2156,8 +2149,8 @@ bf_status batch_one_step(bf_batch* b)
     };
     launch_faraday_batch<float>(dfar, qf, grid(qf, 8), st);
     closures({SLOT_FARADAY, SLOT_STATIONS});
-    launch_gpd_batch<float>(dgpd, qg, grid(qg, 3), st);
-    closures({SLOT_PUSH, SLOT_IONS, SLOT_ANTENNA, SLOT_FILTER});
+    launch_particles_batch<float>(dpart, qp, st);
+    closures({SLOT_PUSH, SLOT_FILTER});
     launch_ampere_batch<float>(damp, qa, grid(qa, 8), st);
     closures({SLOT_AMPERE, SLOT_WINDOW, SLOT_SORT});
     if (!ok) return BF_EDEVICE;

@@ -176,10 +176,11 @@ struct AmpereDesc {
     int gx;
 };
 template <typename R>
-struct GpdDesc {
+struct ParticleDesc {
     Geo g;
     FieldSet<R> f;
     ElectronParams<R> e;
+    SourceParams<R> s;
 };
 
 template <typename R>
@@ -187,7 +188,10 @@ void launch_faraday_batch(const FaradayDesc<R>* d, const QueueRef& q, int nblock
 template <typename R>
 void launch_ampere_batch(const AmpereDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s);
 template <typename R>
-void launch_gpd_batch(const GpdDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s);
+void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, hipStream_t s);
+// workgroups of a run's electrons and sources; sets sp.na
+template <typename R>
+int particle_blocks(const ElectronParams<R>& ep, SourceParams<R>& sp);
 
 // ---- launchers (stream-ordered) -------------------------------------------------------
 // Faraday; clears the raw current for the step's deposit

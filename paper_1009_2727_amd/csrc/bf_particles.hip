@@ -11,7 +11,7 @@
 //    lanes each.
 //  * k_sources: the rigid ions (at rest in the lab) deposit their J_z from z0 - beta c t, and the
 //    laser antenna's +/- sheet particles (Sec. 3.1.2), in FP64 per pair.  k_particles is both
-//    kernels in one launch; they run apart in batched steps and with phase timers.
+//    kernels in one launch (k_particles_batch for several runs); they run apart with phase timers.
 //  * k_advance: the moving window's new rows, and the plasma lattice rows that entered at the
 //    front plane (Sec. 3.1.1).
 //  * k_sort_*: counting sort by tile (histogram, scan, scatter) that also drops absorbed
@@ -682,21 +682,6 @@ __global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
     gpd_segment<R, MC, gpd_threads<R>()>(g, f, ep, blockIdx.x);
 }
 
-template <typename R>
-__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1) k_gpd_batch(const GpdDesc<R>* __restrict__ d,
-                                                                                        QueueRef q)
-{
-    __shared__ int slot;
-    int r = 0;
-    for (;;) {
-        const int it = next_item(q, &slot);
-        if (it < 0) return;
-        r = run_of(q, it, r);
-        const GpdDesc<R>& D = d[r];
-        gpd_segment<R, false, gpd_threads<R>()>(D.g, D.f, D.e, it - q.off[r]);
-    }
-}
-
 // ---- rigid ions --------------------------------------------------------------------------
 // J_z of a particle at fixed x moving (iz+fz) -> (iz1+fz1): the Esirkepov form with DS_x = 0,
 // J_z(m,b) = cz S_x(m) sum_{k<=b} DS_z(k) on the 4 x 5 window with lower corner
@@ -918,6 +903,20 @@ __global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
     const int b = blockIdx.x;
     if (b < ep.nseg) gpd_segment<R, MC, gpd_threads<R>()>(g, f, ep, b);
     else source_block<R, gpd_threads<R>()>(g, f, sp, b - ep.nseg);
+}
+
+// the same for several runs.  One workgroup per segment, as in a run's own launch: the hardware deals
+// them out, and the ions of one run fill the tail of its electrons.  16 runs of about 150 x 1600 cells at 10
+// particles a cell: 1.79 ms a step; electrons by a persistent launch over a queue and each run's
+// sources in a launch of its own took 1.84 ms.
+template <typename R>
+__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
+    k_particles_batch(const ParticleDesc<R>* __restrict__ d, QueueRef q)
+{
+    const int r = run_of(q, blockIdx.x), b = (int)blockIdx.x - q.off[r];
+    const ParticleDesc<R>& D = d[r];
+    if (b < D.e.nseg) gpd_segment<R, false, gpd_threads<R>()>(D.g, D.f, D.e, b);
+    else source_block<R, gpd_threads<R>()>(D.g, D.f, D.s, b - D.e.nseg);
 }
 
 // ---- particle beam through a lab-fixed plane (Sec. 3.1.1) ---------------------------------
@@ -1512,12 +1511,18 @@ void launch_sources(const Geo& g, const FieldSet<R>& f, SourceParams<R> sp, hipS
                            (size_t)tcells<R>() * sizeof(typename LdsAcc<R>::JT), s, g, f, sp);
 }
 
+template <typename R>
+int particle_blocks(const ElectronParams<R>& ep, SourceParams<R>& sp)
+{
+    sp.na = antenna_blocks(sp, gpd_threads<R>());
+    return ep.nseg + sp.nion + sp.na;
+}
+
 template <typename R, bool MC>
 static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, SourceParams<R> sp, hipStream_t s)
 {
     constexpr int threads = gpd_threads<R>();
-    sp.na = antenna_blocks(sp, threads);
-    const int n = ep.nseg + sp.nion + sp.na;
+    const int n = particle_blocks(ep, sp);
     // One launch: the ions and the antenna fill the electrons' tail, and a launch is spared.  20
     // steps against two launches: 75 x 1691 cells at 1 particle a cell 0.96 -> 0.83 ms, 64 x 512 in
     // FP64 1.17 -> 0.83 ms, 187 x 1531 at 5 3.31 -> 3.08 ms, 256 x 4096 at 16 13.2 -> 13.0 ms.
@@ -1538,10 +1543,10 @@ void launch_particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R
 }
 
 template <typename R>
-void launch_gpd_batch(const GpdDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s)
+void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, hipStream_t s)
 {
     if (q.total > 0)
-        hipLaunchKernelGGL((k_gpd_batch<R>), dim3(nblocks), dim3(gpd_threads<R>()), gpd_lds<R>(), s, d, q);
+        hipLaunchKernelGGL((k_particles_batch<R>), dim3(q.total), dim3(gpd_threads<R>()), gpd_lds<R>(), s, d, q);
 }
 
 template <typename R>
@@ -1612,7 +1617,8 @@ void launch_sort_ions(const Geo& g, int tile_x, int tile_z, int ntx, int ntiles,
     template void launch_particles<R>(const Geo&, const FieldSet<R>&, const ElectronParams<R>&,       \
                                       const SourceParams<R>&, bool, hipStream_t);                     \
     template void launch_sources<R>(const Geo&, const FieldSet<R>&, SourceParams<R>, hipStream_t);    \
-    template void launch_gpd_batch<R>(const GpdDesc<R>*, const QueueRef&, int, hipStream_t);          \
+    template int particle_blocks<R>(const ElectronParams<R>&, SourceParams<R>&);                      \
+    template void launch_particles_batch<R>(const ParticleDesc<R>*, const QueueRef&, hipStream_t);    \
     template void launch_beam<R>(const Geo&, const FieldSet<R>&, const BeamArrays&, const BeamParams&, \
                                  const PushParams<double>&, int*, bool, hipStream_t);                 \
     template void launch_advance<R>(const Geo&, const WindowParams<R>*, const ElectronArrays<R>&,     \

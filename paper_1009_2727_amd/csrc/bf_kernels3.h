@@ -127,6 +127,7 @@ struct FiltSeq {
     int n, reach;
     double alpha[FSEQ_MAX];
     int stride[FSEQ_MAX];
+    double c[FREACH_MAX + 1];      // all passes as one symmetric stencil: weights m cells to either side
 };
 // builds the sequence; false when it exceeds FSEQ_MAX passes or FREACH_MAX cells of reach
 bool filter_seq(int npass, int comp, int stride_mask, FiltSeq* fs);

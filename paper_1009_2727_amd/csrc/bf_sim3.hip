@@ -358,7 +358,20 @@ __global__ void __launch_bounds__(NT) k3_ampere(G3 g, F3<R> f, const R* J0, cons
 // the component's stored range held at 0 after every pass (zero padding; periodic axes wrap).
 // Positions beyond the segment's halo read 0; the error that causes moves inwards by at most
 // one stride per pass, so the tseg central cells are exact.  Cells beyond the component's range
-// (its last half node on a non-periodic axis) are copied.
+// (its last half node on a non-periodic axis) are copied.  A segment with all it reads inside the
+// range needs no zeros held: there the passes are one stencil, four outputs a thread in a sliding
+// window (two LDS reads and eight FMAs or adds a tap for the four, no barriers) where a pass costs four LDS
+// accesses and a barrier for each.  Segments at the ends of a non-periodic axis keep the passes and
+// are as short as the reach allows.  Along x, where four consecutive outputs a thread cost bank
+// conflicts, the stencil is taken up to four cells of reach a pass.  Passes / stencil on 187 x 1531
+// cells, x + z: 4 passes and compensation of strides 1 and 2 in FP32 (10 passes, reach 15) 17 + 37 ->
+// 8 + 15 us; stride 4 in FP64 (5, 20) 14 + 20 -> 13 + 13 us; 1 pass and compensation of stride 5 in
+// FP64 (2, 10) 8.7 + 11.9 -> 13.1 + 10.0 us (so x keeps its passes there), of stride 16 (2, 32)
+// 9.6 + 15.7 -> 15.6 + 13.7 us.
+template <int AX> __host__ __device__ constexpr bool composed(const FiltSeq& fs)
+{
+    return fs.n > 0 && (AX != 0 || fs.reach <= 4 * fs.n);
+}
 template <typename TI, typename TO>
 struct Lines3 {
     const TI* in[3];
@@ -369,16 +382,12 @@ struct Lines3 {
 template <int AX> constexpr int fline_bc() { return AX == 0 ? 8 : 32; }
 
 template <int AX, typename TI, typename TO, typename T>
-__global__ void __launch_bounds__(NT) k3_fline(G3 g, Lines3<TI, TO> L, FiltSeq fs, int tseg, int nseg, int ncolb)
+__global__ void __launch_bounds__(NT) k3_fline(G3 g, Lines3<TI, TO> L, FiltSeq fs, int edge, int tcap, int nseg, int ncolb)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     constexpr int BC = fline_bc<AX>();
     constexpr int TPC = NT / BC;                  // threads per line (x) or per column (y, z)
     const int R = fs.reach;
-    const int A = tseg + 2 * R;
-    const int ld = AX == 0 ? A + 1 : BC + 1;
-    T* src = reinterpret_cast<T*>(smem_raw);
-    T* dst = src + (AX == 0 ? BC * ld : A * ld);
     // block -> (component, segment, column block, plane or row across)
     int bid = (int)blockIdx.x;
     const int nother = AX == 0 ? 1 : g.S[AX == 1 ? 2 : 1];
@@ -393,7 +402,14 @@ __global__ void __launch_bounds__(NT) k3_fline(G3 g, Lines3<TI, TO> L, FiltSeq f
     TO* __restrict__ out = L.out[c];
     const int S = g.S[AX], per = g.per[AX];
     const int hi = per ? S - 1 : S - 1 - L.h[c];
-    const int seg0 = seg * tseg;
+    // segments of tcap cells, between two of edge cells at the ends of the axis when edge is not 0
+    const int seg0 = !edge ? seg * tcap : seg == 0 ? 0 : seg == nseg - 1 ? S - edge : edge + (seg - 1) * tcap;
+    const int tseg = !edge ? min(tcap, S - seg0)
+                           : seg == 0 || seg == nseg - 1 ? edge : min(tcap, S - edge - seg0);
+    const int A = tseg + 2 * R;
+    const int ld = AX == 0 ? A + 1 : BC + 1;
+    T* src = reinterpret_cast<T*>(smem_raw);
+    T* dst = src + (AX == 0 ? BC * ld : A * ld);
     // this thread's line / column and first row; the HBM offset of position jj along AX is
     // base + jj * step, with the z ring applied to whichever index runs along z
     const int col = AX == 0 ? (int)threadIdx.x / TPC : (int)threadIdx.x % BC;
@@ -430,7 +446,46 @@ __global__ void __launch_bounds__(NT) k3_fline(G3 g, Lines3<TI, TO> L, FiltSeq f
         src[idx(a)] = v;
     }
     __syncthreads();
-    for (int p = 0; p < fs.n; p++) {
+    const bool one = composed<AX>(fs) && (per || (seg0 >= R && seg0 + tseg - 1 + R <= hi));
+    if (one) {
+        // x: consecutive threads on the BC lines
+        const int col1 = AX == 0 ? (int)threadIdx.x % BC : col, a1 = AX == 0 ? (int)threadIdx.x / BC : a0;
+        for (int a = 4 * a1; a < tseg; a += 4 * TPC) {
+            const T* x = src + (AX == 0 ? col1 * ld + a + R : (a + R) * ld + col1);
+            constexpr int one_ld = AX == 0 ? 1 : BC + 1;
+            // outermost taps first: the small terms are summed before the large ones
+            T l[4], r[4], s[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                l[q] = q > 0 ? x[(q - R - 1) * one_ld] : T(0);       // as of m = R + 1
+                r[q] = q < 3 ? x[(q + R + 1) * one_ld] : T(0);
+                s[q] = T(0);
+            }
+#pragma unroll 4
+            for (int m = R; m > 0; m--) {
+                const T cm = (T)fs.c[m];
+#pragma unroll
+                for (int q = 0; q < 3; q++) l[q] = l[q + 1];
+#pragma unroll
+                for (int q = 3; q > 0; q--) r[q] = r[q - 1];
+                l[3] = x[(3 - m) * one_ld];
+                r[0] = x[m * one_ld];
+#pragma unroll
+                for (int q = 0; q < 4; q++) s[q] += cm * (l[q] + r[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; q++) s[q] += (T)fs.c[0] * x[q * one_ld];
+            T* d = dst + (x - src);
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                if (a + q < tseg) d[q * one_ld] = s[q];
+        }
+        __syncthreads();
+        T* t = src;
+        src = dst;
+        dst = t;
+    }
+    for (int p = one ? fs.n : 0; p < fs.n; p++) {
         const T al = (T)fs.alpha[p], be = (T(1) - al) * T(0.5);
         const int st = fs.stride[p];
         for (int a = a0; a < A; a += TPC) {
@@ -448,7 +503,6 @@ __global__ void __launch_bounds__(NT) k3_fline(G3 g, Lines3<TI, TO> L, FiltSeq f
     if (!ok) return;
     for (int a = a0; a < tseg; a += TPC) {
         const int j = seg0 + a;
-        if (j >= S) break;
         const long o = at(j);
         out[o] = (per || j <= hi) ? (TO)src[idx(a + R)] : (TO)in[o];
     }
@@ -2382,6 +2436,19 @@ bool filter_seq(int npass, int comp, int stride_mask, FiltSeq* fs)
             fs->reach += st;
         }
     }
+    const int R = fs->reach, L = 2 * R + 1;
+    double a[2 * FREACH_MAX + 1] = {}, b[2 * FREACH_MAX + 1];
+    a[R] = 1.0;
+    int r = 0;                     // reach of the passes so far
+    for (int p = 0; p < fs->n; p++) {
+        const double al = fs->alpha[p], be = 0.5 * (1.0 - al);
+        const int st = fs->stride[p];
+        r += st;
+        for (int j = R - r; j <= R + r; j++)
+            b[j] = al * a[j] + be * ((j >= st ? a[j - st] : 0.0) + (j + st < L ? a[j + st] : 0.0));
+        for (int j = R - r; j <= R + r; j++) a[j] = b[j];
+    }
+    for (int m = 0; m <= R; m++) fs->c[m] = a[R + m];
     return true;
 }
 
@@ -2396,27 +2463,32 @@ void fline(const G3& g, const Lines3<TI, TO>& L, int ncomp, const FiltSeq& fs, h
         const int A = t + 2 * fs.reach;
         return 2 * (size_t)(AX == 0 ? BC * (A + 1) : A * (BC + 1)) * sizeof(T);
     };
+    // where the passes are one stencil away from the ends, the ends get segments of their own, no
+    // longer than the reach makes necessary
+    int edge = composed<AX>(fs) && !g.per[AX] ? fs.reach + 1 : 0;
+    if (S < 2 * edge + 16) edge = 0;
+    const int M = S - 2 * edge;
     // segments along AX: the whole line when its halo-padded copy fits a third of the LDS (three
     // workgroups per CU), else equal segments of at most 128 (FP32) or 64 (FP64) cells, so that
     // no segment is mostly halo
     int tseg;
-    if (AX == 0) tseg = S + 2 * fs.reach <= 1024 ? S : 512;
-    else if (lds_of(S) <= 48 * 1024) tseg = S;
+    if (AX == 0) tseg = M + 2 * fs.reach <= 1024 ? M : 512;
+    else if (lds_of(M) <= 48 * 1024) tseg = M;
     else {
         const int cap = sizeof(T) == 4 ? 128 : 64;
-        const int n = (S + cap - 1) / cap;
-        tseg = (S + n - 1) / n;
+        const int n = (M + cap - 1) / cap;
+        tseg = (M + n - 1) / n;
     }
     while (tseg > 16 && lds_of(tseg) > LDS_MAX) tseg /= 2;       // long reaches: shorter segments
-    const size_t lds = lds_of(tseg);
-    const int nseg = (S + tseg - 1) / tseg;
+    const size_t lds = std::max(lds_of(tseg), lds_of(edge));
+    const int nseg = (M + tseg - 1) / tseg + (edge ? 2 : 0);
     const int ncolb = AX == 0 ? (g.S[1] * g.S[2] + BC - 1) / BC : (g.S[0] + BC - 1) / BC;
     const int nother = AX == 0 ? 1 : g.S[AX == 1 ? 2 : 1];
     const long blocks = (long)ncomp * nseg * ncolb * nother;
     (void)hipFuncSetAttribute((const void*)k3_fline<AX, TI, TO, T>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds);
-    hipLaunchKernelGGL((k3_fline<AX, TI, TO, T>), dim3((unsigned)blocks), dim3(NT), lds, s, g, L, fs, tseg, nseg,
-                       ncolb);
+    hipLaunchKernelGGL((k3_fline<AX, TI, TO, T>), dim3((unsigned)blocks), dim3(NT), lds, s, g, L, fs, edge, tseg,
+                       nseg, ncolb);
 }
 
 bool unit_stencil(const FiltSeq& fs, FiltStencil& st)
@@ -2425,15 +2497,7 @@ bool unit_stencil(const FiltSeq& fs, FiltStencil& st)
     if (fs.n < 1 || R < 1 || R > FT_RMAX) return false;
     for (int p = 0; p < fs.n; p++)
         if (fs.stride[p] != 1) return false;
-    double a[2 * FT_RMAX + 1] = {}, b[2 * FT_RMAX + 1];
-    const int L = 2 * R + 1;
-    a[R] = 1.0;
-    for (int p = 0; p < fs.n; p++) {
-        const double al = fs.alpha[p], be = 0.5 * (1.0 - al);
-        for (int j = 0; j < L; j++) b[j] = al * a[j] + be * ((j > 0 ? a[j - 1] : 0.0) + (j + 1 < L ? a[j + 1] : 0.0));
-        for (int j = 0; j < L; j++) a[j] = b[j];
-    }
-    for (int m = 0; m <= FT_RMAX; m++) st.c[m] = m <= R ? a[R + m] : 0.0;
+    for (int m = 0; m <= FT_RMAX; m++) st.c[m] = m <= R ? fs.c[m] : 0.0;
     return true;
 }
 

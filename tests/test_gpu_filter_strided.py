@@ -1,0 +1,65 @@
+"""Strided current filters against the FP64 oracle where the line filter changes its form.
+
+Away from the ends of an axis the passes are applied as one stencil, at the ends of a non-periodic
+axis pass by pass, and short axes are not split.  One step from random fields and random electrons,
+then E, B and the filtered current are compared cell by cell: several segments along z, with PML and
+periodic; a z axis one cell below and at the length from which it is split; the largest stride, where
+only z takes the stencil; and the same along the three axes of a 3D box.  Tolerances as in the other
+filter tests (FP64 1e-11, FP32 2e-6 of the field scale).
+"""
+import numpy as np
+import pytest
+
+import pic_inputs as pi
+from oracle import Oracle
+from oracle.pic3 import Oracle3
+
+gpu = pytest.mark.gpu
+SEEDED = ["Ex", "Ey", "Ez", "Bx", "By", "Bz", "Exo", "Eyo", "Ezo", "Exb", "Eyb", "Ezb"]
+NAMES = SEEDED[:6] + ["Jx", "Jy", "Jz"]
+
+
+def _step_and_compare(cfg, ref, p, real):
+    from paper_1009_2727_amd import Sim
+    sim = Sim(cfg, capacity=4000)
+    for k, name in enumerate(SEEDED):
+        f = pi.random_field(ref.shape, seed=700 + k, amp=0.4)
+        ref.set_field(name, f)
+        sim.set_field(name, f)
+    ref.set_electrons(p)
+    sim.load_electrons(p)
+    ref.step(1)
+    sim.step(1)
+    assert sim.sync_status() == 0
+    tol = 1e-11 if real == "f64" else 2e-6
+    for n in NAMES:
+        a, b = sim.field(n), ref.field(n)
+        assert np.abs(a - b).max() <= tol * max(np.abs(b).max(), 1.0), (n, float(np.abs(a - b).max()))
+
+
+@gpu
+@pytest.mark.parametrize("real", ["f64", "f32"])
+@pytest.mark.parametrize("npass,comp,mask", [(4, 1, 0b11), (2, 1, 0b1000), (1, 1, 0b10000), (1, 0, 1 << 15)])
+@pytest.mark.parametrize("geom", ["pml", "periodic", "below", "at"])
+def test_2d_strided_filter_matches_oracle(geom, npass, comp, mask, real):
+    pml = 0 if geom == "periodic" else 4
+    per = int(geom == "periodic")
+    reach = (npass + comp) * sum(k + 1 for k in range(16) if mask >> k & 1)
+    nz = {"pml": 411, "periodic": 333}.get(geom, 2 * (reach + 1) + 16 - (2 * pml + 1) - (geom == "below"))
+    nx = 45
+    cfg = pi.make_config(nx, nz, 0.1, 0.09, pml_cells=pml, periodic_x=per, periodic_z=per, ck="ck2", theta=0.2,
+                         filter_npass=npass, filter_compensate=comp, real=real, seed=21, filter_strides=mask)
+    _step_and_compare(cfg, Oracle(cfg), pi.random_electrons(3000, nx, nz, 0.1, 0.09, seed=23, umax=3.0,
+                                                            margin=0.0 if per else 1.5), real)
+
+
+@gpu
+@pytest.mark.parametrize("real", ["f64", "f32"])
+@pytest.mark.parametrize("per", [0, 1])
+def test_3d_strided_filter_matches_oracle(per, real):
+    n, d = (41, 60, 83), (0.1, 0.12, 0.09)
+    cfg = pi.make_config3(*n, *d, pml_cells=0 if per else 4, periodic_x=per, periodic_y=per, periodic_z=per,
+                          ck="ck2", theta=0.2, filter_npass=2, filter_compensate=1, real=real, seed=21,
+                          filter_strides=0b11)
+    _step_and_compare(cfg, Oracle3(cfg), pi.random_electrons3(3000, *n, d, seed=23, umax=3.0,
+                                                              margin=0.0 if per else 1.5), real)

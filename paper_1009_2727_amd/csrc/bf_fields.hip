@@ -270,9 +270,10 @@ __global__ void __launch_bounds__(256) k_filter_ampere(Geo g, FieldSet<R> f, Pml
 #pragma unroll
         for (int m = 0; m < 3; m++) {
             const R* r = sA[m] + b * AX + a + RC;
-            R v = c[0] * r[0];
+            R v = R(0);          // outermost taps first: the small terms before the large ones
 #pragma unroll
-            for (int t = 1; t <= RC; t++) v += c[t] * (r[-t] + r[t]);
+            for (int t = RC; t >= 1; t--) v += c[t] * (r[-t] + r[t]);
+            v += c[0] * r[0];
             if (m == 0 && x0 + a == hx[0] + 1) {   // the copied half node of J_x
                 v = x0 + a < g.Sx ? rs[1][b] * f.J[0][ri[1][b] + x0 + a] : R(0);
             }
@@ -289,9 +290,10 @@ __global__ void __launch_bounds__(256) k_filter_ampere(Geo g, FieldSet<R> f, Pml
 #pragma unroll
         for (int m = 0; m < 3; m++) {
             const R* r = sB[m] + (b + RC) * TX + tx;
-            R v = c[0] * r[0];
+            R v = R(0);
 #pragma unroll
-            for (int t = 1; t <= RC; t++) v += c[t] * (r[-t * TX] + r[t * TX]);
+            for (int t = RC; t >= 1; t--) v += c[t] * (r[-t * TX] + r[t * TX]);
+            v += c[0] * r[0];
             j[m] = v;
         }
         if (k == hz[2] + 1) {                      // the copied half node of J_z

@@ -909,9 +909,10 @@ __global__ void __launch_bounds__(FB_NT) k3_filt_box(G3 g, Lines3<double, T> L, 
         for (int i = 0; i < Q + 2 * RC; i++) a[i] = src[i * sd];
 #pragma unroll
         for (int q = 0; q < Q; q++) {
-            T t = c[0] * a[q + RC];
+            T t = T(0);         // outermost taps first: the small terms before the large ones
 #pragma unroll
-            for (int m = 1; m <= RC; m++) t += c[m] * (a[q + RC - m] + a[q + RC + m]);
+            for (int m = RC; m > 0; m--) t += c[m] * (a[q + RC - m] + a[q + RC + m]);
+            t += c[0] * a[q + RC];
             r[q] = q == lc ? raw : t;
         }
     };

@@ -315,12 +315,11 @@ void bf_destroy(bf_sim* sim);
 
 /* ---- batched independent runs -----------------------------------------------------------
    Several handles stepped together, e.g. a scan over boost factor, density, grid and time step
-   (each run follows Sec. 2-4 on its own).  Faraday, the electron push and Ampere are each one
-   persistent launch over a device queue of (run, work item) pairs; the other phases (stations,
-   rigid ions, antenna, current filter, window shift, injection, sort) are each run's own
-   launches, in phase order, spread over the batch stream and three side streams the batch
-   owns (run r on stream r % 4, joined back before each persistent launch).  Results equal each
-   run's
+   (each run follows Sec. 2-4 on its own).  Faraday, the particles (electrons, rigid ions and
+   antenna) and Ampere are each one launch over the work items of all runs; the other phases
+   (stations, current filter, window shift, injection, sort) are each run's own launches, in
+   phase order, spread over the batch stream and three side streams the batch owns (run r on
+   stream r % 4, joined back before each common launch).  Results equal each run's
    bf_step up to the order of floating-point atomic additions.  Runs must be FP32 handles on
    the current device without a sticky error; phase timers are not recorded in batched steps. */
 typedef struct bf_batch bf_batch;

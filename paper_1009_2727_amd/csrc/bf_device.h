@@ -120,7 +120,7 @@ struct QueueRef {
     int nrun, total;
 };
 
-// the workgroup's k-th item of a static grid-stride share of the queue (blockIdx.x + k gridDim.x),
+// the workgroup's k-th item of a static grid-stride share of the items (blockIdx.x + k gridDim.x),
 // or -1 past the end; for phases whose items cost about the same
 __device__ __forceinline__ int stride_item(const QueueRef& q, int k)
 {

@@ -3,7 +3,7 @@
 Away from the ends of an axis the passes are applied as one stencil, at the ends of a non-periodic
 axis pass by pass, and short axes are not split.  One step from random fields and random electrons,
 then E, B and the filtered current are compared cell by cell: several segments along z, with PML and
-periodic; a z axis one cell below and at the length from which it is split; the largest stride, where
+periodic; periodic axes shorter than the stencil, which keep the passes; a z axis one cell below and at the length from which it is split; the largest stride, where
 only z takes the stencil; and the same along the three axes of a 3D box.  Tolerances as in the other
 filter tests (FP64 1e-11, FP32 2e-6 of the field scale).
 """
@@ -40,13 +40,13 @@ def _step_and_compare(cfg, ref, p, real):
 @gpu
 @pytest.mark.parametrize("real", ["f64", "f32"])
 @pytest.mark.parametrize("npass,comp,mask", [(4, 1, 0b11), (2, 1, 0b1000), (1, 1, 0b10000), (1, 0, 1 << 15)])
-@pytest.mark.parametrize("geom", ["pml", "periodic", "below", "at"])
+@pytest.mark.parametrize("geom", ["pml", "periodic", "narrow", "below", "at"])
 def test_2d_strided_filter_matches_oracle(geom, npass, comp, mask, real):
-    pml = 0 if geom == "periodic" else 4
-    per = int(geom == "periodic")
+    per = int(geom in ("periodic", "narrow"))
+    pml = 0 if per else 4
     reach = (npass + comp) * sum(k + 1 for k in range(16) if mask >> k & 1)
-    nz = {"pml": 411, "periodic": 333}.get(geom, 2 * (reach + 1) + 16 - (2 * pml + 1) - (geom == "below"))
-    nx = 45
+    nz = {"pml": 411, "periodic": 333, "narrow": 30}.get(geom, 2 * (reach + 1) + 16 - (2 * pml + 1) - (geom == "below"))
+    nx = 7 if geom == "narrow" else 45
     cfg = pi.make_config(nx, nz, 0.1, 0.09, pml_cells=pml, periodic_x=per, periodic_z=per, ck="ck2", theta=0.2,
                          filter_npass=npass, filter_compensate=comp, real=real, seed=21, filter_strides=mask)
     _step_and_compare(cfg, Oracle(cfg), pi.random_electrons(3000, nx, nz, 0.1, 0.09, seed=23, umax=3.0,

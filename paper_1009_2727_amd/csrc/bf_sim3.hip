@@ -2467,9 +2467,10 @@ void fline(const G3& g, const Lines3<TI, TO>& L, int ncomp, const FiltSeq& fs, h
         return 2 * (size_t)(AX == 0 ? BC * (A + 1) : A * (BC + 1)) * sizeof(T);
     };
     // where the passes are one stencil away from the ends, the ends get segments of their own, no
-    // longer than the reach makes necessary
+    // longer than the reach makes necessary; from a reach of 93 in FP64 along y and z such a segment
+    // with its halo would not fit the LDS, and the axis has equal segments only
     int edge = composed<AX>(fs) && !g.per[AX] ? fs.reach + 1 : 0;
-    if (S < 2 * edge + 16) edge = 0;
+    if (S < 2 * edge + 16 || lds_of(edge) > LDS_MAX) edge = 0;
     const int M = S - 2 * edge;
     // segments along AX: the whole line when its halo-padded copy fits a third of the LDS (three
     // workgroups per CU), else equal segments of at most 128 (FP32) or 64 (FP64) cells, so that

@@ -358,32 +358,41 @@ __global__ void __launch_bounds__(NT) k3_ampere(G3 g, F3<R> f, const R* J0, cons
 // the component's stored range held at 0 after every pass (zero padding; periodic axes wrap).
 // Positions beyond the segment's halo read 0; the error that causes moves inwards by at most
 // one stride per pass, so the tseg central cells are exact.  Cells beyond the component's range
-// (its last half node on a non-periodic axis) are copied.  A segment with all it reads inside the
-// range needs no zeros held: there the passes are one stencil, four outputs a thread in a sliding
-// window (two LDS reads and eight FMAs or adds a tap for the four, no barriers) where a pass costs four LDS
-// accesses and a barrier for each.  A periodic axis shorter than the stencil keeps the passes: they
-// leave its cells all but equal, and sums that begin elsewhere for every cell would round them apart
-// (error of the fields 2.5e-7 -> 2.9e-7 on 24 cells at a reach of 35).  Segments at the ends of a non-periodic axis keep the passes and
-// are as short as the reach allows.  Along x, where four consecutive outputs a thread cost bank
-// conflicts, the stencil is taken up to four cells of reach a pass.  Passes / stencil on 187 x 1531
-// cells, x + z: 4 passes and compensation of strides 1 and 2 in FP32 (10 passes, reach 15) 17 + 37 ->
-// 8 + 15 us; stride 4 in FP64 (5, 20) 14 + 20 -> 13 + 13 us; 1 pass and compensation of stride 5 in
-// FP64 (2, 10) 8.7 + 11.9 -> 13.1 + 10.0 us (so x keeps its passes there), of stride 16 (2, 32)
-// 9.6 + 15.7 -> 15.6 + 13.7 us.
-template <int AX> __host__ __device__ constexpr bool composed(const FiltSeq& fs)
-{
-    return fs.n > 0 && (AX != 0 || fs.reach <= 4 * fs.n);
-}
+// (its last half node on a non-periodic axis) are copied.  With STENCIL, a segment with all it reads
+// inside the range, which needs no zeros held, takes the passes as one stencil, four outputs a thread
+// in a sliding window (two LDS reads and eight FMAs or adds a tap for the four, no barriers) where a
+// pass costs four LDS accesses and a barrier for each.  A periodic axis shorter than the stencil
+// keeps the passes: they leave its cells all but equal, and sums that begin elsewhere for every cell
+// would round them apart (error of the fields 2.5e-7 -> 2.9e-7 on 24 cells at a reach of 35).
+// Segments at the ends of a non-periodic axis keep the passes and are as short as the reach allows;
+// their workgroups come after all others, so that the XCDs, which take workgroups in turn, get equal
+// shares of the long ones (end segments among the others left half of the XCDs with the short ones
+// where an axis had four segments: 425 against 306 us for the filter of 1024 x 4096 cells in FP64,
+// n = 5, R = 10, stencil along x).
+//
+// Where one stencil is taken (us of the filter, passes / stencil, n passes of reach R; the passes
+// took 3 to 8% more in these figures, when one loop served periodic and other axes):
+//  * never for a single pass, which costs less than the end segments;
+//  * periodic axes from two passes on: along y and z up to R = 8 n (FP32 1024 x 4096, z, n = 2, R = 16
+//    127 / 121, R = 32 140 / 143), along x, where four consecutive outputs a thread cost bank
+//    conflicts, up to 3 n (n = 2, R = 4 107 / 98, R = 16 127 / 127; FP64 n = 5, R = 20 on 187 x 1531 34 / 34);
+//  * other axes need 8 R cells, or the end segments with their halos outweigh the rest, and
+//    R <= 6 (n - 1): FP32 128x128x256, y, n = 3, R = 12 304 / 285, R = 24 330 / 358; z, n = 2, R = 4
+//    220 / 210, R = 10 259 / 265.  FP64 along y from eight passes on (n = 5, R = 10 516 / 525; n = 10, R = 15
+//    942 / 841).  Along x only where the end segments come free, since the lines are cut anyway or
+//    the launch leaves CUs idle, and up to 5 n / 2 in FP64 (1024 x 4096, n = 3, R = 7 253 / 239, R = 12
+//    262 / 286): 128x128x256 in FP32, n = 4, R = 6 325 / 367, though 1024 x 4096 166 / 143.
 template <typename TI, typename TO>
 struct Lines3 {
     const TI* in[3];
     TO* out[3];
     int h[3];                          // stagger of each component along the launch's axis
+    int n;                             // components
 };
 
 template <int AX> constexpr int fline_bc() { return AX == 0 ? 8 : 32; }
 
-template <int AX, typename TI, typename TO, typename T>
+template <int AX, bool STENCIL, typename TI, typename TO, typename T>
 __global__ void __launch_bounds__(NT) k3_fline(G3 g, Lines3<TI, TO> L, FiltSeq fs, int edge, int tcap, int nseg, int ncolb)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -393,21 +402,32 @@ __global__ void __launch_bounds__(NT) k3_fline(G3 g, Lines3<TI, TO> L, FiltSeq f
     // block -> (component, segment, column block, plane or row across)
     int bid = (int)blockIdx.x;
     const int nother = AX == 0 ? 1 : g.S[AX == 1 ? 2 : 1];
-    const int per_comp = nseg * ncolb * nother;
-    const int c = bid / per_comp;
-    bid -= c * per_comp;
-    const int seg = bid % nseg;
-    bid /= nseg;
-    const int cb = bid % ncolb;
-    const int other = bid / ncolb;
+    int c, seg, cb, other;
+    if (STENCIL && edge) {
+        cb = bid % ncolb;
+        bid /= ncolb;
+        other = bid % nother;
+        bid /= nother;
+        c = bid % L.n;
+        const int sl = bid / L.n;                 // the segments between the ends, then the ends
+        seg = sl < nseg - 2 ? sl + 1 : sl == nseg - 2 ? 0 : nseg - 1;
+    } else {
+        const int per_comp = nseg * ncolb * nother;
+        c = bid / per_comp;
+        bid -= c * per_comp;
+        seg = bid % nseg;
+        bid /= nseg;
+        cb = bid % ncolb;
+        other = bid / ncolb;
+    }
     const TI* __restrict__ in = L.in[c];
     TO* __restrict__ out = L.out[c];
     const int S = g.S[AX], per = g.per[AX];
     const int hi = per ? S - 1 : S - 1 - L.h[c];
     // segments of tcap cells, between two of edge cells at the ends of the axis when edge is not 0
-    const int seg0 = !edge ? seg * tcap : seg == 0 ? 0 : seg == nseg - 1 ? S - edge : edge + (seg - 1) * tcap;
-    const int tseg = !edge ? min(tcap, S - seg0)
-                           : seg == 0 || seg == nseg - 1 ? edge : min(tcap, S - edge - seg0);
+    const bool end = STENCIL && edge && (seg == 0 || seg == nseg - 1);
+    const int seg0 = !STENCIL || !edge ? seg * tcap : seg == 0 ? 0 : end ? S - edge : edge + (seg - 1) * tcap;
+    const int tseg = end ? edge : min(tcap, S - seg0 - (STENCIL ? edge : 0));
     const int A = tseg + 2 * R;
     const int ld = AX == 0 ? A + 1 : BC + 1;
     T* src = reinterpret_cast<T*>(smem_raw);
@@ -448,7 +468,7 @@ __global__ void __launch_bounds__(NT) k3_fline(G3 g, Lines3<TI, TO> L, FiltSeq f
         src[idx(a)] = v;
     }
     __syncthreads();
-    const bool one = composed<AX>(fs) && (per ? S > 2 * R : (seg0 >= R && seg0 + tseg - 1 + R <= hi));
+    const bool one = STENCIL && (per ? S > 2 * R : (seg0 >= R && seg0 + tseg - 1 + R <= hi));
     if (one) {
         // x: consecutive threads on the BC lines
         const int col1 = AX == 0 ? (int)threadIdx.x % BC : col, a1 = AX == 0 ? (int)threadIdx.x / BC : a0;
@@ -487,20 +507,27 @@ __global__ void __launch_bounds__(NT) k3_fline(G3 g, Lines3<TI, TO> L, FiltSeq f
         src = dst;
         dst = t;
     }
-    for (int p = one ? fs.n : 0; p < fs.n; p++) {
-        const T al = (T)fs.alpha[p], be = (T(1) - al) * T(0.5);
-        const int st = fs.stride[p];
-        for (int a = a0; a < A; a += TPC) {
-            const int j = seg0 - R + a;
-            const T l = a >= st ? src[idx(a - st)] : T(0);
-            const T r = a + st < A ? src[idx(a + st)] : T(0);
-            const T v = al * src[idx(a)] + be * (l + r);
-            dst[idx(a)] = (per || (j >= 0 && j <= hi)) ? v : T(0);
+    // all: every position is in range
+    auto passes = [&](auto all) {
+        for (int p = 0; p < fs.n; p++) {
+            const T al = (T)fs.alpha[p], be = (T(1) - al) * T(0.5);
+            const int st = fs.stride[p];
+            for (int a = a0; a < A; a += TPC) {
+                const int j = seg0 - R + a;
+                const T l = a >= st ? src[idx(a - st)] : T(0);
+                const T r = a + st < A ? src[idx(a + st)] : T(0);
+                const T v = al * src[idx(a)] + be * (l + r);
+                dst[idx(a)] = (decltype(all)::value || (j >= 0 && j <= hi)) ? v : T(0);
+            }
+            __syncthreads();
+            T* t = src;
+            src = dst;
+            dst = t;
         }
-        __syncthreads();
-        T* t = src;
-        src = dst;
-        dst = t;
+    };
+    if (!one) {
+        if (per) passes(std::true_type{});
+        else passes(std::false_type{});
     }
     if (!ok) return;
     for (int a = a0; a < tseg; a += TPC) {
@@ -2455,13 +2482,29 @@ bool filter_seq(int npass, int comp, int stride_mask, FiltSeq* fs)
     return true;
 }
 
+// whether k3_fline takes the passes along axis AX as one stencil, S stored cells and wgs workgroups
+// of whole lines (the figures are at the kernel)
+template <int AX, typename T>
+bool one_stencil(const FiltSeq& fs, int S, int per, long wgs)
+{
+    const int n = fs.n, R = fs.reach;
+    if (n < 2) return false;
+    if (per) return R <= (AX == 0 ? 3 : 8) * n;
+    if (S < 8 * R || R > 6 * (n - 1)) return false;
+    constexpr bool fp64 = sizeof(T) == 8;
+    if (AX == 0) return (S > 1024 || wgs < 1024) && (!fp64 || 2 * R <= 5 * n);
+    return !(AX == 1 && fp64) || n >= 8;
+}
+
 // one launch of k3_fline along AX for ncomp components
 template <int AX, typename TI, typename TO, typename T>
-void fline(const G3& g, const Lines3<TI, TO>& L, int ncomp, const FiltSeq& fs, hipStream_t s)
+void fline(const G3& g, Lines3<TI, TO> L, int ncomp, const FiltSeq& fs, hipStream_t s)
 {
     constexpr int BC = fline_bc<AX>();
     constexpr size_t LDS_MAX = 144 * 1024;
     const int S = g.S[AX];
+    const int ncolb = AX == 0 ? (g.S[1] * g.S[2] + BC - 1) / BC : (g.S[0] + BC - 1) / BC;
+    const int nother = AX == 0 ? 1 : g.S[AX == 1 ? 2 : 1];
     auto lds_of = [&](int t) {
         const int A = t + 2 * fs.reach;
         return 2 * (size_t)(AX == 0 ? BC * (A + 1) : A * (BC + 1)) * sizeof(T);
@@ -2469,7 +2512,8 @@ void fline(const G3& g, const Lines3<TI, TO>& L, int ncomp, const FiltSeq& fs, h
     // where the passes are one stencil away from the ends, the ends get segments of their own, no
     // longer than the reach makes necessary; from a reach of 93 in FP64 along y and z such a segment
     // with its halo would not fit the LDS, and the axis has equal segments only
-    int edge = composed<AX>(fs) && !g.per[AX] ? fs.reach + 1 : 0;
+    const bool one = one_stencil<AX, T>(fs, S, g.per[AX], (long)ncomp * ncolb * nother);
+    int edge = one && !g.per[AX] ? fs.reach + 1 : 0;
     if (S < 2 * edge + 16 || lds_of(edge) > LDS_MAX) edge = 0;
     const int M = S - 2 * edge;
     // segments along AX: the whole line when its halo-padded copy fits a third of the LDS (three
@@ -2486,13 +2530,14 @@ void fline(const G3& g, const Lines3<TI, TO>& L, int ncomp, const FiltSeq& fs, h
     while (tseg > 16 && lds_of(tseg) > LDS_MAX) tseg /= 2;       // long reaches: shorter segments
     const size_t lds = std::max(lds_of(tseg), lds_of(edge));
     const int nseg = (M + tseg - 1) / tseg + (edge ? 2 : 0);
-    const int ncolb = AX == 0 ? (g.S[1] * g.S[2] + BC - 1) / BC : (g.S[0] + BC - 1) / BC;
-    const int nother = AX == 0 ? 1 : g.S[AX == 1 ? 2 : 1];
     const long blocks = (long)ncomp * nseg * ncolb * nother;
-    (void)hipFuncSetAttribute((const void*)k3_fline<AX, TI, TO, T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)lds);
-    hipLaunchKernelGGL((k3_fline<AX, TI, TO, T>), dim3((unsigned)blocks), dim3(NT), lds, s, g, L, fs, edge, tseg,
-                       nseg, ncolb);
+    L.n = ncomp;
+    auto launch = [&](auto kernel) {
+        (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(NT), lds, s, g, L, fs, edge, tseg, nseg, ncolb);
+    };
+    if (one) launch(k3_fline<AX, true, TI, TO, T>);
+    else launch(k3_fline<AX, false, TI, TO, T>);
 }
 
 bool unit_stencil(const FiltSeq& fs, FiltStencil& st)

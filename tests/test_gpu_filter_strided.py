@@ -122,3 +122,32 @@ def test_3d_long_reach_matches_oracle(npass, comp, mask, reach, axis, real):
     p = pi.random_electrons3(3000, *n, d, seed=23, umax=3.0, margin=1.5)
     p["w"] *= 1e-3                       # a charge density of order one
     _long_reach(cfg, Oracle3(cfg), p, real, 0.09)
+
+
+# Sizes on either side of the lengths from which an axis that is not periodic takes the stencil (8
+# cells of it a cell of reach; y in FP64 with eight passes or more)
+@gpu
+@pytest.mark.parametrize("real", ["f64", "f32"])
+@pytest.mark.parametrize("npass,comp,mask", [(4, 1, 0b11), (1, 0, 0b11), (10, 1, 0b1111)])
+@pytest.mark.parametrize("above", [0, 1])
+def test_2d_stencil_from_its_length_matches_oracle(above, npass, comp, mask, real):
+    reach = (npass + comp) * sum(k + 1 for k in range(16) if mask >> k & 1)
+    n = 8 * reach - 1 + above                      # stored cells, layers of 4 on both sides
+    for nx, nz in ((n - 9, 40), (9, n - 9)):
+        cfg = pi.make_config(nx, nz, 0.1, 0.09, pml_cells=4, ck="ck2", theta=0.2, filter_npass=npass,
+                             filter_compensate=comp, real=real, seed=21, filter_strides=mask)
+        _long_reach(cfg, Oracle(cfg), pi.random_electrons(3000, nx, nz, 0.1, 0.09, seed=23, umax=3.0, margin=1.5),
+                    real, 0.09)
+
+
+@gpu
+@pytest.mark.parametrize("real", ["f64", "f32"])
+@pytest.mark.parametrize("npass,comp,mask", [(4, 1, 0b11), (2, 1, 0b11), (1, 0, 0b11)])
+@pytest.mark.parametrize("above", [0, 1])
+def test_3d_stencil_from_its_length_matches_oracle(above, npass, comp, mask, real):
+    d = (0.1, 0.12, 0.09)
+    n = max(8 * 3 * (npass + comp) - 1 + above - 9, 6)
+    for box in ((9, n, 10), (9, 10, n)):
+        cfg = pi.make_config3(*box, *d, pml_cells=4, ck="ck2", theta=0.2, filter_npass=npass, filter_compensate=comp,
+                              real=real, seed=21, filter_strides=mask)
+        _step_and_compare(cfg, Oracle3(cfg), pi.random_electrons3(3000, *box, d, seed=23, umax=3.0, margin=1.5), real)

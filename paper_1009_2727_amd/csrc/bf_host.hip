@@ -1529,7 +1529,8 @@ bf_status gauss3_impl(bf_sim* s, double* out)
     bf3::FiltSeq fs;
     bf3::filter_seq(s->cfg.filter_npass, s->cfg.filter_compensate, s->cfg.filter_strides, &fs);
     const double* res = bf3::launch3_filter_nodal(L.g, a, jacc3(s, 1), jacc3(s, 2), fs, s->stream);
-    e = hipStreamSynchronize(s->stream);
+    e = hipGetLastError();               // a launch that failed left its scratch as it was
+    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return hip_check(s, e, "3D gauss");
     const size_t grid = (size_t)L.g.S[0] * L.g.S[1] * L.g.S[2];
     std::vector<double> rho(grid), E[3];

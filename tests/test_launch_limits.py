@@ -113,3 +113,22 @@ def _child(script, *args):
 def test_line_filter_fits_the_lds_at_every_reach(fake, axis, real):
     runs = int(_child(REACHES, fake, ROOT, real, axis).split()[-1])
     assert runs >= 4 * 128
+
+
+FAILED = CHILD + r"""
+for cfg in (pi.make_config3(8, 8, 8, 0.1, 0.1, 0.1, pml_cells=4, filter_npass=1, real=sys.argv[3]),
+            pi.make_config(8, 8, 0.1, 0.1, pml_cells=4, filter_npass=1, real=sys.argv[3])):
+    r = Run(cfg)
+    assert r.gauss() == 0
+    fake.host_hip_fail(1)
+    assert r.gauss() == -5, "a launch failed and the residual was returned"
+    fake.host_hip_fail(0)
+    assert fake.hipGetLastError() == 0, "the error was left for a later call"
+    r.close()
+print("ok")
+"""
+
+
+@pytest.mark.parametrize("real", ["f64", "f32"])
+def test_gauss_residual_reports_a_failed_launch(fake, real):
+    assert "ok" in _child(FAILED, fake, ROOT, real)

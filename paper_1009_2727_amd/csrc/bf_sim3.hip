@@ -1576,7 +1576,7 @@ __device__ void clamp_box(const E3<R>& e, const Seg3& sg, const Box3& bb, int pz
         m[a] = block_sum3<GT>(m[a], red);
         __syncthreads();   // red is reused
     }
-    if (m[3] == 0.0) return;   // every particle is gone: the box is not used
+    if (m[3] == 0.0) m[3] = 1.0;   // no live particle (rows of vacuum): any window does
 #pragma unroll
     for (int a = 0; a < 3; a++) {
         if (bx.ext[a] <= cap[a]) continue;

@@ -358,3 +358,23 @@ def test_3d_modified_pml_coefficients_match_oracle():
     for n in ("Ex", "Ey", "Ez", "Bx", "By", "Bz"):
         a, b = sim.field(n), ref.field(n)
         assert np.abs(a - b).max() <= 1e-11 * np.abs(f).max(), n
+
+
+@gpu
+@pytest.mark.parametrize("real,tol", [("f64", 1e-10), ("f32", 1e-5)])
+def test_3d_vacuum_rows_in_the_smallest_tiles_match_oracle(real, tol):
+    # rows of zero weight ahead of the plasma in tiles one cell long: their chunks' boxes are a plane
+    # longer than the staged ones and hold no live particle
+    w = pi.small_boosted3(real=real, nx=10, ny=8, nz=40, ppc=2)
+    sim, ref = _sim(w, sort_every=7, tile=(0, 1)), Oracle3.from_workload(w)
+    assert len(ref.particles(0)["w"]) < 2 * 10 * 8 * 40
+    for k, name in enumerate(["Ex", "Ey", "Ez", "Bx", "By", "Bz"]):
+        f = pi.random_field(ref.shape, seed=520 + k, amp=0.2)
+        ref.set_field(name, f)
+        sim.set_field(name, f)
+    for _ in range(2):
+        sim.step(5)
+        ref.step(5)
+        assert sim.sync_status() == 0
+        compare_fields3(sim, ref, tol)
+    assert sim.info()["shift"] > 0

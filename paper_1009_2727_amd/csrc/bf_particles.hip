@@ -47,6 +47,11 @@ constexpr int TPX = 32;                 // row pitch of the staged tile (cells)
 // that four workgroups fit a CU's LDS; the default tile needs 14 rows, and 12 are left for drift
 template <typename R> constexpr int trows() { return sizeof(R) == 4 ? 26 : 21; }
 template <typename R> constexpr int tcells() { return TPX * trows<R>(); }
+// rows of an ion segment's tile, which holds J_z alone: the largest tile (64 cells), its halo and one
+// row of drift.  Ions drift rigidly, so that tiles of 21 cells and more outgrew the electrons' 26 rows
+// whole, and their segments went to global atomics: 256 x 2048 cells at 16 particles a cell in tiles
+// of 24 cells 2.61 -> 1.12 ms a step
+constexpr int ION_ROWS = 70;
 
 // Current accumulator of the staged tile.  FP32 runs accumulate in 64-bit integer fixed
 // point: the integer LDS add is faster than the FP64 one on gfx950 (the FP32 LDS add is far
@@ -731,7 +736,7 @@ __device__ __forceinline__ void ion_segment(const Geo& g, const FieldSet<R>& f, 
     lds.lx = bb.y - bb.x + 6;
     lds.lz = bb.w - bb.z + 6;
     constexpr int TCELLS = tcells<R>();
-    const bool use_lds = lds.lx <= TPX && lds.lz <= trows<R>();
+    const bool use_lds = lds.lx <= TPX && lds.lz <= ION_ROWS;
     // only J_z (component 2) is staged: point j so that component 2 starts at smem
     lds.f = nullptr;
     lds.j = reinterpret_cast<JT*>(smem_raw) - 2 * TCELLS;
@@ -1495,6 +1500,10 @@ template <typename R> constexpr size_t gpd_lds()
     return (size_t)tcells<R>() * (6 * sizeof(R) + 3 * sizeof(typename LdsAcc<R>::JT));
 }
 
+template <typename R> constexpr size_t ion_lds() { return (size_t)TPX * ION_ROWS * sizeof(typename LdsAcc<R>::JT); }
+static_assert(ion_lds<float>() <= gpd_lds<float>() && ion_lds<double>() <= gpd_lds<double>(),
+              "the ions of a launch with electrons fit its LDS");
+
 template <typename R>
 static int antenna_blocks(const SourceParams<R>& sp, int threads)
 {
@@ -1507,8 +1516,7 @@ void launch_sources(const Geo& g, const FieldSet<R>& f, SourceParams<R> sp, hipS
     sp.na = antenna_blocks(sp, NTHR);
     const int n = sp.nion + sp.na;
     if (n > 0)
-        hipLaunchKernelGGL((k_sources<R>), dim3(n), dim3(NTHR),
-                           (size_t)tcells<R>() * sizeof(typename LdsAcc<R>::JT), s, g, f, sp);
+        hipLaunchKernelGGL((k_sources<R>), dim3(n), dim3(NTHR), ion_lds<R>(), s, g, f, sp);
 }
 
 template <typename R>

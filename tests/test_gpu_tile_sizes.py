@@ -1,0 +1,28 @@
+"""Particle tiles beside the default ones against the FP64 oracle: the sizes where the staged tile is
+just long enough or not, for drifting ions and for electrons, and the largest.  A boosted run with
+laser, window and rigid ions, the tiles sorted and stepped until the particles have drifted by
+several cells.  Tolerances as in the parity tests (FP64 1e-10, FP32 1e-5 of the field scales).
+"""
+import pytest
+
+import pic_inputs as pi
+from oracle import Oracle
+
+gpu = pytest.mark.gpu
+
+
+@gpu
+@pytest.mark.parametrize("real,tol", [("f64", 1e-10), ("f32", 1e-5)])
+@pytest.mark.parametrize("tile", [(26, 15), (26, 20), (26, 21), (16, 24), (26, 25), (26, 26), (26, 64), (64, 25)])
+def test_2d_tile_sizes_match_oracle(tile, real, tol):
+    from paper_1009_2727_amd import Sim
+    from test_gpu_parity import compare_fields, compare_particles
+    w = pi.small_boosted(real=real, nx=40, nz=160, ppc=3)
+    sim, ref = Sim.from_workload(w, tile=tile, sort_every=6), Oracle.from_workload(w)
+    sim.step(10)
+    ref.step(10)
+    assert sim.sync_status() == 0
+    compare_fields(sim, ref, tol, tag=f"tile {tile} {real}")
+    if real == "f64":
+        compare_particles(sim, ref, 1e-9, 1e-9)
+        compare_particles(sim, ref, 1e-9, 1e-9, species=1)

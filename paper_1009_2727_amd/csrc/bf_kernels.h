@@ -108,6 +108,7 @@ struct ElectronParams {
     const int4* bbin;
     int4* bbout;
     int nseg;
+    int tile_z;        // cells of a particle tile along z
     PushParams<R> pp;
     int* far;
     int* status;
@@ -187,8 +188,9 @@ template <typename R>
 void launch_faraday_batch(const FaradayDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s);
 template <typename R>
 void launch_ampere_batch(const AmpereDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s);
+// tile_z: of the longest particle tile among the runs
 template <typename R>
-void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, hipStream_t s);
+void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, int tile_z, hipStream_t s);
 // workgroups of a run's electrons and sources; sets sp.na
 template <typename R>
 int particle_blocks(const ElectronParams<R>& ep, SourceParams<R>& sp);

@@ -43,10 +43,14 @@ __device__ __forceinline__ double block_sum(double v, double* red)
 // conflicting when their word indices agree mod 16; a pitch of 0 (mod 16) keeps a lane whose
 // stencil starts one row lower (a z face crossed in the step) on the slot of its column.
 constexpr int TPX = 32;                 // row pitch of the staged tile (cells)
-// rows of the staged tile (6 field planes + 3 current planes of 8 bytes): FP32 tiles take 39 KB, so
-// that four workgroups fit a CU's LDS; the default tile needs 14 rows, and 12 are left for drift
+// Rows of the staged tile (6 field planes + 3 current planes of 8 bytes).  FP32 tiles of 26 rows take
+// 39 KB, so that four workgroups fit a CU's LDS; the default tile needs 14 rows, and 12 are left for
+// drift.  Particle tiles of 21 cells and more fill them with their halo and one row of drift, and the
+// launch takes 31 rows, three workgroups a CU: 256 x 2048 cells at 16 particles a cell in tiles of 24
+// cells 1124 -> 433 us a step (tiles of 20 take 397 us with 26 rows, tiles of 21 420 us with 31).
 template <typename R> constexpr int trows() { return sizeof(R) == 4 ? 26 : 21; }
-template <typename R> constexpr int tcells() { return TPX * trows<R>(); }
+template <typename R> constexpr int trows_tall() { return sizeof(R) == 4 ? 31 : 21; }
+template <typename R> bool tall_tile(int tile_z) { return trows_tall<R>() > trows<R>() && tile_z + 6 > trows<R>(); }
 // rows of an ion segment's tile, which holds J_z alone: the largest tile (64 cells), its halo and one
 // row of drift.  Ions drift rigidly, so that tiles of 21 cells and more outgrew the electrons' 26 rows
 // whole, and their segments went to global atomics: 256 x 2048 cells at 16 particles a cell in tiles
@@ -75,9 +79,9 @@ __device__ __forceinline__ double fix_value(unsigned long long t)
 
 // field component ids inside the staged tile: 0..2 E, 3..5 B (time-centred).
 // A handle is the offset of a stencil's lower corner; stencil nodes are (handle, a, b).
-template <typename R>
+template <typename R, int NR>
 struct LdsAcc {
-    static constexpr int TCELLS = tcells<R>();
+    static constexpr int TCELLS = TPX * NR;
     static constexpr bool FIX = JAcc<R>::fixed;
     using JT = typename JAcc<R>::T;
     R* f;       // 6 planes of TCELLS
@@ -426,9 +430,9 @@ __device__ __forceinline__ void advance_electron(const A& acc, const Geo& g, con
 // sort, as in a heated plasma): along each axis that is too long, the longest window that
 // fits, centred on the particles' mean position; a particle in cell c fits while
 // lo + 2 <= c <= lo + n - 4.
-template <typename R, int NTH>
+template <typename R, int NR, int NTH>
 __device__ __forceinline__ void clamp_window(const ElectronArrays<R>& e, const Segment& sg, const int4& bb,
-                                             LdsAcc<R>& lds, double* redd)
+                                             LdsAcc<R, NR>& lds, double* redd)
 {
     double m[3] = {0.0, 0.0, 0.0};
     for (int p = sg.start + threadIdx.x; p < sg.start + sg.count; p += NTH)
@@ -448,10 +452,10 @@ __device__ __forceinline__ void clamp_window(const ElectronArrays<R>& e, const S
         lds.xb = min(max(lo, bb.x - 2), bb.y + 4 - TPX);
         lds.lx = TPX;
     }
-    if (lds.lz > trows<R>()) {
-        const int lo = (int)floor(m[1] / m[2] - 0.5 * (trows<R>() - 5) + 0.5) - 2;
-        lds.zb = min(max(lo, bb.z - 2), bb.w + 4 - trows<R>());
-        lds.lz = trows<R>();
+    if (lds.lz > NR) {
+        const int lo = (int)floor(m[1] / m[2] - 0.5 * (NR - 5) + 0.5) - 2;
+        lds.zb = min(max(lo, bb.z - 2), bb.w + 4 - NR);
+        lds.lz = NR;
     }
 }
 
@@ -560,7 +564,7 @@ __device__ __forceinline__ void far_electron(const Geo& g, const FieldSet<R>& f,
 // of code and 168 registers, and cold instruction fetches dominated small launches.
 // Per step: 43 -> 15 us on 75 x 1691 cells at 1 particle a cell, 70 -> 23 us on 64 x 512 at 4 in
 // FP64, 0.425 -> 0.38 ms on 256 x 4096 at 16 (16.8 M electrons, four workgroups per CU).
-template <typename R, bool MC, int NTH>
+template <typename R, bool MC, int NR, int NTH>
 __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, int s)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];   // 16-byte aligned: FP64 DS ops
@@ -581,16 +585,17 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
     int p = sg.start + threadIdx.x;
     EState<R> nxt{}, done{};
     if (p < end) nxt = load_electron(e, p);
-    LdsAcc<R> lds;
+    using Acc = LdsAcc<R, NR>;
+    Acc lds;
     lds.xb = bb.x - 2;
     lds.zb = bb.z - 2;
     lds.lx = bb.y - bb.x + 6;
     lds.lz = bb.w - bb.z + 6;
     lds.f = reinterpret_cast<R*>(smem_raw);
-    constexpr int TCELLS = tcells<R>();
-    using JT = typename LdsAcc<R>::JT;
+    constexpr int TCELLS = Acc::TCELLS;
+    using JT = typename Acc::JT;
     lds.j = reinterpret_cast<JT*>(lds.f + 6 * TCELLS);   // 6 TCELLS elements: 8-byte aligned
-    if (lds.lx > TPX || lds.lz > trows<R>()) clamp_window<R, NTH>(e, sg, bb, lds, redd);
+    if (lds.lx > TPX || lds.lz > NR) clamp_window<R, NR, NTH>(e, sg, bb, lds, redd);
     int x0 = INT_MAX, x1 = INT_MIN, z0 = INT_MAX, z1 = INT_MIN;
     const int L = lds.lz * TPX;
     for (int q = threadIdx.x; q < L; q += NTH) {
@@ -617,7 +622,7 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
         for (int c = 0; c < 3; c++) lds.j[c * TCELLS + q] = JT(0);
     }
     double js = 1.0, jq = 1.0;   // current into tile units and back
-    if constexpr (LdsAcc<R>::FIX) {
+    if constexpr (Acc::FIX) {
         double sw = fabs((double)nxt.w);
         for (int q = p + NTH; q < end; q += NTH) sw += fabs((double)e.w[q]);
         sw = block_sum<NTH>(sw, redd);
@@ -663,7 +668,7 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
 #pragma unroll
         for (int c = 0; c < 3; c++) {
             R v;
-            if constexpr (LdsAcc<R>::FIX) v = (R)(fix_value(lds.j[c * TCELLS + q]) * jq);
+            if constexpr (Acc::FIX) v = (R)(fix_value(lds.j[c * TCELLS + q]) * jq);
             else v = (R)lds.j[c * TCELLS + q];
             if (v != R(0)) atomicAdd(&f.J[c][o], v);
         }
@@ -680,11 +685,11 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
 // of 256 leaves two waves per SIMD, so a small grid has too few of them in flight at 256 threads.
 template <typename R> constexpr int gpd_threads() { return sizeof(R) == 4 ? 256 : 512; }
 
-template <typename R, bool MC>
+template <typename R, bool MC, int NR>
 __global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
     k_gpd(Geo g, FieldSet<R> f, ElectronParams<R> ep)
 {
-    gpd_segment<R, MC, gpd_threads<R>()>(g, f, ep, blockIdx.x);
+    gpd_segment<R, MC, NR, gpd_threads<R>()>(g, f, ep, blockIdx.x);
 }
 
 // ---- rigid ions --------------------------------------------------------------------------
@@ -728,14 +733,15 @@ __device__ __forceinline__ void ion_segment(const Geo& g, const FieldSet<R>& f, 
         if (threadIdx.x == 0) bbout[s] = make_int4(INT_MAX, INT_MIN, INT_MAX, INT_MIN);
         return;
     }
-    using JT = typename LdsAcc<R>::JT;
+    using Acc = LdsAcc<R, ION_ROWS>;
+    using JT = typename Acc::JT;
     GlobAcc<R> glb = make_glob<false>(g, f);
-    LdsAcc<R> lds;
+    Acc lds;
     lds.xb = bb.x - 2;
     lds.zb = bb.z - 2;
     lds.lx = bb.y - bb.x + 6;
     lds.lz = bb.w - bb.z + 6;
-    constexpr int TCELLS = tcells<R>();
+    constexpr int TCELLS = Acc::TCELLS;
     const bool use_lds = lds.lx <= TPX && lds.lz <= ION_ROWS;
     // only J_z (component 2) is staged: point j so that component 2 starts at smem
     lds.f = nullptr;
@@ -746,7 +752,7 @@ __device__ __forceinline__ void ion_segment(const Geo& g, const FieldSet<R>& f, 
     const int end = sg.start + sg.count;
     double js = 1.0, jq = 1.0;   // current into tile units and back (fixed-point tile)
     if (use_lds) {
-        if constexpr (LdsAcc<R>::FIX) {
+        if constexpr (Acc::FIX) {
             double sw = 0.0;
             for (int p = sg.start + threadIdx.x; p < end; p += NTH) sw += fabs((double)ion.w[p]);
             sw = block_sum<NTH>(sw, redd);
@@ -789,7 +795,7 @@ __device__ __forceinline__ void ion_segment(const Geo& g, const FieldSet<R>& f, 
         for (int q = threadIdx.x; q < L; q += NTH) {
             const int a = q % lds.lx, b = q / lds.lx;
             R v;
-            if constexpr (LdsAcc<R>::FIX) v = (R)(fix_value(jz[b * TPX + a]) * jq);
+            if constexpr (Acc::FIX) v = (R)(fix_value(jz[b * TPX + a]) * jq);
             else v = (R)jz[b * TPX + a];
             if (v == R(0)) continue;
             const int i = swrap(lds.xb + a + g.Px, g.Sx, g.perx);
@@ -901,12 +907,12 @@ __global__ void __launch_bounds__(NTHR) k_sources(Geo g, FieldSet<R> f, SourcePa
 }
 
 // electrons and sources in one launch (they only add to J)
-template <typename R, bool MC>
+template <typename R, bool MC, int NR>
 __global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
     k_particles(Geo g, FieldSet<R> f, ElectronParams<R> ep, SourceParams<R> sp)
 {
     const int b = blockIdx.x;
-    if (b < ep.nseg) gpd_segment<R, MC, gpd_threads<R>()>(g, f, ep, b);
+    if (b < ep.nseg) gpd_segment<R, MC, NR, gpd_threads<R>()>(g, f, ep, b);
     else source_block<R, gpd_threads<R>()>(g, f, sp, b - ep.nseg);
 }
 
@@ -914,13 +920,13 @@ __global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
 // them out, and the ions of one run fill the tail of its electrons.  16 runs of about 150 x 1600 cells at 10
 // particles a cell: 1.79 ms a step; electrons by a persistent launch over a queue and each run's
 // sources in a launch of its own took 1.84 ms.
-template <typename R>
+template <typename R, int NR>
 __global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
     k_particles_batch(const ParticleDesc<R>* __restrict__ d, QueueRef q)
 {
     const int r = run_of(q, blockIdx.x), b = (int)blockIdx.x - q.off[r];
     const ParticleDesc<R>& D = d[r];
-    if (b < D.e.nseg) gpd_segment<R, false, gpd_threads<R>()>(D.g, D.f, D.e, b);
+    if (b < D.e.nseg) gpd_segment<R, false, NR, gpd_threads<R>()>(D.g, D.f, D.e, b);
     else source_block<R, gpd_threads<R>()>(D.g, D.f, D.s, b - D.e.nseg);
 }
 
@@ -1495,13 +1501,15 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_disperse_i(Geo g, IonArra
 }
 
 // ---- launchers ---------------------------------------------------------------------------------
-template <typename R> constexpr size_t gpd_lds()
+template <typename R, int NR> constexpr size_t gpd_lds()
 {
-    return (size_t)tcells<R>() * (6 * sizeof(R) + 3 * sizeof(typename LdsAcc<R>::JT));
+    return (size_t)TPX * NR * (6 * sizeof(R) + 3 * sizeof(typename LdsAcc<R, NR>::JT));
 }
-
-template <typename R> constexpr size_t ion_lds() { return (size_t)TPX * ION_ROWS * sizeof(typename LdsAcc<R>::JT); }
-static_assert(ion_lds<float>() <= gpd_lds<float>() && ion_lds<double>() <= gpd_lds<double>(),
+template <typename R> constexpr size_t ion_lds()
+{
+    return (size_t)TPX * ION_ROWS * sizeof(typename LdsAcc<R, ION_ROWS>::JT);
+}
+static_assert(ion_lds<float>() <= gpd_lds<float, trows<float>()>() && ion_lds<double>() <= gpd_lds<double, trows<double>()>(),
               "the ions of a launch with electrons fit its LDS");
 
 template <typename R>
@@ -1526,35 +1534,49 @@ int particle_blocks(const ElectronParams<R>& ep, SourceParams<R>& sp)
     return ep.nseg + sp.nion + sp.na;
 }
 
-template <typename R, bool MC>
+template <typename R, bool MC, int NR>
 static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, SourceParams<R> sp, hipStream_t s)
 {
     constexpr int threads = gpd_threads<R>();
+    constexpr size_t lds = gpd_lds<R, NR>();
     const int n = particle_blocks(ep, sp);
     // One launch: the ions and the antenna fill the electrons' tail, and a launch is spared.  20
     // steps against two launches: 75 x 1691 cells at 1 particle a cell 0.96 -> 0.83 ms, 64 x 512 in
     // FP64 1.17 -> 0.83 ms, 187 x 1531 at 5 3.31 -> 3.08 ms, 256 x 4096 at 16 13.2 -> 13.0 ms.
     if (ep.nseg > 0 && n > ep.nseg) {
-        hipLaunchKernelGGL((k_particles<R, MC>), dim3(n), dim3(threads), gpd_lds<R>(), s, g, f, ep, sp);
+        hipLaunchKernelGGL((k_particles<R, MC, NR>), dim3(n), dim3(threads), lds, s, g, f, ep, sp);
         return;
     }
-    if (ep.nseg > 0) hipLaunchKernelGGL((k_gpd<R, MC>), dim3(ep.nseg), dim3(threads), gpd_lds<R>(), s, g, f, ep);
+    if (ep.nseg > 0) hipLaunchKernelGGL((k_gpd<R, MC, NR>), dim3(ep.nseg), dim3(threads), lds, s, g, f, ep);
     launch_sources<R>(g, f, sp, s);
+}
+
+template <typename R, int NR>
+static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
+                      bool mc, hipStream_t s)
+{
+    if (mc) particles<R, true, NR>(g, f, ep, sp, s);
+    else particles<R, false, NR>(g, f, ep, sp, s);
 }
 
 template <typename R>
 void launch_particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
                       bool mc, hipStream_t s)
 {
-    if (mc) particles<R, true>(g, f, ep, sp, s);
-    else particles<R, false>(g, f, ep, sp, s);
+    if (tall_tile<R>(ep.tile_z)) particles<R, trows_tall<R>()>(g, f, ep, sp, mc, s);
+    else particles<R, trows<R>()>(g, f, ep, sp, mc, s);
 }
 
 template <typename R>
-void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, hipStream_t s)
+void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, int tile_z, hipStream_t s)
 {
-    if (q.total > 0)
-        hipLaunchKernelGGL((k_particles_batch<R>), dim3(q.total), dim3(gpd_threads<R>()), gpd_lds<R>(), s, d, q);
+    if (q.total <= 0) return;
+    if (tall_tile<R>(tile_z))
+        hipLaunchKernelGGL((k_particles_batch<R, trows_tall<R>()>), dim3(q.total), dim3(gpd_threads<R>()),
+                           (gpd_lds<R, trows_tall<R>()>()), s, d, q);
+    else
+        hipLaunchKernelGGL((k_particles_batch<R, trows<R>()>), dim3(q.total), dim3(gpd_threads<R>()),
+                           (gpd_lds<R, trows<R>()>()), s, d, q);
 }
 
 template <typename R>
@@ -1626,7 +1648,7 @@ void launch_sort_ions(const Geo& g, int tile_x, int tile_z, int ntx, int ntiles,
                                       const SourceParams<R>&, bool, hipStream_t);                     \
     template void launch_sources<R>(const Geo&, const FieldSet<R>&, SourceParams<R>, hipStream_t);    \
     template int particle_blocks<R>(const ElectronParams<R>&, SourceParams<R>&);                      \
-    template void launch_particles_batch<R>(const ParticleDesc<R>*, const QueueRef&, hipStream_t);    \
+    template void launch_particles_batch<R>(const ParticleDesc<R>*, const QueueRef&, int, hipStream_t); \
     template void launch_beam<R>(const Geo&, const FieldSet<R>&, const BeamArrays&, const BeamParams&, \
                                  const PushParams<double>&, int*, bool, hipStream_t);                 \
     template void launch_advance<R>(const Geo&, const WindowParams<R>*, const ElectronArrays<R>&,     \

@@ -26,3 +26,19 @@ def test_2d_tile_sizes_match_oracle(tile, real, tol):
     if real == "f64":
         compare_particles(sim, ref, 1e-9, 1e-9)
         compare_particles(sim, ref, 1e-9, 1e-9, species=1)
+
+
+@gpu
+def test_batch_of_unlike_tiles_matches_oracle():
+    # one launch for runs whose tiles ask for different rows
+    from paper_1009_2727_amd import Batch, Sim
+    from test_gpu_parity import compare_fields
+    w = [pi.small_boosted(real="f32", nx=40, nz=n, ppc=3, seed=70 + n) for n in (120, 160)]
+    sims = [Sim.from_workload(v, tile=t, sort_every=6) for v, t in zip(w, ((26, 8), (16, 24)))]
+    batch = Batch(sims)
+    batch.step(10)
+    for v, s in zip(w, sims):
+        ref = Oracle.from_workload(v)
+        ref.step(10)
+        assert s.sync_status() == 0
+        compare_fields(s, ref, 1e-5, tag="batch of unlike tiles")

@@ -7,6 +7,7 @@ import pytest
 
 import pic_inputs as pi
 from oracle import Oracle
+from oracle.pic3 import Oracle3
 
 gpu = pytest.mark.gpu
 
@@ -42,3 +43,19 @@ def test_batch_of_unlike_tiles_matches_oracle():
         ref.step(10)
         assert s.sync_status() == 0
         compare_fields(s, ref, 1e-5, tag="batch of unlike tiles")
+
+
+@gpu
+@pytest.mark.parametrize("real,tol", [("f64", 1e-10), ("f32", 1e-5)])
+@pytest.mark.parametrize("tile_z", [3, 7, 8, 9, 14, 15, 24])
+def test_3d_tile_sizes_match_oracle(tile_z, real, tol):
+    from paper_1009_2727_amd import Sim
+    from test_gpu_parity3 import compare_fields3, compare_particles3
+    w = pi.small_boosted3(real=real, nx=10, ny=8, nz=52, ppc=2)
+    sim, ref = Sim.from_workload(w, tile=(0, tile_z), sort_every=6), Oracle3.from_workload(w)
+    sim.step(10)
+    ref.step(10)
+    assert sim.sync_status() == 0
+    compare_fields3(sim, ref, tol)
+    if real == "f64":
+        compare_particles3(sim, ref, 1e-9, 1e-9)

@@ -931,6 +931,7 @@ struct Sim3 {
     bf3::Tiles3 tl{};
     int seg_cap = 0, nseg = 0, bb_cur = 0;   // segments (tiles of the last sort, then injected chunks)
     int pz = 0, pzi = 0;                     // z planes of the LDS box of electrons, of ions
+    bool dense = false;                      // the electrons' field planes are as close as the current's
     int na = 0;
     int eb_cur = 0;                          // which of A3_EB / A3_T holds the Friedman average
 };
@@ -1157,8 +1158,10 @@ bf_status create3(const bf_config* cfg, const bf_buffer_binding* b, int n, void*
         int dev = 0, lds_max = 65536;
         if (hipGetDevice(&dev) == hipSuccess)
             (void)hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-        const int plane = cfg->real_bytes == 4 ? bf3::box_plane_bytes<float>() : bf3::box_plane_bytes<double>();
-        const int fit = lds_max / plane;
+        const bool f32 = cfg->real_bytes == 4;
+        int fit = lds_max / (f32 ? bf3::box_plane_bytes<float, bf3::BOX_FPL>() : bf3::box_plane_bytes<double, bf3::BOX_FPL>());
+        s->d3->dense = f32 && s->d3->tl.t[2] + 6 > fit;
+        if (s->d3->dense) fit = lds_max / bf3::box_plane_bytes<float, bf3::BOX_PL>();
         s->d3->pz = std::min(s->d3->tl.t[2] + 7, fit);
         // the ions' box holds J_z alone and has its own planes: one of drift beside the tile's (the ions
         // are rigid) and nine for a plane of plasma just injected, as far as four workgroups a CU (what
@@ -1303,8 +1306,8 @@ bf_status step3(bf_sim* s, int nsteps)
         const bool mc = s->cfg.gather_kind == 1;
         if (mc) bf3::launch3_nodes<R>(g, f, s->stream);
         bf3::launch3_gpd<R>(g, f, electrons3<R>(s, L.p_cur), seg3<R>(s, 0), box3(s, 0, L.bb_cur),
-                            box3(s, 0, 1 - L.bb_cur), L.nseg, pp, L.pz, w3<int>(s, L.w_status), w3<int>(s, L.w_nmis),
-                            w3<int2>(s, L.w_mis), mc, s->stream);
+                            box3(s, 0, 1 - L.bb_cur), L.nseg, pp, L.pz, L.dense, w3<int>(s, L.w_status),
+                            w3<int>(s, L.w_nmis), w3<int2>(s, L.w_mis), mc, s->stream);
         s->tock(ev, BF_PHASE_PUSH);
         ev = s->tick();
         if (s->have_plasma && s->plasma.ion_mode == 1)

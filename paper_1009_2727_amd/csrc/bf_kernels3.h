@@ -83,11 +83,13 @@ struct Tiles3 { int t[3]; int nt[3]; int ntiles; };
 // a time over 32 banks: LAT_X columns by four rows are 32 distinct ones, and field planes BOX_FPL of
 // 0 (mod 32) apart keep it so with the particles at random heights in their lattice plane.  Waves in
 // rows of 16 and planes of 240 read in 4.5 passes, not 3.7: 13.5 against 12.4 ms a step on
-// 128x128x1024 cells at 8 particles a cell.
+// 128x128x1024 cells at 8 particles a cell.  The wider field planes leave room for 13 in FP32: particle
+// tiles of 8 cells and more, which need 14 with a cell of drift, have field planes BOX_PL apart too
+// (electrons on 64x64x256 cells at 8 particles a cell, tiles of 8 cells: 2.19 -> 0.85 ms).
 constexpr int BOX_PX = 24, BOX_PY = 10, BOX_PL = BOX_PX * BOX_PY, BOX_FPL = 256, LAT_X = 8;
 // LDS bytes per box plane of the electron kernel: 6 field components in the run's type and 3
 // current accumulators of 8 bytes
-template <typename R> constexpr int box_plane_bytes() { return 6 * (int)sizeof(R) * BOX_FPL + 24 * BOX_PL; }
+template <typename R, int FP> constexpr int box_plane_bytes() { return 6 * (int)sizeof(R) * FP + 24 * BOX_PL; }
 
 struct Inject3 {
     int64_t row0;
@@ -161,12 +163,13 @@ void launch3_rho(const G3& g, const E3<R>& e, int ne, const I3<R>& ion, int ni, 
                  int na, int pol, double za, double aw, double vol_inv, double* rho, hipStream_t s);
 // gather, push and deposit of the electrons of nseg segments (one workgroup each); bin holds
 // each segment's cell box at the start of the step, bout receives the box after the push (in
-// the next window frame); pz = z planes of the LDS box
+// the next window frame); pz = z planes of the LDS box, dense: its field planes are BOX_PL apart (FP32)
 // nmis: one int, zero before the call, mis: one int2 per particle slot (particles outside their segment's
 // staged box are pushed in a second pass, on HBM)
 template <typename R>
 void launch3_gpd(const G3& g, const F3<R>& f, const E3<R>& e, const Seg3* seg, const Box3* bin, Box3* bout,
-                 int nseg, const Push3& pp, int pz, int* status, int* nmis, int2* mis, bool mc, hipStream_t s);
+                 int nseg, const Push3& pp, int pz, bool dense, int* status, int* nmis, int2* mis, bool mc,
+                 hipStream_t s);
 // momentum-conserving gather, first step: E^n and B^n = (B^{n-1/2} + B^{n+1/2})/2 interpolated to
 // the nodes (the mean over the Yee locations around each node along the staggered axes) into f.G
 template <typename R> void launch3_nodes(const G3& g, const F3<R>& f, hipStream_t s);

@@ -1162,7 +1162,7 @@ __device__ __forceinline__ R rsq(R x)
 constexpr int GT = 768;        // threads of an electron segment workgroup
 constexpr int GTI = 256;       // threads of an ion segment workgroup
 constexpr int HBM_GRID = 1024; // workgroups of the pass over the particles left to HBM
-constexpr int BPX = BOX_PX, BPY = BOX_PY, BPL = BOX_PL, FPL = BOX_FPL;
+constexpr int BPX = BOX_PX, BPY = BOX_PY, BPL = BOX_PL;
 
 template <typename R> struct Acc3 { using T = double; static constexpr bool fixed = false; };
 template <> struct Acc3<float> { using T = unsigned long long; static constexpr bool fixed = true; };
@@ -1177,12 +1177,13 @@ __device__ __forceinline__ double fx_value(unsigned long long t)
 // stride of axis a in the LDS box (cells)
 __host__ __device__ constexpr int bstride(int a) { return a == 0 ? 1 : (a == 1 ? BPX : BPL); }
 
-template <typename R>
+// FP: cells between the planes of a field component
+template <typename R, int FP>
 struct BoxL {
     using JT = typename Acc3<R>::T;
     JT* j;         // current planes of n cells (3 for electrons, J_z only for ions)
     R* f;          // 6 field planes of n cells: E x, y, z and B x, y, z (time-centred)
-    int n, nf;     // cells per current (BPL * planes) and field component (FPL * planes)
+    int n, nf;     // cells per current (BPL * planes) and field component (FP * planes)
     int lo[3];     // interior cell index of box cell (0, 0, 0)
     int ext[3];    // box extent (cells)
 };
@@ -1202,8 +1203,8 @@ __device__ __forceinline__ double jvalue(typename Acc3<R>::T t, double jq)
 }
 
 // the cell of r and its stencils lie inside the box
-template <typename R>
-__device__ __forceinline__ bool in_box(const BoxL<R>& bx, const double r[3])
+template <typename R, int FP>
+__device__ __forceinline__ bool in_box(const BoxL<R, FP>& bx, const double r[3])
 {
     bool in = true;
 #pragma unroll
@@ -1215,8 +1216,8 @@ __device__ __forceinline__ bool in_box(const BoxL<R>& bx, const double r[3])
 }
 
 // gather of E^n, B^n at r from the staged box, cubic weights at each component's stagger
-template <bool MC, typename R>
-__device__ __forceinline__ void gather_box(const BoxL<R>& bx, const double r[3], R E[3], R B[3])
+template <bool MC, typename R, int FP>
+__device__ __forceinline__ void gather_box(const BoxL<R, FP>& bx, const double r[3], R E[3], R B[3])
 {
     R w[3][2][4];
     int ob[3][2];
@@ -1227,7 +1228,7 @@ __device__ __forceinline__ void gather_box(const BoxL<R>& bx, const double r[3],
             const double xs = r[a] - 0.5 * h;
             const int j0 = (int)floor(xs);
             bspline4((R)(xs - j0), w[a][h]);
-            ob[a][h] = (j0 - 1 - bx.lo[a]) * (a == 2 ? FPL : bstride(a));
+            ob[a][h] = (j0 - 1 - bx.lo[a]) * (a == 2 ? FP : bstride(a));
         }
 #pragma unroll
     for (int c = 0; c < 6; c++) {
@@ -1240,7 +1241,7 @@ __device__ __forceinline__ void gather_box(const BoxL<R>& bx, const double r[3],
             R tk = R(0);
 #pragma unroll
             for (int j = 0; j < 4; j++) {
-                const R* row = F + j * BPX + k * FPL;
+                const R* row = F + j * BPX + k * FP;
                 const R rr = w[0][hx][0] * row[0] + w[0][hx][1] * row[1] + w[0][hx][2] * row[2] + w[0][hx][3] * row[3];
                 tk += w[1][hy][j] * rr;
             }
@@ -1256,8 +1257,8 @@ __device__ __forceinline__ void gather_box(const BoxL<R>& bx, const double r[3],
 // C gains k_C (DS_C[0] + ... + DS_C[m]) T(m1, m2).  Along an axis that no particle of the wave
 // crosses a cell face on, the fifth window node has zero weight and the prefix sum is complete
 // at the fourth node: those adds are skipped for the whole wave.
-template <typename R>
-__device__ __forceinline__ void deposit_box(const BoxL<R>& bx, const double r0[3], const double r1[3],
+template <typename R, int FP>
+__device__ __forceinline__ void deposit_box(const BoxL<R, FP>& bx, const double r0[3], const double r1[3],
                                             const double k[3])
 {
     double S0[3][5], DS[3][5];
@@ -1309,8 +1310,8 @@ __device__ __forceinline__ void deposit_box(const BoxL<R>& bx, const double r0[3
 }
 
 // the same for a rigid ion moving along z only (x, y fixed): T = Sx Sy on 4 x 4 nodes
-template <typename R>
-__device__ __forceinline__ void deposit_box_z(const BoxL<R>& bx, double x, double y, double z0, double z1, double kz)
+template <typename R, int FP>
+__device__ __forceinline__ void deposit_box_z(const BoxL<R, FP>& bx, double x, double y, double z0, double z1, double kz)
 {
     const int ix = (int)floor(x), iy = (int)floor(y), i0 = (int)floor(z0), i1 = (int)floor(z1);
     const int b = min(i0, i1) - 1;
@@ -1339,8 +1340,8 @@ __device__ __forceinline__ void deposit_box_z(const BoxL<R>& bx, double x, doubl
 // box cell (a, b, c) of linear index q = a + ext0 (b + ext1 c), by float reciprocals: q stays below
 // 2^16 and the quotients below 64, so (q + 1/2) / d is at least 1/(2 d) from an integer and the
 // float product lands on the right side of it
-template <typename R>
-__device__ __forceinline__ void box_cell(const BoxL<R>& bx, int q, int& a, int& b, int& c)
+template <typename R, int FP>
+__device__ __forceinline__ void box_cell(const BoxL<R, FP>& bx, int q, int& a, int& b, int& c)
 {
     const int e0 = bx.ext[0], e01 = bx.ext[0] * bx.ext[1];
     c = (int)(((float)q + 0.5f) * (1.0f / (float)e01));
@@ -1350,8 +1351,8 @@ __device__ __forceinline__ void box_cell(const BoxL<R>& bx, int q, int& a, int& 
 }
 
 // stage the box: fields (electrons) and zeroed accumulators (nj planes)
-template <int NTH, typename R, bool FIELDS, bool MC = false>
-__device__ void stage_box(const G3& g, const F3<R>& f, const BoxL<R>& bx, int nj)
+template <int NTH, bool FIELDS, bool MC = false, typename R, int FP>
+__device__ void stage_box(const G3& g, const F3<R>& f, const BoxL<R, FP>& bx, int nj)
 {
     const int L = bx.ext[0] * bx.ext[1] * bx.ext[2];
     for (int q = threadIdx.x; q < L; q += NTH) {
@@ -1375,15 +1376,15 @@ __device__ void stage_box(const G3& g, const F3<R>& f, const BoxL<R>& bx, int nj
                 }
             }
 #pragma unroll
-            for (int cc = 0; cc < 6; cc++) bx.f[cc * bx.nf + a + BPX * b + FPL * c] = v[cc];
+            for (int cc = 0; cc < 6; cc++) bx.f[cc * bx.nf + a + BPX * b + FP * c] = v[cc];
         }
         for (int cc = 0; cc < nj; cc++) bx.j[cc * bx.n + t] = typename Acc3<R>::T(0);
     }
 }
 
 // add the box's accumulators to the FP64 current (planes c0 .. c0 + nj - 1 of J)
-template <int NTH, typename R>
-__device__ void flush_box(const G3& g, const F3<R>& f, const BoxL<R>& bx, int c0, int nj, double jq)
+template <int NTH, typename R, int FP>
+__device__ void flush_box(const G3& g, const F3<R>& f, const BoxL<R, FP>& bx, int c0, int nj, double jq)
 {
     const int L = bx.ext[0] * bx.ext[1] * bx.ext[2];
     for (int q = threadIdx.x; q < L; q += NTH) {
@@ -1451,8 +1452,8 @@ __device__ __forceinline__ void grow(int nb[6], int a, int c)
 // staged box (LDS, one thread a particle) or on the fields and current in HBM (the 64 lanes of a
 // wave share the particle p).  The staged form returns false, leaving the particle untouched,
 // when its cell lies outside the box.
-template <bool LDS, bool MC, typename R>
-__device__ __forceinline__ bool electron3(const G3& g, const F3<R>& f, const BoxL<R>& bx, const E3<R>& e, int p,
+template <bool LDS, bool MC, typename R, int FP>
+__device__ __forceinline__ bool electron3(const G3& g, const F3<R>& f, const BoxL<R, FP>& bx, const E3<R>& e, int p,
                                           const Push3& pp, double js, int* status, int nb[6])
 {
     const R w = e.w[p];
@@ -1542,8 +1543,8 @@ __device__ __forceinline__ bool electron3(const G3& g, const F3<R>& f, const Box
     return true;
 }
 
-template <typename R>
-__device__ __forceinline__ void box_of(const Box3& bb, int pz, BoxL<R>& bx, bool& lds)
+template <typename R, int FP>
+__device__ __forceinline__ void box_of(const Box3& bb, int pz, BoxL<R, FP>& bx, bool& lds)
 {
 #pragma unroll
     for (int a = 0; a < 3; a++) {
@@ -1551,7 +1552,7 @@ __device__ __forceinline__ void box_of(const Box3& bb, int pz, BoxL<R>& bx, bool
         bx.ext[a] = bb.hi[a] - bb.lo[a] + 6;
     }
     bx.n = BPL * pz;
-    bx.nf = FPL * pz;
+    bx.nf = FP * pz;
     lds = bx.ext[0] <= BPX && bx.ext[1] <= BPY && bx.ext[2] <= pz;
 }
 
@@ -1559,8 +1560,8 @@ __device__ __forceinline__ void box_of(const Box3& bb, int pz, BoxL<R>& bx, bool
 // axis that is too long, the longest window that fits, centred on the particles' mean position.
 // A tile of 4 rows leaves one row of slack, so a few particles that left it on either side are
 // enough to get here; nearly all are still inside the window.
-template <typename R>
-__device__ void clamp_box(const E3<R>& e, const Seg3& sg, const Box3& bb, int pz, BoxL<R>& bx, double* red)
+template <typename R, int FP>
+__device__ void clamp_box(const E3<R>& e, const Seg3& sg, const Box3& bb, int pz, BoxL<R, FP>& bx, double* red)
 {
     const int cap[3] = {BPX, BPY, pz};
     double m[4] = {0.0, 0.0, 0.0, 0.0};
@@ -1593,7 +1594,7 @@ __device__ void clamp_box(const E3<R>& e, const Seg3& sg, const Box3& bb, int pz
 // segment that outgrew the pitches stages the window clamp_box chooses and lists only the
 // particles outside it; sending such segments to HBM whole cost 4.9 of 24 ms per step on
 // 128x128x1024 cells with the laser at its peak, and 1.97 of 2.7 ms on 61x45x203.
-template <typename R, bool MC>
+template <typename R, bool MC, int FP>
 __global__ void __launch_bounds__(GT) k3_gpd(G3 g, F3<R> f, E3<R> e, const Seg3* __restrict__ seg,
                                              const Box3* __restrict__ bin, Box3* __restrict__ bout, Push3 pp, int pz,
                                              int* status, int2* mis, int* nmis)
@@ -1605,7 +1606,7 @@ __global__ void __launch_bounds__(GT) k3_gpd(G3 g, F3<R> f, E3<R> e, const Seg3*
     const Box3 bb = bin[blockIdx.x];
     int nb[6] = {INT_MAX, INT_MIN, INT_MAX, INT_MIN, INT_MAX, INT_MIN};
     if (sg.count > 0 && bb.lo[0] <= bb.hi[0] && bb.lo[1] <= bb.hi[1] && bb.lo[2] <= bb.hi[2]) {
-        BoxL<R> bx;
+        BoxL<R, FP> bx;
         bool lds;
         box_of(bb, pz, bx, lds);
         if (!lds) clamp_box(e, sg, bb, pz, bx, redd);
@@ -1620,7 +1621,7 @@ __global__ void __launch_bounds__(GT) k3_gpd(G3 g, F3<R> f, E3<R> e, const Seg3*
             const double bound = fmax(fabs(pp.jk[0]), fmax(fabs(pp.jk[1]), fabs(pp.jk[2]))) * sw;
             if (bound > 0.0) { js = FX_RANGE / bound; jq = bound / FX_RANGE; }
         }
-        stage_box<GT, R, true, MC>(g, f, bx, 3);
+        stage_box<GT, true, MC>(g, f, bx, 3);
         __syncthreads();
         for (int p = sg.start + threadIdx.x; p < end; p += GT)
             if (!electron3<true, MC>(g, f, bx, e, p, pp, js, status, nb)) mis[atomicAdd(nmis, 1)] = make_int2(blockIdx.x, p);
@@ -1639,7 +1640,7 @@ template <typename R, bool MC>
 __global__ void __launch_bounds__(NT) k3_gpd_hbm(G3 g, F3<R> f, E3<R> e, Box3* __restrict__ bout, Push3 pp,
                                                  int* status, const int2* mis, const int* nmis)
 {
-    const BoxL<R> none{};
+    const BoxL<R, BOX_FPL> none{};
     const int nm = *nmis, nw = gridDim.x * (NT / 64), lane = threadIdx.x & 63;
     for (int i = __builtin_amdgcn_readfirstlane(blockIdx.x * (NT / 64) + threadIdx.x / 64); i < nm; i += nw) {
         int nb[6] = {INT_MAX, INT_MIN, INT_MAX, INT_MIN, INT_MAX, INT_MIN};
@@ -1667,7 +1668,7 @@ __global__ void __launch_bounds__(GTI, 4) k3_gpi(G3 g, F3<R> f, I3<R> ion, const
     const Box3 bb = bin[blockIdx.x];
     int nb[6] = {INT_MAX, INT_MIN, INT_MAX, INT_MIN, INT_MAX, INT_MIN};
     if (sg.count > 0 && bb.lo[0] <= bb.hi[0] && bb.lo[1] <= bb.hi[1] && bb.lo[2] <= bb.hi[2]) {
-        BoxL<R> bx;
+        BoxL<R, BOX_FPL> bx;
         bool lds;
         box_of(bb, pz, bx, lds);
         bx.j = reinterpret_cast<typename Acc3<R>::T*>(smem3);
@@ -1682,7 +1683,7 @@ __global__ void __launch_bounds__(GTI, 4) k3_gpi(G3 g, F3<R> f, I3<R> ion, const
                 const double bound = fabs(pp.jk[2]) * sw;
                 if (bound > 0.0) { js = FX_RANGE / bound; jq = bound / FX_RANGE; }
             }
-            stage_box<GTI, R, false>(g, f, bx, 1);
+            stage_box<GTI, false>(g, f, bx, 1);
             __syncthreads();
         }
         // the next ion's state is loaded while the current one deposits, so each iteration
@@ -2689,23 +2690,30 @@ void launch3_rho(const G3& g, const E3<R>& e, int ne, const I3<R>& ion, int ni, 
 
 template <typename R, bool MC>
 void gpd_launch(const G3& g, const F3<R>& f, const E3<R>& e, const Seg3* seg, const Box3* bin, Box3* bout,
-                int nseg, const Push3& pp, int pz, int* status, int* nmis, int2* mis, hipStream_t s)
+                int nseg, const Push3& pp, int pz, bool dense, int* status, int* nmis, int2* mis, hipStream_t s)
 {
-    const size_t lds = (size_t)box_plane_bytes<R>() * pz;
-    (void)hipFuncSetAttribute((const void*)k3_gpd<R, MC>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((k3_gpd<R, MC>), dim3(nseg), dim3(GT), lds, s, g, f, e, seg, bin, bout, pp, pz, status, mis,
-                       nmis);
+    const int lds = (dense ? box_plane_bytes<R, BOX_PL>() : box_plane_bytes<R, BOX_FPL>()) * pz;
+    auto launch = [&](auto kernel) {
+        (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipLaunchKernelGGL(kernel, dim3(nseg), dim3(GT), lds, s, g, f, e, seg, bin, bout, pp, pz, status, mis, nmis);
+    };
+    if constexpr (sizeof(R) == 4) {
+        if (dense) launch(k3_gpd<R, MC, BOX_PL>);
+        else launch(k3_gpd<R, MC, BOX_FPL>);
+    } else {
+        launch(k3_gpd<R, MC, BOX_FPL>);
+    }
     hipLaunchKernelGGL((k3_gpd_hbm<R, MC>), dim3(std::min(HBM_GRID, nseg)), dim3(NT), 0, s, g, f, e, bout, pp, status,
                        mis, nmis);
 }
 
 template <typename R>
 void launch3_gpd(const G3& g, const F3<R>& f, const E3<R>& e, const Seg3* seg, const Box3* bin, Box3* bout,
-                 int nseg, const Push3& pp, int pz, int* status, int* nmis, int2* mis, bool mc, hipStream_t s)
+                 int nseg, const Push3& pp, int pz, bool dense, int* status, int* nmis, int2* mis, bool mc, hipStream_t s)
 {
     if (nseg <= 0) return;
-    if (mc) gpd_launch<R, true>(g, f, e, seg, bin, bout, nseg, pp, pz, status, nmis, mis, s);
-    else gpd_launch<R, false>(g, f, e, seg, bin, bout, nseg, pp, pz, status, nmis, mis, s);
+    if (mc) gpd_launch<R, true>(g, f, e, seg, bin, bout, nseg, pp, pz, dense, status, nmis, mis, s);
+    else gpd_launch<R, false>(g, f, e, seg, bin, bout, nseg, pp, pz, dense, status, nmis, mis, s);
 }
 
 // ---- momentum-conserving gather: fields to the nodes ---------------------------------------------
@@ -2834,7 +2842,7 @@ void launch3_stations(const G3& g, const F3<R>& f, const double* zlab, int nst, 
                                  int, double, double, double, double*, hipStream_t);                       \
     template void launch3_count_live<R>(const R*, int, int*, hipStream_t);                                  \
     template void launch3_gpd<R>(const G3&, const F3<R>&, const E3<R>&, const Seg3*, const Box3*, Box3*, int,  \
-                                 const Push3&, int, int*, int*, int2*, bool, hipStream_t);                  \
+                                 const Push3&, int, bool, int*, int*, int2*, bool, hipStream_t);            \
     template void launch3_nodes<R>(const G3&, const F3<R>&, hipStream_t);                                   \
     template void launch3_gpi<R>(const G3&, const F3<R>&, const I3<R>&, const Seg3*, const Box3*, Box3*, int,  \
                                  double, double, double, const Push3&, int, hipStream_t);                   \

@@ -868,13 +868,24 @@ __global__ void __launch_bounds__(FT_NT) k3_filt3(G3 g, Lines3<double, TO> L, Fi
 // along x, y and z in LDS, three barriers in all, at the price of (1 + 2 RC / FB)^3 loads a cell.
 // Row, column or plane N of the staged cube holds the raw values just past the component's range
 // on its own axis (the copied cells), when they fall in the cube.  Bound by latency up to one
-// round of resident workgroups, then by the LDS passes.  Box against ring kernel with 4 passes and
-// compensation, PML of 8: 12 / 48 us on 12x10x48 cells, 43 / 49 us on 48x48x48 and 61 / 49 us on
-// 64x64x48 in FP64; 36 / 45 us on 64x64x48 and 58 / 45 us on 64x64x96 in FP32.  With 2 passes:
-// 23 / 25 us on 48x48x48 and 33 / 25 us on 64x64x48, FP32 22 / 24 and 33 / 26 us.
+// round of resident workgroups, then by the LDS passes.  Ring against box kernel at reach 5: 48 / 28
+// us on 53x55x54 periodic cells in FP64, 42 / 30 us on 109x103x30 stored cells with layers in FP32.
 constexpr int FB = 8, FB_NT = 256;
-// cubes (three components) up to which this is the faster kernel
-template <typename R> constexpr long fb_max() { return sizeof(R) == 4 ? 3500 : 2300; }
+// Cubes (three components) up to which the box kernel is the faster one, for each reach: the ring
+// kernel walks its planes in the same time whatever the reach leaves idle, while the box kernel's
+// workgroups grow with the reach and fewer fit a CU.  Ring / box in us just below and above the line,
+// periodic, over grids of 13x15 to 157x159 stored cells across:
+//   FP32  reach 1: 13.2 / 13.2 at 2400 cubes, 13.4 / 14.0 at 2484    FP64  1: 14.6 / 14.6 at 2484
+//         2: 18.6 / 18.0 at 3000, 19.0 / 20.5 at 3492                      2: 21.0 / 18.9 at 2484
+//         3: 24.0 / 24.4 at 2988, 23.6 / 22.7 at 2730                      3: 24.7 / 24.7 at 2016, 24.5 / 26.3 at 2184
+//         4: 31.8 / 31.0 at 3000, 31.5 / 36.2 at 3492                      4: 35.8 / 33.0 at 1638, 34.1 / 40.8 at 2184
+//         5: 41.4 / 41.8 at 3492, 41.3 / 43.6 at 3600                      5: 50.1 / 45.8 at 2184, 46.4 / 49.1 at 2400
+//         6: 59.9 / 49.7 at 2730, 50.3 / 54.4 at 2940                      6: 57.9 / 54.0 at 1029, 62.5 / 65.3 at 1470
+template <int RC, typename R> constexpr long fb_max()
+{
+    constexpr long f32[6] = {2450, 3200, 2900, 3100, 3500, 2800}, f64[6] = {2300, 2300, 2000, 1650, 2300, 1100};
+    return sizeof(R) == 4 ? f32[RC - 1] : f64[RC - 1];
+}
 
 template <int RC, typename T>
 __global__ void __launch_bounds__(FB_NT) k3_filt_box(G3 g, Lines3<double, T> L, FiltStencil st, int ntx, int nty, int ntz)
@@ -2564,7 +2575,7 @@ bool filt3(const G3& g, const F3<R>& f, const FiltStencil& st, hipStream_t s)
         L.out[c] = f.Jf[c];
     }
     const int nb[3] = {(g.S[0] + FB - 1) / FB, (g.S[1] + FB - 1) / FB, (g.S[2] + FB - 1) / FB};
-    if (3l * nb[0] * nb[1] * nb[2] <= fb_max<R>()) {
+    if (3l * nb[0] * nb[1] * nb[2] <= fb_max<RC, R>()) {
         hipLaunchKernelGGL((k3_filt_box<RC, R>), dim3(3u * nb[0] * nb[1] * nb[2]), dim3(FB_NT), 0, s, g, L, st, nb[0], nb[1],
                            nb[2]);
         return true;

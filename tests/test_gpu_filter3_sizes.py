@@ -47,3 +47,37 @@ def test_3d_filter_around_the_size_line_matches_oracle(real, geom, above):
     for n in NAMES:
         a, b = sim.field(n), ref.field(n)
         assert np.abs(a - b).max() <= tol * max(np.abs(b).max(), 1.0), (n, float(np.abs(a - b).max()))
+
+
+# the line for each other reach
+LINES = {"f32": {1: 2450, 2: 3200, 3: 2900, 4: 3100, 6: 2800}, "f64": {1: 2300, 2: 2300, 3: 2000, 4: 1650, 6: 1100}}
+
+
+@gpu
+@pytest.mark.parametrize("above", [0, 1])
+@pytest.mark.parametrize("reach", [1, 2, 3, 4, 6])
+@pytest.mark.parametrize("real", ["f64", "f32"])
+def test_3d_filter_around_the_size_line_of_its_reach_matches_oracle(real, reach, above):
+    layers = LINES[real][reach] // (3 * 20) + above
+    comp = int(reach > 2)
+    nx, ny, nz = 35 - 9, 29 - 9, 8 * layers - 3 - 9
+    d = (0.1, 0.12, 0.09)
+    cfg = pi.make_config3(nx, ny, nz, *d, pml_cells=4, ck="ck2", theta=0.2, filter_npass=reach - comp,
+                          filter_compensate=comp, real=real, seed=21)
+    from paper_1009_2727_amd import Sim
+    sim = Sim(cfg, capacity=6000)
+    ref = Oracle3(cfg)
+    for k, name in enumerate(["Ex", "Ey", "Ez", "Bx", "By", "Bz"]):
+        f = pi.random_field(ref.shape, seed=700 + k, amp=0.4)
+        ref.set_field(name, f)
+        sim.set_field(name, f)
+    p = pi.random_electrons3(4000, nx, ny, nz, d, seed=23, umax=3.0, margin=1.5)
+    ref.set_electrons(p)
+    sim.load_electrons(p)
+    ref.step(1)
+    sim.step(1)
+    assert sim.sync_status() == 0
+    tol = 1e-11 if real == "f64" else 2e-6
+    for n in NAMES:
+        a, b = sim.field(n), ref.field(n)
+        assert np.abs(a - b).max() <= tol * max(np.abs(b).max(), 1.0), (n, float(np.abs(a - b).max()))

@@ -1085,21 +1085,13 @@ struct Move3 {
 // Esirkepov's 3D deposit of a move:
 //   W_C = DS_C (S0_A1 S0_A2 + DS_A1 S0_A2 / 2 + S0_A1 DS_A2 / 2 + DS_A1 DS_A2 / 3),
 //   J_C(node + 1/2) - J_C(node - 1/2) = k_C W_C   (k_C = -q w / (d_A1 d_A2 dt))
-// here node m1 of the window along A1, (C, A1, A2) cyclic, and nodes m0 .. m0 + NC - 1 along C
+// here nodes m10 .. m11 - 1 of the window along A1, (C, A1, A2) cyclic, and m0 .. m0 + NC - 1 along C
 template <int C, int NC>
-__device__ __forceinline__ void esirkepov3_row(const G3& g, double* const* J, const Move3& mv, double k, int m1,
-                                               int m0)
+__device__ __forceinline__ void esirkepov3_rows(const G3& g, double* const* J, const Move3& mv, double k, int m10,
+                                                int m11, int m0)
 {
     constexpr int A1 = (C + 1) % 3, A2 = (C + 2) % 3;
-    const int s1 = sidx(g, A1, mv.base[A1] + m1);
-    if (k == 0.0 || s1 < 0) return;
-    double sa = 0.0, da = 0.0;
-#pragma unroll
-    for (int m = 0; m < 5; m++)
-        if (m == m1) {
-            sa = mv.S0[A1][m];
-            da = mv.DS[A1][m];
-        }
+    if (k == 0.0) return;
     int sc[NC];
     double kp[NC], pd = 0.0;
 #pragma unroll
@@ -1111,21 +1103,33 @@ __device__ __forceinline__ void esirkepov3_row(const G3& g, double* const* J, co
     }
 #pragma unroll
     for (int n = 0; n < NC; n++) sc[n] = sidx(g, C, mv.base[C] + m0 + n);
+#pragma unroll 1
+    for (int m1 = m10; m1 < m11; m1++) {
+        const int s1 = sidx(g, A1, mv.base[A1] + m1);
+        if (s1 < 0) continue;
+        double sa = 0.0, da = 0.0;
 #pragma unroll
-    for (int m2 = 0; m2 < 5; m2++) {
-        const int s2 = sidx(g, A2, mv.base[A2] + m2);
-        const double T = sa * (mv.S0[A2][m2] + 0.5 * mv.DS[A2][m2]) +
-                         da * (0.5 * mv.S0[A2][m2] + mv.DS[A2][m2] * (1.0 / 3.0));
-        if (s2 < 0 || T == 0.0) continue;
+        for (int m = 0; m < 5; m++)
+            if (m == m1) {
+                sa = mv.S0[A1][m];
+                da = mv.DS[A1][m];
+            }
 #pragma unroll
-        for (int n = 0; n < NC; n++) {
-            const double v = kp[n] * T;
-            if (v == 0.0 || sc[n] < 0) continue;
-            int q[3];
-            q[C] = sc[n];
-            q[A1] = s1;
-            q[A2] = s2;
-            atomicAdd(&J[C][o3(g, q[0], q[1], q[2])], v);
+        for (int m2 = 0; m2 < 5; m2++) {
+            const int s2 = sidx(g, A2, mv.base[A2] + m2);
+            const double T = sa * (mv.S0[A2][m2] + 0.5 * mv.DS[A2][m2]) +
+                             da * (0.5 * mv.S0[A2][m2] + mv.DS[A2][m2] * (1.0 / 3.0));
+            if (s2 < 0 || T == 0.0) continue;
+#pragma unroll
+            for (int n = 0; n < NC; n++) {
+                const double v = kp[n] * T;
+                if (v == 0.0 || sc[n] < 0) continue;
+                int q[3];
+                q[C] = sc[n];
+                q[A1] = s1;
+                q[A2] = s2;
+                atomicAdd(&J[C][o3(g, q[0], q[1], q[2])], v);
+            }
         }
     }
 }
@@ -1134,7 +1138,7 @@ __device__ __forceinline__ void esirkepov3_row(const G3& g, double* const* J, co
 __device__ void esirkepov3_z(const G3& g, double* const* J, const double r0[3], const double r1[3], double kz)
 {
     const Move3 mv(r0, r1);
-    for (int m1 = 0; m1 < 5; m1++) esirkepov3_row<2, 4>(g, J, mv, kz, m1, 0);
+    esirkepov3_rows<2, 4>(g, J, mv, kz, 0, 5, 0);
 }
 
 // the whole deposit by the 64 lanes of a wave (r0, r1, k the same in every lane): four lanes, one
@@ -1144,9 +1148,9 @@ __device__ __forceinline__ void esirkepov3_wave(const G3& g, double* const* J, c
 {
     const Move3 mv(r0, r1);
     const int lane = threadIdx.x & 63, row = (lane >> 2) % 5, m = lane & 3, c = lane / 20;
-    if (c == 0) esirkepov3_row<0, 1>(g, J, mv, k[0], row, m);
-    else if (c == 1) esirkepov3_row<1, 1>(g, J, mv, k[1], row, m);
-    else if (c == 2) esirkepov3_row<2, 1>(g, J, mv, k[2], row, m);
+    if (c == 0) esirkepov3_rows<0, 1>(g, J, mv, k[0], row, row + 1, m);
+    else if (c == 1) esirkepov3_rows<1, 1>(g, J, mv, k[1], row, row + 1, m);
+    else if (c == 2) esirkepov3_rows<2, 1>(g, J, mv, k[2], row, row + 1, m);
 }
 
 template <typename R>
@@ -1744,14 +1748,17 @@ __global__ void __launch_bounds__(GTI, 4) k3_gpi(G3 g, F3<R> f, I3<R> ion, const
 // laser antenna: per transverse cell a + particle fixed at the cell centre and a - particle
 // moving along the polarisation (x or y) with the sheet current K = -2 E_perp (FP64
 // throughout); xm holds the moving particle's coordinate along the polarisation.  AT threads share
-// a pair, one for each current component and node along one of its transverse axes: one thread
-// per pair is a chain of up to 600 adds, 40 us on 12 x 10 and 61 x 45 cells against 13 and 19 us
-// (128 x 128 cells: 50 us against 69 us, each thread repeating the pair's shape factors).
-constexpr int AT = 15, AP = 16;          // threads of a pair, pairs of a workgroup
-template <typename R>
-__global__ void __launch_bounds__(AT * AP) k3_antenna(G3 g, F3<R> f, double* xm, const double* xh, const double* yh,
+// a pair: 15, one for each current component and node along one of its transverse axes, on small
+// grids, where one thread per pair is a chain of up to 600 adds (24x24x1024 cells 44 -> 13 us, 80x80x1024
+// 41 -> 35 us); one on large grids, which the pairs fill by themselves while 15 threads each repeat the
+// shape factors (92x92x1024 cells 45 -> 41 us, 128x128x1024 81 -> 49 us).
+constexpr int ANTENNA_SHARED = 8000;     // pairs up to which 15 threads share one
+template <int AT> constexpr int antenna_pairs() { return AT == 1 ? 64 : 16; }   // of a workgroup
+template <typename R, int AT>
+__global__ void __launch_bounds__(AT * antenna_pairs<AT>()) k3_antenna(G3 g, F3<R> f, double* xm, const double* xh, const double* yh,
                                                       Antenna3 a, Push3 pp)
 {
+    constexpr int AP = antenna_pairs<AT>();
     const int part = (int)threadIdx.x / AP, q = blockIdx.x * AP + (int)threadIdx.x % AP;
     double x1 = 0.0;
     if (q < a.n) {
@@ -1770,16 +1777,23 @@ __global__ void __launch_bounds__(AT * AP) k3_antenna(G3 g, F3<R> f, double* xm,
         const double h0[3] = {xh[q], yh[q], a.za}, h1[3] = {xh[q], yh[q], a.zb};
         const double kp[3] = {-km[0], -km[1], -km[2]};                           // q = +1
         const Move3 mm(m0, m1), mh(h0, h1);
-        const int row = part % 5;
-        if (part < 5) {
-            esirkepov3_row<0, 4>(g, f.J, mm, km[0], row, 0);
-            esirkepov3_row<0, 4>(g, f.J, mh, kp[0], row, 0);
-        } else if (part < 10) {
-            esirkepov3_row<1, 4>(g, f.J, mm, km[1], row, 0);
-            esirkepov3_row<1, 4>(g, f.J, mh, kp[1], row, 0);
+        auto component = [&](auto c, int row, int end) {
+            constexpr int C = decltype(c)::value;
+            esirkepov3_rows<C, 4>(g, f.J, mm, km[C], row, end, 0);
+            esirkepov3_rows<C, 4>(g, f.J, mh, kp[C], row, end, 0);
+        };
+        const std::integral_constant<int, 0> x;
+        const std::integral_constant<int, 1> y;
+        const std::integral_constant<int, 2> z;
+        if constexpr (AT == 1) {
+            component(x, 0, 5);
+            component(y, 0, 5);
+            component(z, 0, 5);
         } else {
-            esirkepov3_row<2, 4>(g, f.J, mm, km[2], row, 0);
-            esirkepov3_row<2, 4>(g, f.J, mh, kp[2], row, 0);
+            const int row = part % 5;
+            if (part < 5) component(x, row, row + 1);
+            else if (part < 10) component(y, row, row + 1);
+            else component(z, row, row + 1);
         }
     }
     __syncthreads();                     // every thread of the pair has read xm
@@ -2776,7 +2790,11 @@ void launch3_antenna(const G3& g, const F3<R>& f, double* xm, const double* xh, 
                      const Antenna3& a, const Push3& pp, hipStream_t s)
 {
     if (a.n <= 0) return;
-    hipLaunchKernelGGL((k3_antenna<R>), dim3((a.n + AP - 1) / AP), dim3(AT * AP), 0, s, g, f, xm, xh, yh, a, pp);
+    auto launch = [&](auto kernel, int threads, int pairs) {
+        hipLaunchKernelGGL(kernel, dim3((a.n + pairs - 1) / pairs), dim3(threads * pairs), 0, s, g, f, xm, xh, yh, a, pp);
+    };
+    if (a.n <= ANTENNA_SHARED) launch(k3_antenna<R, 15>, 15, antenna_pairs<15>());
+    else launch(k3_antenna<R, 1>, 1, antenna_pairs<1>());
 }
 
 template <typename R>

@@ -378,3 +378,19 @@ def test_3d_vacuum_rows_in_the_smallest_tiles_match_oracle(real, tol):
         assert sim.sync_status() == 0
         compare_fields3(sim, ref, tol)
     assert sim.info()["shift"] > 0
+
+
+@gpu
+@pytest.mark.parametrize("nx,ny", [(89, 89), (90, 89)])
+@pytest.mark.parametrize("pol", [0, 1])
+def test_3d_antenna_on_either_side_of_its_split_matches_oracle(pol, nx, ny):
+    # 7921 pairs have 15 threads each, 8010 one thread each
+    w = pi.small_boosted3(real="f64", nx=nx, ny=ny, nz=30, ppc=1)
+    w["config"].update(pml_cells=4)
+    w["laser"].update(pol=pol, t_peak_fs=2.67)
+    sim, ref = _sim(w, plasma=False), Oracle3.from_workload(w, plasma=False)
+    sim.step(4)
+    ref.step(4)
+    assert sim.sync_status() == 0
+    compare_fields3(sim, ref, 1e-10)
+    np.testing.assert_allclose(sim.antenna(), ref.antenna(), atol=1e-12)

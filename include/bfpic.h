@@ -256,13 +256,16 @@ enum {
 };
 #define BF_PARTICLE_BLOCK 65536
 
-/* phases of one bf_step (BF_DIAG_TIMERS rows) */
+/* phases of one bf_step (BF_DIAG_TIMERS rows).  A 2D step has the electrons, the ions and the
+   antenna in one launch; with phase_timers it launches them one after another, so that each has
+   its own row, and takes a little longer.  The 2D bilinear filter with stride 1 and a reach of at
+   most 6 cells is one launch with Ampere, whose time is then in the filter's row. */
 enum {
     BF_PHASE_FARADAY = 0,  /* Faraday + Friedman + PML, stations, clearing the current      */
     BF_PHASE_PUSH,         /* electrons: gather, push, deposit                              */
     BF_PHASE_IONS,         /* rigid-ion current                                             */
     BF_PHASE_ANTENNA,      /* laser antenna current                                         */
-    BF_PHASE_FILTER,       /* current filter                                                */
+    BF_PHASE_FILTER,       /* current filter (2D, stride 1: and Ampere + PML)               */
     BF_PHASE_AMPERE,       /* Ampere + PML                                                  */
     BF_PHASE_WINDOW,       /* window shift and plasma injection                             */
     BF_PHASE_SORT,         /* tile sort                                                     */

@@ -779,13 +779,21 @@ bf_status step_impl(bf_sim* s, int nsteps)
             }
         }
         if (!rb) {
-            // with phase timers the ions and the antenna are launched, and timed, by themselves
+            // with phase timers the electrons, the ions and the antenna are launched, and timed, each by
+            // itself
             if (c.phase_timers) {
                 launch_particles<R>(g, f, ep, SourceParams<R>{}, c.gather_kind == 1, s->stream);
                 s->tock(t_ph, BF_PHASE_PUSH);
                 t_ph = s->tick();
-                launch_sources<R>(g, f, sp, s->stream);
+                SourceParams<R> part = sp;
+                part.ap.active = 0;
+                launch_sources<R>(g, f, part, s->stream);
                 s->tock(t_ph, BF_PHASE_IONS);
+                t_ph = s->tick();
+                part = sp;
+                part.nion = 0;
+                launch_sources<R>(g, f, part, s->stream);
+                s->tock(t_ph, BF_PHASE_ANTENNA);
             } else {
                 launch_particles<R>(g, f, ep, sp, c.gather_kind == 1, s->stream);
             }

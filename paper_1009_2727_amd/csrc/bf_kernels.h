@@ -244,7 +244,7 @@ void launch_nodes(const Geo& g, const FieldSet<R>& f, hipStream_t s);
 template <typename R>
 void launch_particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
                       bool mc, hipStream_t s);
-// the sources alone (batched runs, whose electrons have their own launch)
+// the sources alone (steps with phase timers, and runs without electrons)
 template <typename R>
 void launch_sources(const Geo& g, const FieldSet<R>& f, SourceParams<R> sp, hipStream_t s);
 // the window's advance (null: none) and the plasma rows of ip (ip.nrows 0: none), in one launch

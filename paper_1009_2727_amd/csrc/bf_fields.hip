@@ -231,7 +231,8 @@ __global__ void __launch_bounds__(256) k_filter_ampere(Geo g, FieldSet<R> f, Pml
     constexpr int AX = TX + 2 * RC, AZ = TZ + 2 * RC, NQ = TX * TZ / 256;
     __shared__ R sA[3][AZ * AX];
     __shared__ R sB[3][AZ * TX];
-    __shared__ int ci[2][AX], ri[2][AZ];   // column and row of each staged position under the continuation
+    __shared__ int ci[2][AX];              // column of each staged position under the continuation
+    __shared__ long ri[2][AZ];             // offset of its row
     __shared__ R cs[2][AX], rs[2][AZ];     // ... and its sign; [0]: the component that ends a half node early
     const int x0 = (int)blockIdx.x * TX, z0 = (int)blockIdx.y * TZ;
     // last filtered position of J_x, J_y, J_z along x and z
@@ -248,8 +249,7 @@ __global__ void __launch_bounds__(256) k_filter_ampere(Geo g, FieldSet<R> f, Pml
             cs[h][a] = (R)sg;
         } else {
             const int h = (q - 2 * AX) / AZ, b = (q - 2 * AX) % AZ;
-            ri[h][b] = filt_pos(z0 - RC + b, g.Sz, hz[2 - 2 * h], g.perz, sg);
-            ri[h][b] = prow(g, ri[h][b]) * g.pitch;
+            ri[h][b] = gofs(g, 0, filt_pos(z0 - RC + b, g.Sz, hz[2 - 2 * h], g.perz, sg));
             rs[h][b] = (R)sg;
         }
     }
@@ -258,7 +258,8 @@ __global__ void __launch_bounds__(256) k_filter_ampere(Geo g, FieldSet<R> f, Pml
 #pragma unroll 4
     for (int q = threadIdx.x; q < AZ * AX; q += 256) {
         const int a = q % AX, b = q / AX;
-        const int i0 = ci[0][a], i1 = ci[1][a], k0 = ri[0][b], k1 = ri[1][b];
+        const int i0 = ci[0][a], i1 = ci[1][a];
+        const long k0 = ri[0][b], k1 = ri[1][b];
         const R x0s = cs[0][a], x1s = cs[1][a], z0s = rs[0][b], z1s = rs[1][b];
         sA[0][q] = x0s * z1s * f.J[0][k1 + i0];
         sA[1][q] = x1s * z1s * f.J[1][k1 + i1];

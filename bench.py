@@ -295,7 +295,7 @@ def bench_scan(args):
     """The batched scan: independent boosted runs of uneven grid, boost, density, time step
     and ppc.  Tiles and sort cadence per run class come from the autotuner.  The same runs are
     timed stepped one after another (one launch per phase and run) and as one batch (one
-    persistent launch per heavy phase for all runs)."""
+    launch per heavy phase for all runs)."""
     import torch
     import pic_inputs as pi
     from paper_1009_2727_amd import Batch, Sim
@@ -726,8 +726,8 @@ def main():
     ap.add_argument("--beam-real", choices=["f32", "f64"], default="f32")
     ap.add_argument("--workload", choices=["c3", "c2", "c4", "c5", "dtscan", "pml", "beam"], default="c3",
                     help="c3: the 3D 128x128x1024 boosted run (default, with c2 beside it); c2: the 256x4096 "
-                         "boosted run; c4: the batched scan of independent boosted runs (persistent batched "
-                         "launch vs one run at a time); c5: learned vs plain current filter; dtscan: "
+                         "boosted run; c4: the batched scan of independent boosted runs (batched "
+                         "launches vs one run at a time); c5: learned vs plain current filter; dtscan: "
                          "instability growth rate against the time step for both gathers")
     ap.add_argument("--cpu-steps3", type=int, default=8)
     ap.add_argument("--c4-runs", type=int, default=64)

@@ -5,8 +5,9 @@ how far particles drift across tiles between sorts and how much work a tile hold
 class the tuner times a few steps of a trial run (the class's first workload, its grid capped
 to keep the trial short, plasma pre-loaded) for every candidate tile shape at a fixed sort
 cadence, then every candidate cadence at the best tile, and keeps the fastest pair.  The LDS
-tile of the particle kernel holds a segment's box plus a 5-cell halo within 33 x 31 cells, so
-the candidate tiles stay well inside it.
+tile of the particle kernel holds a segment's box plus a 5-cell halo within 32 x 26 cells in FP32
+(32 x 31 for tiles of 21 cells and more along z, 32 x 21 in FP64), so the candidate tiles stay well
+inside it.
 """
 from __future__ import annotations
 

@@ -16,7 +16,7 @@
 namespace bf {
 
 // sticky status bits
-enum : int { ST_CAPACITY = 1, ST_NONFINITE = 2, ST_SEGMENTS = 4 };
+enum : int { ST_CAPACITY = 1, ST_NONFINITE = 2 };
 
 struct Geo {
     int Nx, Nz;       // interior cells

@@ -343,7 +343,7 @@ void launch_nodes(const Geo& g, const FieldSet<R>& f, hipStream_t s)
     hipLaunchKernelGGL((k_nodes<R>), grid, dim3(256), 0, s, g, f);
 }
 
-// ---- batched runs: one persistent launch per phase over the cell blocks of all runs ---------
+// ---- batched runs: one launch per phase over the cell blocks of all runs ---------------------
 template <typename R>
 __global__ void __launch_bounds__(256) k_faraday_batch(const FaradayDesc<R>* __restrict__ d, QueueRef q)
 {

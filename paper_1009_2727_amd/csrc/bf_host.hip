@@ -1025,7 +1025,7 @@ void layout3(const bf_config* c, Sim3* L)
         L->w_box_i[k] = take(sizeof(bf3::Box3) * L->seg_cap);
     }
     L->w_counts = take(sizeof(int) * L->tl.ntiles);
-    L->w_nmis = take(sizeof(int) * (2 + (size_t)L->seg_cap));   // one is used; the size keeps the layout
+    L->w_nmis = take(sizeof(int) * (2 + (size_t)L->seg_cap));   // one is used; saved work buffers keep their layout
     L->w_mis = take(sizeof(int) * 2 * (size_t)L->cap);
     L->w_cursor = take(sizeof(int) * L->tl.ntiles);
     L->w_pml = take(sizeof(double) * 3 * 2 * 3 * (size_t)(L->g.S[0] + L->g.S[1] + L->g.S[2]));

@@ -158,7 +158,7 @@ struct StationParams {
     int cap;
 };
 
-// ---- batched runs: per-run arguments of the persistent launch of each phase ------------
+// ---- batched runs: per-run arguments of the common launch of each phase ----------------
 constexpr int FARADAY_TX = 32, FARADAY_TZ = 8;   // cells of a Faraday workgroup
 template <typename R>
 struct FaradayDesc {

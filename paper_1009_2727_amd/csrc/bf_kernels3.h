@@ -194,8 +194,8 @@ void launch3_window(const G3& g, const F3<R>& f, const Pml3& pml, int d, hipStre
 // counting sort of the live particles (w != 0) of slots [0, *nused) of src by tile, through dst
 // (scatter by tile into dst, then each tile back into src in plasma-lattice order, ppc
 // particles per lattice cell):
-// segment t = tile t with its cell box, *nused = live count; counts/cursor hold ntiles ints
-// (counts zero before the call and after it), tot one int of scratch.  Ions are binned at z0 - zsh.
+// segment t = tile t with its cell box, *nused = live count; counts/cursor hold ntiles ints of
+// scratch, tot one.  Ions are binned at z0 - zsh.
 template <typename R>
 void launch3_sort_e(const G3& g, const Tiles3& tl, const E3<R>& src, const E3<R>& dst, int* nused, int* counts,
                     int* cursor, int* tot, Seg3* seg, Box3* box, int64_t cap, int ppc, hipStream_t s);

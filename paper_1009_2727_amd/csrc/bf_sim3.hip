@@ -376,12 +376,15 @@ __global__ void __launch_bounds__(NT) k3_ampere(G3 g, F3<R> f, const R* J0, cons
 //  * periodic axes from two passes on: along y and z up to R = 8 n (FP32 1024 x 4096, z, n = 2, R = 16
 //    127 / 121, R = 32 140 / 143), along x, where four consecutive outputs a thread cost bank
 //    conflicts, up to 3 n (n = 2, R = 4 107 / 98, R = 16 127 / 127; FP64 n = 5, R = 20 on 187 x 1531 34 / 34);
-//  * other axes need 8 R cells, or the end segments with their halos outweigh the rest, and
-//    R <= 6 (n - 1): FP32 128x128x256, y, n = 3, R = 12 304 / 285, R = 24 330 / 358; z, n = 2, R = 4
-//    220 / 210, R = 10 259 / 265.  FP64 along y from eight passes on (n = 5, R = 10 516 / 525; n = 10, R = 15
-//    942 / 841).  Along x only where the end segments come free, since the lines are cut anyway or
-//    the launch leaves CUs idle, and up to 5 n / 2 in FP64 (1024 x 4096, n = 3, R = 7 253 / 239, R = 12
-//    262 / 286): 128x128x256 in FP32, n = 4, R = 6 325 / 367, though 1024 x 4096 166 / 143.
+//  * other axes where the launch leaves CUs idle anyway, so that the end segments come free, from 3 R
+//    cells on: along z up to 8 n (FP32 187 x 1531, n = 5, R = 40 49 / 40), along x up to 4 n (n = 5, R = 20
+//    43 / 40);
+//  * elsewhere they need 8 R cells along y and z, or the end segments with their halos outweigh the
+//    rest, and R <= 6 (n - 1): FP32 128x128x256, y, n = 3, R = 12 304 / 285, R = 24 330 / 358; z, n = 2,
+//    R = 4 220 / 210, R = 10 259 / 265.  FP64 along y from eight passes on (n = 5, R = 10 516 / 525; n = 10,
+//    R = 15 942 / 841).  Along x lines that are cut anyway, and up to 5 n / 2 in FP64 (1024 x 4096, n = 3,
+//    R = 7 253 / 239, R = 12 262 / 286): 128x128x256 in FP32, n = 4, R = 6 325 / 367, though 1024 x 4096
+//    166 / 143.
 template <typename TI, typename TO>
 struct Lines3 {
     const TI* in[3];
@@ -2516,10 +2519,11 @@ bool one_stencil(const FiltSeq& fs, int S, int per, long wgs)
     const int n = fs.n, R = fs.reach;
     if (n < 2) return false;
     if (per) return R <= (AX == 0 ? 3 : 8) * n;
-    if (S < 8 * R || R > 6 * (n - 1)) return false;
+    if (S >= 3 * R && (AX == 0 ? wgs < 1024 && R <= 4 * n : wgs < 256 && R <= 8 * n)) return true;
+    if (R > 6 * (n - 1)) return false;
     constexpr bool fp64 = sizeof(T) == 8;
-    if (AX == 0) return (S > 1024 || wgs < 1024) && (!fp64 || 2 * R <= 5 * n);
-    return !(AX == 1 && fp64) || n >= 8;
+    if (AX == 0) return S > 1024 && (!fp64 || 2 * R <= 5 * n);
+    return S >= 8 * R && (!(AX == 1 && fp64) || n >= 8);
 }
 
 // one launch of k3_fline along AX for ncomp components

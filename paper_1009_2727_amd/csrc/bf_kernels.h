@@ -99,8 +99,8 @@ struct AntennaParams {
     int pol;           // 0: the - sheet moves along x (J_x); 1: along y, out of the plane (J_y)
 };
 
-// the electrons of nseg segments.  far: one int per particle slot of scratch, where a segment lists
-// its electrons outside the staged window (in its own slots' range)
+// the electrons of nseg segments.  far, far2: one int per particle slot of scratch each, where a
+// segment lists its electrons outside the staged window (in its own slots' range)
 template <typename R>
 struct ElectronParams {
     ElectronArrays<R> e;
@@ -108,9 +108,9 @@ struct ElectronParams {
     const int4* bbin;
     int4* bbout;
     int nseg;
-    int tile_z;        // cells of a particle tile along z
+    int tile_x, tile_z;   // cells of a particle tile
     PushParams<R> pp;
-    int* far;
+    int *far, *far2;
     int* status;
 };
 
@@ -188,9 +188,9 @@ template <typename R>
 void launch_faraday_batch(const FaradayDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s);
 template <typename R>
 void launch_ampere_batch(const AmpereDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s);
-// tile_z: of the longest particle tile among the runs
+// tile_x, tile_z: of the largest particle tiles among the runs
 template <typename R>
-void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, int tile_z, hipStream_t s);
+void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, int tile_x, int tile_z, hipStream_t s);
 // workgroups of a run's electrons and sources; sets sp.na
 template <typename R>
 int particle_blocks(const ElectronParams<R>& ep, SourceParams<R>& sp);

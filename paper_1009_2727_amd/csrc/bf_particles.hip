@@ -45,12 +45,13 @@ __device__ __forceinline__ double block_sum(double v, double* red)
 constexpr int TPX = 32;                 // row pitch of the staged tile (cells)
 // Rows of the staged tile (6 field planes + 3 current planes of 8 bytes).  FP32 tiles of 26 rows take
 // 39 KB, so that four workgroups fit a CU's LDS; the default tile needs 14 rows, and 12 are left for
-// drift.  Particle tiles of 21 cells and more fill them with their halo and one row of drift, and the
-// launch takes 31 rows, three workgroups a CU: 256 x 2048 cells at 16 particles a cell in tiles of 24
-// cells 1124 -> 433 us a step (tiles of 20 take 397 us with 26 rows, tiles of 21 420 us with 31).
+// drift.  Particle tiles that outgrow the staged one with their halo and a cell of drift take the
+// launch for wide tiles: 31 rows in FP32, three workgroups a CU, and as many windows a segment as its
+// box needs.  256 x 2048 cells at 16 particles a cell in tiles of 24 cells 1124 -> 433 us a step (tiles of
+// 20 take 397 us with 26 rows, tiles of 21 420 us with 31).
 template <typename R> constexpr int trows() { return sizeof(R) == 4 ? 26 : 21; }
-template <typename R> constexpr int trows_tall() { return sizeof(R) == 4 ? 31 : 21; }
-template <typename R> bool tall_tile(int tile_z) { return trows_tall<R>() > trows<R>() && tile_z + 6 > trows<R>(); }
+template <typename R, bool WIDE> constexpr int tile_rows() { return sizeof(R) == 4 && WIDE ? 31 : trows<R>(); }
+template <typename R> bool wide_tile(int tile_x, int tile_z) { return tile_x + 6 > TPX || tile_z + 6 > trows<R>(); }
 // rows of an ion segment's tile, which holds J_z alone: the largest tile (64 cells), its halo and one
 // row of drift.  Ions drift rigidly, so that tiles of 21 cells and more outgrew the electrons' 26 rows
 // whole, and their segments went to global atomics: 256 x 2048 cells at 16 particles a cell in tiles
@@ -557,46 +558,11 @@ __device__ __forceinline__ void far_electron(const Geo& g, const FieldSet<R>& f,
     if (n == 0) store_electron(e, p, st);
 }
 
-// Gather, push and deposit of particle segment s by one workgroup of NTH threads.  Bound by VALU
-// issue on large grids (about 650 instructions per 64 electrons) and by the chain of its phases'
-// latencies on small ones.  Particles outside the staged window are listed (far) and pushed on HBM
-// after the tile: with the global accessors unrolled here for one thread a particle it was 203 KB
-// of code and 168 registers, and cold instruction fetches dominated small launches.
-// Per step: 43 -> 15 us on 75 x 1691 cells at 1 particle a cell, 70 -> 23 us on 64 x 512 at 4 in
-// FP64, 0.425 -> 0.38 ms on 256 x 4096 at 16 (16.8 M electrons, four workgroups per CU).
-template <typename R, bool MC, int NR, int NTH>
-__device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, int s)
+// the fields of the staged window and a zeroed current
+template <typename R, bool MC, int NTH, int NR>
+__device__ __forceinline__ void stage_tile(const Geo& g, const FieldSet<R>& f, const LdsAcc<R, NR>& lds)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];   // 16-byte aligned: FP64 DS ops
-    __shared__ int4 red[NTH / 64];
-    __shared__ double redd[NTH / 64];
-    __shared__ int nfar;
-    const Segment sg = ep.seg[s];
-    const int4 bb = ep.bbin[s];
-    const ElectronArrays<R>& e = ep.e;
-    const PushParams<R>& pp = ep.pp;
-    if (threadIdx.x == 0) nfar = 0;      // a barrier comes before its first use
-    if (sg.count <= 0 || bb.x > bb.y || bb.z > bb.w) {
-        if (threadIdx.x == 0) ep.bbout[s] = make_int4(INT_MAX, INT_MIN, INT_MAX, INT_MIN);
-        return;
-    }
-    const int end = sg.start + sg.count;
-    // the first particle's state travels while the tile is staged
-    int p = sg.start + threadIdx.x;
-    EState<R> nxt{}, done{};
-    if (p < end) nxt = load_electron(e, p);
     using Acc = LdsAcc<R, NR>;
-    Acc lds;
-    lds.xb = bb.x - 2;
-    lds.zb = bb.z - 2;
-    lds.lx = bb.y - bb.x + 6;
-    lds.lz = bb.w - bb.z + 6;
-    lds.f = reinterpret_cast<R*>(smem_raw);
-    constexpr int TCELLS = Acc::TCELLS;
-    using JT = typename Acc::JT;
-    lds.j = reinterpret_cast<JT*>(lds.f + 6 * TCELLS);   // 6 TCELLS elements: 8-byte aligned
-    if (lds.lx > TPX || lds.lz > NR) clamp_window<R, NR, NTH>(e, sg, bb, lds, redd);
-    int x0 = INT_MAX, x1 = INT_MIN, z0 = INT_MAX, z1 = INT_MIN;
     const int L = lds.lz * TPX;
     for (int q = threadIdx.x; q < L; q += NTH) {
         const int a = q % TPX, b = q / TPX;
@@ -617,10 +583,81 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
             }
         }
 #pragma unroll
-        for (int c = 0; c < 6; c++) lds.f[c * TCELLS + q] = v[c];
+        for (int c = 0; c < 6; c++) lds.f[c * Acc::TCELLS + q] = v[c];
 #pragma unroll
-        for (int c = 0; c < 3; c++) lds.j[c * TCELLS + q] = JT(0);
+        for (int c = 0; c < 3; c++) lds.j[c * Acc::TCELLS + q] = typename Acc::JT(0);
     }
+}
+
+// adds the window's current to the grid's
+template <typename R, int NTH, int NR>
+__device__ __forceinline__ void flush_tile(const Geo& g, const FieldSet<R>& f, const LdsAcc<R, NR>& lds, double jq)
+{
+    using Acc = LdsAcc<R, NR>;
+    const int L = lds.lz * TPX;
+    for (int q = threadIdx.x; q < L; q += NTH) {
+        const int a = q % TPX, b = q / TPX;
+        const int i = a < lds.lx ? swrap(lds.xb + a + g.Px, g.Sx, g.perx) : -1;
+        const int k = swrap(lds.zb + b + g.Pz, g.Sz, g.perz);
+        if (i < 0 || k < 0) continue;
+        const long o = gofs(g, i, k);
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            R v;
+            if constexpr (Acc::FIX) v = (R)(fix_value(lds.j[c * Acc::TCELLS + q]) * jq);
+            else v = (R)lds.j[c * Acc::TCELLS + q];
+            if (v != R(0)) atomicAdd(&f.J[c][o], v);
+        }
+    }
+}
+
+// Gather, push and deposit of particle segment s by one workgroup of NTH threads.  Bound by VALU
+// issue on large grids (about 650 instructions per 64 electrons) and by the chain of its phases'
+// latencies on small ones.  Particles outside the staged window are listed (far) and pushed on HBM
+// after the tile: with the global accessors unrolled here for one thread a particle it was 203 KB
+// of code and 168 registers, and cold instruction fetches dominated small launches.
+// Per step: 43 -> 15 us on 75 x 1691 cells at 1 particle a cell, 70 -> 23 us on 64 x 512 at 4 in
+// FP64, 0.425 -> 0.38 ms on 256 x 4096 at 16 (16.8 M electrons, four workgroups per CU).
+// WIDE, for tiles that outgrow the staged one (64 x 64 cells, or 13 x 30): while the list holds more
+// than FAR_FEW particles a window of the whole box, the next window that holds one of them is staged.
+// Tiles of 64 x 64 cells on 112 x 1049 at 16 particles a cell 13.7 -> 2.93 ms a step in FP32, 13 x 30 on
+// 59 x 1861 478 -> 268 us.
+constexpr int FAR_FEW = 64;
+template <typename R, bool MC, bool WIDE, int NTH>
+__device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, int s)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];   // 16-byte aligned: FP64 DS ops
+    __shared__ int4 red[NTH / 64];
+    __shared__ double redd[NTH / 64];
+    __shared__ int nfar;
+    const Segment sg = ep.seg[s];
+    const int4 bb = ep.bbin[s];
+    const ElectronArrays<R>& e = ep.e;
+    const PushParams<R>& pp = ep.pp;
+    if (threadIdx.x == 0) nfar = 0;      // a barrier comes before its first use
+    if (sg.count <= 0 || bb.x > bb.y || bb.z > bb.w) {
+        if (threadIdx.x == 0) ep.bbout[s] = make_int4(INT_MAX, INT_MIN, INT_MAX, INT_MIN);
+        return;
+    }
+    const int end = sg.start + sg.count;
+    // the first particle's state travels while the tile is staged
+    int p = sg.start + threadIdx.x;
+    EState<R> nxt{}, done{};
+    if (p < end) nxt = load_electron(e, p);
+    constexpr int NR = tile_rows<R, WIDE>();
+    using Acc = LdsAcc<R, NR>;
+    Acc lds;
+    lds.xb = bb.x - 2;
+    lds.zb = bb.z - 2;
+    lds.lx = bb.y - bb.x + 6;
+    lds.lz = bb.w - bb.z + 6;
+    lds.f = reinterpret_cast<R*>(smem_raw);
+    constexpr int TCELLS = Acc::TCELLS;
+    using JT = typename Acc::JT;
+    lds.j = reinterpret_cast<JT*>(lds.f + 6 * TCELLS);   // 6 TCELLS elements: 8-byte aligned
+    if (lds.lx > TPX || lds.lz > NR) clamp_window<R, NR, NTH>(e, sg, bb, lds, redd);
+    int x0 = INT_MAX, x1 = INT_MIN, z0 = INT_MAX, z1 = INT_MIN;
+    stage_tile<R, MC, NTH>(g, f, lds);
     double js = 1.0, jq = 1.0;   // current into tile units and back
     if constexpr (Acc::FIX) {
         double sw = fabs((double)nxt.w);
@@ -659,24 +696,48 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
     }
     if (pdone >= 0) store_electron(e, pdone, done);
     __syncthreads();
-    for (int q = threadIdx.x; q < L; q += NTH) {
-        const int a = q % TPX, b = q / TPX;
-        const int i = a < lds.lx ? swrap(lds.xb + a + g.Px, g.Sx, g.perx) : -1;
-        const int k = swrap(lds.zb + b + g.Pz, g.Sz, g.perz);
-        if (i < 0 || k < 0) continue;
-        const long o = gofs(g, i, k);
-#pragma unroll
-        for (int c = 0; c < 3; c++) {
-            R v;
-            if constexpr (Acc::FIX) v = (R)(fix_value(lds.j[c * TCELLS + q]) * jq);
-            else v = (R)lds.j[c * TCELLS + q];
-            if (v != R(0)) atomicAdd(&f.J[c][o], v);
+    flush_tile<R, NTH>(g, f, lds, jq);
+    int n = nfar;                        // the barrier before the flush ordered the list's writes
+    int* far = ep.far + sg.start;
+    if constexpr (WIDE) {
+        // Windows a whole box takes, each of WX x WZ cells of particles.  Each that is staged takes all
+        // listed particles of its part of the box, so as many as there are parts are enough (a position
+        // that is no number belongs to none).
+        constexpr int WX = TPX - 5, WZ = NR - 5;
+        const long windows = (((long)bb.y - bb.x + WX) / WX) * (((long)bb.w - bb.z + WZ) / WZ);
+        int* other = ep.far2 + sg.start;
+        for (long w = 0; w < windows && n > FAR_FEW * windows; w++) {
+            const int first = far[0];
+            lds.xb = bb.x + ((int)floor(e.x[first]) - bb.x) / WX * WX - 2;
+            lds.zb = bb.z + ((int)floor(e.z[first]) - bb.z) / WZ * WZ - 2;
+            lds.lx = TPX;
+            lds.lz = NR;
+            __syncthreads();             // everyone has read nfar and is done with the tile
+            if (threadIdx.x == 0) nfar = 0;
+            stage_tile<R, MC, NTH>(g, f, lds);
+            __syncthreads();
+            for (int i = threadIdx.x; i < n; i += NTH) {
+                const int pl = far[i];
+                EState<R> cur = load_electron(e, pl);
+                const int ix = (int)floor(cur.x), iz = (int)floor(cur.z);
+                if (!lds.inside(ix - 2, ix + 3, iz - 2, iz + 3)) {
+                    other[atomicAdd(&nfar, 1)] = pl;
+                    continue;
+                }
+                advance_electron<MC>(lds, g, pp, cur, js, ep.status, x0, x1, z0, z1);
+                store_electron(e, pl, cur);
+            }
+            __syncthreads();
+            flush_tile<R, NTH>(g, f, lds, jq);
+            int* const t = far;
+            far = other;
+            other = t;
+            n = nfar;
         }
     }
-    // the listed particles (the barrier before the flush ordered the list's writes)
-    if (__builtin_expect(nfar > 0, 0))
-        for (int q = threadIdx.x / 16; q < nfar; q += NTH / 16)
-            far_electron<MC>(g, f, e, pp, ep.status, ep.far[sg.start + q], x0, x1, z0, z1);
+    if (__builtin_expect(n > 0, 0))
+        for (int q = threadIdx.x / 16; q < n; q += NTH / 16)
+            far_electron<MC>(g, f, e, pp, ep.status, far[q], x0, x1, z0, z1);
     block_bbox(x0, x1, z0, z1, red);
     if (threadIdx.x == 0) ep.bbout[s] = make_int4(x0, x1, z0, z1);
 }
@@ -685,11 +746,11 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
 // of 256 leaves two waves per SIMD, so a small grid has too few of them in flight at 256 threads.
 template <typename R> constexpr int gpd_threads() { return sizeof(R) == 4 ? 256 : 512; }
 
-template <typename R, bool MC, int NR>
-__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
+template <typename R, bool MC, bool WIDE>
+__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
     k_gpd(Geo g, FieldSet<R> f, ElectronParams<R> ep)
 {
-    gpd_segment<R, MC, NR, gpd_threads<R>()>(g, f, ep, blockIdx.x);
+    gpd_segment<R, MC, WIDE, gpd_threads<R>()>(g, f, ep, blockIdx.x);
 }
 
 // ---- rigid ions --------------------------------------------------------------------------
@@ -907,12 +968,12 @@ __global__ void __launch_bounds__(NTHR) k_sources(Geo g, FieldSet<R> f, SourcePa
 }
 
 // electrons and sources in one launch (they only add to J)
-template <typename R, bool MC, int NR>
-__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
+template <typename R, bool MC, bool WIDE>
+__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
     k_particles(Geo g, FieldSet<R> f, ElectronParams<R> ep, SourceParams<R> sp)
 {
     const int b = blockIdx.x;
-    if (b < ep.nseg) gpd_segment<R, MC, NR, gpd_threads<R>()>(g, f, ep, b);
+    if (b < ep.nseg) gpd_segment<R, MC, WIDE, gpd_threads<R>()>(g, f, ep, b);
     else source_block<R, gpd_threads<R>()>(g, f, sp, b - ep.nseg);
 }
 
@@ -920,13 +981,13 @@ __global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
 // them out, and the ions of one run fill the tail of its electrons.  16 runs of about 150 x 1600 cells at 10
 // particles a cell: 1.79 ms a step; electrons by a persistent launch over a queue and each run's
 // sources in a launch of its own took 1.84 ms.
-template <typename R, int NR>
-__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? 4 : 1)
+template <typename R, bool WIDE>
+__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
     k_particles_batch(const ParticleDesc<R>* __restrict__ d, QueueRef q)
 {
     const int r = run_of(q, blockIdx.x), b = (int)blockIdx.x - q.off[r];
     const ParticleDesc<R>& D = d[r];
-    if (b < D.e.nseg) gpd_segment<R, false, NR, gpd_threads<R>()>(D.g, D.f, D.e, b);
+    if (b < D.e.nseg) gpd_segment<R, false, WIDE, gpd_threads<R>()>(D.g, D.f, D.e, b);
     else source_block<R, gpd_threads<R>()>(D.g, D.f, D.s, b - D.e.nseg);
 }
 
@@ -1501,15 +1562,16 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_disperse_i(Geo g, IonArra
 }
 
 // ---- launchers ---------------------------------------------------------------------------------
-template <typename R, int NR> constexpr size_t gpd_lds()
+template <typename R, bool WIDE> constexpr size_t gpd_lds()
 {
+    constexpr int NR = tile_rows<R, WIDE>();
     return (size_t)TPX * NR * (6 * sizeof(R) + 3 * sizeof(typename LdsAcc<R, NR>::JT));
 }
 template <typename R> constexpr size_t ion_lds()
 {
     return (size_t)TPX * ION_ROWS * sizeof(typename LdsAcc<R, ION_ROWS>::JT);
 }
-static_assert(ion_lds<float>() <= gpd_lds<float, trows<float>()>() && ion_lds<double>() <= gpd_lds<double, trows<double>()>(),
+static_assert(ion_lds<float>() <= gpd_lds<float, false>() && ion_lds<double>() <= gpd_lds<double, false>(),
               "the ions of a launch with electrons fit its LDS");
 
 template <typename R>
@@ -1534,49 +1596,48 @@ int particle_blocks(const ElectronParams<R>& ep, SourceParams<R>& sp)
     return ep.nseg + sp.nion + sp.na;
 }
 
-template <typename R, bool MC, int NR>
+template <typename R, bool MC, bool WIDE>
 static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, SourceParams<R> sp, hipStream_t s)
 {
     constexpr int threads = gpd_threads<R>();
-    constexpr size_t lds = gpd_lds<R, NR>();
+    constexpr size_t lds = gpd_lds<R, WIDE>();
     const int n = particle_blocks(ep, sp);
     // One launch: the ions and the antenna fill the electrons' tail, and a launch is spared.  20
     // steps against two launches: 75 x 1691 cells at 1 particle a cell 0.96 -> 0.83 ms, 64 x 512 in
     // FP64 1.17 -> 0.83 ms, 187 x 1531 at 5 3.31 -> 3.08 ms, 256 x 4096 at 16 13.2 -> 13.0 ms.
     if (ep.nseg > 0 && n > ep.nseg) {
-        hipLaunchKernelGGL((k_particles<R, MC, NR>), dim3(n), dim3(threads), lds, s, g, f, ep, sp);
+        hipLaunchKernelGGL((k_particles<R, MC, WIDE>), dim3(n), dim3(threads), lds, s, g, f, ep, sp);
         return;
     }
-    if (ep.nseg > 0) hipLaunchKernelGGL((k_gpd<R, MC, NR>), dim3(ep.nseg), dim3(threads), lds, s, g, f, ep);
+    if (ep.nseg > 0) hipLaunchKernelGGL((k_gpd<R, MC, WIDE>), dim3(ep.nseg), dim3(threads), lds, s, g, f, ep);
     launch_sources<R>(g, f, sp, s);
 }
 
-template <typename R, int NR>
+template <typename R, bool WIDE>
 static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
                       bool mc, hipStream_t s)
 {
-    if (mc) particles<R, true, NR>(g, f, ep, sp, s);
-    else particles<R, false, NR>(g, f, ep, sp, s);
+    if (mc) particles<R, true, WIDE>(g, f, ep, sp, s);
+    else particles<R, false, WIDE>(g, f, ep, sp, s);
 }
 
 template <typename R>
 void launch_particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
                       bool mc, hipStream_t s)
 {
-    if (tall_tile<R>(ep.tile_z)) particles<R, trows_tall<R>()>(g, f, ep, sp, mc, s);
-    else particles<R, trows<R>()>(g, f, ep, sp, mc, s);
+    if (wide_tile<R>(ep.tile_x, ep.tile_z)) particles<R, true>(g, f, ep, sp, mc, s);
+    else particles<R, false>(g, f, ep, sp, mc, s);
 }
 
 template <typename R>
-void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, int tile_z, hipStream_t s)
+void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, int tile_x, int tile_z, hipStream_t s)
 {
     if (q.total <= 0) return;
-    if (tall_tile<R>(tile_z))
-        hipLaunchKernelGGL((k_particles_batch<R, trows_tall<R>()>), dim3(q.total), dim3(gpd_threads<R>()),
-                           (gpd_lds<R, trows_tall<R>()>()), s, d, q);
+    const dim3 grid(q.total), block(gpd_threads<R>());
+    if (wide_tile<R>(tile_x, tile_z))
+        hipLaunchKernelGGL((k_particles_batch<R, true>), grid, block, (gpd_lds<R, true>()), s, d, q);
     else
-        hipLaunchKernelGGL((k_particles_batch<R, trows<R>()>), dim3(q.total), dim3(gpd_threads<R>()),
-                           (gpd_lds<R, trows<R>()>()), s, d, q);
+        hipLaunchKernelGGL((k_particles_batch<R, false>), grid, block, (gpd_lds<R, false>()), s, d, q);
 }
 
 template <typename R>
@@ -1648,7 +1709,7 @@ void launch_sort_ions(const Geo& g, int tile_x, int tile_z, int ntx, int ntiles,
                                       const SourceParams<R>&, bool, hipStream_t);                     \
     template void launch_sources<R>(const Geo&, const FieldSet<R>&, SourceParams<R>, hipStream_t);    \
     template int particle_blocks<R>(const ElectronParams<R>&, SourceParams<R>&);                      \
-    template void launch_particles_batch<R>(const ParticleDesc<R>*, const QueueRef&, int, hipStream_t); \
+    template void launch_particles_batch<R>(const ParticleDesc<R>*, const QueueRef&, int, int, hipStream_t); \
     template void launch_beam<R>(const Geo&, const FieldSet<R>&, const BeamArrays&, const BeamParams&, \
                                  const PushParams<double>&, int*, bool, hipStream_t);                 \
     template void launch_advance<R>(const Geo&, const WindowParams<R>*, const ElectronArrays<R>&,     \

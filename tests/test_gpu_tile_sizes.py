@@ -59,3 +59,26 @@ def test_3d_tile_sizes_match_oracle(tile_z, real, tol):
     compare_fields3(sim, ref, tol)
     if real == "f64":
         compare_particles3(sim, ref, 1e-9, 1e-9)
+
+
+@gpu
+@pytest.mark.parametrize("real,tol", [("f64", 1e-10), ("f32", 1e-5)])
+@pytest.mark.parametrize("tile,gather", [((64, 64), 0), ((64, 64), 1), ((13, 64), 0), ((64, 8), 1)])
+def test_tiles_of_several_windows_match_oracle(tile, gather, real, tol):
+    # more particles beside the first window than the list may keep, in up to three windows an axis
+    from paper_1009_2727_amd import Batch, Sim
+    from test_gpu_parity import compare_fields, compare_particles
+    w = pi.small_boosted(real=real, nx=72, nz=160, ppc=6)
+    w["config"]["gather_kind"] = gather
+    sim, ref = Sim.from_workload(w, tile=tile, sort_every=6), Oracle.from_workload(w)
+    sim.step(10)
+    ref.step(10)
+    assert sim.sync_status() == 0
+    compare_fields(sim, ref, tol, tag=f"windows of tile {tile} {real}")
+    if real == "f64":
+        compare_particles(sim, ref, 1e-9, 1e-9)
+    elif gather == 0:
+        one = Sim.from_workload(w, tile=tile, sort_every=6)
+        Batch([one]).step(10)
+        assert one.sync_status() == 0
+        compare_fields(one, ref, tol, tag=f"windows of tile {tile} in a batch")

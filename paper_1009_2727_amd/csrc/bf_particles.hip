@@ -742,15 +742,18 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
     if (threadIdx.x == 0) ep.bbout[s] = make_int4(x0, x1, z0, z1);
 }
 
-// FP64 workgroups are twice as large: their tiles hold the same particles, but a register budget
-// of 256 leaves two waves per SIMD, so a small grid has too few of them in flight at 256 threads.
+// FP64 workgroups are twice as large where there are few: at 135 registers a CU holds one of 512
+// threads or three of 256, so that up to three segments a CU finish sooner with 512 (64 x 512 cells at 4
+// particles a cell 53 -> 49 us a step, at 40 204 -> 179 us) and more of them with 256 (150 x 1600 at 4
+// 145 -> 110 us, at 40 672 -> 632 us; in tiles of 8 x 4 cells 340 -> 183 us).
+constexpr int GPD_FEW = 768;
 template <typename R> constexpr int gpd_threads() { return sizeof(R) == 4 ? 256 : 512; }
 
-template <typename R, bool MC, bool WIDE>
-__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
+template <typename R, bool MC, bool WIDE, int NTH>
+__global__ void __launch_bounds__(NTH, sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
     k_gpd(Geo g, FieldSet<R> f, ElectronParams<R> ep)
 {
-    gpd_segment<R, MC, WIDE, gpd_threads<R>()>(g, f, ep, blockIdx.x);
+    gpd_segment<R, MC, WIDE, NTH>(g, f, ep, blockIdx.x);
 }
 
 // ---- rigid ions --------------------------------------------------------------------------
@@ -968,13 +971,13 @@ __global__ void __launch_bounds__(NTHR) k_sources(Geo g, FieldSet<R> f, SourcePa
 }
 
 // electrons and sources in one launch (they only add to J)
-template <typename R, bool MC, bool WIDE>
-__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
+template <typename R, bool MC, bool WIDE, int NTH>
+__global__ void __launch_bounds__(NTH, sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
     k_particles(Geo g, FieldSet<R> f, ElectronParams<R> ep, SourceParams<R> sp)
 {
     const int b = blockIdx.x;
-    if (b < ep.nseg) gpd_segment<R, MC, WIDE, gpd_threads<R>()>(g, f, ep, b);
-    else source_block<R, gpd_threads<R>()>(g, f, sp, b - ep.nseg);
+    if (b < ep.nseg) gpd_segment<R, MC, WIDE, NTH>(g, f, ep, b);
+    else source_block<R, NTH>(g, f, sp, b - ep.nseg);
 }
 
 // the same for several runs.  One workgroup per segment, as in a run's own launch: the hardware deals
@@ -1596,37 +1599,45 @@ int particle_blocks(const ElectronParams<R>& ep, SourceParams<R>& sp)
     return ep.nseg + sp.nion + sp.na;
 }
 
-template <typename R, bool MC, bool WIDE>
+template <typename R, bool MC, bool WIDE, int NTH>
 static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, SourceParams<R> sp, hipStream_t s)
 {
-    constexpr int threads = gpd_threads<R>();
     constexpr size_t lds = gpd_lds<R, WIDE>();
-    const int n = particle_blocks(ep, sp);
+    sp.na = antenna_blocks(sp, NTH);
+    const int n = ep.nseg + sp.nion + sp.na;
     // One launch: the ions and the antenna fill the electrons' tail, and a launch is spared.  20
     // steps against two launches: 75 x 1691 cells at 1 particle a cell 0.96 -> 0.83 ms, 64 x 512 in
     // FP64 1.17 -> 0.83 ms, 187 x 1531 at 5 3.31 -> 3.08 ms, 256 x 4096 at 16 13.2 -> 13.0 ms.
     if (ep.nseg > 0 && n > ep.nseg) {
-        hipLaunchKernelGGL((k_particles<R, MC, WIDE>), dim3(n), dim3(threads), lds, s, g, f, ep, sp);
+        hipLaunchKernelGGL((k_particles<R, MC, WIDE, NTH>), dim3(n), dim3(NTH), lds, s, g, f, ep, sp);
         return;
     }
-    if (ep.nseg > 0) hipLaunchKernelGGL((k_gpd<R, MC, WIDE>), dim3(ep.nseg), dim3(threads), lds, s, g, f, ep);
+    if (ep.nseg > 0) hipLaunchKernelGGL((k_gpd<R, MC, WIDE, NTH>), dim3(ep.nseg), dim3(NTH), lds, s, g, f, ep);
     launch_sources<R>(g, f, sp, s);
 }
 
-template <typename R, bool WIDE>
+template <typename R, bool WIDE, int NTH>
 static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
                       bool mc, hipStream_t s)
 {
-    if (mc) particles<R, true, WIDE>(g, f, ep, sp, s);
-    else particles<R, false, WIDE>(g, f, ep, sp, s);
+    if (mc) particles<R, true, WIDE, NTH>(g, f, ep, sp, s);
+    else particles<R, false, WIDE, NTH>(g, f, ep, sp, s);
 }
 
 template <typename R>
 void launch_particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
                       bool mc, hipStream_t s)
 {
-    if (wide_tile<R>(ep.tile_x, ep.tile_z)) particles<R, true>(g, f, ep, sp, mc, s);
-    else particles<R, false>(g, f, ep, sp, mc, s);
+    const bool wide = wide_tile<R>(ep.tile_x, ep.tile_z);
+    if constexpr (gpd_threads<R>() > NTHR) {
+        if (ep.nseg > GPD_FEW) {
+            if (wide) particles<R, true, NTHR>(g, f, ep, sp, mc, s);
+            else particles<R, false, NTHR>(g, f, ep, sp, mc, s);
+            return;
+        }
+    }
+    if (wide) particles<R, true, gpd_threads<R>()>(g, f, ep, sp, mc, s);
+    else particles<R, false, gpd_threads<R>()>(g, f, ep, sp, mc, s);
 }
 
 template <typename R>

@@ -82,3 +82,21 @@ def test_tiles_of_several_windows_match_oracle(tile, gather, real, tol):
         Batch([one]).step(10)
         assert one.sync_status() == 0
         compare_fields(one, ref, tol, tag=f"windows of tile {tile} in a batch")
+
+
+@gpu
+@pytest.mark.parametrize("tile,nz", [((4, 2), 160), ((27, 1), 400)])
+@pytest.mark.parametrize("gather", [0, 1])
+def test_many_fp64_segments_match_oracle(tile, nz, gather):
+    # more than three segments a CU, in tiles that fit the staged one and that do not
+    from paper_1009_2727_amd import Sim
+    from test_gpu_parity import compare_fields, compare_particles
+    w = pi.small_boosted(real="f64", nx=40, nz=nz, ppc=3)
+    w["config"]["gather_kind"] = gather
+    sim, ref = Sim.from_workload(w, tile=tile, sort_every=6), Oracle.from_workload(w)
+    sim.step(10)
+    ref.step(10)
+    assert sim.sync_status() == 0
+    compare_fields(sim, ref, 1e-10, tag=f"many segments of tile {tile}")
+    compare_particles(sim, ref, 1e-9, 1e-9)
+    compare_particles(sim, ref, 1e-9, 1e-9, species=1)

@@ -739,7 +739,6 @@ bf_status step_impl(bf_sim* s, int nsteps)
         ep.bbin = bb_e(s, s->bb_cur);
         ep.bbout = bb_e(s, 1 - s->bb_cur);
         ep.nseg = s->nseg_e;
-        ep.tile_x = L.tile_x;
         ep.tile_z = L.tile_z;
         ep.pp = pp;
         // the x array of the sort's scratch copy, free between sorts
@@ -2169,12 +2168,9 @@ bf_status batch_one_step(bf_batch* b)
     };
     launch_faraday_batch<float>(dfar, qf, grid(qf, 8), st);
     closures({SLOT_FARADAY, SLOT_STATIONS});
-    int tile_x = 0, tile_z = 0;
-    for (const auto& d : rec.particles) {
-        tile_x = std::max(tile_x, d.e.tile_x);
-        tile_z = std::max(tile_z, d.e.tile_z);
-    }
-    launch_particles_batch<float>(dpart, qp, tile_x, tile_z, st);
+    int tile_z = 0;
+    for (const auto& d : rec.particles) tile_z = std::max(tile_z, d.e.tile_z);
+    launch_particles_batch<float>(dpart, qp, tile_z, st);
     closures({SLOT_PUSH, SLOT_FILTER});
     launch_ampere_batch<float>(damp, qa, grid(qa, 8), st);
     closures({SLOT_AMPERE, SLOT_WINDOW, SLOT_SORT});

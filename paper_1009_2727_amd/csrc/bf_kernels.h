@@ -108,7 +108,7 @@ struct ElectronParams {
     const int4* bbin;
     int4* bbout;
     int nseg;
-    int tile_x, tile_z;   // cells of a particle tile
+    int tile_z;           // rows of a particle tile
     PushParams<R> pp;
     int *far, *far2;
     int* status;
@@ -188,9 +188,9 @@ template <typename R>
 void launch_faraday_batch(const FaradayDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s);
 template <typename R>
 void launch_ampere_batch(const AmpereDesc<R>* d, const QueueRef& q, int nblocks, hipStream_t s);
-// tile_x, tile_z: of the largest particle tiles among the runs
+// tile_z: rows of the largest particle tile among the runs
 template <typename R>
-void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, int tile_x, int tile_z, hipStream_t s);
+void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, int tile_z, hipStream_t s);
 // workgroups of a run's electrons and sources; sets sp.na
 template <typename R>
 int particle_blocks(const ElectronParams<R>& ep, SourceParams<R>& sp);

@@ -45,13 +45,12 @@ __device__ __forceinline__ double block_sum(double v, double* red)
 constexpr int TPX = 32;                 // row pitch of the staged tile (cells)
 // Rows of the staged tile (6 field planes + 3 current planes of 8 bytes).  FP32 tiles of 26 rows take
 // 39 KB, so that four workgroups fit a CU's LDS; the default tile needs 14 rows, and 12 are left for
-// drift.  Particle tiles that outgrow the staged one with their halo and a cell of drift take the
-// launch for wide tiles: 31 rows in FP32, three workgroups a CU, and as many windows a segment as its
-// box needs.  256 x 2048 cells at 16 particles a cell in tiles of 24 cells 1124 -> 433 us a step (tiles of
-// 20 take 397 us with 26 rows, tiles of 21 420 us with 31).
+// drift.  Particle tiles of 21 cells and more fill them with their halo and one row of drift, and the
+// launch takes 31 rows, three workgroups a CU: 256 x 2048 cells at 16 particles a cell in tiles of 24
+// cells 1124 -> 433 us a step (tiles of 20 take 397 us with 26 rows, tiles of 21 420 us with 31).
 template <typename R> constexpr int trows() { return sizeof(R) == 4 ? 26 : 21; }
-template <typename R, bool WIDE> constexpr int tile_rows() { return sizeof(R) == 4 && WIDE ? 31 : trows<R>(); }
-template <typename R> bool wide_tile(int tile_x, int tile_z) { return tile_x + 6 > TPX || tile_z + 6 > trows<R>(); }
+template <typename R> constexpr int trows_tall() { return sizeof(R) == 4 ? 31 : 21; }
+template <typename R> bool tall_tile(int tile_z) { return trows_tall<R>() > trows<R>() && tile_z + 6 > trows<R>(); }
 // rows of an ion segment's tile, which holds J_z alone: the largest tile (64 cells), its halo and one
 // row of drift.  Ions drift rigidly, so that tiles of 21 cells and more outgrew the electrons' 26 rows
 // whole, and their segments went to global atomics: 256 x 2048 cells at 16 particles a cell in tiles
@@ -618,12 +617,14 @@ __device__ __forceinline__ void flush_tile(const Geo& g, const FieldSet<R>& f, c
 // of code and 168 registers, and cold instruction fetches dominated small launches.
 // Per step: 43 -> 15 us on 75 x 1691 cells at 1 particle a cell, 70 -> 23 us on 64 x 512 at 4 in
 // FP64, 0.425 -> 0.38 ms on 256 x 4096 at 16 (16.8 M electrons, four workgroups per CU).
-// WIDE, for tiles that outgrow the staged one (64 x 64 cells, or 13 x 30): while the list holds more
-// than FAR_FEW particles a window of the whole box, the next window that holds one of them is staged.
-// Tiles of 64 x 64 cells on 112 x 1049 at 16 particles a cell 13.7 -> 2.93 ms a step in FP32, 13 x 30 on
-// 59 x 1861 478 -> 268 us.
+// While the list holds more than FAR_FEW particles a window of the whole box, the next window that
+// holds one of them is staged.  A strong laser scatters a few segments' electrons beside their window,
+// and those segments' lists were the launch: 93 x 1689 cells at 40 particles a cell behind a pulse that
+// expels 0.3% of them 690 -> 407 us a step.  Tiles larger than the staged one live by it: 64 x 64 cells
+// on 112 x 1049 at 16 13.7 -> 2.93 ms in FP32, 13 x 30 on 59 x 1861 478 -> 268 us.  It costs registers
+// (121 -> 127 in FP32, 135 -> 152 in FP64), none of them a wave, and 1% of 64 x 512 at 4 in FP64.
 constexpr int FAR_FEW = 64;
-template <typename R, bool MC, bool WIDE, int NTH>
+template <typename R, bool MC, int NR, int NTH>
 __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, int s)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];   // 16-byte aligned: FP64 DS ops
@@ -644,7 +645,6 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
     int p = sg.start + threadIdx.x;
     EState<R> nxt{}, done{};
     if (p < end) nxt = load_electron(e, p);
-    constexpr int NR = tile_rows<R, WIDE>();
     using Acc = LdsAcc<R, NR>;
     Acc lds;
     lds.xb = bb.x - 2;
@@ -699,7 +699,7 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
     flush_tile<R, NTH>(g, f, lds, jq);
     int n = nfar;                        // the barrier before the flush ordered the list's writes
     int* far = ep.far + sg.start;
-    if constexpr (WIDE) {
+    if (__builtin_expect(n > FAR_FEW, 0)) {
         // Windows a whole box takes, each of WX x WZ cells of particles.  Each that is staged takes all
         // listed particles of its part of the box, so as many as there are parts are enough (a position
         // that is no number belongs to none).
@@ -742,18 +742,20 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
     if (threadIdx.x == 0) ep.bbout[s] = make_int4(x0, x1, z0, z1);
 }
 
-// FP64 workgroups are twice as large where there are few: at 135 registers a CU holds one of 512
+// FP64 workgroups are twice as large where there are few: at 137 to 152 registers a CU holds one of 512
 // threads or three of 256, so that up to three segments a CU finish sooner with 512 (64 x 512 cells at 4
 // particles a cell 53 -> 49 us a step, at 40 204 -> 179 us) and more of them with 256 (150 x 1600 at 4
 // 145 -> 110 us, at 40 672 -> 632 us; in tiles of 8 x 4 cells 340 -> 183 us).
 constexpr int GPD_FEW = 768;
 template <typename R> constexpr int gpd_threads() { return sizeof(R) == 4 ? 256 : 512; }
+// waves a SIMD that the registers must leave room for: as many as the tiles' LDS allows
+template <typename R, int NR> constexpr int gpd_waves() { return sizeof(R) == 8 ? 1 : NR > trows<R>() ? 3 : 4; }
 
-template <typename R, bool MC, bool WIDE, int NTH>
-__global__ void __launch_bounds__(NTH, sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
+template <typename R, bool MC, int NR, int NTH>
+__global__ void __launch_bounds__(NTH, (gpd_waves<R, NR>()))
     k_gpd(Geo g, FieldSet<R> f, ElectronParams<R> ep)
 {
-    gpd_segment<R, MC, WIDE, NTH>(g, f, ep, blockIdx.x);
+    gpd_segment<R, MC, NR, NTH>(g, f, ep, blockIdx.x);
 }
 
 // ---- rigid ions --------------------------------------------------------------------------
@@ -971,12 +973,12 @@ __global__ void __launch_bounds__(NTHR) k_sources(Geo g, FieldSet<R> f, SourcePa
 }
 
 // electrons and sources in one launch (they only add to J)
-template <typename R, bool MC, bool WIDE, int NTH>
-__global__ void __launch_bounds__(NTH, sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
+template <typename R, bool MC, int NR, int NTH>
+__global__ void __launch_bounds__(NTH, (gpd_waves<R, NR>()))
     k_particles(Geo g, FieldSet<R> f, ElectronParams<R> ep, SourceParams<R> sp)
 {
     const int b = blockIdx.x;
-    if (b < ep.nseg) gpd_segment<R, MC, WIDE, NTH>(g, f, ep, b);
+    if (b < ep.nseg) gpd_segment<R, MC, NR, NTH>(g, f, ep, b);
     else source_block<R, NTH>(g, f, sp, b - ep.nseg);
 }
 
@@ -984,13 +986,13 @@ __global__ void __launch_bounds__(NTH, sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
 // them out, and the ions of one run fill the tail of its electrons.  16 runs of about 150 x 1600 cells at 10
 // particles a cell: 1.79 ms a step; electrons by a persistent launch over a queue and each run's
 // sources in a launch of its own took 1.84 ms.
-template <typename R, bool WIDE>
-__global__ void __launch_bounds__(gpd_threads<R>(), sizeof(R) == 4 ? (WIDE ? 3 : 4) : 1)
+template <typename R, int NR>
+__global__ void __launch_bounds__(gpd_threads<R>(), (gpd_waves<R, NR>()))
     k_particles_batch(const ParticleDesc<R>* __restrict__ d, QueueRef q)
 {
     const int r = run_of(q, blockIdx.x), b = (int)blockIdx.x - q.off[r];
     const ParticleDesc<R>& D = d[r];
-    if (b < D.e.nseg) gpd_segment<R, false, WIDE, gpd_threads<R>()>(D.g, D.f, D.e, b);
+    if (b < D.e.nseg) gpd_segment<R, false, NR, gpd_threads<R>()>(D.g, D.f, D.e, b);
     else source_block<R, gpd_threads<R>()>(D.g, D.f, D.s, b - D.e.nseg);
 }
 
@@ -1565,16 +1567,15 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_disperse_i(Geo g, IonArra
 }
 
 // ---- launchers ---------------------------------------------------------------------------------
-template <typename R, bool WIDE> constexpr size_t gpd_lds()
+template <typename R, int NR> constexpr size_t gpd_lds()
 {
-    constexpr int NR = tile_rows<R, WIDE>();
     return (size_t)TPX * NR * (6 * sizeof(R) + 3 * sizeof(typename LdsAcc<R, NR>::JT));
 }
 template <typename R> constexpr size_t ion_lds()
 {
     return (size_t)TPX * ION_ROWS * sizeof(typename LdsAcc<R, ION_ROWS>::JT);
 }
-static_assert(ion_lds<float>() <= gpd_lds<float, false>() && ion_lds<double>() <= gpd_lds<double, false>(),
+static_assert(ion_lds<float>() <= gpd_lds<float, trows<float>()>() && ion_lds<double>() <= gpd_lds<double, trows<double>()>(),
               "the ions of a launch with electrons fit its LDS");
 
 template <typename R>
@@ -1599,56 +1600,49 @@ int particle_blocks(const ElectronParams<R>& ep, SourceParams<R>& sp)
     return ep.nseg + sp.nion + sp.na;
 }
 
-template <typename R, bool MC, bool WIDE, int NTH>
+template <typename R, bool MC, int NR, int NTH>
 static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, SourceParams<R> sp, hipStream_t s)
 {
-    constexpr size_t lds = gpd_lds<R, WIDE>();
+    constexpr size_t lds = gpd_lds<R, NR>();
     sp.na = antenna_blocks(sp, NTH);
     const int n = ep.nseg + sp.nion + sp.na;
     // One launch: the ions and the antenna fill the electrons' tail, and a launch is spared.  20
     // steps against two launches: 75 x 1691 cells at 1 particle a cell 0.96 -> 0.83 ms, 64 x 512 in
     // FP64 1.17 -> 0.83 ms, 187 x 1531 at 5 3.31 -> 3.08 ms, 256 x 4096 at 16 13.2 -> 13.0 ms.
     if (ep.nseg > 0 && n > ep.nseg) {
-        hipLaunchKernelGGL((k_particles<R, MC, WIDE, NTH>), dim3(n), dim3(NTH), lds, s, g, f, ep, sp);
+        hipLaunchKernelGGL((k_particles<R, MC, NR, NTH>), dim3(n), dim3(NTH), lds, s, g, f, ep, sp);
         return;
     }
-    if (ep.nseg > 0) hipLaunchKernelGGL((k_gpd<R, MC, WIDE, NTH>), dim3(ep.nseg), dim3(NTH), lds, s, g, f, ep);
+    if (ep.nseg > 0) hipLaunchKernelGGL((k_gpd<R, MC, NR, NTH>), dim3(ep.nseg), dim3(NTH), lds, s, g, f, ep);
     launch_sources<R>(g, f, sp, s);
 }
 
-template <typename R, bool WIDE, int NTH>
+template <typename R, int NR, int NTH>
 static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
                       bool mc, hipStream_t s)
 {
-    if (mc) particles<R, true, WIDE, NTH>(g, f, ep, sp, s);
-    else particles<R, false, WIDE, NTH>(g, f, ep, sp, s);
+    if (mc) particles<R, true, NR, NTH>(g, f, ep, sp, s);
+    else particles<R, false, NR, NTH>(g, f, ep, sp, s);
 }
 
 template <typename R>
 void launch_particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
                       bool mc, hipStream_t s)
 {
-    const bool wide = wide_tile<R>(ep.tile_x, ep.tile_z);
-    if constexpr (gpd_threads<R>() > NTHR) {
-        if (ep.nseg > GPD_FEW) {
-            if (wide) particles<R, true, NTHR>(g, f, ep, sp, mc, s);
-            else particles<R, false, NTHR>(g, f, ep, sp, mc, s);
-            return;
-        }
-    }
-    if (wide) particles<R, true, gpd_threads<R>()>(g, f, ep, sp, mc, s);
-    else particles<R, false, gpd_threads<R>()>(g, f, ep, sp, mc, s);
+    if (tall_tile<R>(ep.tile_z)) particles<R, trows_tall<R>(), gpd_threads<R>()>(g, f, ep, sp, mc, s);
+    else if (gpd_threads<R>() == NTHR || ep.nseg > GPD_FEW) particles<R, trows<R>(), NTHR>(g, f, ep, sp, mc, s);
+    else particles<R, trows<R>(), gpd_threads<R>()>(g, f, ep, sp, mc, s);
 }
 
 template <typename R>
-void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, int tile_x, int tile_z, hipStream_t s)
+void launch_particles_batch(const ParticleDesc<R>* d, const QueueRef& q, int tile_z, hipStream_t s)
 {
     if (q.total <= 0) return;
     const dim3 grid(q.total), block(gpd_threads<R>());
-    if (wide_tile<R>(tile_x, tile_z))
-        hipLaunchKernelGGL((k_particles_batch<R, true>), grid, block, (gpd_lds<R, true>()), s, d, q);
+    if (tall_tile<R>(tile_z))
+        hipLaunchKernelGGL((k_particles_batch<R, trows_tall<R>()>), grid, block, (gpd_lds<R, trows_tall<R>()>()), s, d, q);
     else
-        hipLaunchKernelGGL((k_particles_batch<R, false>), grid, block, (gpd_lds<R, false>()), s, d, q);
+        hipLaunchKernelGGL((k_particles_batch<R, trows<R>()>), grid, block, (gpd_lds<R, trows<R>()>()), s, d, q);
 }
 
 template <typename R>
@@ -1720,7 +1714,7 @@ void launch_sort_ions(const Geo& g, int tile_x, int tile_z, int ntx, int ntiles,
                                       const SourceParams<R>&, bool, hipStream_t);                     \
     template void launch_sources<R>(const Geo&, const FieldSet<R>&, SourceParams<R>, hipStream_t);    \
     template int particle_blocks<R>(const ElectronParams<R>&, SourceParams<R>&);                      \
-    template void launch_particles_batch<R>(const ParticleDesc<R>*, const QueueRef&, int, int, hipStream_t); \
+    template void launch_particles_batch<R>(const ParticleDesc<R>*, const QueueRef&, int, hipStream_t); \
     template void launch_beam<R>(const Geo&, const FieldSet<R>&, const BeamArrays&, const BeamParams&, \
                                  const PushParams<double>&, int*, bool, hipStream_t);                 \
     template void launch_advance<R>(const Geo&, const WindowParams<R>*, const ElectronArrays<R>&,     \

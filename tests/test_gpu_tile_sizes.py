@@ -100,3 +100,29 @@ def test_many_fp64_segments_match_oracle(tile, nz, gather):
     compare_fields(sim, ref, 1e-10, tag=f"many segments of tile {tile}")
     compare_particles(sim, ref, 1e-9, 1e-9)
     compare_particles(sim, ref, 1e-9, 1e-9, species=1)
+
+
+@gpu
+@pytest.mark.parametrize("real,tol,xtol,utol", [("f64", 1e-11, 1e-9, 1e-9), ("f32", 1e-5, 2e-5, 1e-4)])
+@pytest.mark.parametrize("umax", [0.3, 6.0])
+def test_spread_electrons_in_default_tiles_match_oracle(umax, real, tol, xtol, utol):
+    # stepped with no sort until a segment's electrons lie in many windows: a few beside the first one
+    # (the list as it is) and most of them (window after window, across a periodic edge too)
+    from paper_1009_2727_amd import Sim
+    from test_gpu_parity import compare_fields, compare_particles
+    nx, nz = 60, 53
+    cfg = pi.make_config(nx, nz, 0.1, 0.13, periodic_x=1, periodic_z=1, pml_cells=0, ck="ck2",
+                         theta=0.3, filter_npass=2, filter_compensate=1, real=real, seed=6)
+    sim, ref = Sim(cfg, capacity=30000, sort_every=1000), Oracle(cfg)
+    for k, name in enumerate(["Ex", "Ey", "Ez", "Bx", "By", "Bz", "Exo", "Eyo", "Ezo", "Exb", "Eyb", "Ezb"]):
+        f = pi.random_field(ref.shape, seed=300 + k, amp=0.2)
+        ref.set_field(name, f)
+        sim.set_field(name, f)
+    p = pi.random_electrons(20000, nx, nz, 0.1, 0.13, seed=12, umax=umax, margin=0.0)
+    ref.set_electrons(p)
+    sim.load_electrons(p)
+    ref.step(12)
+    sim.step(12)
+    assert sim.sync_status() == 0
+    compare_fields(sim, ref, tol, tag=f"spread over windows {umax} {real}")
+    compare_particles(sim, ref, xtol, utol)

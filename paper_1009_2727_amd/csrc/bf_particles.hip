@@ -742,17 +742,23 @@ __device__ __forceinline__ void gpd_segment(const Geo& g, const FieldSet<R>& f, 
     if (threadIdx.x == 0) ep.bbout[s] = make_int4(x0, x1, z0, z1);
 }
 
-// FP64 workgroups are twice as large where there are few: at 137 to 152 registers a CU holds one of 512
+// FP64 workgroups are twice as large where there are few: at 152 registers a CU holds one of 512
 // threads or three of 256, so that up to three segments a CU finish sooner with 512 (64 x 512 cells at 4
 // particles a cell 53 -> 49 us a step, at 40 204 -> 179 us) and more of them with 256 (150 x 1600 at 4
-// 145 -> 110 us, at 40 672 -> 632 us; in tiles of 8 x 4 cells 340 -> 183 us).
+// 145 -> 110 us, at 40 672 -> 632 us; in tiles of 8 x 4 cells 340 -> 183 us).  With node fields two of 512
+// fit, and they stay (104 x 1600 at 40 458 us, three of 256 477 us).
 constexpr int GPD_FEW = 768;
 template <typename R> constexpr int gpd_threads() { return sizeof(R) == 4 ? 256 : 512; }
-// waves a SIMD that the registers must leave room for: as many as the tiles' LDS allows
-template <typename R, int NR> constexpr int gpd_waves() { return sizeof(R) == 8 ? 1 : NR > trows<R>() ? 3 : 4; }
+// Waves a SIMD that the registers must leave room for.  FP32: as many as the tiles' LDS allows.  FP64 with
+// node fields: a second workgroup of 512 on a CU (20 steps of a lab frame run of 61 x 1225 cells at 1
+// particle a cell 893 us with 28 bytes of spills a lane, 1050 us with 137 registers and none).
+template <typename R, bool MC, int NR> constexpr int gpd_waves()
+{
+    return sizeof(R) == 8 ? (MC ? 4 : 1) : NR > trows<R>() ? 3 : 4;
+}
 
 template <typename R, bool MC, int NR, int NTH>
-__global__ void __launch_bounds__(NTH, (gpd_waves<R, NR>()))
+__global__ void __launch_bounds__(NTH, (gpd_waves<R, MC, NR>()))
     k_gpd(Geo g, FieldSet<R> f, ElectronParams<R> ep)
 {
     gpd_segment<R, MC, NR, NTH>(g, f, ep, blockIdx.x);
@@ -974,7 +980,7 @@ __global__ void __launch_bounds__(NTHR) k_sources(Geo g, FieldSet<R> f, SourcePa
 
 // electrons and sources in one launch (they only add to J)
 template <typename R, bool MC, int NR, int NTH>
-__global__ void __launch_bounds__(NTH, (gpd_waves<R, NR>()))
+__global__ void __launch_bounds__(NTH, (gpd_waves<R, MC, NR>()))
     k_particles(Geo g, FieldSet<R> f, ElectronParams<R> ep, SourceParams<R> sp)
 {
     const int b = blockIdx.x;
@@ -987,7 +993,7 @@ __global__ void __launch_bounds__(NTH, (gpd_waves<R, NR>()))
 // particles a cell: 1.79 ms a step; electrons by a persistent launch over a queue and each run's
 // sources in a launch of its own took 1.84 ms.
 template <typename R, int NR>
-__global__ void __launch_bounds__(gpd_threads<R>(), (gpd_waves<R, NR>()))
+__global__ void __launch_bounds__(gpd_threads<R>(), (gpd_waves<R, false, NR>()))
     k_particles_batch(const ParticleDesc<R>* __restrict__ d, QueueRef q)
 {
     const int r = run_of(q, blockIdx.x), b = (int)blockIdx.x - q.off[r];
@@ -1617,21 +1623,21 @@ static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R
     launch_sources<R>(g, f, sp, s);
 }
 
-template <typename R, int NR, int NTH>
+template <typename R, int NR>
 static void particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
                       bool mc, hipStream_t s)
 {
-    if (mc) particles<R, true, NR, NTH>(g, f, ep, sp, s);
-    else particles<R, false, NR, NTH>(g, f, ep, sp, s);
+    if (mc) particles<R, true, NR, gpd_threads<R>()>(g, f, ep, sp, s);
+    else if (ep.nseg > GPD_FEW) particles<R, false, NR, NTHR>(g, f, ep, sp, s);
+    else particles<R, false, NR, gpd_threads<R>()>(g, f, ep, sp, s);
 }
 
 template <typename R>
 void launch_particles(const Geo& g, const FieldSet<R>& f, const ElectronParams<R>& ep, const SourceParams<R>& sp,
                       bool mc, hipStream_t s)
 {
-    if (tall_tile<R>(ep.tile_z)) particles<R, trows_tall<R>(), gpd_threads<R>()>(g, f, ep, sp, mc, s);
-    else if (gpd_threads<R>() == NTHR || ep.nseg > GPD_FEW) particles<R, trows<R>(), NTHR>(g, f, ep, sp, mc, s);
-    else particles<R, trows<R>(), gpd_threads<R>()>(g, f, ep, sp, mc, s);
+    if (tall_tile<R>(ep.tile_z)) particles<R, trows_tall<R>()>(g, f, ep, sp, mc, s);
+    else particles<R, trows<R>()>(g, f, ep, sp, mc, s);
 }
 
 template <typename R>
